@@ -1,6 +1,7 @@
 """Thin ctypes binding over the C ABI of ``libfbx.so`` (see ``include/fbx.h``).
 
-Argument marshalling only: every step of the extraction path runs in the
+Argument marshalling only (what runs once per extraction call natively, in
+``csrc/fbx_native.cpp``): every step of the extraction path runs in the
 library's HIP kernels.  PyTorch appears solely as the owner of device memory
 and streams.  If the library has not been built the import of this module
 fails loudly; there is no fallback path.
@@ -13,6 +14,7 @@ from typing import Dict, List, Optional, Tuple
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libfbx.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 OK, E_ARG, E_SPEC, E_NOMEM, E_INPUT, E_HIP = 0, -1, -2, -3, -4, -5
 
@@ -55,15 +57,22 @@ class UnorderedResult(ctypes.Structure):
     _fields_ = [("n_values", ctypes.c_uint64), ("n_malformed_numeric", ctypes.c_uint64), ("pool_head", ctypes.c_uint64)]
 
 
-_lib = None
+_lib = _native = None
+
+
+def _current_stream() -> int:
+    import torch
+
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def lib():
     """Load libfbx.so (built beforehand by ``paper_2210_07768_amd.build``)."""
-    global _lib
+    global _lib, _native
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise ImportError(f"{LIB_PATH} is missing: run `python -m paper_2210_07768_amd.build` first")
+        for path in (LIB_PATH, NATIVE_PATH):
+            if not os.path.exists(path):
+                raise ImportError(f"{path} is missing: run `python -m paper_2210_07768_amd.build` first")
         # PyTorch ships its own HIP runtime; load it first so that libfbx binds to the
         # same runtime instance that owns the device memory and streams it is handed.
         import torch  # noqa: F401
@@ -118,46 +127,18 @@ def lib():
         L.fbx_arena_alloc.argtypes = [vp, vp, u64, vp, u32, vp]
         L.fbx_arena_reset.restype = ctypes.c_int
         L.fbx_arena_reset.argtypes = [vp, u64, vp]
-        _lib = L
+        from . import _native as N
+
+        N.bind(*(ctypes.cast(f, vp).value for f in (L.fbx_extract, L.fbx_extract_static, L.fbx_last_error)))
+        _lib, _native = L, N
     return _lib
 
 
-class Slot:
-    """One emitted slot of a result; ``values`` / ``offsets`` are torch views of the workspace
-    (made when first asked for: a result with hundreds of slots costs nothing to hand over)."""
-
-    def __init__(self, slot_id, fixed_arity, n_values, ws64, values_at, offsets_at, n_offsets, tile_ends_at=None, n_tiles=0):
-        self.slot_id, self.fixed_arity, self.n_values = slot_id, fixed_arity, n_values
-        self._ws64, self._values_at, self._offsets_at, self._n_offsets = ws64, values_at, offsets_at, n_offsets
-        self._tile_ends_at, self._n_tiles = tile_ends_at, n_tiles
-        self._values = self._offsets = None
-
-    @property
-    def tile_ends(self):
-        """Arrival order only (ExtractResult.arrival_tile_records != 0, ragged slot): where each tile's share ends."""
-        if self._tile_ends_at is None:
-            return None
-        return self._ws64[self._tile_ends_at:self._tile_ends_at + self._n_tiles]
-
-    @property
-    def values(self):
-        if self._values is None:
-            self._values = self._ws64[self._values_at:self._values_at + self.n_values]
-        return self._values
-
-    @property
-    def offsets(self):
-        """None for a slot of fixed arity (offsets are implicit)."""
-        if self._offsets_at is None:
-            return None
-        if self._offsets is None:
-            self._offsets = self._ws64[self._offsets_at:self._offsets_at + self._n_offsets]
-        return self._offsets
-
-
 class ExtractResult:
-    """What fbx_extract reported.  ``slots`` (slot id -> Slot) and ``slot_ids`` (in emission order)
-    are built from the library's slot table when first asked for."""
+    """What fbx_extract reported.  ``slots`` (slot id -> slot) and ``slot_ids`` (in emission order)
+    are built from the library's slot table when first asked for.  A slot has ``slot_id``, ``fixed_arity``,
+    ``n_values`` and, as torch views of the workspace made when first asked for, ``values``, ``offsets``
+    (None for a slot of fixed arity) and ``tile_ends`` (arrival order only, see fbx.h)."""
 
     def __init__(self):
         self.n_records = 0
@@ -168,27 +149,17 @@ class ExtractResult:
         self.tile_launches = 0
         self.arrival_tile_records = 0   # 0: ragged slots in record order; k: tiles of k records in arrival order (fbx.h)
         self.note = ""
-        self._table = None   # (bytes of the library's slot table, workspace as int64, its base address, offsets per slot)
+        self._table = None   # (bytes of the library's slot table, the tensor its arrays lie in, that one's address, offsets per slot)
         self._slots = None
         self._slot_ids = None
 
     def _build(self):
-        table, ws64, base, n_offsets = self._table
+        table, home, base, n_offsets = self._table
         k = self.arrival_tile_records
-        n_tiles = -(-(n_offsets - 1) // k) if k else 0
-        n = len(table) // ctypes.sizeof(SlotView)
-        self._slots, self._slot_ids = {}, []
-        for sv in ((SlotView * n).from_buffer_copy(table) if n else ()):
-            v0 = ((sv.values or base) - base) // 8
-            o0 = (sv.offsets - base) // 8 if sv.offsets else None
-            # (the table of tile ends lies in the workspace; with the entry point that allocates nothing it does not, and no view is made)
-            inside = sv.tile_ends and base <= sv.tile_ends < base + ws64.numel() * 8
-            t0 = (sv.tile_ends - base) // 8 if inside else None
-            self._slots[sv.slot_id] = Slot(sv.slot_id, sv.fixed_arity, sv.n_values, ws64, v0, o0, n_offsets, t0, n_tiles)
-            self._slot_ids.append(sv.slot_id)
+        self._slots, self._slot_ids = _native.slots(table, home, base, n_offsets, -(-(n_offsets - 1) // k) if k else 0)
 
     @property
-    def slots(self) -> Dict[int, Slot]:
+    def slots(self) -> Dict[int, "_native.Slot"]:
         if self._slots is None:
             self._build()
         return self._slots
@@ -276,10 +247,8 @@ class Plan:
                           stream: Optional[int] = None) -> UnorderedResult:
         """fbx_extract_unordered: pool (uint8), state (4 x int64), thread_offsets (int64, one per record) and
         lengths (int32, one per record) are CUDA tensors owned by the caller."""
-        import torch
-
         if stream is None:
-            stream = torch.cuda.current_stream().cuda_stream
+            stream = _current_stream()
         res = UnorderedResult()
         st = lib().fbx_extract_unordered(self._h, slot_id, d_raw.data_ptr() if d_raw.numel() else 0, d_raw.numel(),
                                          d_rec_off.data_ptr(), d_rec_off.numel() - 1, pool.data_ptr(), pool.numel(),
@@ -304,35 +273,21 @@ class Plan:
         """d_raw: uint8 CUDA tensor; d_rec_off: int64/uint64 CUDA tensor of n_records + 1 entries.
         With out_buffer (a uint8 CUDA tensor, 256-byte aligned) the call goes to fbx_extract_static:
         no workspace, results in out_buffer."""
-        import torch
-
         if stream is None:
-            stream = torch.cuda.current_stream().cuda_stream
-        n_records = d_rec_off.numel() - 1
-        raw_ptr = d_raw.data_ptr() if d_raw.numel() else 0
-        if out_buffer is None:
-            res = self.extract_raw(raw_ptr, d_raw.numel(), d_rec_off.data_ptr(), n_records, stream)
-            home = self._ws
-        else:
-            res = Result()
-            st = lib().fbx_extract_static(self._h, raw_ptr, d_raw.numel(), d_rec_off.data_ptr(), n_records,
-                                          out_buffer.data_ptr(), out_buffer.numel(), stream, ctypes.byref(res))
-            if st != OK:
-                err = FbxError(st, lib().fbx_last_error(self._h).decode())
-                err.required_bytes = res.arena_high_water if st == E_NOMEM else 0
-                raise err
-            home = out_buffer
+            stream = _current_stream()
+        (st, n_records, n_values, malformed, high_water, n_layers, tile_launches, arrival, note,
+         table) = _native.extract(self._h.value or 0, d_raw, d_rec_off, stream, out_buffer)
+        if st != OK:
+            err = FbxError(st, note)
+            err.required_bytes = high_water if st == E_NOMEM else 0
+            raise err
         out = ExtractResult()
-        out.n_records, out.n_values_total = res.n_records, res.n_values_total
-        out.n_malformed_numeric, out.arena_high_water = res.n_malformed_numeric, res.arena_high_water
-        out.n_layers = res.n_layers
-        out.tile_launches = res.tile_launches
-        out.arrival_tile_records = res.arrival_tile_records
-        out.note = lib().fbx_last_error(self._h).decode()
-        # the library's slot table is overwritten by the next call: copy the plain numbers out now
-        ws64 = home[: home.numel() // 8 * 8].view(torch.int64)
-        table = ctypes.string_at(res.slots, res.n_slots * ctypes.sizeof(SlotView)) if res.n_slots else b""
-        out._table = (table, ws64, home.data_ptr(), n_records + 1)
+        out.n_records, out.n_values_total, out.n_malformed_numeric = n_records, n_values, malformed
+        out.arena_high_water, out.n_layers, out.tile_launches, out.arrival_tile_records = high_water, n_layers, tile_launches, arrival
+        out.note = note
+        # (the library's slot table is overwritten by the next call: these are copies)
+        home = self._ws if out_buffer is None else out_buffer
+        out._table = (table, home, home.data_ptr(), n_records + 1)
         return out
 
 
@@ -403,10 +358,8 @@ class Clean:
 
     def run(self, d_raw, d_rec_off, d_out, d_out_off, scratch, stream: Optional[int] = None) -> CleanResult:
         """All arguments are CUDA tensors owned by the caller (uint8, int64, uint8, int64, uint8)."""
-        import torch
-
         if stream is None:
-            stream = torch.cuda.current_stream().cuda_stream
+            stream = _current_stream()
         res = CleanResult()
         st = lib().fbx_clean_run(self._h, d_raw.data_ptr() if d_raw.numel() else 0, d_raw.numel(), d_rec_off.data_ptr(),
                                  d_rec_off.numel() - 1, d_out.data_ptr() if d_out.numel() else 0, d_out.numel(),

@@ -9,6 +9,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libfbx.so")
+NATIVE = os.path.join(_HERE, "_native.so")          # the part of the Python binding that runs once per call
+NATIVE_SOURCE = os.path.join(CSRC, "fbx_native.cpp")
 SOURCES = ["fbx_plan.cpp", "fbx_api.cpp", "fbx_jit.cpp", "fbx_support.hip", "fbx_walk.hip", "fbx_tile.hip", "fbx_clean.hip"]
 HEADERS = ["fbx_internal.h", "fbx_device.h", "fbx_arena.h", "fbx_split.h", os.path.join(_ROOT, "include", "fbx.h")]
 
@@ -35,8 +37,26 @@ def command() -> list:
     ] + [os.path.join(CSRC, s) for s in SOURCES] + ["-ldl"]
 
 
+def native_command() -> list:
+    import sysconfig
+
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    return [
+        "g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden",
+        f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+        "-I", os.path.join(_ROOT, "include"), "-I", os.path.join(root, "include"),
+        "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-I", sysconfig.get_paths()["include"],
+        "-o", NATIVE, NATIVE_SOURCE,
+        "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
+    ]
+
+
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(NATIVE):
+        return True
+    if os.path.getmtime(NATIVE) < max(os.path.getmtime(NATIVE_SOURCE), os.path.getmtime(HEADERS[-1])):
         return True
     t = os.path.getmtime(LIB)
     deps = [os.path.join(CSRC, s) for s in SOURCES] + [h if os.path.isabs(h) else os.path.join(CSRC, h) for h in HEADERS]
@@ -48,7 +68,10 @@ def build(force: bool = True, verbose: bool = False) -> str:
         cmd = command()
         if verbose:
             print(" ".join(cmd), flush=True)
+        native = subprocess.Popen(native_command())   # (beside the device code, which takes longer)
         subprocess.check_call(cmd)
+        if native.wait():
+            raise subprocess.CalledProcessError(native.returncode, native.args)
     return LIB
 
 
