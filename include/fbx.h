@@ -14,7 +14,9 @@
  *   - Every call returns an fbx_status; nothing throws across this boundary.
  *   - "HOST" / "DEVICE" on a pointer says which memory it must point to.
  *   - The library never allocates device memory: all device storage (tables,
- *     scratch, results) lives in the workspace the caller hands over.
+ *     scratch, results) lives in the workspace the caller hands over.  (A plan's
+ *     first extraction takes a few KB of pinned HOST memory, which the kernels
+ *     write the call's sizes to; fbx_plan_destroy gives it back.)
  *   - A plan is not thread-safe; distinct plans are independent.
  */
 #ifndef FBX_H

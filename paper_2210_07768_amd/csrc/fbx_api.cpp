@@ -40,7 +40,8 @@ struct fbx_plan {
   // constant-table placement inside the workspace (byte offsets)
   uint64_t off_ctrl = 0, off_dyn = 0, off_ops = 0, off_layer_ops = 0, off_layer_begin = 0, off_nonroot = 0,
            off_aux = 0, off_fields = 0, off_field_ops = 0, off_prog_ops = 0, off_prog_fields = 0, off_row_total = 0,
-           off_tile_lists = 0, off_tile_list_begin = 0, off_rnr = 0, off_prof = 0, off_actual = 0, off_cap = 0, off_static_end = 0;
+           off_tile_lists = 0, off_tile_list_begin = 0, off_rnr = 0, off_prof = 0, off_actual = 0, off_cap = 0, off_place_order = 0, off_units = 0,
+           off_static_end = 0;
 
   // options
   int fused = 1;
@@ -72,8 +73,17 @@ struct fbx_plan {
   uint64_t id = 0;                // unique among the plans of this process (a destroyed plan's address may come back)
   std::vector<uint8_t> tables;    // image of the constant tables, as they lie at the head of a workspace
 
+  // where arrays go, worked out on the host when their sizes are known before the call
+  std::vector<uint32_t> place_order;   // see layout()
+  std::vector<uint32_t> units;         // per operator and row, as launch_setup wants them
+  uint32_t n_mh = 0, n_split = 0, n_gen = 0;  // as in TileParams
+  TileResident resident[4];
+
   // results of the last call
-  std::vector<uint8_t> readback;  // Ctrl + OpDyn[n_ops]
+  std::vector<uint8_t> readback;  // Ctrl, OpDyn[n_ops], signs per ragged operator
+  uint64_t* exported = nullptr;   // host memory that the tile kernel writes the same into (null: a copy is enqueued)
+  bool no_export = false;         // there is no such memory to be had
+  std::vector<OpDyn> placed;
   std::vector<fbx_slot_view> slots;
   std::vector<uint32_t> emitted;  // operator index of every emitted slot, spec order
 
@@ -103,7 +113,27 @@ struct fbx_plan {
     off_rnr = o; o = align_up(o + host.derive_tab.size() * 4);
     off_prof = o; o = align_up(o + 32 * 8);
     off_cap = o; o = align_up(o + host.n_ragged * 8ull);
+    off_place_order = o; o = align_up(o + n * 4);
+    off_units = o; o = align_up(o + (n + host.n_ragged > kPlaceInline ? (n + host.n_ragged) * 4ull : 0ull));
     off_static_end = o;
+    // the order in which arrays are placed when nothing is released: what is emitted, then the intermediates layer by layer
+    for (uint32_t i = 0; i < n; ++i)
+      if (host.ops[i].d.flags & F_EMIT) place_order.push_back(i);
+    for (uint32_t i : host.layer_ops)
+      if (!(host.ops[i].d.flags & F_EMIT)) place_order.push_back(i);
+    placed.resize(n);
+    units.resize(n + host.n_ragged);
+    readback.resize(off_actual + host.n_ragged * 8ull);
+    // numbers of the tile kernel's work lists (the ragged roots are sorted: multi-valued hashes, other multi-valued operators, the rest)
+    for (uint32_t i = host.tile_list_begin[TL_RAGROOT]; i < host.tile_list_begin[TL_RAGROOT + 1]; ++i) {
+      const OpDesc& d = host.ops[host.tile_lists[i]].d;
+      if (d.kind == OP_HASH) ++n_mh;
+      if (d.flags & F_MULTI) ++n_split;
+    }
+    for (uint32_t layer = 2; layer <= host.n_layers; ++layer) {
+      const uint32_t list = TL_LAYER + 2u * (layer - 2u) + 1u;
+      n_gen += host.tile_list_begin[list + 1] - host.tile_list_begin[list];
+    }
   }
 
   void build_tables() {
@@ -122,6 +152,7 @@ struct fbx_plan {
     if (!h.tile_lists.empty()) std::memcpy(img + off_tile_lists, h.tile_lists.data(), h.tile_lists.size() * 4);
     std::memcpy(img + off_tile_list_begin, h.tile_list_begin.data(), h.tile_list_begin.size() * 4);
     if (!h.derive_tab.empty()) std::memcpy(img + off_rnr, h.derive_tab.data(), h.derive_tab.size() * 4);
+    if (!place_order.empty()) std::memcpy(img + off_place_order, place_order.data(), place_order.size() * 4);
   }
 };
 
@@ -137,14 +168,10 @@ struct CallGeometry {
 uint32_t round16(uint64_t x) { return static_cast<uint32_t>((x + 15u) & ~uint64_t(15)); }
 
 // LDS layout of the tile kernel for tiles of 2^lt records and raw_cap staged bytes.
-void tile_lds_layout(const PlanHost& h, uint32_t lt, uint32_t raw_cap, TileParams& tp) {
+void tile_lds_layout(const fbx_plan& p, uint32_t lt, uint32_t raw_cap, TileParams& tp) {
+  const PlanHost& h = p.host;
   const uint32_t T = 1u << lt;
-  tp.n_mh = tp.n_split = 0;  // (the list is sorted: multi-valued hashes, other multi-valued operators, the rest)
-  for (uint32_t i = h.tile_list_begin[TL_RAGROOT]; i < h.tile_list_begin[TL_RAGROOT + 1]; ++i) {
-    const OpDesc& d = h.ops[h.tile_lists[i]].d;
-    if (d.kind == OP_HASH) ++tp.n_mh;
-    if (d.flags & F_MULTI) ++tp.n_split;
-  }
+  tp.n_mh = p.n_mh; tp.n_split = p.n_split; tp.n_gen = p.n_gen;
   tp.log2T = lt;
   tp.raw_cap = raw_cap;
   tp.row_stride = (h.n_fields + 1u) | 1u;  // odd: neighbouring records start in different banks
@@ -161,11 +188,6 @@ void tile_lds_layout(const PlanHost& h, uint32_t lt, uint32_t raw_cap, TileParam
   tp.o_base = o; o = round16(o + 8ull * h.n_ragged);
   tp.o_tot = o; o = round16(o + 4ull * h.n_ragged);
   tp.o_cap = o; o = round16(o + 8ull * h.n_ragged);
-  tp.n_gen = 0;
-  for (uint32_t layer = 2; layer <= h.n_layers; ++layer) {
-    const uint32_t list = TL_LAYER + 2u * (layer - 2u) + 1u;
-    tp.n_gen += h.tile_list_begin[list + 1] - h.tile_list_begin[list];
-  }
   tp.o_gfirst = o; o = round16(o + (tp.n_gen ? 4ull * h.ops.size() : 0ull));
   tp.o_gtot = o; o = round16(o + (tp.n_gen ? 4ull * (h.n_layers + 1u) : 0ull));
   tp.o_ioff = o; o = round16(o + 4ull * (tp.n_mh + 1));
@@ -198,7 +220,7 @@ bool tile_geometry(const fbx_plan& p, uint64_t raw_len, uint64_t n_records, Tile
       want = (want + step - 1) / step * step;
     }
     const uint32_t cap = p.raw_cap ? p.raw_cap : round16(std::min<uint64_t>(std::max<uint64_t>(want, 1024), 65000));
-    tile_lds_layout(h, static_cast<uint32_t>(lt), cap, tp);
+    tile_lds_layout(p, static_cast<uint32_t>(lt), cap, tp);
     const uint32_t limit = (lt == lt_lo) ? dev_max : std::min(p.lds_budget, dev_max);
     if (tp.lds_bytes <= limit) return true;
   }
@@ -266,7 +288,6 @@ fbx_status fbx_plan_create(const char* spec, size_t spec_len, fbx_plan** out) {
     if (p->host.ops[i].d.flags & F_EMIT) p->emitted.push_back(i);
   p->slots.resize(p->emitted.size());
   p->layout();
-  p->readback.resize(p->off_actual + p->host.n_ragged * 8ull);
   p->build_tables();
   static std::atomic<uint64_t> next_id{1};
   p->id = next_id.fetch_add(1);
@@ -279,6 +300,7 @@ void fbx_plan_destroy(fbx_plan* plan) {
   for (Timer& t : plan->timers)
     for (hipEvent_t e : t.ev)
       if (e) (void)hipEventDestroy(e);
+  if (plan->exported) (void)hipHostFree(plan->exported);
   delete plan;
 }
 
@@ -448,6 +470,7 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   P.layer_ops = reinterpret_cast<const uint32_t*>(ws + plan->off_layer_ops);
   P.layer_begin = reinterpret_cast<const uint32_t*>(ws + plan->off_layer_begin);
   P.nonroot = reinterpret_cast<const uint32_t*>(ws + plan->off_nonroot);
+  P.place_order = reinterpret_cast<const uint32_t*>(ws + plan->off_place_order);
   P.aux = ws + plan->off_aux;
   P.dyn = dyn; P.ctrl = ctrl;
   P.prog_ops = reinterpret_cast<OpProg*>(ws + plan->off_prog_ops);
@@ -495,15 +518,75 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   auto tile_launch = [&](const TileParams& Q, int mode) -> hipError_t {
     if (plan->compile && !reg.own_tables)
       if (const FixedTileKernel* k = plan->jit.get(Q, mode, plan->host, plan->tile_threads, plan->lane_ops)) return launch_tile_fixed(*k, Q, st);
-    return launch_tile(Q, mode, st);
+    return launch_tile(Q, mode, plan->resident, st);
+  };
+  // What the tile kernel writes into host memory when it is done: control block, then placements and signs per ragged
+  // operator (the latter alone where the host has placed the arrays itself).
+  if (g.tile_engine && g.n_tiles && !plan->exported && !plan->no_export) {
+    void* mem = nullptr;
+    if (hipHostMalloc(&mem, plan->readback.size(), hipHostMallocDefault) == hipSuccess) plan->exported = static_cast<uint64_t*>(mem);
+    else { (void)hipGetLastError(); plan->no_export = true; }
+  }
+  const Ctrl* c = nullptr;                  // of the last attempt
+  const uint64_t* actual = nullptr;
+  constexpr uint64_t kCtrlWords = sizeof(Ctrl) / 8;
+  // Sizes that are known before the launch are turned into addresses here: Algorithm 1 with the operators as its
+  // threads, in the order the allocation kernel takes them.  Returns the end of the last array.
+  auto place_on_host = [&](bool one) -> uint64_t {
+    uint64_t head = g.arena_base;
+    for (uint32_t i : plan->place_order) {
+      const OpDesc& d = h.ops[i].d;
+      const uint64_t n = d.arity ? n_records * d.arity : (one ? plan->cap_host[d.rag_row] : 0);
+      const uint64_t sv = align_up(n * 8, kPlaceUnit), so = d.arity ? 0 : align_up((n_records + 1) * 8, kPlaceUnit);
+      OpDyn& y = plan->placed[i];
+      y.values_off = head;
+      y.offsets_off = so ? head + sv : 0;
+      y.n_values = n;
+      plan->units[i] = static_cast<uint32_t>((head - g.arena_base) / kPlaceUnit);
+      head += sv + so;
+      if (head > (1ull << 60)) return head;
+    }
+    for (uint32_t r = 0; r < h.n_ragged; ++r) plan->units[n_ops + r] = static_cast<uint32_t>(one ? plan->cap_host[r] * 8 / kPlaceUnit : 0);
+    return head;
   };
   // One attempt: everything is enqueued on the stream, then one synchronisation.
   auto run = [&](bool one) -> fbx_status {
     for (Timer& t : plan->timers) t.used = false;
     plan->tile_launch_layer.clear();
-    FBX_LAUNCH(launch_reset(ctrl, g.arena_base, st), "reset");
+    bool copy_back = true;
+    c = reinterpret_cast<const Ctrl*>(plan->readback.data() + plan->off_ctrl);
+    actual = reinterpret_cast<const uint64_t*>(plan->readback.data() + plan->off_actual);
     if (g.tile_engine) {
       // one workgroup per tile takes its records through every layer; offsets are checked tile by tile
+      const bool on_host = one || !h.n_ragged;  // sizes are known before anything runs
+      SetupParams S{};
+      S.ops = P.ops; S.prog = P.prog_ops; S.ctrl = ctrl;
+      S.origin = reg.origin; S.arena_base = g.arena_base; S.n_ops = n_ops; S.n_ragged = h.n_ragged;
+      S.placed = on_host ? 1u : 0u;
+      if (on_host) {
+        const uint64_t end = place_on_host(one);
+        const bool fits = end <= ws_bytes && (end - g.arena_base) / kPlaceUnit <= 0xffffffffull;
+        if (!fits || !g.n_tiles) {  // nothing to run
+          Ctrl* mine = reinterpret_cast<Ctrl*>(plan->readback.data() + plan->off_ctrl);
+          *mine = Ctrl{};
+          mine->required = mine->high_water = end;
+          mine->err = fits ? 0u : static_cast<uint32_t>(CE_NOMEM);
+          return FBX_OK;
+        }
+        S.high_water = end;
+        if (plan->units.size() > kPlaceInline) {
+          FBX_LAUNCH(hipMemcpyAsync(ws + plan->off_units, plan->units.data(), plan->units.size() * 4, hipMemcpyHostToDevice, st), "placement upload");
+          S.units = reinterpret_cast<const uint32_t*>(ws + plan->off_units);
+        }
+        if (one) {
+          S.row_cap = reinterpret_cast<uint64_t*>(ws + plan->off_cap);
+          S.fill = plan->placement ? reinterpret_cast<uint64_t*>(ws + plan->off_actual) : P.tile_base;
+          S.fill_n = plan->placement ? h.n_ragged : uint64_t(h.n_ragged) * g.n_tiles;
+        }
+      }
+      tick(3, 0);
+      FBX_LAUNCH(launch_setup(S, plan->units.data(), st), "set-up kernel");
+      tick(3, 1);
       TileParams Q = g.tp;
       Q.raw = d_raw; Q.raw_len = raw_len; Q.rec_off = d_rec_off; Q.n_records = n_records;
       Q.prog = P.prog_ops;
@@ -530,39 +613,42 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
       Q.prof = reinterpret_cast<uint64_t*>(ws + plan->off_prof);
       FBX_LAUNCH(hipMemsetAsync(Q.prof, 0, 32 * 8, st), "clearing phase counters");
 #endif
-      if (one) {
-        // one launch: arrays sized from what the last call produced, bases found by look-back
-        Q.row_cap = reinterpret_cast<const uint64_t*>(ws + plan->off_cap);
-        Q.row_actual = reinterpret_cast<uint64_t*>(ws + plan->off_actual);
-        Q.lb_state = P.tile_base;
-        FBX_LAUNCH(hipMemcpyAsync(ws + plan->off_cap, plan->cap_host.data(), h.n_ragged * 8ull, hipMemcpyHostToDevice, st),
-                   "capacity upload");
-        tick(3, 0);
-        FBX_LAUNCH(launch_alloc(P, Q.row_cap, ws_bytes, 0, st), "allocation kernel");
-        tick(3, 1);
-        if (plan->placement) FBX_LAUNCH(launch_fill64(Q.row_actual, h.n_ragged, 0, st), "running totals");
-        else FBX_LAUNCH(launch_fill64(Q.lb_state, uint64_t(h.n_ragged) * g.n_tiles, 0, st), "look-back state");
+      auto export_from = [&](uint64_t from) {
+        if (!plan->exported) return;
+        Q.export_to = plan->exported;
+        Q.export_from = reinterpret_cast<const uint64_t*>(ws + from);
+        Q.export_words = static_cast<uint32_t>((plan->readback.size() - from) / 8);
+        c = reinterpret_cast<const Ctrl*>(plan->exported);
+        actual = plan->exported + kCtrlWords + (plan->off_actual - from) / 8;
+        copy_back = false;
+      };
+      if (on_host) {
+        int mode = 1;
+        if (one) {  // arrays sized from what the last call produced, bases found by look-back or in arrival order
+          Q.row_cap = S.row_cap;
+          Q.row_actual = reinterpret_cast<uint64_t*>(ws + plan->off_actual);
+          Q.lb_state = P.tile_base;
+          mode = plan->placement ? 3 : 2;
+        }
+        export_from(plan->off_actual);
         tick(4, 0);
-        FBX_LAUNCH(tile_launch(Q, plan->placement ? 3 : 2), "tile kernel (one launch)");
+        FBX_LAUNCH(tile_launch(Q, mode), "tile kernel");
         tick(4, 1);
         plan->tile_launch_layer.push_back(1);
       } else {
-        if (h.n_ragged) {
-          // the counting launch also needs the per-call programs: sizes are unknown, addresses unused
-          FBX_LAUNCH(launch_programs(P, st), "program kernel");
-          if (g.n_tiles) {
-            tick(1, 0);
-            FBX_LAUNCH(tile_launch(Q, 0), "tile kernel (counting)");
-            tick(1, 1);
-          }
-          tick(2, 0);
-          FBX_LAUNCH(launch_scan(P.tile_cnt, P.tile_base, row_total, reinterpret_cast<uint64_t*>(ws + g.off_scan_part), h.n_ragged, g.n_tiles, ctrl, st), "scan kernel");
-          tick(2, 1);
+        if (g.n_tiles) {
+          tick(1, 0);
+          FBX_LAUNCH(tile_launch(Q, 0), "tile kernel (counting)");
+          tick(1, 1);
         }
+        tick(2, 0);
+        FBX_LAUNCH(launch_scan(P.tile_cnt, P.tile_base, row_total, reinterpret_cast<uint64_t*>(ws + g.off_scan_part), h.n_ragged, g.n_tiles, ctrl, st), "scan kernel");
+        tick(2, 1);
         tick(3, 0);
         FBX_LAUNCH(launch_alloc(P, row_total, ws_bytes, 0, st), "allocation kernel");
         tick(3, 1);
         if (g.n_tiles) {
+          export_from(plan->off_dyn);
           tick(4, 0);
           FBX_LAUNCH(tile_launch(Q, 1), "tile kernel");
           tick(4, 1);
@@ -570,6 +656,7 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
         }
       }
     } else {
+      FBX_LAUNCH(launch_reset(ctrl, g.arena_base, st), "reset");
       tick(0, 0);
       FBX_LAUNCH(launch_validate(d_rec_off, n_records, raw_len, kTileLog2, ctrl, st), "validate");
       tick(0, 1);
@@ -605,8 +692,13 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
         }
       }
     }
-    FBX_LAUNCH(hipMemcpyAsync(plan->readback.data(), ws, plan->readback.size(), hipMemcpyDeviceToHost, st), "read-back");
+    if (copy_back) FBX_LAUNCH(hipMemcpyAsync(plan->readback.data(), ws, plan->readback.size(), hipMemcpyDeviceToHost, st), "read-back");
     FBX_LAUNCH(hipStreamSynchronize(st), "synchronise");
+    if (!(g.tile_engine && (one || !h.n_ragged))) {  // placed on the device
+      const OpDyn* y = copy_back ? reinterpret_cast<const OpDyn*>(plan->readback.data() + plan->off_dyn)
+                                 : reinterpret_cast<const OpDyn*>(plan->exported + kCtrlWords);
+      if (!c->err) std::copy(y, y + n_ops, plan->placed.begin());
+    }
 #ifdef FBX_TILE_PROF
     if (g.tile_engine) {
       uint64_t pc[32];
@@ -647,10 +739,9 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
       // (a sixty-fourth, and sixteen standard deviations of a count that size: operators that yield signs for
       // few records, many at a time, vary far more between batches than their size suggests)
       const unsigned __int128 cap = scaled + scaled / 64 + (unsigned __int128)(16.0 * std::sqrt((double)scaled)) + 256;
-      plan->cap_host[r] = cap > (unsigned __int128)(1ull << 60) ? (1ull << 60) : (uint64_t)cap;
+      plan->cap_host[r] = cap > (unsigned __int128)(1ull << 50) ? (1ull << 50) : ((uint64_t)cap + 15u) & ~15ull;  // (whole units of kPlaceUnit)
     }
   }
-  const Ctrl* c = reinterpret_cast<const Ctrl*>(plan->readback.data() + plan->off_ctrl);
   const char* fell_back = nullptr;
   for (;;) {
     fbx_status rs = run(one);
@@ -681,7 +772,7 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   if (resting && !fell_back) fell_back = "one-launch sequence not tried: a recent batch had a tile larger than the LDS section";
 #undef FBX_LAUNCH
 
-  const OpDyn* y = reinterpret_cast<const OpDyn*>(plan->readback.data() + plan->off_dyn);
+  const OpDyn* y = plan->placed.data();
   if (c->err & CE_OFFSETS) {
     plan->error = "record offsets must be non-decreasing and end within raw_len";
     return FBX_E_INPUT;
@@ -704,7 +795,6 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
     }
     return FBX_E_NOMEM;
   }
-  const uint64_t* actual = reinterpret_cast<const uint64_t*>(plan->readback.data() + plan->off_actual);
   if (h.n_ragged && n_records) {  // remember the sizes for the next call
     plan->learned_total.resize(h.n_ragged);
     for (const HostOp& op : h.ops)

@@ -24,6 +24,7 @@ struct WalkParams {
   const uint32_t* layer_ops;
   const uint32_t* layer_begin;
   const uint32_t* nonroot;
+  const uint32_t* place_order;  // operators in the order in which their arrays are placed when nothing is released
   const uint8_t* aux;
   OpDyn* dyn;
   OpProg* prog_ops;        // [n_ops], per call
@@ -81,6 +82,11 @@ struct TileParams {
   uint32_t o_tot, o_ioff, o_ctab, o_cap, o_gfirst, o_gtot;
   uint32_t item_cap;    // comma positions kept per record and multi-valued hash
   uint32_t lds_bytes;
+  // What the host needs to know when the call is done: the last workgroup to finish copies the control block and
+  // `export_words` words from `export_from` on to `export_to` (host memory; null: nothing is copied).
+  uint64_t* export_to;
+  const uint64_t* export_from;
+  uint32_t export_words;
   uint64_t* prof;  // 32 phase counters (tuning builds only), else NULL
   uint32_t dbg;    // phases to leave out (tuning builds only; results are then wrong)
 };
@@ -112,7 +118,11 @@ struct UnorderedParams {
 // mode 0: counting launch; 1: writing launch (bases from the scan over tiles);
 // 2: counting and writing in one launch (bases by look-back, arrays sized by row_cap);
 // 3: the same with bases by one atomic add per (ragged operator, tile) on row_actual: tiles in arrival order
-hipError_t launch_tile(const TileParams& P, int mode, hipStream_t st);
+struct TileResident {  // how many workgroups of a mode's kernel run at the same time: asked once per device and LDS size
+  int dev = -1;
+  uint32_t lds = 0, workgroups = 0;
+};
+hipError_t launch_tile(const TileParams& P, int mode, TileResident* known, hipStream_t st);  // known: 4 entries, by mode
 hipError_t launch_fill64(uint64_t* p, uint64_t n, uint64_t value, hipStream_t st);
 uint32_t tile_max_lds();  // dynamic LDS a workgroup of the tile kernel may ask for on this device
 
@@ -153,6 +163,29 @@ hipError_t launch_tile_fixed(const FixedTileKernel& k, const TileParams& P, hipS
 std::string tile_kernel_source(const TileParams& P, int mode, const PlanHost& h, uint32_t threads, uint32_t lane_ops);
 uint32_t tile_cu_count();
 
+// Everything that has to be in place before a tile kernel runs, in one launch: the control block, the operators'
+// programs with the addresses the host has chosen, the arrays' capacities, cleared look-back words or totals.
+struct SetupParams {
+  const OpDesc* ops;
+  OpProg* prog;
+  Ctrl* ctrl;
+  uint64_t* row_cap;      // [n_ragged] (placed, one-launch mode), else null
+  uint64_t* fill;         // fill_n words are set to zero
+  uint64_t fill_n;
+  uint64_t origin;        // address that array offsets count from
+  uint64_t arena_base;
+  uint64_t high_water;    // placed: end of the last array
+  const uint32_t* units;  // placement in device memory; null: it came with the launch
+  uint32_t n_ops, n_ragged;
+  uint32_t placed;        // 0: sizes are not known yet, addresses are left zero
+};
+constexpr uint32_t kPlaceUnit = 128;     // bytes: placements are passed on in units of this size
+constexpr uint32_t kPlaceInline = 880;   // placements that fit a launch's arguments (4 KB)
+// units (host, n_ops + n_ragged entries): where an operator's values start (from arena_base), then every row's
+// capacity (in units of kPlaceUnit bytes).  Up to kPlaceInline of them travel with the launch; for more, S.units
+// must point to a copy in device memory.
+hipError_t launch_setup(const SetupParams& S, const uint32_t* units, hipStream_t st);
+
 hipError_t launch_reset(Ctrl* ctrl, uint64_t arena_base, hipStream_t st);
 hipError_t launch_validate(const uint64_t* rec_off, uint64_t n_records, uint64_t raw_len, uint32_t log2T, Ctrl* ctrl,
                            hipStream_t st);
@@ -164,7 +197,6 @@ uint32_t scan_segments(uint32_t n_tiles);
 hipError_t launch_scan(const uint32_t* tile_cnt, uint64_t* tile_base, uint64_t* row_total, uint64_t* part, uint32_t n_ragged,
                        uint32_t n_tiles, const Ctrl* ctrl, hipStream_t st);
 hipError_t launch_alloc(const WalkParams& P, const uint64_t* row_total, uint64_t ws_bytes, int reuse, hipStream_t st);
-hipError_t launch_programs(const WalkParams& P, hipStream_t st);
 hipError_t launch_arena_alloc(uint64_t* head, const uint64_t* sizes, uint64_t n, uint64_t* offsets, uint32_t threads,
                               hipStream_t st);
 hipError_t launch_arena_reset(uint64_t* head, uint64_t value, hipStream_t st);

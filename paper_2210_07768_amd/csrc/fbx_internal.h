@@ -91,7 +91,7 @@ struct OpDyn {
 // Device control block at the head of the workspace (read back once per call).
 struct Ctrl {
   uint32_t err;            // bit 0 bad offsets, bit 1 out of memory, bit 2 count overflow, bit 3 tile too long
-  uint32_t pad0;
+  uint32_t finished;       // workgroups of the tile kernel that are done
   uint64_t required;       // workspace bytes needed (valid when the allocation kernel ran)
   uint64_t head;           // idle-memory head of the arena (byte offset from workspace base)
   uint64_t high_water;

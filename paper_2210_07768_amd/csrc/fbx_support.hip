@@ -13,7 +13,7 @@ namespace fbx {
 // --------------------------------------------------------------- validation
 __global__ void k_reset(Ctrl* ctrl, uint64_t arena_base) {
   if (threadIdx.x == 0) {
-    ctrl->err = 0; ctrl->pad0 = 0; ctrl->required = 0; ctrl->head = arena_base; ctrl->high_water = arena_base;
+    ctrl->err = 0; ctrl->finished = 0; ctrl->required = 0; ctrl->head = arena_base; ctrl->high_water = arena_base;
     ctrl->n_malformed = 0; ctrl->max_tile_bytes = 0; ctrl->slow_tiles = 0; ctrl->ticket[0] = 0; ctrl->ticket[1] = 0;
   }
 }
@@ -120,39 +120,42 @@ __global__ void k_arena_reset(uint64_t* head, uint64_t value) {
 }
 
 // Flattened per-call programs: everything a kernel needs about an operator (or
-// about a single-valued hash field) in one aligned record.  One block of kBlock threads.
-__device__ void write_programs(const WalkParams& P, bool placed) {
+// about a single-valued hash field) in one aligned record.
+__device__ __forceinline__ OpProg op_program(const OpDesc* ops, uint32_t i, uint64_t values, uint64_t offsets) {
+  const OpDesc& d = ops[i];
+  OpProg g;
+  g.kind = d.kind; g.flags = d.flags; g.arity = d.arity; g.rag_row = d.rag_row;
+  g.aux_off = d.aux_off; g.aux_len = d.aux_len; g.a = d.a; g.b = d.b;
+  g.key = d.key;
+  g.values = values;
+  g.offsets = offsets;
+  g.field = d.field;
+  g.stage = d.stage;
+  if (d.kind == OP_CROSS && ops[d.a].arity == 1 && ops[d.b].arity == 1) {
+    // a cross of two single signs finds both in the on-chip table: rows instead of aux data
+    g.aux_off = ops[d.a].stage;
+    g.aux_len = ops[d.b].stage;
+  }
+  if (d.kind == OP_CROSS && d.fuse) {
+    // a cross computed along with its multi-valued hash: the other input's row, and which side the hash is on
+    g.aux_off = ops[d.fuse == 1 ? d.b : d.a].stage;
+    g.aux_len = d.fuse == 1 ? 1u : 0u;
+  }
+  if (d.kind == OP_HASH && !d.arity) {  // a multi-valued hash: its crosses of that kind (first, number)
+    g.a = d.fuse & 0xffffu;
+    g.b = d.fuse >> 16;
+  }
+  return g;
+}
+// One block of kBlock threads, once the arrays are placed.
+__device__ void write_programs(const WalkParams& P) {
   const OpDesc* ops = P.ops;
   const OpDyn* dyn = P.dyn;
   const uint64_t origin = P.origin;
   const uint32_t tid = threadIdx.x;
   __syncthreads();
-  for (uint32_t i = tid; i < P.n_ops; i += kBlock) {
-    const OpDesc& d = ops[i];
-    OpProg g;
-    g.kind = d.kind; g.flags = d.flags; g.arity = d.arity; g.rag_row = d.rag_row;
-    g.aux_off = d.aux_off; g.aux_len = d.aux_len; g.a = d.a; g.b = d.b;
-    g.key = d.key;
-    g.values = placed ? origin + dyn[i].values_off : 0;
-    g.offsets = (placed && !d.arity) ? origin + dyn[i].offsets_off : 0;
-    g.field = d.field;
-    g.stage = d.stage;
-    if (d.kind == OP_CROSS && ops[d.a].arity == 1 && ops[d.b].arity == 1) {
-      // a cross of two single signs finds both in the on-chip table: rows instead of aux data
-      g.aux_off = ops[d.a].stage;
-      g.aux_len = ops[d.b].stage;
-    }
-    if (d.kind == OP_CROSS && d.fuse) {
-      // a cross computed along with its multi-valued hash: the other input's row, and which side the hash is on
-      g.aux_off = ops[d.fuse == 1 ? d.b : d.a].stage;
-      g.aux_len = d.fuse == 1 ? 1u : 0u;
-    }
-    if (d.kind == OP_HASH && !d.arity) {  // a multi-valued hash: its crosses of that kind (first, number)
-      g.a = d.fuse & 0xffffu;
-      g.b = d.fuse >> 16;
-    }
-    P.prog_ops[i] = g;
-  }
+  for (uint32_t i = tid; i < P.n_ops; i += kBlock)
+    P.prog_ops[i] = op_program(ops, i, origin + dyn[i].values_off, ops[i].arity ? 0 : origin + dyn[i].offsets_off);
   for (uint32_t k = tid; k < P.n_fields; k += kBlock) {
     const FieldDesc& f = P.fields[k];
     FieldProg g;
@@ -161,10 +164,39 @@ __device__ void write_programs(const WalkParams& P, bool placed) {
     if (f.cls == FC_HASH1) {
       const uint32_t op = P.field_ops[f.op_begin];
       g.key = ops[op].key;
-      g.dst = placed ? origin + dyn[op].values_off : 0;
+      g.dst = origin + dyn[op].values_off;
     }
     P.prog_fields[k] = g;
   }
+}
+
+// Before a tile kernel whose arrays the host has placed (their sizes are known: fixed arities, or capacities taken
+// from the call before).  A call of a few records is bound by launches and copies: a reset, an upload of the
+// capacities, a placement kernel that walked the layers and a fill took 14 us of kernels and as much again in gaps;
+// this launch takes 3.  The placement is four bytes an operator and travels with the launch's arguments.
+template <uint32_t N>
+struct PlaceArgs { uint32_t u[N]; };
+template <uint32_t N>
+__global__ __launch_bounds__(kBlock) void k_setup(SetupParams S, PlaceArgs<N> inl) {
+  const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+  const uint32_t* far = S.units;
+  auto unit = [&](uint32_t k) -> uint64_t { return (uint64_t)(far ? far[k] : inl.u[k]) * kPlaceUnit; };
+  if (i == 0) {
+    Ctrl c = {};
+    c.head = S.arena_base;
+    c.high_water = c.required = S.high_water;
+    *S.ctrl = c;
+  }
+  if (i < S.n_ops) {
+    uint64_t values = 0, offsets = 0;
+    if (S.placed) {
+      values = S.origin + S.arena_base + unit(i);
+      if (!S.ops[i].arity) offsets = values + unit(S.n_ops + S.ops[i].rag_row);
+    }
+    S.prog[i] = op_program(S.ops, i, values, offsets);
+  }
+  if (S.row_cap && i < S.n_ragged) S.row_cap[i] = unit(S.n_ops + i) / 8u;
+  for (uint64_t k = i; k < S.fill_n; k += (uint64_t)gridDim.x * kBlock) S.fill[k] = 0;
 }
 
 // Carve the operators' value / offset arrays out of the pool, once sizes are
@@ -186,35 +218,53 @@ __global__ __launch_bounds__(kBlock) void k_alloc(WalkParams P, const uint64_t* 
   const uint32_t tid = threadIdx.x;
   uint64_t high = ctrl->head;
   uint64_t persist_end = high;  // end of the emitted operators' storage
-  for (uint32_t pass = 0; pass <= n_layers; ++pass) {  // pass 0: emitted; pass l: intermediates of layer l
-    for (uint32_t c0 = 0; c0 < n_ops; c0 += kBlock) {
-      const uint32_t i = c0 + tid;
-      uint64_t sv = 0, so = 0, nv = 0;
-      bool mine = false;
-      if (i < n_ops) {
-        const OpDesc& d = ops[i];
-        const bool emit = d.flags & F_EMIT;
-        mine = pass == 0 ? emit : (!emit && d.layer == pass);
-        if (mine) {
-          nv = d.arity ? n_records * d.arity : row_total[d.rag_row];
-          sv = round128(nv * 8ull);
-          so = d.arity ? 0 : round128((n_records + 1) * 8ull);
-        }
-      }
-      const uint64_t off = arena_alloc_wg(&ctrl->head, sv + so, s_part);
-      if (mine) {
-        dyn[i].values_off = off;
-        dyn[i].offsets_off = so ? off + sv : 0;
-        dyn[i].n_values = nv;
-        dyn[i].pad = off + sv + so;  // end of this operator's storage
-      }
+  // one Algorithm-1 allocation for the operators of kBlock threads; i: the thread's operator, or none
+  auto place = [&](uint32_t i, bool mine) {
+    uint64_t sv = 0, so = 0, nv = 0;
+    if (mine) {
+      const OpDesc& d = ops[i];
+      nv = d.arity ? n_records * d.arity : row_total[d.rag_row];
+      sv = round128(nv * 8ull);
+      so = d.arity ? 0 : round128((n_records + 1) * 8ull);
     }
-    __threadfence();
+    const uint64_t off = arena_alloc_wg(&ctrl->head, sv + so, s_part);
+    if (mine) {
+      dyn[i].values_off = off;
+      dyn[i].offsets_off = so ? off + sv : 0;
+      dyn[i].n_values = nv;
+      dyn[i].pad = off + sv + so;  // end of this operator's storage
+    }
+    return off + sv + so;
+  };
+  if (!reuse) {  // nothing is released: the same placement without going layer by layer
+    uint64_t end = high;
+    for (uint32_t c0 = 0; c0 < n_ops; c0 += kBlock) {
+      const uint32_t k = c0 + tid;
+      end = max(end, place(k < n_ops ? P.place_order[k] : 0u, k < n_ops));
+    }
+    for (int d = 32; d >= 1; d >>= 1) end = max(end, (uint64_t)__shfl_xor((unsigned long long)end, d, 64));
+    if ((tid & 63u) == 0) s_part[tid >> 6] = end;
     __syncthreads();
-    const uint64_t head_now = *reinterpret_cast<volatile uint64_t*>(&ctrl->head);
-    if (head_now > high) high = head_now;
-    if (pass == 0) persist_end = head_now;
-    if (pass >= 1 && reuse) {
+    for (uint32_t w = 0; w < kBlock / 64; ++w) high = max(high, s_part[w]);
+  } else {
+    for (uint32_t pass = 0; pass <= n_layers; ++pass) {  // pass 0: emitted; pass l: intermediates of layer l
+      for (uint32_t c0 = 0; c0 < n_ops; c0 += kBlock) {
+        const uint32_t i = c0 + tid;
+        bool mine = false;
+        if (i < n_ops) {
+          const bool emit = ops[i].flags & F_EMIT;
+          mine = pass == 0 ? emit : (!emit && ops[i].layer == pass);
+        }
+        place(i, mine);
+      }
+      __threadfence();
+      __syncthreads();
+      const uint64_t head_now = *reinterpret_cast<volatile uint64_t*>(&ctrl->head);
+      if (head_now > high) high = head_now;
+      if (pass == 0) {
+        persist_end = head_now;
+        continue;
+      }
       // release: the head drops to the end of the highest still-live intermediate
       if (tid == 0) s_max = persist_end;
       __syncthreads();
@@ -240,12 +290,8 @@ __global__ __launch_bounds__(kBlock) void k_alloc(WalkParams P, const uint64_t* 
     for (uint32_t i = tid; i < n_ops; i += kBlock)
       if (!ops[i].arity) *reinterpret_cast<uint64_t*>(P.origin + dyn[i].offsets_off) = 0;
   }
-  write_programs(P, true);
+  write_programs(P);
 }
-
-// The per-call programs alone, without placement (array addresses are left zero):
-// all the counting launch of the tile kernel needs.
-__global__ __launch_bounds__(kBlock) void k_programs(WalkParams P) { write_programs(P, false); }
 
 __global__ void k_fill64(uint64_t* p, uint64_t n, uint64_t value) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) p[i] = value;
@@ -305,9 +351,19 @@ hipError_t launch_fill64(uint64_t* p, uint64_t n, uint64_t value, hipStream_t st
   return hipGetLastError();
 }
 
-hipError_t launch_programs(const WalkParams& P, hipStream_t st) {
-  hipLaunchKernelGGL(k_programs, dim3(1), dim3(kBlock), 0, st, P);
+template <uint32_t N>
+static hipError_t launch_setup_n(const SetupParams& S, const uint32_t* units, uint32_t n, hipStream_t st) {
+  PlaceArgs<N> a;
+  if (n) std::copy(units, units + n, a.u);
+  const uint64_t threads = std::max<uint64_t>({1, S.n_ops, S.n_ragged, std::min<uint64_t>(S.fill_n, 2048ull * kBlock)});
+  hipLaunchKernelGGL(k_setup<N>, dim3((uint32_t)((threads + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, S, a);
   return hipGetLastError();
+}
+hipError_t launch_setup(const SetupParams& S, const uint32_t* units, hipStream_t st) {
+  const uint32_t n = S.placed && !S.units ? S.n_ops + S.n_ragged : 0u;
+  if (n <= 64u) return launch_setup_n<64>(S, units, n, st);  // (less to copy for the small plans of small calls)
+  if (n <= 256u) return launch_setup_n<256>(S, units, n, st);
+  return n <= kPlaceInline ? launch_setup_n<kPlaceInline>(S, units, n, st) : hipErrorInvalidValue;
 }
 
 hipError_t launch_arena_alloc(uint64_t* head, const uint64_t* sizes, uint64_t n, uint64_t* offsets, uint32_t threads,

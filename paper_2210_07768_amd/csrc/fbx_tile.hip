@@ -1330,7 +1330,7 @@ __device__ __forceinline__ bool lb_place_row(const TileParams& P, const Sh& sh, 
         small = true;
       } else {
         sh.base[c] = before;
-        if (tile + 1u == P.n_tiles) gptr(P.row_actual)[c] = before + sh.tot[c];
+        if (tile + 1u == P.n_tiles) lb_store(P.row_actual + c, before + sh.tot[c]);
       }
     }
   }
@@ -1341,7 +1341,7 @@ __device__ __forceinline__ bool lb_place_row(const TileParams& P, const Sh& sh, 
   if (lane == 0) {
     lb_store(st + tile, abort ? kLbAbort : (kLbPrefix | (excl + agg)));
     sh.base[row] = excl;
-    if (tile + 1u == P.n_tiles) gptr(P.row_actual)[row] = excl + agg;
+    if (tile + 1u == P.n_tiles) lb_store(P.row_actual + row, excl + agg);
   }
   return !abort;
 }
@@ -1832,6 +1832,29 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
   }
 }
 
+// What the host reads after the call, straight into its memory: a copy enqueued behind the kernel is a launch of its
+// own (4 us and the gap before it).  What is copied was written by earlier kernels or by device-scope atomics, so it
+// needs no cache write-back, only that every wavefront's own have arrived before its workgroup counts as done.
+__device__ __forceinline__ void export_results(const TileParams& P) {
+  __shared__ uint32_t s_last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomicAdd(&P.ctrl->finished, 1u) + 1u == gridDim.x ? 1u : 0u;
+  __syncthreads();
+  if (!s_last) return;
+  constexpr uint32_t kCtrlWords = sizeof(Ctrl) / 8u;
+  for (uint32_t i = threadIdx.x; i < kCtrlWords + P.export_words; i += kTileThreads) {
+    const uint64_t v = lb_load(i < kCtrlWords ? reinterpret_cast<uint64_t*>(P.ctrl) + i : const_cast<uint64_t*>(P.export_from) + (i - kCtrlWords));
+    __hip_atomic_store(P.export_to + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+template <int MODE>
+__device__ __forceinline__ void tile_entry(const TileParams& P) {
+  tile_body<MODE>(P);
+  if (P.export_to) export_results(P);
+}
+
 #ifndef FBX_FIXED_MODE
 // ---- one ragged root operator with in-kernel allocation, results behind per-record pointers
 // Section 5 as the paper uses it (Figure 5): a thread works out how much memory its result needs,
@@ -1893,7 +1916,7 @@ __global__ __launch_bounds__(kBlock) void k_unordered(UnorderedParams U) {
 // The kernel for any plan: everything it needs to know arrives in P.
 template <int MODE>
 __global__ __launch_bounds__(kTileThreads, 4) void k_tile(TileParams P) {
-  tile_body<MODE>(P);
+  tile_entry<MODE>(P);
 }
 #endif
 
@@ -1920,7 +1943,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_tile(TileParams P) {
 extern "C" __global__ __launch_bounds__(kTileThreads, FBX_FIXED_WAVES) FBX_SIZE_ATTR void FBX_FIXED_NAME(TileParams Pin) {
   TileParams P = Pin;
   FBX_FIXED_ASSIGN
-  tile_body<FBX_FIXED_MODE>(P);
+  tile_entry<FBX_FIXED_MODE>(P);
 }
 #endif
 
@@ -1939,23 +1962,31 @@ uint32_t tile_max_lds() {
   return cached;
 }
 
-hipError_t launch_tile(const TileParams& P, int mode, hipStream_t st) {
+hipError_t launch_tile(const TileParams& P, int mode, TileResident* known, hipStream_t st) {
   if (P.n_tiles == 0) return hipSuccess;
-  const void* fn = mode == 0   ? reinterpret_cast<const void*>(&k_tile<0>)
-                   : mode == 1 ? reinterpret_cast<const void*>(&k_tile<1>)
-                   : mode == 2 ? reinterpret_cast<const void*>(&k_tile<2>)
-                               : reinterpret_cast<const void*>(&k_tile<3>);
-  if (P.lds_bytes > 48u * 1024u) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P.lds_bytes);
-    if (e != hipSuccess) return e;
+  TileResident& k = known[mode];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); dev = 0; }
+  if (k.dev != dev || k.lds != P.lds_bytes) {
+    const void* fn = mode == 0   ? reinterpret_cast<const void*>(&k_tile<0>)
+                     : mode == 1 ? reinterpret_cast<const void*>(&k_tile<1>)
+                     : mode == 2 ? reinterpret_cast<const void*>(&k_tile<2>)
+                                 : reinterpret_cast<const void*>(&k_tile<3>);
+    if (P.lds_bytes > 48u * 1024u) {
+      hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P.lds_bytes);
+      if (e != hipSuccess) return e;
+    }
+    // as many workgroups as can run at the same time (the one-launch mode relies on it)
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kTileThreads, P.lds_bytes) != hipSuccess || per_cu < 1) {
+      (void)hipGetLastError();
+      per_cu = 1;
+    }
+    k.dev = dev;
+    k.lds = P.lds_bytes;
+    k.workgroups = tile_cu_count() * (uint32_t)per_cu;
   }
-  // as many workgroups as can run at the same time (the one-launch mode relies on it)
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kTileThreads, P.lds_bytes) != hipSuccess || per_cu < 1) {
-    (void)hipGetLastError();
-    per_cu = 1;
-  }
-  uint32_t capacity = tile_cu_count() * (uint32_t)per_cu;
+  uint32_t capacity = k.workgroups;
   if (P.grid && P.grid < capacity) capacity = P.grid;
   TileParams Q = P;
   const uint32_t grid = std::min(P.n_tiles, capacity);
