@@ -54,6 +54,7 @@ struct CleanOp {
 
 struct OpField {
   uint32_t field, first_op;  // its operators are ops[first_op .. the next entry's first_op)
+  uint32_t keyed;            // the first of them looks a key up
 };
 
 struct CleanParams {
@@ -65,7 +66,8 @@ struct CleanParams {
   const uint32_t* first_op;   // [n_fields + 1] the operators of field k are ops[first_op[k] .. first_op[k + 1])
   const uint8_t* args;
   uint32_t n_fields;
-  uint32_t n_of, n_ops, args_bytes;
+  uint32_t n_of, n_ops, args_bytes, n_keyed;
+  const uint32_t* keyed;      // [n_keyed] entries of `of` whose first operator looks a key up
   const OpField* of;          // [n_of + 1] the fields that have operators, in order
   uint32_t* lens;             // one record per thread.  [2][n_records]: bytes of the cleaned record (0: dropped); 1 if kept
   const uint64_t* base;       // [2][n_records]: where a kept record goes; its number among the kept ones
@@ -84,7 +86,7 @@ struct CleanParams {
   uint32_t log2T;       // records per tile
   uint32_t raw_cap;     // bytes of the text section in LDS (a multiple of 16)
   uint32_t row_stride;  // 16-bit entries per record in the table of field ends
-  uint32_t o_args, o_rows, o_new, o_of, o_ops;  // where the tables start in LDS
+  uint32_t o_args, o_rows, o_new, o_of, o_ops, o_keyed;  // where the tables start in LDS
   uint32_t o_seg, o_later;                      // (the writing launch; the text and the arguments lie at the same places)
   uint64_t* export_to;  // host memory: control block and totals, written by the last workgroup to finish (null: none)
 };
@@ -294,25 +296,34 @@ __global__ __launch_bounds__(kCleanThreads, CLEAN_WAVES) void k_clean_measure_ti
   clean_table(C.o_args, C.args, C.args_bytes);  // (the newline at its end: see fbx_clean_create)
   clean_table(C.o_of, C.of, (C.n_of + 1u) * (uint32_t)sizeof(OpField));
   clean_table(C.o_ops, C.ops, C.n_ops * (uint32_t)sizeof(CleanOp));
+  clean_table(C.o_keyed, C.keyed, C.n_keyed * 4u);
+  const uint32_t* keyed = reinterpret_cast<const uint32_t*>(clean_smem + C.o_keyed);
   const uint32_t newline = C.o_args + C.args_bytes - 1u;
   // lanes that share a record: 256 / T, at most 64
   const uint32_t lg = 8u - C.log2T < 6u ? 8u - C.log2T : 6u;
   const uint32_t gsz = 1u << lg, j = tid & (gsz - 1u), rr = tid >> lg;
   const uintptr_t ok_lo = reinterpret_cast<uintptr_t>(C.raw), ok_hi = ok_lo + C.raw_len;
+  // The next tile's record offsets are requested a tile ahead.  (Touching its text as well gains nothing: vector
+  // instructions bound this kernel.)
+  uint64_t off_next = 0;
+  auto request_offsets = [&](uint32_t tile) {
+    const uint64_t g = ((uint64_t)tile << C.log2T) + tid;
+    if (tid <= T && g <= C.n_records) off_next = C.rec_off[g];
+  };
+  request_offsets(blockIdx.x * C.run);
   uint64_t run_bytes = 0, run_kept = 0;  // (of lane 63 of the first wavefront)
   const uint32_t first_tile = blockIdx.x * C.run, end_tile = min(first_tile + C.run, C.n_tiles);
   for (uint32_t tile = first_tile; tile < end_tile; ++tile) {
+    const uint64_t g0 = (uint64_t)tile << C.log2T;
+    const uint32_t nb = (uint32_t)min((uint64_t)T, C.n_records - g0);
     __syncthreads();  // (the sections are reused by the next tile)
     if (tid == 0) s_bad = 0;
     if (tid < kCleanMaxT) s_drop[tid] = 0;
+    if (tid <= nb) s_off[tid] = off_next;
     __syncthreads();
-    const uint64_t g0 = (uint64_t)tile << C.log2T;
-    const uint32_t nb = (uint32_t)min((uint64_t)T, C.n_records - g0);
     if (tid <= nb) {
-      const uint64_t a = C.rec_off[g0 + tid];
-      s_off[tid] = a;
       if (tid < nb) {
-        const uint64_t b = C.rec_off[g0 + tid + 1];
+        const uint64_t a = off_next, b = s_off[tid + 1u];
         if (a > b || b > C.raw_len) atomicOr(&s_bad, (uint32_t)CE_OFFSETS);
         else if (b - a >= (1ull << 31)) atomicOr(&s_bad, (uint32_t)CE_TILE);
       }
@@ -344,6 +355,7 @@ __global__ __launch_bounds__(kCleanThreads, CLEAN_WAVES) void k_clean_measure_ti
         for (uint32_t c = tid; c < nchunks; c += kCleanThreads)
           *reinterpret_cast<u32x4*>(raw + kCleanRawPad + 16u * c) = text_chunk(a0 + 16u * c, ok_lo, ok_hi);
       }
+      request_offsets(tile + 1u);
       __syncthreads();
       // field ends; entries from the record's tab count on hold its end
       if (act) {
@@ -358,6 +370,38 @@ __global__ __launch_bounds__(kCleanThreads, CLEAN_WAVES) void k_clean_measure_ti
         for (uint32_t kk = tabs + j; kk < F; kk += gsz) row[1u + kk] = (uint16_t)re;
       }
       __syncthreads();
+      // A key is looked up by all lanes of its record, eight bytes of the field a lane: pairs begin at the field's first
+      // byte and after every ';', and the first one that begins with the name and a ':' is the one.  (A name with a
+      // ':' or ';' in it is no key, see fbx_clean_create.  One lane a field, pair by pair, kept the other wavefronts
+      // waiting: 145 of this launch's 357 us.)
+      for (uint32_t q = 0; q < C.n_keyed; ++q) {
+        const uint32_t i = keyed[q];
+        const CleanOp op = ops[of[i].first_op];
+        const uint32_t arg = C.o_args + op.arg_off, len = op.arg_len;
+        uint32_t s = 0, e = 0, at = ~0u;
+        if (act) {
+          const uint16_t* rw = rows + rr * C.row_stride + of[i].field;
+          s = (uint32_t)rw[0] + 1u;
+          e = rw[1];
+          auto is_it = [&](uint32_t p) -> bool { return p + len < e && raw[p + len] == ':' && lds_same(p, arg, len); };
+          for (uint32_t p = s + 8u * j; p < e && at == ~0u; p += 8u * gsz) {
+            if (p == s && is_it(p)) { at = p; break; }
+            uint32_t x0, x1;
+            lds_window(p, x0, x1);
+            uint64_t f = ((uint64_t)eq_flags(x1, 0x3b3b3b3bu) << 32) | eq_flags(x0, 0x3b3b3b3bu);
+            for (; f; f &= f - 1u) {
+              const uint32_t c = p + ((uint32_t)__builtin_ctzll(f) >> 3) + 1u;
+              if (is_it(c)) { at = c; break; }
+            }
+          }
+        }
+        for (uint32_t d = 1; d < gsz; d <<= 1) at = min(at, (uint32_t)__shfl_xor((int)at, (int)d, 64));
+        if (act && j == 0) {
+          const uint32_t v = at + len + 1u;
+          fnew[i * (T + 1u) + rr] = at == ~0u ? two(s, 0u) : two(v, lds_find(v, e, 0x3b3b3b3bu) - v);
+        }
+      }
+      if (C.n_keyed) __syncthreads();
       // lanes as (record, field with operators) pairs, the records of one field side by side: they run the same
       // operators (fields side by side had every wavefront walk the one keyed column with two lanes: 589 instead of
       // 409 vector instructions a record, both launches together)
@@ -368,15 +412,20 @@ __global__ __launch_bounds__(kCleanThreads, CLEAN_WAVES) void k_clean_measure_ti
         const uint16_t* rw = rows + r * C.row_stride + k;
         const uint32_t s = (uint32_t)rw[0] + 1u, e = rw[1];
         Field f{s, e > s ? e - s : 0u};  // (a missing field is empty)
+        uint32_t o = of[i].first_op;
+        if (of[i].keyed) {
+          const uint32_t w = fnew[i * (T + 1u) + r];
+          f = Field{lo16(w), hi16(w)};
+          ++o;
+        }
         bool keep = true;
-        for (uint32_t o = of[i].first_op; o < o1 && keep; ++o) {
+        for (; o < o1 && keep; ++o) {
           const CleanOp op = ops[o];
           const uint32_t arg = C.o_args + op.arg_off;
           if (op.kind == CK_FILL) {
             if (f.n == 0) f = Field{arg, op.arg_len};
           } else if (op.kind == CK_KEY) {
-            // value of the first pair "key:value" (pairs separated by ';') whose key is exactly the name: a
-            // name without ':' and ';' is that key when the pair begins with it and a ':' follows
+            // (not the field's first operator: pair by pair)
             const uint32_t fe = f.at + f.n;
             uint32_t p = f.at;
             for (;;) {
@@ -420,12 +469,15 @@ __global__ __launch_bounds__(kCleanThreads, CLEAN_WAVES) void k_clean_measure_ti
         s_len[rr] = content + pads + grow + 1u;
         s_nseg[rr] = s_drop[rr] ? 0u : 1u + 2u * edits + (pads ? 1u : 0u) + (end_nl && !pads ? 0u : 1u);
       }
-    } else if (tid < nb) {
-      uint64_t n = 0;
-      const bool kept = measure_in_place(C, g0 + tid, n);
-      s_len[tid] = kept ? (uint32_t)n : 0u;
-      s_drop[tid] = kept ? 0u : 1u;
-      s_nseg[tid] = 0;
+    } else {
+      if (tid < nb) {
+        uint64_t n = 0;
+        const bool kept = measure_in_place(C, g0 + tid, n);
+        s_len[tid] = kept ? (uint32_t)n : 0u;
+        s_drop[tid] = kept ? 0u : 1u;
+        s_nseg[tid] = 0;
+      }
+      request_offsets(tile + 1u);
     }
     __syncthreads();
     if (wave == 0) {  // where records go inside the tile
@@ -691,7 +743,8 @@ struct fbx_clean {
   std::vector<uint32_t> first_op;    // n_fields + 1
   std::vector<uint8_t> args;
   std::vector<uint8_t> image;        // ops, first_op, args as they lie in the scratch
-  uint64_t off_ops = 0, off_first = 0, off_args = 0, off_of = 0;
+  uint64_t off_ops = 0, off_first = 0, off_args = 0, off_of = 0, off_keyed = 0;
+  std::vector<uint32_t> keyed;       // entries of the table of fields with operators whose first one looks a key up
   uint32_t n_of = 0, args_bytes = 0;
   uint64_t* exported = nullptr;      // host memory that the tile kernel writes control block and totals to
   bool no_export = false;
@@ -822,19 +875,25 @@ fbx_status fbx_clean_create(const char* spec, size_t spec_len, fbx_clean** out) 
   for (uint32_t k = 0; k < c->n_fields; ++k) c->first_op[k + 1] += c->first_op[k];
   std::vector<OpField> of;
   for (uint32_t k = 0; k < c->n_fields; ++k)
-    if (c->first_op[k + 1] > c->first_op[k]) of.push_back(OpField{k, c->first_op[k]});
+    if (c->first_op[k + 1] > c->first_op[k]) {
+      const bool key = c->ops[c->first_op[k]].kind == CK_KEY;
+      if (key) c->keyed.push_back(static_cast<uint32_t>(of.size()));
+      of.push_back(OpField{k, c->first_op[k], key ? 1u : 0u});
+    }
   c->n_of = static_cast<uint32_t>(of.size());
-  of.push_back(OpField{c->n_fields, static_cast<uint32_t>(c->ops.size())});
+  of.push_back(OpField{c->n_fields, static_cast<uint32_t>(c->ops.size()), 0u});
   c->args.resize(c->args.size() / 4 * 4 + 4, '\n');  // whole words, the last byte a newline
   c->args_bytes = static_cast<uint32_t>(c->args.size());
   uint64_t o = 0;
   c->off_ops = o; o += c->ops.size() * sizeof(CleanOp);
   c->off_of = o; o += of.size() * sizeof(OpField);
+  c->off_keyed = o; o += c->keyed.size() * 4;
   c->off_args = o; o += c->args.size();
   c->off_first = o; o += c->first_op.size() * 4;
   c->image.assign(o, 0);
   if (!c->ops.empty()) std::memcpy(c->image.data() + c->off_ops, c->ops.data(), c->ops.size() * sizeof(CleanOp));
   std::memcpy(c->image.data() + c->off_of, of.data(), of.size() * sizeof(OpField));
+  if (!c->keyed.empty()) std::memcpy(c->image.data() + c->off_keyed, c->keyed.data(), c->keyed.size() * 4);
   std::memcpy(c->image.data() + c->off_args, c->args.data(), c->args.size());
   std::memcpy(c->image.data() + c->off_first, c->first_op.data(), c->first_op.size() * 4);
   *out = c.release();
@@ -886,6 +945,8 @@ fbx_status fbx_clean_run(fbx_clean* clean, const uint8_t* d_raw, uint64_t raw_le
   C.ops = reinterpret_cast<const CleanOp*>(sc + L.tables + clean->off_ops);
   C.first_op = reinterpret_cast<const uint32_t*>(sc + L.tables + clean->off_first);
   C.of = reinterpret_cast<const OpField*>(sc + L.tables + clean->off_of);
+  C.keyed = reinterpret_cast<const uint32_t*>(sc + L.tables + clean->off_keyed);
+  C.n_keyed = static_cast<uint32_t>(clean->keyed.size());
   C.args = sc + L.tables + clean->off_args;
   C.n_fields = clean->n_fields; C.n_of = clean->n_of; C.n_ops = static_cast<uint32_t>(clean->ops.size());
   C.args_bytes = clean->args_bytes;
@@ -899,7 +960,7 @@ fbx_status fbx_clean_run(fbx_clean* clean, const uint8_t* d_raw, uint64_t raw_le
   const uint64_t mean = n_records ? raw_len / n_records + 1 : 1;
   const uint64_t F = clean->n_fields;
   const uint64_t row_stride = (F + 2 + 7) & ~uint64_t(7);
-  const uint64_t fixed = clean->args_bytes + 16 + (clean->n_of + 1) * sizeof(OpField) + C.n_ops * sizeof(CleanOp) + 64;
+  const uint64_t fixed = clean->args_bytes + 16 + (clean->n_of + 1) * sizeof(OpField) + C.n_ops * sizeof(CleanOp) + clean->keyed.size() * 4 + 80;
   auto segs = [&](uint64_t T) { return T * (2ull * clean->n_of + 3) + 1; };
   auto tables = [&](uint64_t T) { return std::max(T * row_stride * 2 + (T + 1) * clean->n_of * 4ull, segs(T) * 6 + 16) + fixed; };
   uint32_t log2T = 6;
@@ -918,7 +979,8 @@ fbx_status fbx_clean_run(fbx_clean* clean, const uint8_t* d_raw, uint64_t raw_le
     C.o_new = up16(C.o_rows + T * row_stride * 2);
     C.o_of = up16(C.o_new + (T + 1) * clean->n_of * 4);
     C.o_ops = up16(C.o_of + (clean->n_of + 1) * sizeof(OpField));
-    lds_measure = up16(C.o_ops + C.n_ops * sizeof(CleanOp)) + 16;
+    C.o_keyed = up16(C.o_ops + C.n_ops * sizeof(CleanOp));
+    lds_measure = up16(C.o_keyed + clean->keyed.size() * 4) + 16;
     C.o_seg = behind;
     // (a chunk that covers several segments holds the end of one of them: no more chunks than those and the two ends)
     C.o_later = up16(C.o_seg + segs(T) * 4);
