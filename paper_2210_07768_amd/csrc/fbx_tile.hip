@@ -1597,15 +1597,22 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
   const uint32_t tid = threadIdx.x;
   const uint32_t T = 1u << P.log2T;
   const FBX_GLOBAL uint64_t* rec_off = gptr(P.rec_off);
-  uint32_t* ticket = &P.ctrl->ticket[WRITE ? 1 : 0];  // (MODE 2 needs the order the counter gives: see lb_place_row)
+  uint32_t* ticket = &P.ctrl->ticket[WRITE ? 1 : 0];
   const uintptr_t ok_lo = reinterpret_cast<uintptr_t>(P.raw), ok_hi = ok_lo + P.raw_len;
-  // Tiles are taken off a counter.  A workgroup takes its next tile when it starts on the
-  // current one (that early, so that the next tile's offsets and text can be on their way),
-  // never more than one ahead: tiles are then started in the order of their numbers, give
-  // or take how long single tiles take, which is what the one-launch placement needs.
+  // Where tiles wait for the tiles before them (MODE 2, see lb_place_row) they are taken off a counter.  A
+  // workgroup takes its next tile when it starts on the current one (that early, so that the
+  // next tile's offsets and text can be on their way), never more than one ahead: tiles are
+  // then started in the order of their numbers, give or take how long single tiles take.
+  // Elsewhere a workgroup's first tile is its own number: adding to one address, the whole chip
+  // gets about 75 answers a microsecond, and the last of 512 workgroups would start 7 us late.
+  // Its further tiles come from the counter where tiles differ in length (ragged operators: the
+  // four-layer workload is 7 % faster that way), else they are every gridDim.x-th one.
+  constexpr bool kInOrder = MODE == 2;
+  const bool counter = kInOrder || P.n_ragged != 0u;
+  const uint32_t counted_from = kInOrder ? 0u : gridDim.x;
   if (tid == 0) {
     s_err = P.ctrl->err;  // set by an earlier kernel of this call: nothing may be written
-    s_cur = atomicAdd(ticket, 1u);
+    s_cur = kInOrder ? atomicAdd(ticket, 1u) : blockIdx.x;
     s_bad[0] = s_bad[1] = 0;
   }
   {  // the operators' programs in the order of the work lists, their inputs a and b renumbered alike
@@ -1665,7 +1672,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
     // its offsets and text with nothing to hide behind (the largest one-layer workload: 5 % faster; a
     // two-layer plan, whose single crosses sit between counts and bases: 7 % slower, so it keeps the early ticket).
     const bool late_ticket = MODE == 2 && P.n_layers == 1u;
-    if (!late_ticket && tid == 0) my_ticket = atomicAdd(ticket, 1u);  // the next tile; the answer is picked up a barrier later
+    if (counter && !late_ticket && tid == 0) my_ticket = counted_from + atomicAdd(ticket, 1u);  // the next tile; the answer is picked up a barrier later
     uint64_t* off = sh.off + par * (T + 1u);
     uint64_t* off2 = sh.off + (par ^ 1u) * (T + 1u);
     const uint64_t g0 = (uint64_t)tile << P.log2T;
@@ -1695,13 +1702,13 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
     // and one byte of every 128-byte line of its text is requested, which brings the text into
     // the L2 cache without holding registers for it.  Only the two outer offsets decide what is
     // touched; the tile itself is checked when its turn comes.
-    uint32_t pf_stage = 0, nxt = 0xffffffffu, nrec2 = 0, touch = 0;
+    uint32_t pf_stage = counter ? 0u : 1u, nxt = 0xffffffffu, nrec2 = 0, touch = 0;
     uint64_t off_next = 0, off_next1 = 0, nx_lo = 0, nx_hi = 0;
     auto next_tile_step = [&]() {  // every lane, right after a barrier
       if (pf_stage == 0) {
         if (tid == 0) s_nxt = late_ticket ? atomicAdd(ticket, 1u) : my_ticket;
       } else if (pf_stage == 1) {
-        nxt = s_nxt;
+        nxt = counter ? s_nxt : tile + gridDim.x;
         if (nxt < P.n_tiles) {
           const uint64_t g1 = (uint64_t)nxt << P.log2T;
           nrec2 = (uint32_t)min((uint64_t)T, P.n_records - g1);
