@@ -77,6 +77,7 @@ struct fbx_plan {
   std::vector<uint32_t> place_order;   // see layout()
   std::vector<uint32_t> units;         // per operator and row, as launch_setup wants them
   uint32_t n_mh = 0, n_split = 0, n_gen = 0;  // as in TileParams
+  uint32_t n_comma_fields = 0;                // fields that some operator reads as a list
   TileResident resident[4];
 
   // results of the last call
@@ -130,6 +131,9 @@ struct fbx_plan {
       if (d.kind == OP_HASH) ++n_mh;
       if (d.flags & F_MULTI) ++n_split;
     }
+    for (uint32_t k = 0; k < host.n_fields; ++k)
+      for (uint32_t i = 0; i < host.fields[k].op_count; ++i)
+        if (host.ops[host.field_ops[host.fields[k].op_begin + i]].d.flags & F_MULTI) { ++n_comma_fields; break; }
     for (uint32_t layer = 2; layer <= host.n_layers; ++layer) {
       const uint32_t list = TL_LAYER + 2u * (layer - 2u) + 1u;
       n_gen += host.tile_list_begin[list + 1] - host.tile_list_begin[list];
@@ -191,8 +195,14 @@ void tile_lds_layout(const fbx_plan& p, uint32_t lt, uint32_t raw_cap, TileParam
   tp.o_gfirst = o; o = round16(o + (tp.n_gen ? 4ull * h.ops.size() : 0ull));
   tp.o_gtot = o; o = round16(o + (tp.n_gen ? 4ull * (h.n_layers + 1u) : 0ull));
   tp.o_ioff = o; o = round16(o + 4ull * (tp.n_mh + 1));
-  tp.item_cap = 16;
-  tp.o_ctab = o; o = round16(o + 2ull * tp.n_mh * T * tp.item_cap);
+  // Commas: along with the tabs when the fields that are lists would get one lane each of a workgroup anyway, or when
+  // filters and buckets of list items can use them too; else a few lanes a field (24 list items a record of 807 bytes:
+  // 4.2 against 4.6 ms; 72 of 2,130: 0.71 against 1.03).
+  tp.walk_commas = p.n_split > p.n_mh || 2u * p.n_mh * T > 512u ? 1u : 0u;
+  tp.comma_cap = tp.walk_commas ? std::min(16u * p.n_comma_fields, 2048u) : 0u;  // (a record with more is rare, and its items are looked for in the text)
+  tp.o_ctab = o; o = round16(o + 2ull * T * (tp.walk_commas ? tp.comma_cap + 2u : p.n_mh * kItemCap));
+  tp.o_ctot = o; o = round16(o + (tp.walk_commas ? 2ull * T : 0ull));
+  tp.o_cfirst = o; o = round16(o + 2ull * T * tp.n_mh);
   tp.o_prog = o; o = round16(o + sizeof(OpProg) * h.ops.size());
   tp.o_lbeg = o; o = round16(o + 4ull * h.tile_list_begin.size());
   tp.o_rnr = o; o = round16(o + 4ull * h.derive_tab.size());
@@ -721,16 +731,18 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   // Ragged arrays can be sized from what the last call produced (plus a margin): then the
   // counting launch is skipped.  A batch that does not fit its arrays, or a tile that needs
   // several passes, sends the call back to the exact sequence.
-  // (every tile reads 512 bytes of placement words per ragged operator that is placed by look-back,
-  // which those whose counts follow from another operator's are not: only worth it when that is
-  // little next to the tile's own text)
+  // (Looking back costs every tile a window of 64 words and some waiting per ragged operator that is placed that way,
+  // which those whose counts follow from another operator's are not; counting costs every tile its text once more.
+  // Measured with 4 such operators on 26 KB tiles, 4.2 against 6.0 ms; with 30 on 34 KB, 1.33 against 1.02 ms; with 76 on
+  // 18 KB, 0.63 against 0.45: the line is drawn at 4 KB of text an operator.  A batch of at most 64 tiles finds all
+  // the tiles before a tile in one window and saves the launches: 52 against 65 us, 65 against 76.)
   // (a batch with a tile that did not fit the LDS section is likely to be followed by more of its kind: the
   // sequence is then left untried for 1, 2, 4 ... up to 64 calls, so that such batches do not pay for two attempts each)
   const bool resting = plan->passes_skip > 0;
   if (resting) --plan->passes_skip;
   bool one = !resting && g.tile_engine && plan->one_launch && plan->learned && h.n_ragged && n_records && plan->learned_records &&
              ws_bytes > plan->margin_failed_ws &&
-             (plan->placement || uint64_t(h.n_ragged - h.n_alias) * 512u * 2u <= (raw_len / n_records) << g.tp.log2T);
+             (plan->placement || g.n_tiles <= 64u || uint64_t(h.n_ragged - h.n_alias) * 4096u <= (raw_len / n_records) << g.tp.log2T);
   if (one) {
     plan->cap_host.resize(h.n_ragged);
     for (uint32_t r = 0; r < h.n_ragged; ++r) {

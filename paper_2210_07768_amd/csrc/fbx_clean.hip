@@ -364,7 +364,7 @@ __global__ __launch_bounds__(kCleanThreads, CLEAN_WAVES) void k_clean_measure_ti
         if (re > rs && raw[re - 1u] == '\n') { --re; end_nl = 1u; }  // one trailing newline is not part of the record
       }
       uint16_t* row = rows + rr * C.row_stride;
-      tabs = split_bytes(raw, rs, re, act, kTabs, lg, j, F, [&](uint32_t k, uint32_t pos) { row[1u + k] = (uint16_t)pos; });
+      tabs = split_bytes<false>(raw, rs, re, act, lg, j, kTabs, F, [&](uint32_t k, uint32_t pos) { row[1u + k] = (uint16_t)pos; }, 0u, 0u, [](uint32_t, uint32_t) {});
       if (act) {
         if (j == 0) row[0] = (uint16_t)(rs - 1u);
         for (uint32_t kk = tabs + j; kk < F; kk += gsz) row[1u + kk] = (uint16_t)re;

@@ -54,141 +54,110 @@ __device__ __forceinline__ uint32_t group_prefix(uint32_t v, uint32_t lg, uint32
   return v;
 }
 
+// Bit i of the result: byte i of the sixteen is NOT the byte repeated in pat (a byte below 0x80).
+// With the top bits out of the way, (w ^ pat) + 0x7f carries into the top bit of every byte that
+// differs; a dot product with the weights 1, 2, 4 ... packs the top bits (0x7f or 0xff a byte; the
+// 0x7f parts sum up to a constant that the accumulator starts from): four vector instructions a
+// word and class, one of them shared between the classes that are looked for in the same text.
+__device__ __forceinline__ uint32_t differs16(const u32x4& w, const u32x4& low7, uint32_t pat) {
+  auto top = [&](uint32_t x, uint32_t l) -> uint32_t { return ((l ^ pat) + 0x7f7f7f7fu) | x | 0x7f7f7f7fu; };
+  uint32_t lo = __builtin_amdgcn_udot4(top(w.x, low7.x), 0x08040201u, 0u - 127u * 255u, false);
+  lo = __builtin_amdgcn_udot4(top(w.y, low7.y), 0x80402010u, lo, false);
+  uint32_t hi = __builtin_amdgcn_udot4(top(w.z, low7.z), 0x08040201u, 0u - 127u * 255u, false);
+  hi = __builtin_amdgcn_udot4(top(w.w, low7.w), 0x80402010u, hi, false);
+  return ((hi << 8) + lo) >> 7;
+}
+
 // 1 << lg neighbouring lanes of a wavefront (j = 0 .. (1 << lg) - 1) split the staged
-// bytes [rs, re) at every delimiter (pat: the delimiter in all four bytes).  Each lane
-// takes an equal run of the 16-byte chunks that cover the range and counts its
-// delimiters; a prefix sum over the group turns the counts into ordinals, and a second
-// walk calls emit(k, position) for the k-th delimiter, k < limit.  Returns the number of
-// delimiters in the whole range.  Every lane of a group calls it; those with
-// act == false (and, with limit == 0, all of them) emit nothing.
-template <class Emit>
-__device__ __forceinline__ uint32_t split_bytes(const uint8_t* raw, uint32_t rs, uint32_t re, bool act, uint32_t pat,
-                                                uint32_t lg, uint32_t j, uint32_t limit, Emit&& emit) {
+// bytes [rs, re) at every delimiter (pat_a: the delimiter in all four bytes) and, with TWO,
+// find those of a second kind in the same walk.  Each lane takes an equal run of the 16-byte
+// chunks that cover the range and counts its delimiters; a prefix sum over the group turns the
+// counts into ordinals, and a second walk calls emit_a(k, position) for the k-th delimiter,
+// k < limit_a (and emit_b, limit_b).  Returns the number of delimiters in the whole range, those
+// of the second kind times 2^16 added (a range holds fewer than 2^16 bytes).  Every lane of a
+// group calls it; those with act == false emit nothing.
+template <bool TWO, class EmitA, class EmitB>
+__device__ __forceinline__ uint32_t split_bytes(const uint8_t* raw, uint32_t rs, uint32_t re, bool act, uint32_t lg, uint32_t j,
+                                                uint32_t pat_a, uint32_t limit_a, EmitA&& emit_a, uint32_t pat_b, uint32_t limit_b,
+                                                EmitB&& emit_b) {
   const uint32_t gsz = 1u << lg;
   const uint32_t ab = rs & ~15u;
   const uint32_t nc = (act && re > rs) ? (re - ab + 15u) >> 4 : 0u;  // 16-byte chunks that cover the range
   const uint32_t c = (nc + gsz - 1u) >> lg;                          // chunks per lane
   const uint32_t c0 = min(j * c, nc), c1 = min(c0 + c, nc);
-  // one bit per byte of chunk ci: set where the byte is a delimiter (bytes outside the range included)
-  auto chunk_bits = [&](uint32_t ci) -> uint32_t {
-    const u32x4 w = *reinterpret_cast<const u32x4*>(raw + ab + 16u * ci);
-    // flag bytes (0x80 or 0) times weights 1, 2, 4 ...: every sum is 128 times the wanted bits
-    uint32_t lo8 = __builtin_amdgcn_udot4(eq_flags(w.x, pat), 0x08040201u, 0u, false);
-    lo8 = __builtin_amdgcn_udot4(eq_flags(w.y, pat), 0x80402010u, lo8, false);
-    uint32_t hi8 = __builtin_amdgcn_udot4(eq_flags(w.z, pat), 0x08040201u, 0u, false);
-    hi8 = __builtin_amdgcn_udot4(eq_flags(w.w, pat), 0x80402010u, hi8, false);
-    return (lo8 | (hi8 << 8)) >> 7;
-  };
-  // the bits [lo, hi) of a mask of n bits that starts at staged position p: those inside the range
-  auto inside = [&](uint32_t p, uint32_t n) -> uint64_t {
-    const uint32_t lo = rs > p ? rs - p : 0u, hi = min(re - p, n);
-    return (hi >= 64u ? ~0ull : (1ull << hi) - 1ull) & (~0ull << lo);
-  };
-  // A lane with at most four chunks (the usual case) keeps one bit per byte: bit i of (mhi:mlo)
-  // is set when byte i of its run is a delimiter.  The second walk then needs no memory at all.
-  // With five to eight chunks (long records) two more words (m2, m3) hold the second 64 bytes.
-  const bool few = c <= 4u, some = c > 4u && c <= 8u;
-  uint32_t mlo = 0, mhi = 0, m2 = 0, m3 = 0, cnt = 0;
-  if (few) {
+  // One bit per byte, for 64 bytes at a time: bit i is set when byte i of the piece (which starts at chunk q0) is a
+  // delimiter of the range and of this lane's run.
+  struct Piece { uint32_t a0, a1, b0, b1; };
+  auto piece = [&](uint32_t q0) -> Piece {
+    uint32_t na0 = ~0u, na1 = ~0u, nb0 = ~0u, nb1 = ~0u;
 #pragma unroll
     for (uint32_t q = 0; q < 4; ++q) {
-      if (c0 + q < c1) {
-        const uint32_t m16 = chunk_bits(c0 + q);
-        if (q == 0) mlo = m16;
-        else if (q == 1) mlo |= m16 << 16;
-        else if (q == 2) mhi = m16;
-        else mhi |= m16 << 16;
+      if (q0 + q < c1) {
+        const u32x4 w = *reinterpret_cast<const u32x4*>(raw + ab + 16u * (q0 + q));
+        u32x4 low7;
+        low7.x = w.x & 0x7f7f7f7fu; low7.y = w.y & 0x7f7f7f7fu; low7.z = w.z & 0x7f7f7f7fu; low7.w = w.w & 0x7f7f7f7fu;
+        const uint32_t da = differs16(w, low7, pat_a);
+        if (q == 0) na0 = da | 0xffff0000u;
+        else if (q == 1) na0 = (na0 & 0xffffu) | (da << 16);
+        else if (q == 2) na1 = da | 0xffff0000u;
+        else na1 = (na1 & 0xffffu) | (da << 16);
+        if (TWO) {
+          const uint32_t db = differs16(w, low7, pat_b);
+          if (q == 0) nb0 = db | 0xffff0000u;
+          else if (q == 1) nb0 = (nb0 & 0xffffu) | (db << 16);
+          else if (q == 2) nb1 = db | 0xffff0000u;
+          else nb1 = (nb1 & 0xffffu) | (db << 16);
+        }
       }
     }
-    if (c0 < c1) {  // (the lane's run starts before re)
-      const uint64_t in = inside(ab + 16u * c0, 64u);
-      mlo &= (uint32_t)in;
-      mhi &= (uint32_t)(in >> 32);
-    }
-    cnt = __popc(mlo) + __popc(mhi);
-  } else if (some) {
-#pragma unroll
-    for (uint32_t q = 0; q < 8; ++q) {
-      if (c0 + q < c1) {
-        const uint32_t m16 = chunk_bits(c0 + q) << (16u * (q & 1u));
-        if (q < 2) mlo |= m16;
-        else if (q < 4) mhi |= m16;
-        else if (q < 6) m2 |= m16;
-        else m3 |= m16;
+    Piece m{0u, 0u, 0u, 0u};
+    if (q0 < c1) {  // (the piece starts before re)
+      const uint32_t p = ab + 16u * q0;
+      const uint32_t lo = rs > p ? rs - p : 0u, hi = min(re - p, 64u);
+      const uint64_t in = (hi >= 64u ? ~0ull : (1ull << hi) - 1ull) & (~0ull << lo);
+      m.a0 = ~na0 & (uint32_t)in;
+      m.a1 = ~na1 & (uint32_t)(in >> 32);
+      if (TWO) {
+        m.b0 = ~nb0 & (uint32_t)in;
+        m.b1 = ~nb1 & (uint32_t)(in >> 32);
       }
     }
-    if (c0 < c1) {
-      const uint64_t in = inside(ab + 16u * c0, 64u);
-      mlo &= (uint32_t)in;
-      mhi &= (uint32_t)(in >> 32);
-    }
-    if (c0 + 4u < c1) {  // (the second 64 bytes start before re)
-      const uint64_t in = inside(ab + 16u * c0 + 64u, 64u);
-      m2 &= (uint32_t)in;
-      m3 &= (uint32_t)(in >> 32);
-    }
-    cnt = __popc(mlo) + __popc(mhi) + __popc(m2) + __popc(m3);
-  } else {
-    for (uint32_t ci = c0; ci < c1; ++ci) cnt += __popc(chunk_bits(ci) & (uint32_t)inside(ab + 16u * ci, 16u));
+    return m;
+  };
+  auto count = [](const Piece& m) -> uint32_t { return __popc(m.a0) + __popc(m.a1) + (TWO ? (__popc(m.b0) + __popc(m.b1)) << 16 : 0u); };
+  // A lane's first two pieces (128 bytes, all there is in all but very long records) are kept for the second walk.
+  const Piece first = piece(c0);
+  uint32_t cnt = count(first);
+  Piece second{0u, 0u, 0u, 0u};
+  if (c > 4u) {
+    second = piece(c0 + 4u);
+    cnt += count(second);
+    for (uint32_t q = c0 + 8u; q < c1; q += 4u) cnt += count(piece(q));
   }
   const uint32_t incl = group_prefix(cnt, lg, j);
   const uint32_t total = __shfl(incl, (int)(lane_id() | (gsz - 1u)), 64);
-  if (!act || !limit) return total;
-  uint32_t k = incl - cnt;
-  if (few) {
-    uint32_t base = ab + 16u * c0;
-    uint32_t m = mlo;
-    uint32_t room = k < limit ? limit - k : 0u;  // delimiters this lane may still report
-#pragma unroll
-    for (uint32_t word = 0; word < 2; ++word) {
-      uint32_t n = min((uint32_t)__popc(m), room);
-      room -= n;
-      for (; n; --n) {
-        const uint32_t i = (uint32_t)__builtin_ctz(m);  // (m is not zero here)
-        emit(k, base + i);
-        ++k;
-        m &= m - 1u;
-      }
-      m = mhi;
-      base += 32u;
+  if (!act) return total;
+  uint32_t ka = (incl - cnt) & 0xffffu, kb = (incl - cnt) >> 16;
+  auto walk = [&](uint32_t m, uint32_t base, uint32_t& k, uint32_t limit, auto&& emit) {
+    for (uint32_t n = min((uint32_t)__popc(m), k < limit ? limit - k : 0u); n; --n) {
+      emit(k, base + (uint32_t)__builtin_ctz(m));  // (m is not zero here)
+      ++k;
+      m &= m - 1u;
     }
-  } else if (some) {
-    uint32_t base = ab + 16u * c0;
-    uint32_t m = mlo;
-    uint32_t room = k < limit ? limit - k : 0u;
-#pragma unroll
-    for (uint32_t word = 0; word < 4; ++word) {
-      uint32_t n = min((uint32_t)__popc(m), room);
-      room -= n;
-      for (; n; --n) {
-        const uint32_t i = (uint32_t)__builtin_ctz(m);  // (m is not zero here)
-        emit(k, base + i);
-        ++k;
-        m &= m - 1u;
-      }
-      m = word == 0 ? mhi : (word == 1 ? m2 : m3);
-      base += 32u;
+  };
+  auto walk_piece = [&](const Piece& m, uint32_t q0) {
+    const uint32_t base = ab + 16u * q0;
+    walk(m.a0, base, ka, limit_a, emit_a);
+    walk(m.a1, base + 32u, ka, limit_a, emit_a);
+    if (TWO) {
+      walk(m.b0, base, kb, limit_b, emit_b);
+      walk(m.b1, base + 32u, kb, limit_b, emit_b);
     }
-  } else {
-    // second walk of a long run: from delimiter to delimiter.  A window of eight bytes at the
-    // current position (any alignment) shows the next one, so every lane places one per turn.
-    const uint32_t* raw32 = reinterpret_cast<const uint32_t*>(raw);
-    const uint32_t be = min(re, ab + 16u * c1);
-    uint32_t p = max(rs, ab + 16u * c0);
-    while (p < be) {
-      const uint32_t a = p >> 2, sh8 = (p & 3u) * 8u;
-      const uint32_t w0 = raw32[a], w1 = raw32[a + 1], w2 = raw32[a + 2];
-      const uint32_t f0 = eq_flags(__builtin_amdgcn_alignbit(w1, w0, sh8), pat);
-      const uint32_t f1 = eq_flags(__builtin_amdgcn_alignbit(w2, w1, sh8), pat);
-      const uint32_t i0 = ((uint32_t)__ffs((int)f0) - 1u) >> 3, i1 = 4u + (((uint32_t)__ffs((int)f1) - 1u) >> 3);
-      const uint32_t idx = f0 ? i0 : (f1 ? i1 : 8u);
-      p += idx;
-      if (idx < 8u && p < be) {
-        if (k < limit) emit(k, p);
-        ++k;
-        ++p;
-      }
-    }
+  };
+  walk_piece(first, c0);
+  if (c > 4u) {
+    walk_piece(second, c0 + 4u);
+    for (uint32_t q = c0 + 8u; q < c1; q += 4u) walk_piece(piece(q), q);
   }
   return total;
 }

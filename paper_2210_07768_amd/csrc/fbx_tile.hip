@@ -13,8 +13,10 @@
 //  2. Splitting at the delimiter (Section 5, first paragraph): groups of lanes
 //     share a record, find its tabs sixteen bytes at a time and write a table of
 //     field ends (16-bit LDS positions).  No per-thread array is allocated; the
-//     table has one entry per (record, field).  The same routine splits the item
-//     lists of multi-valued fields at their commas.
+//     table has one entry per (record, field).  Where many fields are lists the same
+//     walk leaves every record's commas in a list of positions, and the items of a
+//     field are the stretch between its two ends; where few are, a few lanes split
+//     each of them at its commas (TileParams::walk_commas says which).
 //  3. Layer 1: lanes are (record, operator) pairs.  A lane looks up its field in
 //     the table and hashes / parses it out of LDS; T neighbouring lanes hold T
 //     consecutive records of one operator, so a slot is written in runs of 8 T
@@ -64,6 +66,7 @@ namespace {
 constexpr uint32_t kNoRow = 0xffffffffu;
 constexpr uint64_t kPrime = 0x100000001b3ull;
 constexpr uint32_t kMaxCount = 0x3ffffffu;  // signs per record and operator
+constexpr uint32_t kNoComma = 0xffffu;      // there are more commas than the table holds: look for them in the text
 
 
 // Pointers the compiler knows to be global memory (plain global loads and stores
@@ -146,7 +149,10 @@ struct Sh {
   uint32_t* gfirst; // [n_ops] list operators of layers >= 2, by program position: first sign among the signs of the layer's list operators in this pass
   uint32_t* gtot;   // [n_layers + 1] signs of all list operators of a layer in this pass
   uint32_t* ioff;   // [n_mh + 1] first item of every multi-valued hash among the pass's items
-  uint16_t* ctab;   // [n_mh][T][item_cap] comma positions of the multi-valued hash fields
+  uint16_t* ctab;   // comma positions: [T][comma_cap + 2] a record's first ones (two more, so that neighbouring records
+                    // start in different banks), or [n_mh][T][kItemCap] those of a multi-valued hash's field
+  uint16_t* ctot;   // [T] how many the record has (walk_commas)
+  uint16_t* cfirst; // [n_mh][T] where in ctab the commas of a multi-valued hash's field start; kNoComma
   // plan tables, copied once per workgroup so that no lane waits on memory for a descriptor
   const OpProg* prog;          // [n_ops], in the order of the work lists
   const uint32_t* list_begin;
@@ -185,6 +191,8 @@ __device__ __forceinline__ Sh views(const TileParams& P) {
   s.gtot = reinterpret_cast<uint32_t*>(smem + P.o_gtot);
   s.ioff = reinterpret_cast<uint32_t*>(smem + P.o_ioff);
   s.ctab = reinterpret_cast<uint16_t*>(smem + P.o_ctab);
+  s.ctot = reinterpret_cast<uint16_t*>(smem + P.o_ctot);
+  s.cfirst = reinterpret_cast<uint16_t*>(smem + P.o_cfirst);
   s.prog = reinterpret_cast<const OpProg*>(smem + P.o_prog);
   s.list_begin = reinterpret_cast<const uint32_t*>(smem + P.o_lbeg);
   s.rnr = reinterpret_cast<const uint32_t*>(smem + P.o_rnr);
@@ -202,10 +210,25 @@ __device__ __forceinline__ bool row_follows(const TileParams& P, const Sh& sh, u
 }
 
 struct LdsSrc {
-  static constexpr bool kTable = true;  // positions fit the 16-bit comma table
+  static constexpr bool kTable = true;  // positions fit the 16-bit comma lists
   const uint8_t* raw8;
   const uint16_t* rows;
   uint32_t stride;
+  const uint16_t *ctab, *ctot;
+  uint32_t cap;  // 0: there are no lists of a record's commas
+  // The commas of record r inside [s, e): entries [lo, hi) of its list; false when the list does not hold them all.
+  __device__ __forceinline__ bool commas(uint32_t r, uint32_t s, uint32_t e, const uint16_t*& list, uint32_t& lo, uint32_t& hi) const {
+    lo = hi = 0;
+    list = ctab + r * (cap + 2u);
+    if (cap == 0u) return false;
+    const uint32_t n = ctot[r];
+    if (n > cap) return false;
+    for (uint32_t step = 1u << (31u - (uint32_t)__clz((int)(n | 1u))); step; step >>= 1) {  // (two searches side by side)
+      if (lo + step <= n && list[lo + step - 1u] < s) lo += step;
+      if (hi + step <= n && list[hi + step - 1u] < e) hi += step;
+    }
+    return true;
+  }
   __device__ __forceinline__ uint32_t byte(uint32_t p) const { return raw8[p]; }
   // Field k of staged record r: [s, e).  A missing field is empty.
   __device__ __forceinline__ void span(uint32_t r, uint32_t k, uint32_t& s, uint32_t& e) const {
@@ -266,9 +289,17 @@ __device__ __forceinline__ void tokenize(const TileParams& P, const Sh& sh, uint
     if (re > rs && sh.raw[re - 1u] == '\n') --re;  // one trailing newline is not part of the record
   }
   uint16_t* row = sh.rows + r * P.row_stride;
-  const uint32_t total = split_bytes(sh.raw, rs, re, act, kTabs, lg, j, F, [&](uint32_t k, uint32_t pos) {
-    row[1u + k] = (uint16_t)pos;
-  });
+  auto put_tab = [&](uint32_t k, uint32_t pos) { row[1u + k] = (uint16_t)pos; };
+  uint32_t total;
+  if (P.walk_commas) {
+    uint16_t* list = sh.ctab + r * (P.comma_cap + 2u);
+    total = split_bytes<true>(sh.raw, rs, re, act, lg, j, kTabs, F, put_tab, kCommas, P.comma_cap,
+                              [&](uint32_t k, uint32_t pos) { list[k] = (uint16_t)pos; });
+    if (act && j == 0) sh.ctot[r] = (uint16_t)(total >> 16);
+    total &= 0xffffu;
+  } else {
+    total = split_bytes<false>(sh.raw, rs, re, act, lg, j, kTabs, F, put_tab, 0u, 0u, [](uint32_t, uint32_t) {});
+  }
   if (!act) return;
   if (j == 0) row[0] = (uint16_t)(rs - 1u);
   for (uint32_t kk = total + j; kk < F; kk += gsz) row[1u + kk] = (uint16_t)re;
@@ -546,7 +577,22 @@ __device__ __forceinline__ bool starts_with(const GlobalSrc& src, uint32_t t, ui
 // Calls f(t, te) for every token [t, te) of the field [s, e), in order: the field itself, or with
 // multi its comma-separated parts (one more than it has commas, empty ones included).
 template <class Src, class F>
-__device__ __forceinline__ void for_each_token(const Src& src, uint32_t s, uint32_t e, bool multi, F&& f) {
+__device__ __forceinline__ void for_each_token(const Src& src, uint32_t r, uint32_t s, uint32_t e, bool multi, F&& f) {
+  if constexpr (Src::kTable) {
+    const uint16_t* list;
+    uint32_t lo, hi;
+    if (!multi) { f(s, e); return; }
+    if (src.commas(r, s, e, list, lo, hi)) {
+      uint32_t t = s;
+      for (; lo < hi; ++lo) {
+        const uint32_t te = list[lo];
+        f(t, te);
+        t = te + 1u;
+      }
+      f(t, e);
+      return;
+    }
+  }
   uint32_t t = s;
   for (;;) {
     const uint32_t te = multi ? next_comma(src, t, e) : e;
@@ -558,18 +604,26 @@ __device__ __forceinline__ void for_each_token(const Src& src, uint32_t s, uint3
 
 // Number of signs a ragged root operator (not n-gram) produces on [s, e).
 template <class Src>
-__device__ __forceinline__ uint32_t ragged_root_count(const Src& src, const OpProg& d, const uint8_t* aux, uint32_t s,
+__device__ __forceinline__ uint32_t ragged_root_count(const Src& src, const OpProg& d, const uint8_t* aux, uint32_t r, uint32_t s,
                                                       uint32_t e) {
-  if (d.kind != OP_FILTER) return count_commas(src, s, e) + 1u;  // multi-valued hash / bucket
+  if (d.kind != OP_FILTER) {  // multi-valued hash / bucket
+    if constexpr (Src::kTable) {
+      const uint16_t* list;
+      uint32_t lo, hi;
+      if (src.commas(r, s, e, list, lo, hi)) return hi - lo + 1u;
+    }
+    return count_commas(src, s, e) + 1u;
+  }
+  if (d.flags & F_NEVER) return 0u;
   const Prefix pre(aux, d);
   uint32_t cnt = 0;
-  for_each_token(src, s, e, d.flags & F_MULTI, [&](uint32_t t, uint32_t te) { cnt += starts_with(src, t, te, pre) ? 1u : 0u; });
+  for_each_token(src, r, s, e, d.flags & F_MULTI, [&](uint32_t t, uint32_t te) { cnt += starts_with(src, t, te, pre) ? 1u : 0u; });
   return cnt;
 }
 
 // Writes the signs of a ragged root operator (not n-gram) on [s, e) to dst[0 .. count).
 template <class Src>
-__device__ __forceinline__ void ragged_root_emit(const Src& src, const OpProg& d, const uint8_t* aux, uint32_t s,
+__device__ __forceinline__ void ragged_root_emit(const Src& src, const OpProg& d, const uint8_t* aux, uint32_t r, uint32_t s,
                                                  uint32_t e, G64 dst, uint32_t& malformed) {
   const bool multi = d.flags & F_MULTI;
   if (d.kind == OP_HASH) {  // a ragged hash is always multi-valued
@@ -583,7 +637,7 @@ __device__ __forceinline__ void ragged_root_emit(const Src& src, const OpProg& d
   } else if (d.kind == OP_FILTER) {  // only the tokens that pass are hashed
     const Prefix pre(aux, d);
     const uint64_t key = d.key;
-    for_each_token(src, s, e, multi, [&](uint32_t t, uint32_t te) {
+    for_each_token(src, r, s, e, multi, [&](uint32_t t, uint32_t te) {
       if (starts_with(src, t, te, pre)) *dst++ = hash_span(src, t, te, key);
     });
   } else {  // OP_BUCKET, multi-valued
@@ -671,8 +725,6 @@ struct Pass {
   uint32_t& malformed;
   bool& overflow;
   uint32_t lb_tile;   // tile number when counts are to be published (one-launch mode), else kNoRow
-  bool need_table;    // the pass goes on to write: keep comma positions while counting
-  bool split_all;     // filters and buckets with lists are counted a few lanes a field, like the hashes (counting launch)
 
   // This lane's place in a unit, worked out anew (and hidden from the optimiser's view of the
   // tile loop): otherwise every address that follows from it is computed once per kernel and
@@ -695,11 +747,9 @@ struct Pass {
   }
 
   // ---- counts of the ragged root operators
-  // Multi-valued hashes of staged records (the first P.n_mh entries of the ragged root list):
-  // every wavefront takes part.  A few neighbouring lanes share one (operator, record) and
-  // split the field at its commas: the item count, and the first item_cap comma positions
-  // for the lanes that later hash the items.
-  __device__ __forceinline__ void split_items() {
+  // Multi-valued hashes of staged records where few fields are lists (!walk_commas): a few neighbouring lanes share one
+  // (operator, record) and split the field at its commas.  Every wavefront takes part.
+  __device__ __forceinline__ void split_items(bool keep) {  // keep: the pass goes on to hash the items
     const uint32_t tid = thread_id();
     const uint32_t np = P.n_mh * T;  // (operator, record slot) pairs
     uint32_t lg = 0;                 // log2 of the lanes per pair
@@ -708,103 +758,113 @@ struct Pass {
     for (uint32_t p0 = 0; p0 < np; p0 += kTileThreads >> lg) {
       const uint32_t pr = p0 + (tid >> lg);
       const uint32_t i = pr / T, rr = pr & (T - 1u);
-      const bool act = pr < np && rr < nb;
-      uint32_t s = 0, e = 0, row = 0;
-      if (act) {
-        const OpProg& d = sh.prog[sh.lbeg(TL_RAGROOT) + i];
-        src.span(rr, d.field, s, e);
-        row = d.rag_row;
-      } else if (pr < np) {
-        row = sh.prog[sh.lbeg(TL_RAGROOT) + i].rag_row;
-      }
-      uint16_t* tab = sh.ctab + pr * P.item_cap;
-      const uint32_t cap = P.item_cap;
-      const uint32_t commas = split_bytes(src.raw8, s, e, act, kCommas, lg, j, need_table ? cap : 0u, [&](uint32_t k, uint32_t pos) {
-        tab[k] = (uint16_t)pos;
-      });
-      if (pr < np && j == 0) sh.cnt[row * T + rr] = act ? commas + 1u : 0u;  // items = commas + 1 (far below kMaxCount)
-    }
-  }
-  // The other multi-valued root operators of staged records (filters and buckets: entries n_mh ..
-  // n_split - 1 of the ragged root list) are counted the same way, a few lanes a field: a bucket
-  // list has one sign per item; a filter tests the token that starts the field and the one after
-  // every comma.  (A token is as long as the prefix or longer exactly when the prefix's bytes
-  // follow its start and hold no comma: a prefix with a comma passes nothing, F_NEVER.)
-  __device__ __forceinline__ void split_others() {
-    const uint32_t tid = thread_id();
-    const uint32_t np = (P.n_split - P.n_mh) * T;
-    uint32_t lg = 0;
-    while (lg < 6u && (np << (lg + 1u)) <= kTileThreads) ++lg;
-    const uint32_t j = tid & ((1u << lg) - 1u);
-    for (uint32_t p0 = 0; p0 < np; p0 += kTileThreads >> lg) {
-      const uint32_t pr = p0 + (tid >> lg);
-      const uint32_t i = pr / T, rr = pr & (T - 1u);
       const bool in = pr < np, act = in && rr < nb;
-      const OpProg& d = sh.prog[sh.lbeg(TL_RAGROOT) + P.n_mh + (in ? i : 0u)];
-      const bool filter = d.kind == OP_FILTER;
+      const OpProg& d = sh.prog[sh.lbeg(TL_RAGROOT) + (in ? i : 0u)];
       uint32_t s = 0, e = 0;
       if (act) src.span(rr, d.field, s, e);
-      uint32_t c;
-      if (filter) {  // (uniform over the lanes of a field)
-        const Prefix pre(sh.aux, d);
-        uint32_t hits = (act && j == 0 && starts_with(src, s, e, pre)) ? 1u : 0u;
-        split_bytes(src.raw8, s, e, act, kCommas, lg, j, ~0u, [&](uint32_t, uint32_t pos) {
-          hits += starts_with(src, pos + 1u, e, pre) ? 1u : 0u;
-        });
-        for (uint32_t w = 1; w < (1u << lg); w <<= 1) hits += __shfl_xor(hits, (int)w, 64);
-        c = (d.flags & F_NEVER) ? 0u : hits;
-      } else {
-        c = split_bytes(src.raw8, s, e, act, kCommas, lg, j, 0u, [](uint32_t, uint32_t) {}) + 1u;
+      uint16_t* tab = sh.ctab + pr * kItemCap;
+      const uint32_t commas = split_bytes<false>(src.raw8, s, e, act, lg, j, kCommas, keep ? kItemCap : 0u, [&](uint32_t k, uint32_t pos) {
+        tab[k] = (uint16_t)pos;
+      }, 0u, 0u, [](uint32_t, uint32_t) {});
+      if (in && j == 0) {
+        sh.cnt[d.rag_row * T + rr] = act ? commas + 1u : 0u;  // items = commas + 1 (far below kMaxCount)
+        sh.cfirst[pr] = (uint16_t)(commas <= kItemCap ? pr * kItemCap : kNoComma);
       }
-      if (in && j == 0) sh.cnt[d.rag_row * T + rr] = act ? c : 0u;
     }
   }
-  // The single-valued filters and the n-grams (lists TL_RAGROOT and TL_NGRAM, taken as one), G
-  // operators per unit; records read in place count all their ragged root operators here.
-  __device__ __forceinline__ uint32_t count_skip() const { return !Src::kTable ? 0u : (split_all ? P.n_split : P.n_mh); }
-  __device__ __forceinline__ uint32_t count_root_units() const {
-    return (sh.lbeg(TL_RAGROOT + 1) - sh.lbeg(TL_RAGROOT) - count_skip() + G - 1u) / G;
+  // Units of a wavefront: multi-valued hashes, G operators; other multi-valued operators (filters, buckets), eight
+  // lanes a field; single-valued filters and n-grams, G operators.  They run side by side on different wavefronts, so
+  // what counts is the longest one.
+  __device__ __forceinline__ uint32_t mh_count_units() const { return P.walk_commas || !Src::kTable ? (P.n_mh + G - 1u) / G : 0u; }
+  __device__ __forceinline__ uint32_t split_count_units() const { return ((P.n_split - P.n_mh) * T + 7u) >> 3; }
+  __device__ __forceinline__ uint32_t other_count_units() const {
+    return (sh.lbeg(TL_RAGROOT + 1) - sh.lbeg(TL_RAGROOT) - P.n_split + G - 1u) / G;
   }
-  __device__ __forceinline__ uint32_t count_units() const { return count_root_units() + units_of(TL_NGRAM); }
+  __device__ __forceinline__ uint32_t count_units() const {
+    return split_count_units() + mh_count_units() + other_count_units() + units_of(TL_NGRAM);
+  }
   __device__ __forceinline__ void count_unit(uint32_t u) {
     refresh();
-    const uint32_t ur = count_root_units();
+    if (u < split_count_units()) { count_split_unit(u); return; }
+    u -= split_count_units();
+    const uint32_t lb = sh.lbeg(TL_RAGROOT);
+    if (u < mh_count_units()) { count_mh_unit(u); return; }
+    u -= mh_count_units();
     const OpProg* d;
-    uint32_t i = 0;  // position in the ragged root list
-    if (u < ur) {
-      const uint32_t lb = sh.lbeg(TL_RAGROOT), m = sh.lbeg(TL_RAGROOT + 1) - lb;
-      i = count_skip() + u * G + og;
-      d = i < m ? &sh.prog[lb + i] : nullptr;
+    if (u < other_count_units()) {
+      const uint32_t i = P.n_split + u * G + og;
+      d = lb + i < sh.lbeg(TL_RAGROOT + 1) ? &sh.prog[lb + i] : nullptr;
     } else {
-      d = op_of(TL_NGRAM, u - ur);
+      d = op_of(TL_NGRAM, u - other_count_units());
     }
     if (!d) return;
     uint32_t c = 0;
     if (live) {
       uint32_t s, e;
       src.span(r, d->field, s, e);
-      if (d->kind == OP_NGRAM) {
-        c = e - s >= d->aux_len ? e - s - d->aux_len + 1u : 0u;
-      } else if (d->kind == OP_HASH && !need_table) {
-        c = count_commas(src, s, e) + 1u;  // counting launch: nobody reads the comma table
-      } else if (d->kind == OP_HASH) {
-        // multi-valued hash: from comma to comma; the first item_cap positions are kept for the item lanes
-        uint16_t* tab = sh.ctab + (i * T + r) * P.item_cap;
-        uint32_t p = s;
-        for (;;) {
-          p = next_comma(src, p, e);
-          if (p >= e) break;
-          if (Src::kTable && c < P.item_cap) tab[c] = (uint16_t)p;
-          ++c;
-          ++p;
-        }
-        ++c;  // items = commas + 1
-      } else {
-        c = ragged_root_count(src, *d, sh.aux, s, e);
-      }
+      if (d->kind == OP_NGRAM) c = e - s >= d->aux_len ? e - s - d->aux_len + 1u : 0u;
+      else c = starts_with(src, s, e, Prefix(sh.aux, *d)) ? 1u : 0u;
     }
     if (c > kMaxCount) overflow = true;
     sh.cnt[d->rag_row * T + r] = c;
+  }
+  // A multi-valued hash has one sign more than its field has commas; where they start is kept for the lanes that hash
+  // the items.
+  __device__ __forceinline__ void count_mh_unit(uint32_t u) {
+    const uint32_t i = u * G + og;
+    if (i >= P.n_mh) return;
+    const OpProg& d = sh.prog[sh.lbeg(TL_RAGROOT) + i];
+    uint32_t c = 0;
+    if (live) {
+      uint32_t s, e, at = kNoComma;
+      src.span(r, d.field, s, e);
+      bool listed = false;
+      if constexpr (Src::kTable) {
+        const uint16_t* list;
+        uint32_t lo, hi;
+        if (src.commas(r, s, e, list, lo, hi)) {
+          c = hi - lo + 1u;
+          at = (uint32_t)(list - sh.ctab) + lo;
+          listed = true;
+        }
+      }
+      if (!listed) c = count_commas(src, s, e) + 1u;
+      sh.cfirst[i * T + r] = (uint16_t)at;
+    }
+    if (c > kMaxCount) overflow = true;
+    sh.cnt[d.rag_row * T + r] = c;
+  }
+  // Eight lanes an (operator, record): a bucket list has one sign per item; a filter tests the token that starts the
+  // field and the one after every comma.
+  __device__ __forceinline__ void count_split_unit(uint32_t u) {
+    const uint32_t lane = lane_id(), q = lane & 7u, pr = u * 8u + (lane >> 3);
+    const uint32_t i = pr >> P.log2T, rr = pr & (T - 1u);
+    const bool in = i < P.n_split - P.n_mh, act = in && rr < nb;
+    const OpProg& d = sh.prog[sh.lbeg(TL_RAGROOT) + P.n_mh + (in ? i : 0u)];
+    uint32_t c = 0;
+    if (act) {
+      uint32_t s, e;
+      src.span(rr, d.field, s, e);
+      bool listed = false;
+      if constexpr (Src::kTable) {
+        const uint16_t* list;
+        uint32_t lo, hi;
+        if (src.commas(rr, s, e, list, lo, hi)) {
+          listed = true;
+          if (d.kind != OP_FILTER) {
+            c = q == 0u ? hi - lo + 1u : 0u;
+          } else if (!(d.flags & F_NEVER)) {
+            const Prefix pre(sh.aux, d);
+            for (uint32_t t = lo + q; t <= hi; t += 8u)  // the token in front of comma t (the last one: in front of e)
+              c += starts_with(src, t == lo ? s : (uint32_t)list[t - 1u] + 1u, t == hi ? e : list[t], pre) ? 1u : 0u;
+          }
+        }
+      }
+      if (!listed && q == 0u) c = ragged_root_count(src, d, sh.aux, rr, s, e);
+    }
+    for (uint32_t w = 1; w < 8u; w <<= 1) c += __shfl_xor(c, (int)w, 64);
+    if (c > kMaxCount) overflow = true;
+    if (in && q == 0u) sh.cnt[d.rag_row * T + rr] = c;
   }
 
   // Counts of the later layers follow from the inputs' counts, record by record and layer
@@ -939,7 +999,7 @@ struct Pass {
     const uint64_t first = place(*d, r, g);
     uint32_t s, e;
     src.span(r, d->field, s, e);
-    ragged_root_emit(src, *d, sh.aux, s, e, gptr<uint64_t>(d->values) + first, malformed);
+    ragged_root_emit(src, *d, sh.aux, r, s, e, gptr<uint64_t>(d->values) + first, malformed);
   }
   // Multi-valued hashes (the first P.n_mh entries of the ragged root list): lanes
   // are items.  All items of the pass, operator after operator and record after
@@ -989,20 +1049,16 @@ struct Pass {
     const uint32_t rr = lo, j = pos - st[rr], cnt = sh.cnt[row * T + rr];
     uint32_t s, e;
     src.span(rr, d.field, s, e);
-    const uint16_t* tab = sh.ctab + (i * T + rr) * P.item_cap;
-    const uint32_t cap = Src::kTable ? P.item_cap : 0u;
-    uint32_t is, ie;
-    if (j == 0) {
-      is = s;
-    } else if (j <= cap) {
-      is = (uint32_t)tab[j - 1u] + 1u;
-    } else {  // beyond the table: walk on from its last comma
-      is = cap ? (uint32_t)tab[cap - 1u] + 1u : s;
-      for (uint32_t c = cap; c < j; ++c) is = next_comma(src, is, e) + 1u;
+    uint32_t is = s, ie = e;
+    const uint32_t cf = sh.cfirst[i * T + rr];
+    if (cf != kNoComma) {
+      const uint16_t* list = sh.ctab + cf;
+      if (j) is = (uint32_t)list[j - 1u] + 1u;
+      if (j + 1u < cnt) ie = list[j];
+    } else {
+      for (uint32_t c = 0; c < j; ++c) is = next_comma(src, is, e) + 1u;
+      if (j + 1u < cnt) ie = next_comma(src, is, e);
     }
-    if (j + 1u == cnt) ie = e;
-    else if (j < cap) ie = tab[j];
-    else ie = next_comma(src, is, e);
     const uint64_t first = sh.base[row] + pos;
     if (j == 0 && (d.flags & F_EMIT)) {
       G64 off = gptr<uint64_t>(d.offsets);
@@ -1355,7 +1411,7 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
   constexpr bool WRITE = MODE != 0;
   const uint32_t tid = thread_id(), lane = tid & 63u, wave = tid >> 6;
   const uint32_t T = 1u << P.log2T;
-  Pass<Src> ps{P, sh, src, nb, g_first, T, 64u >> P.log2T, lane & (T - 1u), lane >> P.log2T, false, 0, malformed, overflow, MODE == 2 ? tile : kNoRow, WRITE, MODE == 0};
+  Pass<Src> ps{P, sh, src, nb, g_first, T, 64u >> P.log2T, lane & (T - 1u), lane >> P.log2T, false, 0, malformed, overflow, MODE == 2 ? tile : kNoRow};
   ps.live = ps.r < nb;
   ps.g = g_first + ps.r;
   // the single-valued hashes and buckets of layer 1 fill whatever phase has idle wavefronts
@@ -1384,7 +1440,8 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
   auto critical_phase = [&](uint32_t total, uint32_t* ctr, uint32_t* done, auto&& unit) {
     for (uint32_t u = grab_unit(ctr); u < total; u = grab_unit(ctr)) {
       unit(u);
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      // (what the unit left in LDS is there; the text requested ahead and signs on their way to memory are not waited for)
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       if (lane == 0) atomicAdd(done, 1u);
     }
     if (WRITE) {
@@ -1396,14 +1453,7 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
   // ---- phase A: counts of the ragged root operators
   bool absurd = false;
   if constexpr (Src::kTable) {
-    if (P.n_mh) ps.split_items();
-    if (P.n_mh && FBX_SKIP(0x200u)) {  // (tuning builds: once more, to weigh it)
-      __syncthreads();
-      ps.split_items();
-    }
-    // (the counting launch only: a launch that writes has single-valued fields to hash while a few
-    // wavefronts count these operators unit by unit, below)
-    if (MODE == 0 && P.n_split > P.n_mh) ps.split_others();
+    if (P.n_mh && !P.walk_commas) ps.split_items(WRITE);
   }
   if (P.n_ragged) critical_phase(ps.count_units(), &s_ctr[1], &s_done, [&](uint32_t u) { ps.count_unit(u); });
   else __syncthreads();
@@ -1785,7 +1835,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
         }
         __syncthreads();
         FBX_MARK(3);
-        LdsSrc src{sh.raw, sh.rows, P.row_stride};
+        LdsSrc src{sh.raw, sh.rows, P.row_stride, sh.ctab, sh.ctot, P.walk_commas ? P.comma_cap : 0u};
         run_pass<MODE>(P, sh, src, nb, g0 + r0, tile, malformed, overflow, next_tile_hook);
         r0 = r1;
       } else {
@@ -1886,7 +1936,7 @@ __global__ __launch_bounds__(kBlock) void k_unordered(UnorderedParams U) {
       src = GlobalSrc{gptr(U.raw) + a, len};
       src.span(0, d.field, s, e);
       if (d.kind == OP_NGRAM) cnt = e - s >= d.aux_len ? e - s - d.aux_len + 1u : 0u;
-      else cnt = (d.kind == OP_FILTER && (d.flags & F_NEVER)) ? 0u : ragged_root_count(src, d, U.aux, s, e);
+      else cnt = ragged_root_count(src, d, U.aux, 0u, s, e);
       if (cnt > kMaxCount) { err = CE_OVERFLOW; ok = false; cnt = 0; }
     }
   }
@@ -1904,7 +1954,7 @@ __global__ __launch_bounds__(kBlock) void k_unordered(UnorderedParams U) {
       if (d.kind == OP_NGRAM) {
         for (uint32_t q = 0; q < cnt; ++q) dst[q] = hash_span(src, s + q, s + q + d.aux_len, d.key);
       } else {
-        ragged_root_emit(src, d, U.aux, s, e, dst, malformed);
+        ragged_root_emit(src, d, U.aux, 0u, s, e, dst, malformed);
       }
     }
   }
