@@ -363,19 +363,19 @@ __device__ __forceinline__ uint32_t xor_byte(uint32_t a, uint32_t w) {
 // FNV-1a over the bytes [s, e) from state h: h = (h ^ b) * (2^40 + 435) per byte.  Only the low
 // word's product needs the wide multiply-add; the high word's own terms, 435 hi + (lo << 8), go
 // in as its addend.
+template <int K>
+__device__ __forceinline__ uint64_t fnv_step(uint64_t h, uint32_t w) {  // byte K of w
+  static_assert(kPrime == ((1ull << 40) | 435ull), "FNV-1a prime");
+  const uint32_t lo = xor_byte<K>((uint32_t)h, w);
+  const uint32_t top = (uint32_t)(h >> 32) * 435u + (lo << 8);
+  uint64_t r, carry;
+  asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(r), "=s"(carry) : "v"(lo), "s"(435u), "v"((uint64_t)top << 32));
+  return r;
+}
 template <class Src>
 __device__ __forceinline__ uint64_t hash_span(const Src& src, uint32_t s, uint32_t e, uint64_t h) {
-  static_assert(kPrime == ((1ull << 40) | 435ull), "FNV-1a prime");
-  uint32_t lo = (uint32_t)h, hi = (uint32_t)(h >> 32);
-  for_each_byte_of_word(src, s, e, [&](uint32_t w, auto k) {
-    lo = xor_byte<decltype(k)::value>(lo, w);
-    const uint32_t top = hi * 435u + (lo << 8);
-    uint64_t r, carry;
-    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(r), "=s"(carry) : "v"(lo), "s"(435u), "v"((uint64_t)top << 32));
-    lo = (uint32_t)r;
-    hi = (uint32_t)(r >> 32);
-  });
-  return ((uint64_t)hi << 32) | lo;
+  for_each_byte_of_word(src, s, e, [&](uint32_t w, auto k) { h = fnv_step<decltype(k)::value>(h, w); });
+  return h;
 }
 
 // 0x80 in exactly the zero bytes of x.
@@ -1101,7 +1101,23 @@ struct Pass {
     first = __shfl(first, 0, 64);
     G64 vals = gptr<uint64_t>(d.values) + first;
     const uint64_t key = d.key;
-    for (uint32_t q = lane; q < ng; q += 64) vals[q] = hash_span(src, s + q, s + q + n, key);
+    const bool stream = d.flags & F_STREAM;
+    if constexpr (Src::kTable) {
+      if (n <= 4u) {  // one word holds a gram, and every lane hashes as many bytes
+        const uint32_t* raw32 = reinterpret_cast<const uint32_t*>(src.raw8);
+        for (uint32_t q = lane; q < ng; q += 64) {
+          const uint32_t p = s + q, a = p >> 2;
+          const uint32_t w = __builtin_amdgcn_alignbit(raw32[a + 1u], raw32[a], (p & 3u) * 8u);
+          uint64_t h = fnv_step<0>(key, w);
+          if (n > 1u) h = fnv_step<1>(h, w);
+          if (n > 2u) h = fnv_step<2>(h, w);
+          if (n > 3u) h = fnv_step<3>(h, w);
+          store_sign(vals + q, h, stream);
+        }
+        return;
+      }
+    }
+    for (uint32_t q = lane; q < ng; q += 64) store_sign(vals + q, hash_span(src, s + q, s + q + n, key), stream);
   }
 
   // A 64-bit literal of generated code, handed over in scalar registers at the place of its use (otherwise
@@ -1180,23 +1196,25 @@ struct Pass {
 
   // ---- later layers
   // crosses of two single signs, both on chip
-  static constexpr uint32_t kCrossesPerLane = 2;  // (two a lane: half the hand-outs; measured 0.7 % on the largest workload)
+  // (two a lane: half the hand-outs, measured 0.7 % on the largest workload; one where two would leave wavefronts idle)
+  static constexpr uint32_t kCrossesPerLane = 2;
+  __device__ __forceinline__ uint32_t crosses_per_lane(uint32_t m) const { return m <= kWaves * G ? 1u : kCrossesPerLane; }
   __device__ __forceinline__ uint32_t x11_units(uint32_t layer) const {
-    const uint32_t list = TL_LAYER + 2u * (layer - 2u);
-    return (sh.lbeg(list + 1) - sh.lbeg(list) + kCrossesPerLane * G - 1u) / (kCrossesPerLane * G);
+    const uint32_t list = TL_LAYER + 2u * (layer - 2u), m = sh.lbeg(list + 1) - sh.lbeg(list), c = crosses_per_lane(m) * G;
+    return (m + c - 1u) / c;
   }
   __device__ __forceinline__ void x11_unit(uint32_t layer, uint32_t u) {
     refresh();
     if (!live) return;
     const uint32_t list = TL_LAYER + 2u * (layer - 2u);
-    const uint32_t lb = sh.lbeg(list), m = sh.lbeg(list + 1) - lb;
+    const uint32_t lb = sh.lbeg(list), m = sh.lbeg(list + 1) - lb, c = crosses_per_lane(m);
     // (a cross never reads a cross of its own layer: the crosses of a unit are independent, their inputs are requested together)
     const OpProg* d[kCrossesPerLane];
     uint64_t a[kCrossesPerLane], b[kCrossesPerLane];
 #pragma unroll
     for (uint32_t k = 0; k < kCrossesPerLane; ++k) {
-      const uint32_t i = (u * kCrossesPerLane + k) * G + og;
-      d[k] = i < m ? &sh.prog[lb + i] : nullptr;
+      const uint32_t i = (u * c + k) * G + og;
+      d[k] = k < c && i < m ? &sh.prog[lb + i] : nullptr;
     }
 #pragma unroll
     for (uint32_t k = 0; k < kCrossesPerLane; ++k)
@@ -1236,6 +1254,32 @@ struct Pass {
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   }
+  // a / b for the sizes that occur: by way of a float quotient, which below 2^22 is off by at most one
+  __device__ __forceinline__ static uint32_t small_div(uint32_t a, uint32_t b) {
+    if (__ballot(a >= (1u << 22))) return a / b;
+    uint32_t x = (uint32_t)((float)a * __builtin_amdgcn_rcpf((float)b));
+    const uint32_t r = a - x * b;  // (in 0 .. b - 1, or one b to either side of that)
+    if ((int32_t)r < 0) --x;
+    else if (r >= b) ++x;
+    return x;
+  }
+  // The last record of the pass whose first position in a ragged row is <= pos: the one that has the sign there.
+  __device__ __forceinline__ uint32_t record_at(uint32_t row, uint32_t pos) const {
+    const uint32_t* st = sh.start + row * T;
+    if (P.log2T <= 3u) {  // few records: all of them at once instead of one look-up after the other (those beyond nb start at the end)
+      uint32_t n = 0;
+#pragma unroll
+      for (uint32_t k = 1; k < 8u; ++k)
+        if (k < T) n += st[k] <= pos && k < nb ? 1u : 0u;
+      return n;
+    }
+    uint32_t lo = 0, hi = nb - 1u;
+    while (lo < hi) {
+      const uint32_t mid = (lo + hi + 1u) >> 1;
+      if (st[mid] <= pos) lo = mid; else hi = mid - 1u;
+    }
+    return lo;
+  }
   // sign x of record rr of an earlier operator (single signs from the on-chip table, lists
   // from the arrays this workgroup wrote before the layer barrier)
   __device__ __forceinline__ uint64_t input_sign(const OpProg& d, uint32_t rr, uint32_t x) const {
@@ -1259,34 +1303,43 @@ struct Pass {
       }
       return;
     }
-    const uint32_t q = (u - up) * 64u + lane_id();
-    if (q >= sh.gtot[layer]) return;
     // operator: the last one whose first sign is <= q (operators without signs in this pass share
-    // their first sign with the one after them and are passed over)
-    uint32_t lo = 0, hi = m - 1u;
-    while (lo < hi) {
-      const uint32_t mid = (lo + hi + 1u) >> 1;
-      if (sh.gfirst[lb + mid] <= q) lo = mid; else hi = mid - 1u;
+    // their first sign with the one after them and are passed over).  Most units lie inside one or two operators: the
+    // wavefront finds the one its first sign belongs to with one look at all their first signs, and goes on from there.
+    const uint32_t lane = lane_id(), q0 = (u - up) * 64u, q = q0 + lane, total = sh.gtot[layer];
+    uint32_t lo = 0, op_first = 0;
+    if (m <= 64u) {
+      const uint32_t f = lane < m ? sh.gfirst[lb + lane] : ~0u;
+      const uint64_t at_or_before = __ballot(f <= q0), inside = __ballot(f > q0 && f <= q0 + 63u && f < total);
+      lo = (uint32_t)__popcll(at_or_before) - 1u;
+      op_first = (uint32_t)__builtin_amdgcn_readlane((int)f, (int)__builtin_amdgcn_readfirstlane(lo));
+      for (uint64_t left = inside; left; left &= left - 1u) {
+        const uint32_t k = (uint32_t)__builtin_ctzll(left);
+        const uint32_t fk = (uint32_t)__builtin_amdgcn_readlane((int)f, (int)k);
+        if (q >= fk) { lo = k; op_first = fk; }
+      }
+    } else {
+      uint32_t hi = m - 1u;
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1u) >> 1;
+        if (sh.gfirst[lb + mid] <= q) lo = mid; else hi = mid - 1u;
+      }
+      op_first = sh.gfirst[lb + lo];
     }
+    if (q >= total) return;
     const OpProg& d = sh.prog[lb + lo];
-    const uint32_t qq = q - sh.gfirst[lb + lo];  // the sign's number among the operator's signs of this pass
+    const uint32_t qq = q - op_first;  // the sign's number among the operator's signs of this pass
     const uint32_t row = d.rag_row;
     uint32_t rr, j;
     uint64_t at;  // where the sign goes
     if (d.arity) {
-      rr = qq / d.arity;
+      rr = small_div(qq, d.arity);
       j = qq - rr * d.arity;
       at = (g_first + rr) * d.arity + j;
     } else {
       const uint32_t pos = sh.run[row] - sh.tot[row] + qq;  // position inside the tile (earlier passes come first)
-      const uint32_t* st = sh.start + row * T;
-      uint32_t l2 = 0, h2 = nb - 1u;  // the last record whose first position is <= pos (it is the one that has the sign)
-      while (l2 < h2) {
-        const uint32_t mid = (l2 + h2 + 1u) >> 1;
-        if (st[mid] <= pos) l2 = mid; else h2 = mid - 1u;
-      }
-      rr = l2;
-      j = pos - st[rr];
+      rr = record_at(row, pos);
+      j = pos - sh.start[row * T + rr];
       at = sh.base[row] + pos;
     }
     const OpProg& da = sh.prog[d.a];
@@ -1295,7 +1348,7 @@ struct Pass {
     const uint32_t nbv = db.arity ? db.arity : sh.cnt[db.rag_row * T + rr];
     uint64_t v;
     if (d.kind == OP_CROSS) {  // A outer, B inner
-      const uint32_t x = j / nbv, y = j - x * nbv;
+      const uint32_t x = small_div(j, nbv), y = j - x * nbv;
       v = mix64(mix64(input_sign(da, rr, x) + d.key) + input_sign(db, rr, y));
     } else {
       v = j < na ? input_sign(da, rr, j) : input_sign(db, rr, j - na);
