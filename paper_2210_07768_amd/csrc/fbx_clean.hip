@@ -742,7 +742,8 @@ struct fbx_clean {
   std::vector<CleanOp> ops;          // sorted by field (stable)
   std::vector<uint32_t> first_op;    // n_fields + 1
   std::vector<uint8_t> args;
-  std::vector<uint8_t> image;        // ops, first_op, args as they lie in the scratch
+  std::vector<uint8_t> image;        // ops, first_op, args, and what only the tile kernels read, as they lie in the scratch
+  uint64_t core = 0;                 // bytes up to the end of args
   uint64_t off_ops = 0, off_first = 0, off_args = 0, off_of = 0, off_keyed = 0;
   std::vector<uint32_t> keyed;       // entries of the table of fields with operators whose first one looks a key up
   uint32_t n_of = 0, args_bytes = 0;
@@ -760,24 +761,26 @@ struct CleanLayout {
   uint64_t run_sums, sums, n_segs, rec_out, segs, end;      // tiles (in the same place)
 };
 
-CleanLayout clean_layout(const fbx_clean& c, uint64_t n) {
+// small: what one record per thread needs, a tenth of what the tile kernels do (their segments).
+CleanLayout clean_layout(const fbx_clean& c, uint64_t n, bool small) {
   CleanLayout L{};
   uint64_t o = 0;
   L.ctrl = o; o = up256(o + sizeof(Ctrl));
   L.total = o; o = up256(o + 16);
-  L.tables = o; o = up256(o + c.image.size());
+  L.tables = o; o = up256(o + (small ? c.core : c.image.size()));
   const uint64_t shared = o;
   L.lens = o; o = up256(o + 2 * n * 4);
   L.base = o; o = up256(o + 2 * n * 8);
   L.part = o; o = up256(o + 2ull * scan_segments(static_cast<uint32_t>(n)) * 8);
-  const uint64_t end1 = o;
+  L.end = o;
+  if (small) return L;
   o = shared;
   L.run_sums = o; o = up256(o + 2ull * kMaxRuns * 8);
   L.sums = o; o = up256(o + n * 8);                         // (a tile has a record at least)
   L.n_segs = o; o = up256(o + n * 4);
   L.rec_out = o; o = up256(o + n * 8);
   L.segs = o; o = up256(o + n * (2ull * c.n_of + 3) * 4);
-  L.end = std::max(end1, o);
+  L.end = std::max(L.end, o);
   return L;
 }
 
@@ -882,14 +885,15 @@ fbx_status fbx_clean_create(const char* spec, size_t spec_len, fbx_clean** out) 
     }
   c->n_of = static_cast<uint32_t>(of.size());
   of.push_back(OpField{c->n_fields, static_cast<uint32_t>(c->ops.size()), 0u});
-  c->args.resize(c->args.size() / 4 * 4 + 4, '\n');  // whole words, the last byte a newline
-  c->args_bytes = static_cast<uint32_t>(c->args.size());
   uint64_t o = 0;
   c->off_ops = o; o += c->ops.size() * sizeof(CleanOp);
+  c->off_first = o; o += c->first_op.size() * 4;
+  c->off_args = o; c->core = o + c->args.size();
+  c->args.resize(c->args.size() / 4 * 4 + 4, '\n');  // whole words, the last byte a newline
+  c->args_bytes = static_cast<uint32_t>(c->args.size());
+  o += c->args.size();
   c->off_of = o; o += of.size() * sizeof(OpField);
   c->off_keyed = o; o += c->keyed.size() * 4;
-  c->off_args = o; o += c->args.size();
-  c->off_first = o; o += c->first_op.size() * 4;
   c->image.assign(o, 0);
   if (!c->ops.empty()) std::memcpy(c->image.data() + c->off_ops, c->ops.data(), c->ops.size() * sizeof(CleanOp));
   std::memcpy(c->image.data() + c->off_of, of.data(), of.size() * sizeof(OpField));
@@ -909,7 +913,7 @@ const char* fbx_clean_last_error(const fbx_clean* clean) { return clean ? clean-
 
 fbx_status fbx_clean_scratch_hint(const fbx_clean* clean, uint64_t n_records, uint64_t* bytes) {
   if (!clean || !bytes || n_records >= (1ull << 32)) return FBX_E_ARG;
-  *bytes = clean_layout(*clean, n_records).end;
+  *bytes = clean_layout(*clean, n_records, false).end;
   return FBX_OK;
 }
 
@@ -924,13 +928,15 @@ fbx_status fbx_clean_run(fbx_clean* clean, const uint8_t* d_raw, uint64_t raw_le
     clean->error = "a call takes fewer than 2^32 records and a 256-byte aligned scratch buffer";
     return FBX_E_ARG;
   }
-  const CleanLayout L = clean_layout(*clean, n_records);
+  CleanLayout L = clean_layout(*clean, n_records, false);
   out->n_kept = out->out_len = 0;
   out->required_scratch = L.end;
-  if (scratch_bytes < L.end) {
+  const bool small = scratch_bytes < L.end;  // (a buffer without room for the tiles' segments still does for one record per thread)
+  if (small && scratch_bytes < clean_layout(*clean, n_records, true).end) {
     clean->error = "scratch buffer too small: need " + std::to_string(L.end) + " bytes";
     return FBX_E_NOMEM;
   }
+  if (small) L = clean_layout(*clean, n_records, true);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   uint8_t* sc = static_cast<uint8_t*>(d_scratch);
   auto hip_failed = [&](hipError_t e, const char* where) {
@@ -965,7 +971,7 @@ fbx_status fbx_clean_run(fbx_clean* clean, const uint8_t* d_raw, uint64_t raw_le
   auto tables = [&](uint64_t T) { return std::max(T * row_stride * 2 + (T + 1) * clean->n_of * 4ull, segs(T) * 6 + 16) + fixed; };
   uint32_t log2T = 6;
   while (log2T && ((mean << log2T) * 5 / 4 > kTextMax || tables(1ull << log2T) > kTableMax)) --log2T;
-  const bool tiles = n_records && tables(1ull << log2T) <= kTableMax;
+  const bool tiles = n_records && !small && tables(1ull << log2T) <= kTableMax;
   uint32_t lds_measure = 0, lds_write = 0;
   if (tiles) {
     const uint64_t T = 1ull << log2T;
@@ -993,20 +999,21 @@ fbx_status fbx_clean_run(fbx_clean* clean, const uint8_t* d_raw, uint64_t raw_le
     C.segs = reinterpret_cast<uint32_t*>(sc + L.segs);
     if (!clean->exported && !clean->no_export) {
       void* mem = nullptr;
-      if (hipHostMalloc(&mem, sizeof(Ctrl) + 16, hipHostMallocDefault) == hipSuccess) clean->exported = static_cast<uint64_t*>(mem);
+      if (hipHostMalloc(&mem, sizeof(Ctrl) + 16, hipHostMallocPortable) == hipSuccess) clean->exported = static_cast<uint64_t*>(mem);
       else { (void)hipGetLastError(); clean->no_export = true; }
     }
   }
   struct { Ctrl c; uint8_t pad[256 - sizeof(Ctrl)]; uint64_t total[2]; } back;
   static_assert(sizeof(back) == 256 + 16, "read-back layout");
   // set-up: the tables go along as arguments of the launch if they are small
-  const bool inl = clean->image.size() <= kImageInline;
+  const uint64_t image_bytes = small ? (clean->core + 3) & ~uint64_t(3) : clean->image.size();  // (whole words)
+  const bool inl = image_bytes <= kImageInline;
   hipError_t e = hipSuccess;
-  if (!inl) e = hipMemcpyAsync(sc + L.tables, clean->image.data(), clean->image.size(), hipMemcpyHostToDevice, st);
+  if (!inl) e = hipMemcpyAsync(sc + L.tables, clean->image.data(), image_bytes, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) {
     ImageArgs<kImageInline> image;
-    if (inl) std::memcpy(image.w, clean->image.data(), clean->image.size());
-    const uint32_t table_words = inl ? static_cast<uint32_t>(clean->image.size() / 4) : 0u;
+    if (inl) std::memcpy(image.w, clean->image.data(), image_bytes);
+    const uint32_t table_words = inl ? static_cast<uint32_t>(image_bytes / 4) : 0u;
     hipLaunchKernelGGL(k_clean_setup<kImageInline>, dim3((table_words + kBlock) / kBlock), dim3(kBlock), 0, st, ctrl, total,
                        reinterpret_cast<uint32_t*>(sc + L.tables), table_words, image);
     e = hipGetLastError();

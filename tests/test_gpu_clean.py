@@ -96,6 +96,37 @@ def test_clean_tiles_of_every_shape(F, n, long_every, n_ops, width):
     assert bool((d_out[res.out_len:] == 0x21).all()), "written beyond the cleaned text"
 
 
+def test_a_scratch_buffer_without_room_for_segments_still_does():
+    """24 bytes a record and the tables: too little for the tile kernels, enough for one record per thread."""
+    import torch
+    n = 1000
+    spec = ("fbxclean 1\nfields 100\n" + "".join(f"fill field={k} value=30\n" for k in range(30))
+            + "key field=40 name=6b31\nkeep field=5 prefix=61\n")
+    rng = random.Random(5)
+    recs = [("\t".join("" if rng.random() < 0.3 else rng.choice(["a1", "b", "k1:x;k2:y"]) for _ in range(100)) + "\n").encode() for _ in range(n)]
+    raw, off = _cat(recs)
+    want_raw, want_off = C.clean(spec, raw, off)
+    clean = B.Clean(spec)
+    d_raw, d_off = to_device(raw, off, 3)
+    hint = clean.scratch_hint(n)
+    tables = 512 + 512 + 256  # 32 operators of 16 bytes, 101 words, the arguments: each in whole 256 bytes
+    little = 2 * 256 + tables + 8192 + 16128 + 256
+    assert little < hint
+    for size in (little, hint - 256, hint):
+        d_out = torch.empty(want_raw.size + 64, dtype=torch.uint8, device="cuda").fill_(0x21)
+        d_out_off = torch.full((n + 1,), -1, dtype=torch.int64, device="cuda")
+        buf = torch.empty(size + 256, dtype=torch.uint8, device="cuda").fill_(0x6B)
+        res = clean.run(d_raw, d_off, d_out, d_out_off, buf[:size])
+        assert res.n_kept == len(want_off) - 1 and res.out_len == want_raw.size
+        assert np.array_equal(d_out_off[:res.n_kept + 1].cpu().numpy().view(np.uint64), want_off)
+        assert np.array_equal(d_out[:res.out_len].cpu().numpy(), want_raw)
+        assert bool((buf[size:] == 0x6B).all()), "written beyond the scratch buffer"
+    with pytest.raises(B.FbxError) as e:
+        clean.run(d_raw, d_off, d_out, d_out_off, buf[:little // 2])
+    assert e.value.status == B.E_NOMEM
+    clean.close()
+
+
 def test_clean_edge_cases_and_errors():
     import torch
     recs = [b"ann\tage:3;city:rome;x:1\tok1\t5\n", b"\tcity:;age:4\tokay\t\n", b"bob\tage:3\tok\t1", b"cy\tcity:oslo\tnot ok\t2\n",
