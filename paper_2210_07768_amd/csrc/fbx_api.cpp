@@ -40,8 +40,7 @@ struct fbx_plan {
   // constant-table placement inside the workspace (byte offsets)
   uint64_t off_ctrl = 0, off_dyn = 0, off_ops = 0, off_layer_ops = 0, off_layer_begin = 0, off_nonroot = 0,
            off_aux = 0, off_fields = 0, off_field_ops = 0, off_prog_ops = 0, off_prog_fields = 0, off_row_total = 0,
-           off_tile_lists = 0, off_tile_list_begin = 0, off_rnr = 0, off_prof = 0, off_actual = 0, off_cap = 0, off_place_order = 0, off_units = 0,
-           off_static_end = 0;
+           off_tile_lists = 0, off_tile_list_begin = 0, off_rnr = 0, off_prof = 0, off_actual = 0, off_cap = 0, off_static_end = 0;
 
   // options
   int fused = 1;
@@ -74,7 +73,6 @@ struct fbx_plan {
   std::vector<uint8_t> tables;    // image of the constant tables, as they lie at the head of a workspace
 
   // where arrays go, worked out on the host when their sizes are known before the call
-  std::vector<uint32_t> place_order;   // see layout()
   std::vector<uint32_t> units;         // per operator and row, as launch_setup wants them
   uint32_t n_mh = 0, n_split = 0, n_gen = 0;  // as in TileParams
   uint32_t n_comma_fields = 0;                // fields that some operator reads as a list
@@ -114,14 +112,7 @@ struct fbx_plan {
     off_rnr = o; o = align_up(o + host.derive_tab.size() * 4);
     off_prof = o; o = align_up(o + 32 * 8);
     off_cap = o; o = align_up(o + host.n_ragged * 8ull);
-    off_place_order = o; o = align_up(o + n * 4);
-    off_units = o; o = align_up(o + (n + host.n_ragged > kPlaceInline ? (n + host.n_ragged) * 4ull : 0ull));
     off_static_end = o;
-    // the order in which arrays are placed when nothing is released: what is emitted, then the intermediates layer by layer
-    for (uint32_t i = 0; i < n; ++i)
-      if (host.ops[i].d.flags & F_EMIT) place_order.push_back(i);
-    for (uint32_t i : host.layer_ops)
-      if (!(host.ops[i].d.flags & F_EMIT)) place_order.push_back(i);
     placed.resize(n);
     units.resize(n + host.n_ragged);
     readback.resize(off_actual + host.n_ragged * 8ull);
@@ -156,7 +147,6 @@ struct fbx_plan {
     if (!h.tile_lists.empty()) std::memcpy(img + off_tile_lists, h.tile_lists.data(), h.tile_lists.size() * 4);
     std::memcpy(img + off_tile_list_begin, h.tile_list_begin.data(), h.tile_list_begin.size() * 4);
     if (!h.derive_tab.empty()) std::memcpy(img + off_rnr, h.derive_tab.data(), h.derive_tab.size() * 4);
-    if (!place_order.empty()) std::memcpy(img + off_place_order, place_order.data(), place_order.size() * 4);
   }
 };
 
@@ -480,7 +470,6 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   P.layer_ops = reinterpret_cast<const uint32_t*>(ws + plan->off_layer_ops);
   P.layer_begin = reinterpret_cast<const uint32_t*>(ws + plan->off_layer_begin);
   P.nonroot = reinterpret_cast<const uint32_t*>(ws + plan->off_nonroot);
-  P.place_order = reinterpret_cast<const uint32_t*>(ws + plan->off_place_order);
   P.aux = ws + plan->off_aux;
   P.dyn = dyn; P.ctrl = ctrl;
   P.prog_ops = reinterpret_cast<OpProg*>(ws + plan->off_prog_ops);
@@ -534,7 +523,7 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   // operator (the latter alone where the host has placed the arrays itself).
   if (g.tile_engine && g.n_tiles && !plan->exported && !plan->no_export) {
     void* mem = nullptr;
-    if (hipHostMalloc(&mem, plan->readback.size(), hipHostMallocDefault) == hipSuccess) plan->exported = static_cast<uint64_t*>(mem);
+    if (hipHostMalloc(&mem, plan->readback.size(), hipHostMallocPortable) == hipSuccess) plan->exported = static_cast<uint64_t*>(mem);
     else { (void)hipGetLastError(); plan->no_export = true; }
   }
   const Ctrl* c = nullptr;                  // of the last attempt
@@ -544,7 +533,8 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   // threads, in the order the allocation kernel takes them.  Returns the end of the last array.
   auto place_on_host = [&](bool one) -> uint64_t {
     uint64_t head = g.arena_base;
-    for (uint32_t i : plan->place_order) {
+    for (const HostOp& turn : h.ops) {
+      const uint32_t i = turn.d.placed;
       const OpDesc& d = h.ops[i].d;
       const uint64_t n = d.arity ? n_records * d.arity : (one ? plan->cap_host[d.rag_row] : 0);
       const uint64_t sv = align_up(n * 8, kPlaceUnit), so = d.arity ? 0 : align_up((n_records + 1) * 8, kPlaceUnit);
@@ -585,8 +575,9 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
         }
         S.high_water = end;
         if (plan->units.size() > kPlaceInline) {
-          FBX_LAUNCH(hipMemcpyAsync(ws + plan->off_units, plan->units.data(), plan->units.size() * 4, hipMemcpyHostToDevice, st), "placement upload");
-          S.units = reinterpret_cast<const uint32_t*>(ws + plan->off_units);
+          // (where placements made on the device would lie: eight words an operator)
+          FBX_LAUNCH(hipMemcpyAsync(dyn, plan->units.data(), plan->units.size() * 4, hipMemcpyHostToDevice, st), "placement upload");
+          S.units = reinterpret_cast<const uint32_t*>(dyn);
         }
         if (one) {
           S.row_cap = reinterpret_cast<uint64_t*>(ws + plan->off_cap);

@@ -24,7 +24,6 @@ struct WalkParams {
   const uint32_t* layer_ops;
   const uint32_t* layer_begin;
   const uint32_t* nonroot;
-  const uint32_t* place_order;  // operators in the order in which their arrays are placed when nothing is released
   const uint8_t* aux;
   OpDyn* dyn;
   OpProg* prog_ops;        // [n_ops], per call

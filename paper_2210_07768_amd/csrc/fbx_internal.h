@@ -33,7 +33,8 @@ struct OpDesc {
                      // cross/bucket: slot key mix64(seed)
   uint32_t rag_row;  // row among ragged operators (count tables), 0xffffffff if fixed
   uint32_t layer;    // 1-based
-  uint32_t birth;    // == layer
+  uint32_t placed;   // the operator whose arrays are placed in this one's turn when nothing is released: emitted
+                     // operators first, then layer by layer
   uint32_t death;    // last layer that reads this operator's output (>= layer)
   uint32_t stage;    // row of the on-chip sign table (single-sign operators that feed a later
                      // operator), 0xffffffff if none

@@ -250,7 +250,7 @@ fbx_status parse_plan(const char* spec, size_t len, PlanHost& plan, std::string&
     if (op.d.flags & F_EMIT) {
       if (!emitted_slot.emplace(op.slot, 0).second) return fail("slot " + std::to_string(op.slot) + " is emitted twice");
     }
-    op.d.birth = op.d.death = op.d.layer;
+    op.d.death = op.d.layer;
     by_id.emplace(op.id, static_cast<uint32_t>(plan.ops.size()));
     plan.ops.push_back(std::move(op));
   }
@@ -284,6 +284,11 @@ fbx_status parse_plan(const char* spec, size_t len, PlanHost& plan, std::string&
     plan.layer_ops.insert(plan.layer_ops.end(), ids.begin(), ids.end());
   }
   plan.layer_begin[plan.n_layers] = static_cast<uint32_t>(plan.layer_ops.size());
+  uint32_t turn = 0;
+  for (uint32_t i = 0; i < plan.ops.size(); ++i)
+    if (plan.ops[i].d.flags & F_EMIT) plan.ops[turn++].d.placed = i;
+  for (uint32_t i : plan.layer_ops)
+    if (!(plan.ops[i].d.flags & F_EMIT)) plan.ops[turn++].d.placed = i;
   // Rows of the ragged operators: those of the last layer (if it is not the first) come last, in
   // spec order, because the tile kernel derives their counts in the same step that scans them.
   for (int last = 0; last < 2; ++last)

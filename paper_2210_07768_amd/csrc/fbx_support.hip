@@ -240,7 +240,7 @@ __global__ __launch_bounds__(kBlock) void k_alloc(WalkParams P, const uint64_t* 
     uint64_t end = high;
     for (uint32_t c0 = 0; c0 < n_ops; c0 += kBlock) {
       const uint32_t k = c0 + tid;
-      end = max(end, place(k < n_ops ? P.place_order[k] : 0u, k < n_ops));
+      end = max(end, place(k < n_ops ? ops[k].placed : 0u, k < n_ops));
     }
     for (int d = 32; d >= 1; d >>= 1) end = max(end, (uint64_t)__shfl_xor((unsigned long long)end, d, 64));
     if ((tid & 63u) == 0) s_part[tid >> 6] = end;

@@ -191,3 +191,12 @@ def test_rows_that_follow_other_rows_are_found():
     plan = B.Plan(w.spec)
     assert re.search(r"P\.n_alias = 4u;", plan.kernel_source(787_000, 1000, 2))  # the four crosses of a single sign with a list
     plan.close()
+
+
+@pytest.mark.parametrize("cfg,tables", [(1, 6912), (2, 24832), (3, 26624), (4, 59136), (5, 40192)])
+def test_a_workspace_holds_no_more_tables_than_it_was_sized_for(cfg, tables):
+    """Programs keep the size of a workspace: what a plan takes of it for its tables does not grow."""
+    plan = B.Plan(W.get(cfg, 100).spec)
+    assert B.lib().fbx_plan_set_workspace(plan._h, 256, 1) == B.E_NOMEM
+    assert int(re.search(r"\((\d+) bytes\)", B.lib().fbx_last_error(plan._h).decode()).group(1)) <= tables
+    plan.close()
