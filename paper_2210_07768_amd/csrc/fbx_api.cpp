@@ -724,16 +724,20 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   // several passes, sends the call back to the exact sequence.
   // (Looking back costs every tile a window of 64 words and some waiting per ragged operator that is placed that way,
   // which those whose counts follow from another operator's are not; counting costs every tile its text once more.
-  // Measured with 4 such operators on 26 KB tiles, 4.2 against 6.0 ms; with 30 on 34 KB, 1.33 against 1.02 ms; with 76 on
-  // 18 KB, 0.63 against 0.45: the line is drawn at 4 KB of text an operator.  A batch of at most 64 tiles finds all
-  // the tiles before a tile in one window and saves the launches: 52 against 65 us, 65 against 76.)
+  // A workgroup's eight wavefronts look back for one operator each behind the work that needs no base; further operators
+  // are rounds that the tile waits for.  Measured with 4 operators on 26 KB tiles, 4.2 against 6.0 ms; with 24 on 34 KB,
+  // 1.33 against 1.02; with 42 on 18 KB, 0.63 against 0.45: up to eight operators the line is at 1 KB of text an operator,
+  // beyond at 4 KB.  A batch of at most 64 tiles finds all the tiles before a tile in one window and saves the launches,
+  // up to six rounds: 52 against 65 us with 24 operators, 65 against 76 with 42.)
   // (a batch with a tile that did not fit the LDS section is likely to be followed by more of its kind: the
   // sequence is then left untried for 1, 2, 4 ... up to 64 calls, so that such batches do not pay for two attempts each)
   const bool resting = plan->passes_skip > 0;
   if (resting) --plan->passes_skip;
+  const uint32_t n_back = h.n_ragged - h.n_alias;
   bool one = !resting && g.tile_engine && plan->one_launch && plan->learned && h.n_ragged && n_records && plan->learned_records &&
              ws_bytes > plan->margin_failed_ws &&
-             (plan->placement || g.n_tiles <= 64u || uint64_t(h.n_ragged - h.n_alias) * 4096u <= (raw_len / n_records) << g.tp.log2T);
+             (plan->placement || (g.n_tiles <= 64u && n_back <= 48u) ||
+              uint64_t(n_back) * (n_back <= 8u ? 1024u : 4096u) <= (raw_len / n_records) << g.tp.log2T);
   if (one) {
     plan->cap_host.resize(h.n_ragged);
     for (uint32_t r = 0; r < h.n_ragged; ++r) {
