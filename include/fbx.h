@@ -351,7 +351,10 @@ fbx_status fbx_extract_unordered(fbx_plan* plan, uint32_t slot_id, const uint8_t
  *                  (entry n_kept = length of the cleaned text), ready to be handed to fbx_extract
  *     d_scratch  : DEVICE, 256-byte aligned, scratch_bytes bytes, the caller's; contents unspecified afterwards
  *     out        : HOST: kept records, bytes of cleaned text, scratch bytes needed
- *   Enqueues on hip_stream and synchronises it once.  Errors: FBX_E_ARG, FBX_E_INPUT (bad offsets),
+ *   Enqueues on hip_stream and synchronises it once.  One fbx_clean may be run by several threads at the
+ *   same time, each with buffers of its own (fbx_clean_last_error is then about any of their calls; sizes come
+ *   back through a few hundred bytes of pinned HOST memory a call, which the first calls allocate and
+ *   fbx_clean_destroy gives back).  Errors: FBX_E_ARG, FBX_E_INPUT (bad offsets),
  *   FBX_E_HIP, FBX_E_NOMEM: scratch too small (out->required_scratch), or d_out too small: nothing
  *   is written to it and out->out_len holds the bytes needed.
  */

@@ -30,6 +30,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -724,6 +725,8 @@ __global__ __launch_bounds__(kBlock) void k_clean_setup(Ctrl* ctrl, uint64_t* to
   if (i < table_words) tables[i] = image.w[i];
 }
 
+constexpr size_t kMaxExports = 16;  // calls at the same time that get host memory to export to (further ones copy)
+
 uint64_t up256(uint64_t x) { return (x + 255u) & ~uint64_t(255); }
 
 int hex_digit(char c) {
@@ -747,13 +750,61 @@ struct fbx_clean {
   uint64_t off_ops = 0, off_first = 0, off_args = 0, off_of = 0, off_keyed = 0;
   std::vector<uint32_t> keyed;       // entries of the table of fields with operators whose first one looks a key up
   uint32_t n_of = 0, args_bytes = 0;
-  uint64_t* exported = nullptr;      // host memory that the tile kernel writes control block and totals to
-  bool no_export = false;
-  uint32_t grid_lds = 0, grid = 0;   // workgroups of the measuring kernel that run at the same time with that much LDS
+  // Several threads may run one specification at the same time: what calls leave here is under the lock.
+  std::mutex lock;
+  std::vector<uint64_t*> exports, idle;  // host memory that the tile kernel writes control block and totals to: all there is, and what no call uses
+  int grid_dev = -1;
+  uint32_t grid_lds = 0, grid = 0;   // workgroups of the measuring kernel that run at the same time on that device with that much LDS
   std::string error;
 };
 
 namespace {
+
+void clean_error(fbx_clean& c, const std::string& why) {
+  std::lock_guard<std::mutex> hold(c.lock);
+  c.error = why;
+}
+
+// Host memory for the sizes of one call, its own until the call is over: two calls at the same time must not read each
+// other's.  None (a copy is enqueued instead) when there is none to be had or kMaxExports calls have theirs.
+uint64_t* export_taken(fbx_clean& c) {
+  std::lock_guard<std::mutex> hold(c.lock);
+  if (c.idle.empty() && c.exports.size() < kMaxExports) {
+    void* mem = nullptr;
+    if (hipHostMalloc(&mem, sizeof(Ctrl) + 16, hipHostMallocPortable) == hipSuccess) {
+      c.exports.push_back(static_cast<uint64_t*>(mem));
+      c.idle.push_back(static_cast<uint64_t*>(mem));
+    } else {
+      (void)hipGetLastError();
+    }
+  }
+  if (c.idle.empty()) return nullptr;
+  uint64_t* mine = c.idle.back();
+  c.idle.pop_back();
+  return mine;
+}
+void export_returned(fbx_clean& c, uint64_t* mem) {
+  std::lock_guard<std::mutex> hold(c.lock);
+  c.idle.push_back(mem);
+}
+
+// Workgroups of the measuring kernel that run at the same time (the LDS decides): asked once per device and size.
+uint32_t clean_grid(fbx_clean& c, uint32_t lds) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); dev = 0; }
+  std::lock_guard<std::mutex> hold(c.lock);
+  if (c.grid_dev != dev || c.grid_lds != lds) {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&k_clean_measure_tile), kCleanThreads, lds) != hipSuccess || per_cu < 1) {
+      (void)hipGetLastError();
+      per_cu = 1;
+    }
+    c.grid_dev = dev;
+    c.grid_lds = lds;
+    c.grid = std::min(kMaxRuns, tile_cu_count() * static_cast<uint32_t>(per_cu));
+  }
+  return c.grid;
+}
 
 struct CleanLayout {
   uint64_t ctrl, total, tables;
@@ -905,7 +956,8 @@ fbx_status fbx_clean_create(const char* spec, size_t spec_len, fbx_clean** out) 
 }
 
 void fbx_clean_destroy(fbx_clean* clean) {
-  if (clean && clean->exported) (void)hipHostFree(clean->exported);
+  if (!clean) return;
+  for (uint64_t* mem : clean->exports) (void)hipHostFree(mem);
   delete clean;
 }
 
@@ -921,11 +973,11 @@ fbx_status fbx_clean_run(fbx_clean* clean, const uint8_t* d_raw, uint64_t raw_le
                          uint64_t n_records, uint8_t* d_out, uint64_t out_cap, uint64_t* d_out_off, void* d_scratch,
                          uint64_t scratch_bytes, void* hip_stream, fbx_clean_result* out) {
   if (!clean || !out || !d_rec_off || (!d_raw && raw_len) || !d_out_off || (!d_out && out_cap) || !d_scratch) {
-    if (clean) clean->error = "NULL argument";
+    if (clean) clean_error(*clean, "NULL argument");
     return FBX_E_ARG;
   }
   if (n_records >= (1ull << 32) || (reinterpret_cast<uintptr_t>(d_scratch) & 255u)) {
-    clean->error = "a call takes fewer than 2^32 records and a 256-byte aligned scratch buffer";
+    clean_error(*clean, "a call takes fewer than 2^32 records and a 256-byte aligned scratch buffer");
     return FBX_E_ARG;
   }
   CleanLayout L = clean_layout(*clean, n_records, false);
@@ -933,14 +985,14 @@ fbx_status fbx_clean_run(fbx_clean* clean, const uint8_t* d_raw, uint64_t raw_le
   out->required_scratch = L.end;
   const bool small = scratch_bytes < L.end;  // (a buffer without room for the tiles' segments still does for one record per thread)
   if (small && scratch_bytes < clean_layout(*clean, n_records, true).end) {
-    clean->error = "scratch buffer too small: need " + std::to_string(L.end) + " bytes";
+    clean_error(*clean, "scratch buffer too small: need " + std::to_string(L.end) + " bytes");
     return FBX_E_NOMEM;
   }
   if (small) L = clean_layout(*clean, n_records, true);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   uint8_t* sc = static_cast<uint8_t*>(d_scratch);
   auto hip_failed = [&](hipError_t e, const char* where) {
-    clean->error = std::string(where) + ": " + hipGetErrorString(e);
+    clean_error(*clean, std::string(where) + ": " + hipGetErrorString(e));
     (void)hipGetLastError();
     return FBX_E_HIP;
   };
@@ -997,11 +1049,6 @@ fbx_status fbx_clean_run(fbx_clean* clean, const uint8_t* d_raw, uint64_t raw_le
     C.n_segs = reinterpret_cast<uint32_t*>(sc + L.n_segs);
     C.rec_out = reinterpret_cast<uint64_t*>(sc + L.rec_out);
     C.segs = reinterpret_cast<uint32_t*>(sc + L.segs);
-    if (!clean->exported && !clean->no_export) {
-      void* mem = nullptr;
-      if (hipHostMalloc(&mem, sizeof(Ctrl) + 16, hipHostMallocPortable) == hipSuccess) clean->exported = static_cast<uint64_t*>(mem);
-      else { (void)hipGetLastError(); clean->no_export = true; }
-    }
   }
   struct { Ctrl c; uint8_t pad[256 - sizeof(Ctrl)]; uint64_t total[2]; } back;
   static_assert(sizeof(back) == 256 + 16, "read-back layout");
@@ -1020,22 +1067,13 @@ fbx_status fbx_clean_run(fbx_clean* clean, const uint8_t* d_raw, uint64_t raw_le
   }
   if (e != hipSuccess) return hip_failed(e, "set-up");
   if (tiles) {
-    // as many workgroups as run at the same time (the LDS decides: asked once per size), each a run of tiles; the
-    // writing launch takes the same runs
-    if (clean->grid_lds != lds_measure) {
-      int per_cu = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&k_clean_measure_tile), kCleanThreads, lds_measure) != hipSuccess || per_cu < 1) {
-        (void)hipGetLastError();
-        per_cu = 1;
-      }
-      clean->grid_lds = lds_measure;
-      clean->grid = std::min(kMaxRuns, tile_cu_count() * static_cast<uint32_t>(per_cu));
-    }
-    C.run = (C.n_tiles + clean->grid - 1) / clean->grid;
+    // as many workgroups as run at the same time, each a run of tiles; the writing launch takes the same runs
+    const uint32_t at_once = clean_grid(*clean, lds_measure);
+    C.run = (C.n_tiles + at_once - 1) / at_once;
     const uint32_t grid = (C.n_tiles + C.run - 1) / C.run;
     hipLaunchKernelGGL(k_clean_measure_tile, dim3(grid), dim3(kCleanThreads), lds_measure, st, C);
     e = hipGetLastError();
-    C.export_to = clean->exported;
+    if (e == hipSuccess) C.export_to = export_taken(*clean);
     if (e == hipSuccess) hipLaunchKernelGGL(k_clean_write_tile, dim3(grid), dim3(kCleanThreads), lds_write, st, C);
     if (e == hipSuccess) e = hipGetLastError();
   } else {
@@ -1058,16 +1096,17 @@ fbx_status fbx_clean_run(fbx_clean* clean, const uint8_t* d_raw, uint64_t raw_le
   if (C.export_to) {
     std::memcpy(&back.c, C.export_to, sizeof back.c);
     std::memcpy(back.total, C.export_to + sizeof(Ctrl) / 8, sizeof back.total);
+    export_returned(*clean, C.export_to);  // (after an error of the runtime it stays out of use: a kernel may still write it)
   }
-  if (back.c.err & CE_OFFSETS) { clean->error = "record offsets must be non-decreasing and end within raw_len"; return FBX_E_INPUT; }
-  if (back.c.err & CE_TILE) { clean->error = "a record of 2 GiB or more, or one that cleans to 4 GiB or more"; return FBX_E_INPUT; }
+  if (back.c.err & CE_OFFSETS) { clean_error(*clean, "record offsets must be non-decreasing and end within raw_len"); return FBX_E_INPUT; }
+  if (back.c.err & CE_TILE) { clean_error(*clean, "a record of 2 GiB or more, or one that cleans to 4 GiB or more"); return FBX_E_INPUT; }
   out->n_kept = back.total[1];
   out->out_len = back.total[0];
   if (back.c.err & CE_NOMEM) {
-    clean->error = "output buffer too small: need " + std::to_string(back.total[0]) + " bytes";
+    clean_error(*clean, "output buffer too small: need " + std::to_string(back.total[0]) + " bytes");
     return FBX_E_NOMEM;
   }
-  clean->error.clear();
+  clean_error(*clean, "");
   return FBX_OK;
 }
 

@@ -197,3 +197,40 @@ def test_cleaned_text_feeds_extraction_on_the_device():
     got, ws = B.extract_with_retry(plan, d_out[:res.out_len], d_out_off[:res.n_kept + 1])
     assert_same({s: expand(got.slots[s], res.n_kept) for s in got.slot_ids}, got, want, "clean then extract")
     plan.close()
+
+
+def test_threads_share_a_specification():
+    """Calls that run at the same time on one specification, with buffers of their own, get their own sizes back."""
+    import threading
+
+    import torch
+    spec = "fbxclean 1\nfields 3\nfill field=1 value=30\nkeep field=0 prefix=61\n"
+    clean = B.Clean(spec)
+    rng = random.Random(8)
+    cases = []
+    for n in (40, 700, 3, 1500):  # (from one tile to many: calls of different lengths)
+        raw, off = _cat([(rng.choice("ab") + "\t" + rng.choice(["", "x"]) + "\tend\n").encode() for _ in range(n)])
+        want_raw, want_off = C.clean(spec, raw, off)
+        d_raw, d_off = to_device(raw, off)
+        cases.append((d_raw, d_off, len(want_off) - 1, want_raw, torch.empty(want_raw.size + 64, dtype=torch.uint8, device="cuda"),
+                      torch.empty(n + 1, dtype=torch.int64, device="cuda"),
+                      torch.empty(clean.scratch_hint(n), dtype=torch.uint8, device="cuda"), torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    wrong = []
+
+    def calls(d_raw, d_off, n_kept, want, d_out, d_out_off, scratch, stream):
+        for i in range(300):
+            res = clean.run(d_raw, d_off, d_out, d_out_off, scratch, stream=stream.cuda_stream)
+            if (res.n_kept, res.out_len) != (n_kept, want.size):
+                wrong.append((i, res.n_kept, n_kept, res.out_len, want.size))
+                return
+
+    threads = [threading.Thread(target=calls, args=c) for c in cases]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong, wrong
+    for d_raw, d_off, n_kept, want, d_out, *_ in cases:
+        assert np.array_equal(d_out[:want.size].cpu().numpy(), want)
+    clean.close()
