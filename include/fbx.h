@@ -343,8 +343,12 @@ fbx_status fbx_extract_unordered(fbx_plan* plan, uint32_t slot_id, const uint8_t
  *
  * fbx_clean_create   : HOST only.  Errors: FBX_E_ARG, FBX_E_SPEC (fbx_clean_last_error(NULL) says why).
  * fbx_clean_scratch_hint : bytes of scratch that fbx_clean_run needs for n_records records.
- *   (A buffer that holds only 24 bytes a record and the specification's tables does too: such a call takes
- *   a thread a record and is slower.)
+ *   (20 bytes a record and 4 for each of up to 2 k + 3 runs of bytes that a record's cleaned form can consist of,
+ *   k fields having operators.  A buffer that holds only 24 bytes a record and the specification's tables does
+ *   too: such a call finds those runs twice instead of keeping them, takes about five times as long, and
+ *   fbx_clean_last_error says after it how much would have been enough.  Nor are they kept, and the hint is
+ *   24 bytes a record, for a specification with more than about 35 KB of operators, at 16 bytes and their
+ *   arguments each, or too many fields for 32 KB of tables.)
  * fbx_clean_run      : d_raw / d_rec_off as for fbx_extract (DEVICE).
  *     d_out      : DEVICE, out_cap bytes: receives the cleaned text
  *     d_out_off  : DEVICE, n_records + 1 u64: entries 0 .. n_kept receive the kept records' offsets

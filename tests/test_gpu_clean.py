@@ -18,12 +18,12 @@ def _cat(records):
     return np.frombuffer(b"".join(records), np.uint8), np.cumsum([0] + [len(r) for r in records]).astype(np.uint64)
 
 
-def _gpu_clean(spec, raw, off, out_cap=None, misalign=0):
+def _gpu_clean(spec, raw, off, out_cap=None, misalign=0, scratch_bytes=None):
     import torch
     n = len(off) - 1
     clean = B.Clean(spec)
     d_raw, d_off = to_device(raw, off, misalign)
-    scratch = torch.empty(clean.scratch_hint(n), dtype=torch.uint8, device="cuda").fill_(0x6B)
+    scratch = torch.empty(scratch_bytes or clean.scratch_hint(n), dtype=torch.uint8, device="cuda").fill_(0x6B)
     d_out = torch.empty(raw.size + 64 * n + 64 if out_cap is None else out_cap, dtype=torch.uint8, device="cuda").fill_(0x21)
     d_out_off = torch.full((n + 1,), -1, dtype=torch.int64, device="cuda")
     res = clean.run(d_raw, d_off, d_out, d_out_off, scratch)
@@ -81,15 +81,20 @@ def _wide_case(rng, F, n, long_every=0, n_ops=12, width=10, keep_all=False):
     (100, 2500, 97, 30, 8),      # now and then a tile whose text does not fit the section: read in place
     (1, 9000, 0, 2, 6),          # tiles of 64 short records
     (7, 700, 5, 6, 300),         # long fields: few records per tile, many tiles read in place
-    (5000, 24, 0, 50, 3),        # more fields than the tables in LDS hold: one record per thread
+    (5000, 24, 0, 50, 3),        # more fields than the tables of the kernel without segments hold: a record per thread
+    (20000, 5, 0, 50, 3),        # more than any table in LDS holds
+    (100, 900, 50, 2500, 6),     # more operators than LDS holds beside the text: no segments are kept
 ])
-def test_clean_tiles_of_every_shape(F, n, long_every, n_ops, width):
+@pytest.mark.parametrize("keep", [True, False])
+def test_clean_tiles_of_every_shape(F, n, long_every, n_ops, width, keep):
+    """keep: with room for segments in the scratch buffer (where the specification allows it), or with 24 bytes a record."""
     rng = random.Random(F * 1000 + n)
     spec, recs = _wide_case(rng, F, n, long_every, n_ops, width, keep_all=n % 2 == 1)
     raw, off = _cat(recs)
     want_raw, want_off = C.clean(spec, raw, off)
     assert 0 < len(want_off) - 1, "the case keeps no record"
-    res, d_out, d_out_off = _gpu_clean(spec, raw, off, out_cap=want_raw.size + 1000, misalign=n % 5)
+    little = 24 * n + 16 * n_ops + 4 * F + 9 * n_ops + 3 * 4096  # (records; operators, fields and arguments; alignment)
+    res, d_out, d_out_off = _gpu_clean(spec, raw, off, out_cap=want_raw.size + 1000, misalign=n % 5, scratch_bytes=None if keep else little)
     assert res.n_kept == len(want_off) - 1 and res.out_len == want_raw.size
     assert np.array_equal(d_out_off[:res.n_kept + 1].cpu().numpy().view(np.uint64), want_off)
     assert np.array_equal(d_out[:res.out_len].cpu().numpy(), want_raw)
@@ -97,7 +102,7 @@ def test_clean_tiles_of_every_shape(F, n, long_every, n_ops, width):
 
 
 def test_a_scratch_buffer_without_room_for_segments_still_does():
-    """24 bytes a record and the tables: too little for the tile kernels, enough for one record per thread."""
+    """24 bytes a record and the tables: too little to keep segments, enough for the kernel that keeps none."""
     import torch
     n = 1000
     spec = ("fbxclean 1\nfields 100\n" + "".join(f"fill field={k} value=30\n" for k in range(30))
@@ -121,6 +126,8 @@ def test_a_scratch_buffer_without_room_for_segments_still_does():
         assert np.array_equal(d_out_off[:res.n_kept + 1].cpu().numpy().view(np.uint64), want_off)
         assert np.array_equal(d_out[:res.out_len].cpu().numpy(), want_raw)
         assert bool((buf[size:] == 0x6B).all()), "written beyond the scratch buffer"
+        note = B.lib().fbx_clean_last_error(clean._h).decode()
+        assert str(hint) in note if size < hint else note == ""
     with pytest.raises(B.FbxError) as e:
         clean.run(d_raw, d_off, d_out, d_out_off, buf[:little // 2])
     assert e.value.status == B.E_NOMEM

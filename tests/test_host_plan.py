@@ -200,3 +200,13 @@ def test_a_workspace_holds_no_more_tables_than_it_was_sized_for(cfg, tables):
     assert B.lib().fbx_plan_set_workspace(plan._h, 256, 1) == B.E_NOMEM
     assert int(re.search(r"\((\d+) bytes\)", B.lib().fbx_last_error(plan._h).decode()).group(1)) <= tables
     plan.close()
+
+
+def test_scratch_for_segments_is_asked_for_only_where_they_can_be_kept():
+    """1,000 fields with an operator each leave no room for the kernels that keep segments (4 bytes each, 2,003 a record)."""
+    clean = B.Clean("fbxclean 1\nfields 1000\n" + "".join(f"fill field={k} value=30313233\n" for k in range(1000)))
+    assert clean.scratch_hint(1_000_000) <= 25 * 1_000_000
+    clean.close()
+    clean = B.Clean("fbxclean 1\nfields 100\nfill field=3 value=30\n")
+    assert 1_000_000 * (20 + 4 * 5) <= clean.scratch_hint(1_000_000) <= 1_000_000 * (20 + 4 * 5) + (1 << 18)
+    clean.close()
