@@ -9,7 +9,7 @@ from oracle import fbx_oracle as O
 from paper_2210_07768_amd import binding as B
 from paper_2210_07768_amd import workloads as W
 from helpers import FOLLOW_SPEC, FRAMING_RECORDS, FRAMING_SPEC, random_dag
-from gpu_harness import assert_same, check, check_window, device_workload, run_gpu, to_device
+from gpu_harness import assert_same, check, check_window, device_workload, expand, run_gpu, to_device
 from oracle_ranges import check_every_sign, extract_parallel
 
 pytestmark = pytest.mark.gpu
@@ -806,3 +806,24 @@ def test_batches_with_a_tile_that_does_not_fit_stop_trying_the_one_launch_sequen
     res = plan.extract(*d_long)
     assert "fell back" in res.note
     plan.close()
+
+
+def test_plans_with_different_lds_sections_take_turns():
+    """The kernel for any plan is one function: what one plan asks of it must not be in another one's way."""
+    w = W.get(5, 300)
+    raw, off = w.generate()
+    want = O.extract(w.spec, raw, off)
+    d_raw, d_off = to_device(raw, off)
+    plans = []
+    for cap in (60000, 8000, 60000):  # (sections of more than 64 KB with the tables, and of less)
+        plan = B.Plan(w.spec)
+        plan.set_option("tile_log2", 5)
+        plan.set_option("raw_cap", cap)
+        plan.set_option("one_launch", 0)
+        plans.append(plan)
+        B.extract_with_retry(plan, d_raw, d_off)
+    for plan in plans + plans[::-1]:
+        res = plan.extract(d_raw, d_off)
+        assert_same({s: expand(res.slots[s], 300) for s in res.slot_ids}, res, want)
+    for plan in plans:
+        plan.close()
