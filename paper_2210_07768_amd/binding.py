@@ -134,6 +134,13 @@ def lib():
     return _lib
 
 
+def __getattr__(name):
+    if name == "Slot":  # (the type of a result's slots, which the native part defines)
+        lib()
+        return _native.Slot
+    raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
+
+
 class ExtractResult:
     """What fbx_extract reported.  ``slots`` (slot id -> slot) and ``slot_ids`` (in emission order)
     are built from the library's slot table when first asked for.  A slot has ``slot_id``, ``fixed_arity``,

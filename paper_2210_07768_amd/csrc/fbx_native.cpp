@@ -92,6 +92,8 @@ PyGetSetDef slot_getset[] = {
 
 PyTypeObject SlotType = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
+const char kStrided[] = "the buffer must be contiguous";
+
 // slots(table, home, base, n_offsets, n_tiles) -> (dict of slot id -> Slot, list of slot ids).  table: the library's
 // slot table as bytes; home: the tensor whose first byte lies at address base.
 PyObject* slots(PyObject*, PyObject* args) {
@@ -106,6 +108,10 @@ PyObject* slots(PyObject*, PyObject* args) {
     return nullptr;
   }
   const at::Tensor& t = THPVariable_Unpack(home);
+  if (!t.is_contiguous()) {  // (a view made from places in the storage would show what lies between its elements)
+    PyErr_SetString(PyExc_RuntimeError, kStrided);
+    return nullptr;
+  }
   const unsigned long long size = t.numel() * t.element_size() / 8 * 8;
   const long long first_byte = t.storage_offset() * static_cast<long long>(t.element_size());
   if (first_byte % 8 != 0) {
@@ -161,14 +167,33 @@ PyObject* slots(PyObject*, PyObject* args) {
   return Py_BuildValue("(NN)", dict, list);
 }
 
+// Elements and address (0 for none of them) of a tensor, or of anything else that has numel() and data_ptr().
+bool array(PyObject* o, uint64_t& n, uint64_t& address) {
+  if (THPVariable_Check(o)) {
+    const at::Tensor& t = THPVariable_Unpack(o);
+    n = t.numel();
+    address = n ? reinterpret_cast<uint64_t>(t.data_ptr()) : 0;
+    return true;
+  }
+  auto ask = [&](const char* method, uint64_t& v) -> bool {
+    PyObject* r = PyObject_CallMethod(o, method, nullptr);
+    if (!r) return false;
+    v = PyLong_AsUnsignedLongLong(r);
+    Py_DECREF(r);
+    return !PyErr_Occurred();
+  };
+  address = 0;
+  return ask("numel", n) && (!n || ask("data_ptr", address));
+}
+
 // extract(plan, raw, rec_off, stream, out_buffer or None) -> (status, records, signs, malformed numerics, high water,
 // layers, tile launches, records of a tile in arrival order, note, slot table as bytes)
 PyObject* extract(PyObject*, PyObject* args) {
   unsigned long long plan, stream;
   PyObject *raw, *off, *buffer;
   if (!PyArg_ParseTuple(args, "KOOKO", &plan, &raw, &off, &stream, &buffer)) return nullptr;
-  if (!THPVariable_Check(raw) || !THPVariable_Check(off) || (buffer != Py_None && !THPVariable_Check(buffer))) {
-    PyErr_SetString(PyExc_TypeError, "text, offsets and output buffer must be torch tensors");
+  if (buffer != Py_None && !THPVariable_Check(buffer)) {
+    PyErr_SetString(PyExc_TypeError, "the output buffer must be a torch tensor");
     return nullptr;
   }
   fbx_plan* p = reinterpret_cast<fbx_plan*>(plan);
@@ -176,10 +201,15 @@ PyObject* extract(PyObject*, PyObject* args) {
   fbx_status st;
   const char* error = nullptr;
   try {
-    const at::Tensor &d_raw = THPVariable_Unpack(raw), &d_off = THPVariable_Unpack(off);
-    const uint64_t raw_len = d_raw.numel(), n_records = d_off.numel() - 1;
-    const uint8_t* text = raw_len ? static_cast<const uint8_t*>(d_raw.data_ptr()) : nullptr;
-    const uint64_t* offsets = static_cast<const uint64_t*>(d_off.data_ptr());
+    if (buffer != Py_None && !THPVariable_Unpack(buffer).is_contiguous()) {
+      PyErr_SetString(PyExc_RuntimeError, kStrided);
+      return nullptr;
+    }
+    uint64_t raw_len, n_offsets, raw_at, off_at;
+    if (!array(raw, raw_len, raw_at) || !array(off, n_offsets, off_at)) return nullptr;
+    const uint64_t n_records = n_offsets - 1;
+    const uint8_t* text = reinterpret_cast<const uint8_t*>(raw_at);
+    const uint64_t* offsets = reinterpret_cast<const uint64_t*>(off_at);
     void* out = buffer == Py_None ? nullptr : THPVariable_Unpack(buffer).data_ptr();
     const uint64_t out_bytes = buffer == Py_None ? 0 : THPVariable_Unpack(buffer).numel();
     Py_BEGIN_ALLOW_THREADS

@@ -210,3 +210,26 @@ def test_scratch_for_segments_is_asked_for_only_where_they_can_be_kept():
     clean = B.Clean("fbxclean 1\nfields 100\nfill field=3 value=30\n")
     assert 1_000_000 * (20 + 4 * 5) <= clean.scratch_hint(1_000_000) <= 1_000_000 * (20 + 4 * 5) + (1 << 18)
     clean.close()
+
+
+def test_what_the_native_part_of_the_binding_takes_and_refuses():
+    """Buffers whose elements do not lie side by side are refused; offsets and text may be anything with numel() and data_ptr()."""
+    import torch
+
+    B.lib()
+    buf = torch.zeros(64, dtype=torch.uint8)
+    assert B._native.slots(b"", buf, buf.data_ptr(), 1, 0) == ({}, [])
+    with pytest.raises(RuntimeError, match="contiguous"):
+        B._native.slots(b"", buf[::2], buf.data_ptr(), 1, 0)
+    off = torch.zeros(2, dtype=torch.int64)
+    with pytest.raises(RuntimeError, match="contiguous"):
+        B._native.extract(0, buf, off, 0, buf[::2])
+
+    class Array:  # (a stranger's device array)
+        def __init__(self, t):
+            self.numel, self.data_ptr = t.numel, t.data_ptr
+
+    assert B._native.extract(0, Array(buf), Array(off), 0, None)[0] == B.E_ARG  # (no plan: the arguments were read)
+    with pytest.raises(AttributeError):
+        B._native.extract(0, object(), Array(off), 0, None)
+    assert isinstance(B.Slot, type)
