@@ -2082,8 +2082,13 @@ hipError_t launch_tile(const TileParams& P, int mode, TileResident* known, hipSt
                      : mode == 1 ? reinterpret_cast<const void*>(&k_tile<1>)
                      : mode == 2 ? reinterpret_cast<const void*>(&k_tile<2>)
                                  : reinterpret_cast<const void*>(&k_tile<3>);
-    if (P.lds_bytes > 48u * 1024u) {  // (the limit belongs to the function, which all plans share: never this plan's size, which may be less than another's)
-      hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)std::max(P.lds_bytes, tile_max_lds()));
+    if (P.lds_bytes > 48u * 1024u) {
+      // (the limit belongs to the function, which all plans share: what the device has beside the kernel's own, never
+      // this plan's size, which may be less than another's)
+      hipFuncAttributes own{};
+      hipError_t e = hipFuncGetAttributes(&own, fn);
+      if (e == hipSuccess)
+        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)std::max(P.lds_bytes, tile_max_lds() - (uint32_t)own.sharedSizeBytes));
       if (e != hipSuccess) return e;
     }
     // as many workgroups as can run at the same time (the one-launch mode relies on it)
