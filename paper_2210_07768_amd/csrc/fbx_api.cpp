@@ -161,8 +161,8 @@ struct CallGeometry {
 
 uint32_t round16(uint64_t x) { return static_cast<uint32_t>((x + 15u) & ~uint64_t(15)); }
 
-// LDS layout of the tile kernel for tiles of 2^lt records and raw_cap staged bytes.
-void tile_lds_layout(const fbx_plan& p, uint32_t lt, uint32_t raw_cap, TileParams& tp) {
+// LDS layout of the tile kernel for tiles of 2^lt records and raw_cap staged bytes, where `want` would hold most tiles.
+void tile_lds_layout(const fbx_plan& p, uint32_t lt, uint64_t want, uint32_t raw_cap, TileParams& tp) {
   const PlanHost& h = p.host;
   const uint32_t T = 1u << lt;
   tp.n_mh = p.n_mh; tp.n_split = p.n_split; tp.n_gen = p.n_gen;
@@ -185,14 +185,21 @@ void tile_lds_layout(const fbx_plan& p, uint32_t lt, uint32_t raw_cap, TileParam
   tp.o_gfirst = o; o = round16(o + (tp.n_gen ? 4ull * h.ops.size() : 0ull));
   tp.o_gtot = o; o = round16(o + (tp.n_gen ? 4ull * (h.n_layers + 1u) : 0ull));
   tp.o_ioff = o; o = round16(o + 4ull * (tp.n_mh + 1));
-  // Commas: along with the tabs when the fields that are lists would get one lane each of a workgroup anyway, or when
-  // filters and buckets of list items can use them too; else a few lanes a field (24 list items a record of 807 bytes:
-  // 4.2 against 4.6 ms; 72 of 2,130: 0.71 against 1.03).
-  tp.walk_commas = p.n_split > p.n_mh || 2u * p.n_mh * T > 512u ? 1u : 0u;
-  tp.comma_cap = tp.walk_commas ? std::min(16u * p.n_comma_fields, 2048u) : 0u;  // (a record with more is rare, and its items are looked for in the text)
-  tp.o_ctab = o; o = round16(o + 2ull * T * (tp.walk_commas ? tp.comma_cap + 2u : p.n_mh * kItemCap));
-  tp.o_ctot = o; o = round16(o + (tp.walk_commas ? 2ull * T : 0ull));
-  tp.o_cfirst = o; o = round16(o + 2ull * T * tp.n_mh);
+  // Commas.  Finding them along with the tabs classifies every byte of the text twice, whatever the field; finding them field
+  // by field is a phase of its own and, of filters, a walk from item to item when they are written.
+  // Hashes only: along with the tabs when the fields that are lists would get one lane each of a workgroup (24 list items a
+  // record of 807 bytes: 4.6 ms that way and 4.2 by field; 72 of 2,130: 0.71 and 1.03; 18 lists in 24 fields of 2.1 KB:
+  // 1.01 and 1.08).  With filters or buckets of lists: from 2 KB a record on (14 lists, 2.3 KB: 1.77 ms and 1.95; 4 filters,
+  // 2.8 KB: 0.49 and 0.57; 1 filter, 0.8 KB: 0.63 and 0.46; 24 filters, 1.4 KB: 1.69 and 0.89; 40 lists and 14
+  // filters of them, 1.9 KB: 1.15 and 1.08).  (want is five quarters of what the records take on average.)
+  const bool others = p.n_split > p.n_mh;
+  const bool along = others ? want >= T * (2048ull * 5u / 4u) : 2u * p.n_mh * T > 512u;
+  tp.commas = along ? kCommasWithTabs : (others ? kCommasByField : kCommasOfHashes);
+  // (a record with more is rare; places in the table are kept in 15 bits)
+  tp.comma_cap = along ? std::min({16u * p.n_comma_fields, 2048u, 32767u / T - 2u}) : 0u;
+  tp.o_ctab = o; o = round16(o + 2ull * T * (along ? tp.comma_cap + 2u : p.n_mh * kItemCap));
+  tp.o_ctot = o; o = round16(o + (along ? 2ull * T : 0ull));
+  tp.o_cfirst = o; o = round16(o + (along ? 2ull * T * tp.n_mh : 0ull));
   tp.o_prog = o; o = round16(o + sizeof(OpProg) * h.ops.size());
   tp.o_lbeg = o; o = round16(o + 4ull * h.tile_list_begin.size());
   tp.o_rnr = o; o = round16(o + 4ull * h.derive_tab.size());
@@ -220,7 +227,7 @@ bool tile_geometry(const fbx_plan& p, uint64_t raw_len, uint64_t n_records, Tile
       want = (want + step - 1) / step * step;
     }
     const uint32_t cap = p.raw_cap ? p.raw_cap : round16(std::min<uint64_t>(std::max<uint64_t>(want, 1024), 65000));
-    tile_lds_layout(p, static_cast<uint32_t>(lt), cap, tp);
+    tile_lds_layout(p, static_cast<uint32_t>(lt), p.raw_cap ? p.raw_cap : want, cap, tp);
     const uint32_t limit = (lt == lt_lo) ? dev_max : std::min(p.lds_budget, dev_max);
     if (tp.lds_bytes <= limit) return true;
   }

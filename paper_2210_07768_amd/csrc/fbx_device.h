@@ -44,7 +44,10 @@ struct WalkParams {
 #define FBX_TILE_THREADS 512
 #endif
 constexpr int kTileThreads = FBX_TILE_THREADS;
-constexpr uint32_t kItemCap = 16; // comma positions kept per record and multi-valued hash (TileParams::walk_commas == 0)
+// How a tile's commas are found: field by field, where all fields that are read as lists are hashed, or where some are
+// filtered or put into buckets as lists; or along with a record's tabs.
+enum : int { kCommasOfHashes = 0, kCommasByField = 1, kCommasWithTabs = 2 };
+constexpr uint32_t kItemCap = 16; // comma positions kept per record and multi-valued hash, where they are kept field by field
 constexpr uint32_t kRawPad = 16;  // first byte position of the staged raw text inside its LDS section
 
 struct TileParams {
@@ -80,8 +83,8 @@ struct TileParams {
   uint32_t o_off, o_rs, o_re, o_rows, o_raw, o_stage, o_cnt, o_start, o_run, o_base;
   uint32_t o_prog, o_lbeg, o_rnr, o_aux;  // plan tables
   uint32_t o_tot, o_ioff, o_ctab, o_ctot, o_cfirst, o_cap, o_gfirst, o_gtot;
-  uint32_t walk_commas; // 1: a record's commas are found along with its tabs; 0: field by field
-  uint32_t comma_cap;   // comma positions kept per record (walk_commas)
+  uint32_t commas;      // how commas are found (kCommas...)
+  uint32_t comma_cap;   // comma positions kept per record (kCommasWithTabs)
   uint32_t lds_bytes;
   // What the host needs to know when the call is done: the last workgroup to finish copies the control block and
   // `export_words` words from `export_from` on to `export_to` (host memory; null: nothing is copied).
@@ -113,14 +116,15 @@ struct UnorderedParams {
   X(n_ops) X(n_layers) X(n_ragged) X(n_rnr) X(n_lists) X(aux_bytes) X(rnr_words) X(alias_at) X(n_alias) X(n_mh) X(n_split) X(n_gen) X(n_fields) \
   X(n_stage) X(log2T) X(raw_cap) X(row_stride) X(o_off) X(o_rs) X(o_re) X(o_rows) X(o_raw) X(o_stage) X(o_cnt)     \
   X(o_start) X(o_run) X(o_base) X(o_prog) X(o_lbeg) X(o_rnr) X(o_aux) X(o_tot) X(o_ioff) X(o_ctab) X(o_ctot) X(o_cfirst) X(o_cap) \
-  X(o_gfirst) X(o_gtot) X(walk_commas) X(comma_cap) X(lds_bytes)
+  X(o_gfirst) X(o_gtot) X(commas) X(comma_cap) X(lds_bytes)
 
 #ifndef __HIPCC_RTC__  // (the launch wrappers are host code: not for the run-time compiler)
 // mode 0: counting launch; 1: writing launch (bases from the scan over tiles);
 // 2: counting and writing in one launch (bases by look-back, arrays sized by row_cap);
 // 3: the same with bases by one atomic add per (ragged operator, tile) on row_actual: tiles in arrival order
-struct TileResident {  // how many workgroups of a mode's kernel run at the same time: asked once per device and LDS size
+struct TileResident {  // how many workgroups of a mode's kernel run at the same time: asked once per device, kernel and LDS size
   int dev = -1;
+  const void* fn = nullptr;
   uint32_t lds = 0, workgroups = 0;
 };
 hipError_t launch_tile(const TileParams& P, int mode, TileResident* known, hipStream_t st);  // known: 4 entries, by mode

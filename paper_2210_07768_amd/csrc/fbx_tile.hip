@@ -16,7 +16,7 @@
 //     table has one entry per (record, field).  Where many fields are lists the same
 //     walk leaves every record's commas in a list of positions, and the items of a
 //     field are the stretch between its two ends; where few are, a few lanes split
-//     each of them at its commas (TileParams::walk_commas says which).
+//     each of them at its commas (TileParams::commas says which).
 //  3. Layer 1: lanes are (record, operator) pairs.  A lane looks up its field in
 //     the table and hashes / parses it out of LDS; T neighbouring lanes hold T
 //     consecutive records of one operator, so a slot is written in runs of 8 T
@@ -66,7 +66,7 @@ namespace {
 constexpr uint32_t kNoRow = 0xffffffffu;
 constexpr uint64_t kPrime = 0x100000001b3ull;
 constexpr uint32_t kMaxCount = 0x3ffffffu;  // signs per record and operator
-constexpr uint32_t kNoComma = 0xffffu;      // there are more commas than the table holds: look for them in the text
+constexpr uint32_t kFewCommas = 0x8000u, kNoComma = 0xffffu;  // beside a place in the table of commas: only the first kItemCap are there; none
 
 
 // Pointers the compiler knows to be global memory (plain global loads and stores
@@ -151,8 +151,8 @@ struct Sh {
   uint32_t* ioff;   // [n_mh + 1] first item of every multi-valued hash among the pass's items
   uint16_t* ctab;   // comma positions: [T][comma_cap + 2] a record's first ones (two more, so that neighbouring records
                     // start in different banks), or [n_mh][T][kItemCap] those of a multi-valued hash's field
-  uint16_t* ctot;   // [T] how many the record has (walk_commas)
-  uint16_t* cfirst; // [n_mh][T] where in ctab the commas of a multi-valued hash's field start; kNoComma
+  uint16_t* ctot;   // [T] how many the record has (kCommasWithTabs)
+  uint16_t* cfirst; // [n_mh][T] where in ctab the commas of a multi-valued hash's field start (below 2^15); kFewCommas, kNoComma (kCommasWithTabs)
   // plan tables, copied once per workgroup so that no lane waits on memory for a descriptor
   const OpProg* prog;          // [n_ops], in the order of the work lists
   const uint32_t* list_begin;
@@ -210,25 +210,12 @@ __device__ __forceinline__ bool row_follows(const TileParams& P, const Sh& sh, u
 }
 
 struct LdsSrc {
-  static constexpr bool kTable = true;  // positions fit the 16-bit comma lists
+  static constexpr bool kTable = true;    // positions fit the 16-bit tables of commas
+  static constexpr bool kLists = false;   // a record's commas were found along with its tabs
+  static constexpr bool kOthers = false;  // there are multi-valued root operators besides hashes
   const uint8_t* raw8;
   const uint16_t* rows;
   uint32_t stride;
-  const uint16_t *ctab, *ctot;
-  uint32_t cap;  // 0: there are no lists of a record's commas
-  // The commas of record r inside [s, e): entries [lo, hi) of its list; false when the list does not hold them all.
-  __device__ __forceinline__ bool commas(uint32_t r, uint32_t s, uint32_t e, const uint16_t*& list, uint32_t& lo, uint32_t& hi) const {
-    lo = hi = 0;
-    list = ctab + r * (cap + 2u);
-    if (cap == 0u) return false;
-    const uint32_t n = ctot[r];
-    if (n > cap) return false;
-    for (uint32_t step = 1u << (31u - (uint32_t)__clz((int)(n | 1u))); step; step >>= 1) {  // (two searches side by side)
-      if (lo + step <= n && list[lo + step - 1u] < s) lo += step;
-      if (hi + step <= n && list[hi + step - 1u] < e) hi += step;
-    }
-    return true;
-  }
   __device__ __forceinline__ uint32_t byte(uint32_t p) const { return raw8[p]; }
   // Field k of staged record r: [s, e).  A missing field is empty.
   __device__ __forceinline__ void span(uint32_t r, uint32_t k, uint32_t& s, uint32_t& e) const {
@@ -238,10 +225,30 @@ struct LdsSrc {
     if (e < s) e = s;
   }
 };
+struct LdsOthersSrc : LdsSrc {
+  static constexpr bool kOthers = true;
+};
+struct LdsListSrc : LdsSrc {
+  static constexpr bool kLists = true, kOthers = true;
+  const uint16_t *ctab, *ctot;
+  uint32_t cap;
+  // The commas of record r inside [s, e): entries [lo, hi) of its list; false when the list does not hold all of them.
+  __device__ __forceinline__ bool commas(uint32_t r, uint32_t s, uint32_t e, const uint16_t*& list, uint32_t& lo, uint32_t& hi) const {
+    lo = hi = 0;
+    list = ctab + r * (cap + 2u);
+    const uint32_t n = ctot[r];
+    if (n > cap) return false;
+    for (uint32_t step = 1u << (31u - (uint32_t)__clz((int)(n | 1u))); step; step >>= 1) {  // (two searches side by side)
+      if (lo + step <= n && list[lo + step - 1u] < s) lo += step;
+      if (hi + step <= n && list[hi + step - 1u] < e) hi += step;
+    }
+    return true;
+  }
+};
 
 // One record read in place (it does not fit the LDS section); positions count from its first byte.
 struct GlobalSrc {
-  static constexpr bool kTable = false;
+  static constexpr bool kTable = false, kLists = false, kOthers = true;
   const FBX_GLOBAL uint8_t* rec;
   uint32_t len;  // newline dropped
   __device__ __forceinline__ uint32_t byte(uint32_t p) const { return rec[p]; }
@@ -274,6 +281,7 @@ struct GlobalSrc {
 // Field table of the staged records.  kTileThreads / T lanes (at most 64) share a
 // record and place its tabs.  Entries from the record's tab count on hold the
 // record's end.
+template <int COMMAS>
 __device__ __forceinline__ void tokenize(const TileParams& P, const Sh& sh, uint32_t nb) {
   const uint32_t tid = thread_id();
   constexpr uint32_t kLogThreads = kTileThreads == 1024 ? 10u : (kTileThreads == 512 ? 9u : 8u);
@@ -291,7 +299,7 @@ __device__ __forceinline__ void tokenize(const TileParams& P, const Sh& sh, uint
   uint16_t* row = sh.rows + r * P.row_stride;
   auto put_tab = [&](uint32_t k, uint32_t pos) { row[1u + k] = (uint16_t)pos; };
   uint32_t total;
-  if (P.walk_commas) {
+  if constexpr (COMMAS == kCommasWithTabs) {
     uint16_t* list = sh.ctab + r * (P.comma_cap + 2u);
     total = split_bytes<true>(sh.raw, rs, re, act, lg, j, kTabs, F, put_tab, kCommas, P.comma_cap,
                               [&](uint32_t k, uint32_t pos) { list[k] = (uint16_t)pos; });
@@ -578,7 +586,7 @@ __device__ __forceinline__ bool starts_with(const GlobalSrc& src, uint32_t t, ui
 // multi its comma-separated parts (one more than it has commas, empty ones included).
 template <class Src, class F>
 __device__ __forceinline__ void for_each_token(const Src& src, uint32_t r, uint32_t s, uint32_t e, bool multi, F&& f) {
-  if constexpr (Src::kTable) {
+  if constexpr (Src::kLists) {
     const uint16_t* list;
     uint32_t lo, hi;
     if (!multi) { f(s, e); return; }
@@ -607,7 +615,7 @@ template <class Src>
 __device__ __forceinline__ uint32_t ragged_root_count(const Src& src, const OpProg& d, const uint8_t* aux, uint32_t r, uint32_t s,
                                                       uint32_t e) {
   if (d.kind != OP_FILTER) {  // multi-valued hash / bucket
-    if constexpr (Src::kTable) {
+    if constexpr (Src::kLists) {
       const uint16_t* list;
       uint32_t lo, hi;
       if (src.commas(r, s, e, list, lo, hi)) return hi - lo + 1u;
@@ -725,6 +733,7 @@ struct Pass {
   uint32_t& malformed;
   bool& overflow;
   uint32_t lb_tile;   // tile number when counts are to be published (one-launch mode), else kNoRow
+  bool need_table;    // the pass goes on to write: keep comma positions while counting
 
   // This lane's place in a unit, worked out anew (and hidden from the optimiser's view of the
   // tile loop): otherwise every address that follows from it is computed once per kernel and
@@ -747,52 +756,73 @@ struct Pass {
   }
 
   // ---- counts of the ragged root operators
-  // Multi-valued hashes of staged records where few fields are lists (!walk_commas): a few neighbouring lanes share one
-  // (operator, record) and split the field at its commas.  Every wavefront takes part.
-  __device__ __forceinline__ void split_items(bool keep) {  // keep: the pass goes on to hash the items
+  // Where commas are found field by field (!Src::kLists): a few neighbouring lanes share one (operator, record) and split
+  // the field at its commas.  Every wavefront takes part.
+  // HASHES: multi-valued hashes (the first P.n_mh entries of the ragged root list): the item count, and the first kItemCap
+  // comma positions for the lanes that later hash the items.
+  // Else the other multi-valued operators (the entries up to P.n_split): a bucket list has one sign per item; a filter tests
+  // the token that starts the field and the one after every comma.  (A token is as long as the prefix or longer exactly
+  // when the prefix's bytes follow its start and hold no comma: a prefix with a comma passes nothing, F_NEVER.)
+  // (One loop for both is slower where there are hashes only: 1.30 against 1.22 ms for 200,000 records with 18 lists.)
+  template <bool HASHES>
+  __device__ __forceinline__ void split_lists() {
     const uint32_t tid = thread_id();
-    const uint32_t np = P.n_mh * T;  // (operator, record slot) pairs
-    uint32_t lg = 0;                 // log2 of the lanes per pair
+    const uint32_t first = HASHES ? 0u : P.n_mh;
+    const uint32_t np = ((HASHES ? P.n_mh : P.n_split) - first) * T;  // (operator, record slot) pairs
+    uint32_t lg = 0;                                                  // log2 of the lanes per pair
     while (lg < 6u && (np << (lg + 1u)) <= kTileThreads) ++lg;
     const uint32_t j = tid & ((1u << lg) - 1u);
     for (uint32_t p0 = 0; p0 < np; p0 += kTileThreads >> lg) {
       const uint32_t pr = p0 + (tid >> lg);
       const uint32_t i = pr / T, rr = pr & (T - 1u);
       const bool in = pr < np, act = in && rr < nb;
-      const OpProg& d = sh.prog[sh.lbeg(TL_RAGROOT) + (in ? i : 0u)];
-      uint32_t s = 0, e = 0;
+      const OpProg& d = sh.prog[sh.lbeg(TL_RAGROOT) + first + (in ? i : 0u)];
+      uint32_t s = 0, e = 0, c;
       if (act) src.span(rr, d.field, s, e);
-      uint16_t* tab = sh.ctab + pr * kItemCap;
-      const uint32_t commas = split_bytes<false>(src.raw8, s, e, act, lg, j, kCommas, keep ? kItemCap : 0u, [&](uint32_t k, uint32_t pos) {
-        tab[k] = (uint16_t)pos;
-      }, 0u, 0u, [](uint32_t, uint32_t) {});
-      if (in && j == 0) {
-        sh.cnt[d.rag_row * T + rr] = act ? commas + 1u : 0u;  // items = commas + 1 (far below kMaxCount)
-        sh.cfirst[pr] = (uint16_t)(commas <= kItemCap ? pr * kItemCap : kNoComma);
+      if constexpr (HASHES) {
+        uint16_t* tab = sh.ctab + pr * kItemCap;
+        c = split_bytes<false>(src.raw8, s, e, act, lg, j, kCommas, need_table ? kItemCap : 0u,
+                               [&](uint32_t k, uint32_t pos) { tab[k] = (uint16_t)pos; }, 0u, 0u, [](uint32_t, uint32_t) {}) + 1u;
+      } else {
+        const bool filter = d.kind == OP_FILTER;  // (the same for all lanes of a field)
+        const Prefix pre(sh.aux, d);
+        uint32_t hits = (act && filter && j == 0 && starts_with(src, s, e, pre)) ? 1u : 0u;
+        c = split_bytes<false>(src.raw8, s, e, act, lg, j, kCommas, filter ? ~0u : 0u,
+                               [&](uint32_t, uint32_t pos) { hits += starts_with(src, pos + 1u, e, pre) ? 1u : 0u; },
+                               0u, 0u, [](uint32_t, uint32_t) {}) + 1u;
+        for (uint32_t w = 1; w < (1u << lg); w <<= 1) hits += __shfl_xor(hits, (int)w, 64);
+        if (filter) c = (d.flags & F_NEVER) ? 0u : hits;
       }
+      if (in && j == 0) sh.cnt[d.rag_row * T + rr] = act ? c : 0u;  // (far below kMaxCount)
     }
   }
-  // Units of a wavefront: multi-valued hashes, G operators; other multi-valued operators (filters, buckets), eight
-  // lanes a field; single-valued filters and n-grams, G operators.  They run side by side on different wavefronts, so
-  // what counts is the longest one.
-  __device__ __forceinline__ uint32_t mh_count_units() const { return P.walk_commas || !Src::kTable ? (P.n_mh + G - 1u) / G : 0u; }
-  __device__ __forceinline__ uint32_t split_count_units() const { return ((P.n_split - P.n_mh) * T + 7u) >> 3; }
+  // Units of a wavefront.  Where a record's commas are listed: other multi-valued operators than hashes, eight lanes a
+  // field; multi-valued hashes, G operators; single-valued filters, G operators.  Elsewhere: what split_lists does
+  // not count, G operators (records read in place: all).  Then n-grams, G operators.  They run side by side on
+  // different wavefronts, so what counts is the longest one.
+  __device__ __forceinline__ uint32_t split_count_units() const { return Src::kLists ? ((P.n_split - P.n_mh) * T + 7u) >> 3 : 0u; }
+  __device__ __forceinline__ uint32_t mh_count_units() const { return Src::kLists ? (P.n_mh + G - 1u) / G : 0u; }
+  __device__ __forceinline__ uint32_t count_skip() const {
+    return Src::kTable ? P.n_split : 0u;
+  }
   __device__ __forceinline__ uint32_t other_count_units() const {
-    return (sh.lbeg(TL_RAGROOT + 1) - sh.lbeg(TL_RAGROOT) - P.n_split + G - 1u) / G;
+    return (sh.lbeg(TL_RAGROOT + 1) - sh.lbeg(TL_RAGROOT) - count_skip() + G - 1u) / G;
   }
   __device__ __forceinline__ uint32_t count_units() const {
     return split_count_units() + mh_count_units() + other_count_units() + units_of(TL_NGRAM);
   }
   __device__ __forceinline__ void count_unit(uint32_t u) {
     refresh();
-    if (u < split_count_units()) { count_split_unit(u); return; }
-    u -= split_count_units();
     const uint32_t lb = sh.lbeg(TL_RAGROOT);
-    if (u < mh_count_units()) { count_mh_unit(u); return; }
-    u -= mh_count_units();
+    if constexpr (Src::kLists) {
+      if (u < split_count_units()) { count_split_unit(u); return; }
+      u -= split_count_units();
+      if (u < mh_count_units()) { count_mh_unit(u); return; }
+      u -= mh_count_units();
+    }
     const OpProg* d;
     if (u < other_count_units()) {
-      const uint32_t i = P.n_split + u * G + og;
+      const uint32_t i = count_skip() + u * G + og;
       d = lb + i < sh.lbeg(TL_RAGROOT + 1) ? &sh.prog[lb + i] : nullptr;
     } else {
       d = op_of(TL_NGRAM, u - other_count_units());
@@ -803,32 +833,42 @@ struct Pass {
       uint32_t s, e;
       src.span(r, d->field, s, e);
       if (d->kind == OP_NGRAM) c = e - s >= d->aux_len ? e - s - d->aux_len + 1u : 0u;
-      else c = starts_with(src, s, e, Prefix(sh.aux, *d)) ? 1u : 0u;
+      else if constexpr (Src::kTable) c = starts_with(src, s, e, Prefix(sh.aux, *d)) ? 1u : 0u;
+      else c = ragged_root_count(src, *d, sh.aux, r, s, e);
     }
     if (c > kMaxCount) overflow = true;
     sh.cnt[d->rag_row * T + r] = c;
   }
   // A multi-valued hash has one sign more than its field has commas; where they start is kept for the lanes that hash
-  // the items.
+  // the items.  A record with more commas than its list holds (a field of many items, or commas in fields that nobody reads
+  // as lists) uses the list's memory as the other scheme does: kItemCap positions an operator, found by its lane.
   __device__ __forceinline__ void count_mh_unit(uint32_t u) {
     const uint32_t i = u * G + og;
     if (i >= P.n_mh) return;
     const OpProg& d = sh.prog[sh.lbeg(TL_RAGROOT) + i];
     uint32_t c = 0;
     if (live) {
-      uint32_t s, e, at = kNoComma;
+      uint32_t s, e, lo, hi, at;
+      const uint16_t* list;
       src.span(r, d.field, s, e);
-      bool listed = false;
-      if constexpr (Src::kTable) {
-        const uint16_t* list;
-        uint32_t lo, hi;
-        if (src.commas(r, s, e, list, lo, hi)) {
-          c = hi - lo + 1u;
-          at = (uint32_t)(list - sh.ctab) + lo;
-          listed = true;
+      if (src.commas(r, s, e, list, lo, hi)) {
+        c = hi - lo + 1u;
+        at = (uint32_t)(list - sh.ctab) + lo;
+      } else if (!need_table) {
+        c = count_commas(src, s, e) + 1u;
+        at = kNoComma;
+      } else {
+        const uint32_t mine = r * (src.cap + 2u) + i * kItemCap;
+        const bool room = (i + 1u) * kItemCap <= src.cap;
+        for (uint32_t p = s;; ++p) {
+          p = next_comma(src, p, e);
+          if (p >= e) break;
+          if (room && c < kItemCap) sh.ctab[mine + c] = (uint16_t)p;
+          ++c;
         }
+        ++c;
+        at = room ? mine | kFewCommas : kNoComma;
       }
-      if (!listed) c = count_commas(src, s, e) + 1u;
       sh.cfirst[i * T + r] = (uint16_t)at;
     }
     if (c > kMaxCount) overflow = true;
@@ -843,24 +883,18 @@ struct Pass {
     const OpProg& d = sh.prog[sh.lbeg(TL_RAGROOT) + P.n_mh + (in ? i : 0u)];
     uint32_t c = 0;
     if (act) {
-      uint32_t s, e;
+      uint32_t s, e, lo, hi;
+      const uint16_t* list;
       src.span(rr, d.field, s, e);
-      bool listed = false;
-      if constexpr (Src::kTable) {
-        const uint16_t* list;
-        uint32_t lo, hi;
-        if (src.commas(rr, s, e, list, lo, hi)) {
-          listed = true;
-          if (d.kind != OP_FILTER) {
-            c = q == 0u ? hi - lo + 1u : 0u;
-          } else if (!(d.flags & F_NEVER)) {
-            const Prefix pre(sh.aux, d);
-            for (uint32_t t = lo + q; t <= hi; t += 8u)  // the token in front of comma t (the last one: in front of e)
-              c += starts_with(src, t == lo ? s : (uint32_t)list[t - 1u] + 1u, t == hi ? e : list[t], pre) ? 1u : 0u;
-          }
-        }
+      if (!src.commas(rr, s, e, list, lo, hi)) {
+        if (q == 0u) c = ragged_root_count(src, d, sh.aux, rr, s, e);
+      } else if (d.kind != OP_FILTER) {
+        c = q == 0u ? hi - lo + 1u : 0u;
+      } else if (!(d.flags & F_NEVER)) {
+        const Prefix pre(sh.aux, d);
+        for (uint32_t t = lo + q; t <= hi; t += 8u)  // the token in front of comma t (the last one: in front of e)
+          c += starts_with(src, t == lo ? s : (uint32_t)list[t - 1u] + 1u, t == hi ? e : list[t], pre) ? 1u : 0u;
       }
-      if (!listed && q == 0u) c = ragged_root_count(src, d, sh.aux, rr, s, e);
     }
     for (uint32_t w = 1; w < 8u; w <<= 1) c += __shfl_xor(c, (int)w, 64);
     if (c > kMaxCount) overflow = true;
@@ -1049,16 +1083,21 @@ struct Pass {
     const uint32_t rr = lo, j = pos - st[rr], cnt = sh.cnt[row * T + rr];
     uint32_t s, e;
     src.span(rr, d.field, s, e);
-    uint32_t is = s, ie = e;
-    const uint32_t cf = sh.cfirst[i * T + rr];
-    if (cf != kNoComma) {
-      const uint16_t* list = sh.ctab + cf;
-      if (j) is = (uint32_t)list[j - 1u] + 1u;
-      if (j + 1u < cnt) ie = list[j];
-    } else {
-      for (uint32_t c = 0; c < j; ++c) is = next_comma(src, is, e) + 1u;
-      if (j + 1u < cnt) ie = next_comma(src, is, e);
+    // the item's bounds: of the positions that are kept, then comma by comma from the last of them on
+    const uint16_t* list = sh.ctab;
+    uint32_t kept = 0;
+    if constexpr (Src::kLists) {
+      const uint32_t at = sh.cfirst[i * T + rr];
+      kept = (at & kFewCommas) == 0u ? cnt : (at == kNoComma ? 0u : kItemCap);
+      list += at & ~kFewCommas;
+    } else if constexpr (Src::kTable) {
+      kept = kItemCap;
+      list += (i * T + rr) * kItemCap;
     }
+    const uint32_t known = min(j, kept);
+    uint32_t is = known ? (uint32_t)list[known - 1u] + 1u : s, ie = e;
+    for (uint32_t c = known; c < j; ++c) is = next_comma(src, is, e) + 1u;
+    if (j + 1u < cnt) ie = j < kept ? (uint32_t)list[j] : next_comma(src, is, e);
     const uint64_t first = sh.base[row] + pos;
     if (j == 0 && (d.flags & F_EMIT)) {
       G64 off = gptr<uint64_t>(d.offsets);
@@ -1464,7 +1503,7 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
   constexpr bool WRITE = MODE != 0;
   const uint32_t tid = thread_id(), lane = tid & 63u, wave = tid >> 6;
   const uint32_t T = 1u << P.log2T;
-  Pass<Src> ps{P, sh, src, nb, g_first, T, 64u >> P.log2T, lane & (T - 1u), lane >> P.log2T, false, 0, malformed, overflow, MODE == 2 ? tile : kNoRow};
+  Pass<Src> ps{P, sh, src, nb, g_first, T, 64u >> P.log2T, lane & (T - 1u), lane >> P.log2T, false, 0, malformed, overflow, MODE == 2 ? tile : kNoRow, WRITE};
   ps.live = ps.r < nb;
   ps.g = g_first + ps.r;
   // the single-valued hashes and buckets of layer 1 fill whatever phase has idle wavefronts
@@ -1505,8 +1544,11 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
 
   // ---- phase A: counts of the ragged root operators
   bool absurd = false;
-  if constexpr (Src::kTable) {
-    if (P.n_mh && !P.walk_commas) ps.split_items(WRITE);
+  if constexpr (Src::kTable && !Src::kLists) {
+    if (P.n_mh) ps.template split_lists<true>();
+    if constexpr (Src::kOthers) {
+      if (P.n_split > P.n_mh) ps.template split_lists<false>();
+    }
   }
   if (P.n_ragged) critical_phase(ps.count_units(), &s_ctr[1], &s_done, [&](uint32_t u) { ps.count_unit(u); });
   else __syncthreads();
@@ -1687,7 +1729,7 @@ __device__ __forceinline__ u32x4 load_chunk(uintptr_t ca, uintptr_t ok_lo, uintp
 
 // Workgroups are persistent: each copies the plan tables into LDS once and then
 // takes tiles off a shared counter until none is left.
-template <int MODE>
+template <int MODE, int COMMAS>
 __device__ __forceinline__ void tile_body(const TileParams& P) {
   constexpr bool WRITE = MODE != 0;
   __shared__ uint32_t s_err, s_len, s_cur, s_nxt;
@@ -1881,14 +1923,16 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
         }
         __syncthreads();
         FBX_MARK(2);
-        if (!FBX_SKIP(8u)) tokenize(P, sh, nb);
+        if (!FBX_SKIP(8u)) tokenize<COMMAS>(P, sh, nb);
         if (FBX_SKIP(0x100u)) {  // (tuning builds: once more, to weigh it)
           __syncthreads();
-          tokenize(P, sh, nb);
+          tokenize<COMMAS>(P, sh, nb);
         }
         __syncthreads();
         FBX_MARK(3);
-        LdsSrc src{sh.raw, sh.rows, P.row_stride, sh.ctab, sh.ctot, P.walk_commas ? P.comma_cap : 0u};
+        std::conditional_t<COMMAS == kCommasWithTabs, LdsListSrc, std::conditional_t<COMMAS == kCommasByField, LdsOthersSrc, LdsSrc>> src;
+        src.raw8 = sh.raw; src.rows = sh.rows; src.stride = P.row_stride;
+        if constexpr (COMMAS == kCommasWithTabs) { src.ctab = sh.ctab; src.ctot = sh.ctot; src.cap = P.comma_cap; }
         run_pass<MODE>(P, sh, src, nb, g0 + r0, tile, malformed, overflow, next_tile_hook);
         r0 = r1;
       } else {
@@ -1959,9 +2003,9 @@ __device__ __forceinline__ void export_results(const TileParams& P) {
   }
 }
 
-template <int MODE>
+template <int MODE, int COMMAS>
 __device__ __forceinline__ void tile_entry(const TileParams& P) {
-  tile_body<MODE>(P);
+  tile_body<MODE, COMMAS>(P);
   if (P.export_to) export_results(P);
 }
 
@@ -2024,9 +2068,10 @@ __global__ __launch_bounds__(kBlock) void k_unordered(UnorderedParams U) {
 }
 
 // The kernel for any plan: everything it needs to know arrives in P.
-template <int MODE>
+// COMMAS: P.commas.
+template <int MODE, int COMMAS>
 __global__ __launch_bounds__(kTileThreads, 4) void k_tile(TileParams P) {
-  tile_entry<MODE>(P);
+  tile_entry<MODE, COMMAS>(P);
 }
 #endif
 
@@ -2053,7 +2098,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_tile(TileParams P) {
 extern "C" __global__ __launch_bounds__(kTileThreads, FBX_FIXED_WAVES) FBX_SIZE_ATTR void FBX_FIXED_NAME(TileParams Pin) {
   TileParams P = Pin;
   FBX_FIXED_ASSIGN
-  tile_entry<FBX_FIXED_MODE>(P);
+  tile_entry<FBX_FIXED_MODE, FBX_FIXED_COMMAS>(P);
 }
 #endif
 
@@ -2072,16 +2117,26 @@ uint32_t tile_max_lds() {
   return cached;
 }
 
+template <int MODE>
+static const void* tile_kernel_of(uint32_t commas) {
+  return commas == kCommasOfHashes  ? reinterpret_cast<const void*>(&k_tile<MODE, kCommasOfHashes>)
+         : commas == kCommasByField ? reinterpret_cast<const void*>(&k_tile<MODE, kCommasByField>)
+                                    : reinterpret_cast<const void*>(&k_tile<MODE, kCommasWithTabs>);
+}
+static const void* tile_kernel(int mode, uint32_t commas) {
+  return mode == 0   ? tile_kernel_of<0>(commas)
+         : mode == 1 ? tile_kernel_of<1>(commas)
+         : mode == 2 ? tile_kernel_of<2>(commas)
+                     : tile_kernel_of<3>(commas);
+}
+
 hipError_t launch_tile(const TileParams& P, int mode, TileResident* known, hipStream_t st) {
   if (P.n_tiles == 0) return hipSuccess;
   TileResident& k = known[mode];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); dev = 0; }
-  if (k.dev != dev || k.lds != P.lds_bytes) {
-    const void* fn = mode == 0   ? reinterpret_cast<const void*>(&k_tile<0>)
-                     : mode == 1 ? reinterpret_cast<const void*>(&k_tile<1>)
-                     : mode == 2 ? reinterpret_cast<const void*>(&k_tile<2>)
-                                 : reinterpret_cast<const void*>(&k_tile<3>);
+  const void* fn = tile_kernel(mode, P.commas);
+  if (k.dev != dev || k.lds != P.lds_bytes || k.fn != fn) {
     if (P.lds_bytes > 48u * 1024u) {
       // (the limit belongs to the function, which all plans share: what the device has beside the kernel's own, never
       // this plan's size, which may be less than another's)
@@ -2099,17 +2154,14 @@ hipError_t launch_tile(const TileParams& P, int mode, TileResident* known, hipSt
     }
     k.dev = dev;
     k.lds = P.lds_bytes;
+    k.fn = fn;
     k.workgroups = tile_cu_count() * (uint32_t)per_cu;
   }
   uint32_t capacity = k.workgroups;
   if (P.grid && P.grid < capacity) capacity = P.grid;
   TileParams Q = P;
-  const uint32_t grid = std::min(P.n_tiles, capacity);
-  if (mode == 0) hipLaunchKernelGGL(k_tile<0>, dim3(grid), dim3(kTileThreads), P.lds_bytes, st, Q);
-  else if (mode == 1) hipLaunchKernelGGL(k_tile<1>, dim3(grid), dim3(kTileThreads), P.lds_bytes, st, Q);
-  else if (mode == 2) hipLaunchKernelGGL(k_tile<2>, dim3(grid), dim3(kTileThreads), P.lds_bytes, st, Q);
-  else hipLaunchKernelGGL(k_tile<3>, dim3(grid), dim3(kTileThreads), P.lds_bytes, st, Q);
-  return hipGetLastError();
+  void* args[] = {&Q};
+  return hipLaunchKernel(fn, dim3(std::min(P.n_tiles, capacity)), dim3(kTileThreads), args, P.lds_bytes, st);
 }
 
 hipError_t launch_unordered(const UnorderedParams& U, hipStream_t st) {

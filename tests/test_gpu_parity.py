@@ -827,3 +827,50 @@ def test_plans_with_different_lds_sections_take_turns():
         assert_same({s: expand(res.slots[s], 300) for s in res.slot_ids}, res, want)
     for plan in plans:
         plan.close()
+
+
+@pytest.mark.parametrize("lists,others,pad,commas", [
+    (3, 0, 0, 0),      # hashes only: field by field
+    (3, 4, 0, 1),      # filters and buckets of lists as well
+    (3, 4, 3000, 2),   # the same on records of 3 KB: along with the tabs
+    (40, 0, 0, 2),     # many lists: along with the tabs
+])
+@pytest.mark.parametrize("options", [{}, {"one_launch": 0}, {"placement": 1}, {"compile": 1}], ids=["default", "counting", "arrival", "compiled"])
+def test_lists_around_the_commas_that_are_kept(lists, others, pad, commas, options):
+    """Lists of up to 16 commas have all their places kept; longer ones, and records with more commas than their table holds
+    (in fields that nobody reads as lists, too), are walked on from the last place."""
+    rng = random.Random(lists * 100 + others)
+    F = lists + others + 2
+    spec = f"fbx 1\nfields {F}\nop t hash slot=900 seed=1 emit=1 field=0 multi=0\n"
+    spec += "".join(f"op h{k} hash slot={k} seed={k} emit=1 field={1 + k} multi=1\n" for k in range(lists))
+    for k in range(others):
+        spec += (f"op o{k} filter slot={100 + k} seed={k} emit=1 field={1 + lists + k} multi=1 prefix={b'ab'[:k % 3].hex()}\n" if k % 2 == 0 else
+                 f"op o{k} bucket slot={100 + k} seed={k} emit=1 field={1 + lists + k} multi=1 bounds=1000000,5000000\n")
+    spec += "op x cross slot=901 seed=5 emit=1 a=h0 b=h1\nop y cross slot=902 seed=6 emit=1 a=t b=h2\n"
+    recs = []
+    for i in range(450):
+        few = lambda: rng.choice([0, 1, 3, 3, 5]) if rng.random() < 0.9 else rng.choice([15, 16, 17, 18, 33, 60])
+        items = lambda n: ",".join(rng.choice(["", "a", "ab", "abc7", "5.25", "x" * 20]) for _ in range(n + 1))
+        text = "".join(rng.choice("ab,") for _ in range(rng.choice([0, 10, 700] if i % 5 == 0 else [0, 8])))
+        fields = [text] + [items(few()) for _ in range(lists + others)] + ["z" * (pad + rng.randrange(20))]
+        recs.append(("\t".join(fields) + "\n").encode())
+    raw, off = _cat(recs)
+    raw = np.frombuffer(raw, np.uint8)
+    want = O.extract(spec, raw, off)
+    plan = B.Plan(spec)
+    for k, v in options.items():
+        if k != "placement":
+            plan.set_option(k, v)
+    assert f"P.commas = {commas}u;" in plan.kernel_source(raw.size, 450, 1)
+    d_raw, d_off = to_device(raw, off, 3)
+    B.extract_with_retry(plan, d_raw, d_off)
+    for k, v in options.items():
+        if k == "placement":
+            plan.set_option(k, v)
+    for _ in range(2):
+        res = plan.extract(d_raw, d_off)
+        if "placement" in options:
+            assert res.n_values_total == want.n_values_total and res.n_malformed_numeric == want.n_malformed_numeric
+            continue
+        assert_same({s: expand(res.slots[s], 450) for s in res.slot_ids}, res, want)
+    plan.close()

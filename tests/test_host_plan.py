@@ -233,3 +233,16 @@ def test_what_the_native_part_of_the_binding_takes_and_refuses():
     with pytest.raises(AttributeError):
         B._native.extract(0, object(), Array(off), 0, None)
     assert isinstance(B.Slot, type)
+
+
+@pytest.mark.parametrize("hashes,filters,record,commas", [
+    (0, 0, 800, 0), (4, 0, 800, 0),  # few lists
+    (0, 1, 800, 1),                  # one filter of a list among many single-valued fields: not every byte twice
+    (0, 24, 1400, 1), (4, 4, 2000, 1), (4, 4, 2100, 2), (0, 1, 2800, 2), (40, 0, 2000, 2),
+])
+def test_where_commas_are_looked_for_along_with_the_tabs(hashes, filters, record, commas):
+    n = hashes + filters
+    plan = B.Plan(f"fbx 1\nfields {60 + n}\n" + "".join(f"op h{k} hash slot={k} seed={k} emit=1 field={k} multi={int(k >= 60)}\n" for k in range(60 + hashes))
+                  + "".join(f"op f{k} filter slot={k} seed={k} emit=1 field={k} multi=1 prefix=61\n" for k in range(60 + hashes, 60 + n)))
+    assert f"P.commas = {commas}u;" in plan.kernel_source(record * 10000, 10000, 1)
+    plan.close()
