@@ -1235,25 +1235,24 @@ struct Pass {
 
   // ---- later layers
   // crosses of two single signs, both on chip
-  // (two a lane: half the hand-outs, measured 0.7 % on the largest workload; one where two would leave wavefronts idle)
+  // (two a lane: half the hand-outs, measured 0.7 % on the largest workload)
   static constexpr uint32_t kCrossesPerLane = 2;
-  __device__ __forceinline__ uint32_t crosses_per_lane(uint32_t m) const { return m <= kWaves * G ? 1u : kCrossesPerLane; }
   __device__ __forceinline__ uint32_t x11_units(uint32_t layer) const {
-    const uint32_t list = TL_LAYER + 2u * (layer - 2u), m = sh.lbeg(list + 1) - sh.lbeg(list), c = crosses_per_lane(m) * G;
-    return (m + c - 1u) / c;
+    const uint32_t list = TL_LAYER + 2u * (layer - 2u);
+    return (sh.lbeg(list + 1) - sh.lbeg(list) + kCrossesPerLane * G - 1u) / (kCrossesPerLane * G);
   }
   __device__ __forceinline__ void x11_unit(uint32_t layer, uint32_t u) {
     refresh();
     if (!live) return;
     const uint32_t list = TL_LAYER + 2u * (layer - 2u);
-    const uint32_t lb = sh.lbeg(list), m = sh.lbeg(list + 1) - lb, c = crosses_per_lane(m);
+    const uint32_t lb = sh.lbeg(list), m = sh.lbeg(list + 1) - lb;
     // (a cross never reads a cross of its own layer: the crosses of a unit are independent, their inputs are requested together)
     const OpProg* d[kCrossesPerLane];
     uint64_t a[kCrossesPerLane], b[kCrossesPerLane];
 #pragma unroll
     for (uint32_t k = 0; k < kCrossesPerLane; ++k) {
-      const uint32_t i = (u * c + k) * G + og;
-      d[k] = k < c && i < m ? &sh.prog[lb + i] : nullptr;
+      const uint32_t i = (u * kCrossesPerLane + k) * G + og;
+      d[k] = i < m ? &sh.prog[lb + i] : nullptr;
     }
 #pragma unroll
     for (uint32_t k = 0; k < kCrossesPerLane; ++k)
@@ -1305,13 +1304,18 @@ struct Pass {
   // The last record of the pass whose first position in a ragged row is <= pos: the one that has the sign there.
   __device__ __forceinline__ uint32_t record_at(uint32_t row, uint32_t pos) const {
     const uint32_t* st = sh.start + row * T;
-    if (P.log2T <= 3u) {  // few records: all of them at once instead of one look-up after the other (those beyond nb start at the end)
+#ifdef FBX_FIXED_MODE
+    // Few records: all of them at once instead of one look-up after the other (those beyond nb start at the end).  Only where
+    // the tile size is a literal: a kernel that holds both ways is slower for all plans (3,000,000 records of the
+    // 100-field workload 4.15 against 3.77 ms, 1,000,000 of the numeric one 0.81 against 0.76).
+    if (P.log2T <= 3u) {
       uint32_t n = 0;
 #pragma unroll
       for (uint32_t k = 1; k < 8u; ++k)
         if (k < T) n += st[k] <= pos && k < nb ? 1u : 0u;
       return n;
     }
+#endif
     uint32_t lo = 0, hi = nb - 1u;
     while (lo < hi) {
       const uint32_t mid = (lo + hi + 1u) >> 1;
@@ -1751,9 +1755,15 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
   // Elsewhere a workgroup's first tile is its own number: adding to one address, the whole chip
   // gets about 75 answers a microsecond, and the last of 512 workgroups would start 7 us late.
   // Its further tiles come from the counter where tiles differ in length (ragged operators: the
-  // four-layer workload is 7 % faster that way), else they are every gridDim.x-th one.
+  // four-layer workload is 7 % faster that way), else they are every gridDim.x-th one; the kernel for any
+  // plan always asks the counter (a million records of 16 single-valued fields: 0.43 ms with the choice
+  // left to run time, 0.39 without).
   constexpr bool kInOrder = MODE == 2;
+#ifdef FBX_FIXED_MODE
   const bool counter = kInOrder || P.n_ragged != 0u;
+#else
+  constexpr bool counter = true;
+#endif
   const uint32_t counted_from = kInOrder ? 0u : gridDim.x;
   if (tid == 0) {
     s_err = P.ctrl->err;  // set by an earlier kernel of this call: nothing may be written
@@ -1989,7 +1999,9 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
 // What the host reads after the call, straight into its memory: a copy enqueued behind the kernel is a launch of its
 // own (4 us and the gap before it).  What is copied was written by earlier kernels or by device-scope atomics, so it
 // needs no cache write-back, only that every wavefront's own have arrived before its workgroup counts as done.
-__device__ __forceinline__ void export_results(const TileParams& P) {
+template <class Params>
+__device__ __forceinline__ void export_results(Params& P) {
+  if (!P.export_to) return;
   __shared__ uint32_t s_last;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -2006,7 +2018,17 @@ __device__ __forceinline__ void export_results(const TileParams& P) {
 template <int MODE, int COMMAS>
 __device__ __forceinline__ void tile_entry(const TileParams& P) {
   tile_body<MODE, COMMAS>(P);
-  if (P.export_to) export_results(P);
+#ifndef FBX_FIXED_MODE
+  if constexpr (COMMAS != kCommasWithTabs) {
+    // the launch's arguments where they lie, so that the main loop does not hold on to those that only this needs (a million
+    // records of 16 single-valued fields: 0.394 -> 0.383 ms; 1 % the other way for lists, and for kernels compiled for the plan)
+    const FBX_CONSTANT TileParams* args = (const FBX_CONSTANT TileParams*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    export_results(*args);
+    return;
+  }
+#endif
+  export_results(P);
 }
 
 #ifndef FBX_FIXED_MODE
@@ -2068,7 +2090,10 @@ __global__ __launch_bounds__(kBlock) void k_unordered(UnorderedParams U) {
 }
 
 // The kernel for any plan: everything it needs to know arrives in P.
-// COMMAS: P.commas.
+// COMMAS: P.commas.  (All ways to find commas in one kernel, and other choices left to run time, cost all plans: what is
+// spilled and where shifts with every addition.  3,000,000 records of the 100-field workload: 4.16 ms for one kernel with
+// both ways, both cross layouts and both record searches, 3.82 for this one; a million of 16 single-valued fields: 0.41
+// and 0.37.)
 template <int MODE, int COMMAS>
 __global__ __launch_bounds__(kTileThreads, 4) void k_tile(TileParams P) {
   tile_entry<MODE, COMMAS>(P);
