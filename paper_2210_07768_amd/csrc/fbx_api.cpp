@@ -732,10 +732,11 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   // (Looking back costs every tile a window of 64 words and some waiting per ragged operator that is placed that way,
   // which those whose counts follow from another operator's are not; counting costs every tile its text once more.
   // A workgroup's eight wavefronts look back for one operator each behind the work that needs no base; further operators
-  // are rounds that the tile waits for.  Measured with 4 operators on 26 KB tiles, 4.2 against 6.0 ms; with 24 on 34 KB,
-  // 1.33 against 1.02; with 42 on 18 KB, 0.63 against 0.45: up to eight operators the line is at 1 KB of text an operator,
-  // beyond at 4 KB.  A batch of at most 64 tiles finds all the tiles before a tile in one window and saves the launches,
-  // up to six rounds: 52 against 65 us with 24 operators, 65 against 76 with 42.)
+  // are rounds that the tile waits for.  One launch against counting, with the tile's text per operator: 4 operators,
+  // 6.5 KB: 4.2 and 6.0 ms; 8, 3.2 KB: 0.37 and 0.45; 9, 3 KB: 0.44 and 0.51; 12, 2.5 KB: 0.50 and 0.57; 16, 1.9 KB: 0.37 and
+  // 0.46; 24, 1.4 KB: 1.39 and 1.00; 16, 1.1 KB: 0.70 and 0.66; 24, 0.9 KB: 1.16 and 0.93: beyond eight operators the line
+  // is at 1.75 KB.  A batch of at most 64 tiles finds all the tiles before a tile in one window and saves the launches: 48 against
+  // 64 us with 9 operators, 56 and 69 with 24, 72 and 84 with 48, where the line is left: 91 and 100 with 80.)
   // (a batch with a tile that did not fit the LDS section is likely to be followed by more of its kind: the
   // sequence is then left untried for 1, 2, 4 ... up to 64 calls, so that such batches do not pay for two attempts each)
   const bool resting = plan->passes_skip > 0;
@@ -744,7 +745,7 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   bool one = !resting && g.tile_engine && plan->one_launch && plan->learned && h.n_ragged && n_records && plan->learned_records &&
              ws_bytes > plan->margin_failed_ws &&
              (plan->placement || (g.n_tiles <= 64u && n_back <= 48u) ||
-              uint64_t(n_back) * (n_back <= 8u ? 1024u : 4096u) <= (raw_len / n_records) << g.tp.log2T);
+              uint64_t(n_back) * (n_back <= 8u ? 1024u : 1792u) <= (raw_len / n_records) << g.tp.log2T);
   if (one) {
     plan->cap_host.resize(h.n_ragged);
     for (uint32_t r = 0; r < h.n_ragged; ++r) {

@@ -874,3 +874,47 @@ def test_lists_around_the_commas_that_are_kept(lists, others, pad, commas, optio
             continue
         assert_same({s: expand(res.slots[s], 450) for s in res.slot_ids}, res, want)
     plan.close()
+
+
+@pytest.mark.parametrize("n_ops", [63, 64, 65, 255, 256, 257, 879, 880, 881, 1500])
+def test_plans_of_many_operators(n_ops):
+    """Placements travel with the set-up launch in blocks of 64, 256 and 880, or in memory beyond that."""
+    rng = random.Random(n_ops)
+    spec = "fbx 1\nfields 5\n" + "".join(f"op h{k} hash slot={k} seed={rng.getrandbits(64)} emit=1 field={k % 5} multi=0\n" for k in range(n_ops))
+    raw, off = _cat([("\t".join("abc"[:rng.randrange(4)] for _ in range(5)) + "\n").encode() for _ in range(130)])
+    check(spec, raw, off, label=str(n_ops))
+
+
+@pytest.mark.parametrize("n_lists", [31, 32, 127, 129, 439, 441])
+def test_plans_of_many_list_operators(n_lists):
+    """The same where every operator has an offsets array of its own: two placements an operator, made on the host in the
+    second call (a batch of one tile, whose arrival order is the records')."""
+    import torch
+    rng = random.Random(n_lists)
+    spec = "fbx 1\nfields 5\n" + "".join(f"op h{k} hash slot={k} seed={rng.getrandbits(64)} emit=1 field={k % 5} multi=1\n" for k in range(n_lists))
+    raw, off = _cat([("\t".join("a,bc,,d"[:rng.randrange(8)] for _ in range(5)) + "\n").encode() for _ in range(4)])
+    raw = np.frombuffer(raw, np.uint8)
+    want = O.extract(spec, raw, off)
+    plan = B.Plan(spec)
+    plan.set_option("placement", 1)
+    plan.set_option("tile_log2", 2)
+    d_raw, d_off = to_device(raw, off)
+    ws = torch.empty(16 << 20, dtype=torch.uint8, device="cuda")
+    plan.set_workspace(ws)
+    plan.extract(d_raw, d_off)
+    res = plan.extract(d_raw, d_off)
+    assert res.tile_launches == 1 and 4 == res.arrival_tile_records, res.note
+    assert_same({s: expand(res.slots[s], 4) for s in res.slot_ids}, res, want)
+    plan.close()
+
+
+@pytest.mark.parametrize("crosses", [63, 64, 65, 150])
+@pytest.mark.parametrize("tile_log2", [2, 5])
+def test_layers_of_many_list_crosses(crosses, tile_log2):
+    """Up to 64 list operators of a layer are found with one look by a wavefront, more by a search (and records by either)."""
+    rng = random.Random(crosses)
+    spec = "fbx 1\nfields 6\n" + "".join(f"op h{k} hash slot={k} seed={k} emit=1 field={k} multi=1\n" for k in range(6))
+    spec += "".join(f"op x{k} cross slot={100 + k} seed={rng.getrandbits(64)} emit=1 a=h{rng.randrange(6)} b=h{rng.randrange(6)}\n" for k in range(crosses))
+    raw, off = _cat([("\t".join(rng.choice(["a", "a,bc", ",,d", "q,w,e,r"]) for _ in range(6)) + "\n").encode() for _ in range(101)])
+    for compiled in (0, 1):
+        check(spec, raw, off, {"tile_log2": tile_log2, "compile": compiled}, label=f"{crosses} {tile_log2} {compiled}")
