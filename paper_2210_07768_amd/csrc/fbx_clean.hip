@@ -40,12 +40,6 @@
 
 using namespace fbx;
 
-#ifndef CLEAN_WAVES
-#define CLEAN_WAVES 6
-#endif
-#ifndef CLEAN_TEXT
-#define CLEAN_TEXT 24576
-#endif
 namespace {
 
 enum CleanKind : uint32_t { CK_FILL = 1, CK_KEY = 2, CK_KEEP = 3, CK_NONE = 4 };  // (CK_NONE: a key that no pair can have)
@@ -96,6 +90,7 @@ struct CleanParams {
 constexpr uint64_t kDropped = ~0ull;
 constexpr uint32_t kInPlace = ~0u, kMaxRuns = 4096;
 
+constexpr uint32_t kCleanWaves = 6;  // a SIMD: six workgroups of four wavefronts on a compute unit, what the LDS admits
 constexpr uint32_t kCleanThreads = 256, kCleanRawPad = 16, kCleanMaxT = 64;
 constexpr uint32_t kTabRun = 0xffffu;  // a segment's source: tabs, as many as it takes (fields that the record lacks)
 
@@ -288,7 +283,7 @@ __device__ __forceinline__ void clean_table(uint32_t to, const void* from, uint3
 
 // Measures tiles.  500,000 records of 826 bytes, 100 fields, 30 of them with operators, half of the records kept: both
 // launches together 2.66 ms before (tables of all fields, twice; single-byte stores).
-__global__ __launch_bounds__(kCleanThreads, CLEAN_WAVES) void k_clean_measure_tile(CleanParams C) {
+__global__ __launch_bounds__(kCleanThreads, kCleanWaves) void k_clean_measure_tile(CleanParams C) {
   __shared__ uint64_t s_off[kCleanMaxT + 1];
   __shared__ uint32_t s_len[kCleanMaxT], s_drop[kCleanMaxT];
   __shared__ uint32_t s_nseg[kCleanMaxT + 1];  // segments of a record, then the number of its first one
@@ -569,7 +564,7 @@ __global__ __launch_bounds__(kCleanThreads, CLEAN_WAVES) void k_clean_measure_ti
 }
 
 // Writes tiles.
-__global__ __launch_bounds__(kCleanThreads, CLEAN_WAVES) void k_clean_write_tile(CleanParams C) {
+__global__ __launch_bounds__(kCleanThreads, kCleanWaves) void k_clean_write_tile(CleanParams C) {
   __shared__ uint64_t s_wave[4][kCleanThreads / 64];
   __shared__ uint64_t s_off[kCleanMaxT + 1], s_out[kCleanMaxT];
   __shared__ uint32_t s_later, s_go;
@@ -926,7 +921,7 @@ thread_local std::string g_clean_create_error;
 namespace {
 // A tile's LDS: text, tables, and all of it (without asking for more than the 64 KiB that every workgroup gets; positions
 // in the text and the arguments behind it are 16-bit).
-constexpr uint64_t kTextMax = CLEAN_TEXT, kTableMax = 32768, kLdsMax = 62000;
+constexpr uint64_t kTextMax = 24576, kTableMax = 32768, kLdsMax = 62000;
 }  // namespace
 
 struct fbx_clean {
