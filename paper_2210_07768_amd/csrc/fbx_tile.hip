@@ -382,6 +382,28 @@ __device__ __forceinline__ uint64_t fnv_step(uint64_t h, uint32_t w) {  // byte 
 }
 template <class Src>
 __device__ __forceinline__ uint64_t hash_span(const Src& src, uint32_t s, uint32_t e, uint64_t h) {
+  if constexpr (Src::kTable) {
+    // Staged text: the odd bytes first (1 to 8 of them), then whole windows of eight.  What bounds this is vector issue, four
+    // instructions a byte and one that asks whether there is a next byte; whole windows need not ask, and tokens of up to
+    // eight bytes run as before.  (1,000,003 records of 16 single-valued fields of 4 to 32 bytes: 246 us a call with the odd
+    // bytes last and every byte asked for, 233 this way; 3 to 8 bytes a token: the same.)
+    if (s >= e) return h;
+    const uint32_t n = ((e - s - 1u) & 7u) + 1u;
+    uint32_t x0, x1;
+    window8(src, s, x0, x1);
+    h = fnv_step<0>(h, x0);
+#define FBX_STEP(J, X) if (n > (uint32_t)J) { h = fnv_step<(J & 3)>(h, X);
+    FBX_STEP(1, x0) FBX_STEP(2, x0) FBX_STEP(3, x0)
+    FBX_STEP(4, x1) FBX_STEP(5, x1) FBX_STEP(6, x1) FBX_STEP(7, x1)
+    }}}}}}}
+#undef FBX_STEP
+    for (uint32_t p = s + n; p < e; p += 8u) {
+      window8(src, p, x0, x1);
+      h = fnv_step<3>(fnv_step<2>(fnv_step<1>(fnv_step<0>(h, x0), x0), x0), x0);
+      h = fnv_step<3>(fnv_step<2>(fnv_step<1>(fnv_step<0>(h, x1), x1), x1), x1);
+    }
+    return h;
+  }
   for_each_byte_of_word(src, s, e, [&](uint32_t w, auto k) { h = fnv_step<decltype(k)::value>(h, w); });
   return h;
 }
