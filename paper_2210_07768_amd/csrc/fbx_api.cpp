@@ -75,6 +75,7 @@ struct fbx_plan {
   // where arrays go, worked out on the host when their sizes are known before the call
   std::vector<uint32_t> units;         // per operator and row, as launch_setup wants them
   uint32_t n_mh = 0, n_split = 0, n_gen = 0;  // as in TileParams
+  bool keeps_roots = false;  // a later operator reads lists of layer 1, or lists made along with them
   uint32_t n_comma_fields = 0;                // fields that some operator reads as a list
   TileResident resident[4];
 
@@ -129,6 +130,8 @@ struct fbx_plan {
       const uint32_t list = TL_LAYER + 2u * (layer - 2u) + 1u;
       n_gen += host.tile_list_begin[list + 1] - host.tile_list_begin[list];
     }
+    for (const HostOp& op : host.ops)
+      if ((op.d.layer == 1 || (op.d.kind == OP_CROSS && op.d.fuse)) && !(op.d.flags & F_STREAM)) keeps_roots = true;
   }
 
   void build_tables() {
@@ -204,6 +207,15 @@ void tile_lds_layout(const fbx_plan& p, uint32_t lt, uint64_t want, uint32_t raw
   tp.o_lbeg = o; o = round16(o + 4ull * h.tile_list_begin.size());
   tp.o_rnr = o; o = round16(o + 4ull * h.derive_tab.size());
   tp.o_aux = o; o = round16(o + h.aux.size());
+  tp.o_lists = o;
+  // What is left of a workgroup's share of a compute unit's LDS, so that no fewer of them run (the kernel for any plan: two, its
+  // registers admit no more).  A four-layer plan with 53 KB a workgroup takes 1.63 ms for 250,000 records with three
+  // workgroups and none of these lists on chip, 1.95 with two and all of them; lists of 64 KB, where two run either
+  // way: 0.92 ms without and 0.88 with them for 200,000 records.
+  const uint32_t dev_max = tile_max_lds(), groups = p.compile ? std::min(4u, std::max(1u, dev_max / std::max(o, 1u))) : 2u;
+  const uint32_t share = dev_max / groups - 1024u;  // (beside the kernel's own)
+  tp.list_cap = p.keeps_roots && o < share ? (share - o) / 16u * 2u : 0u;
+  o += 8u * tp.list_cap;
   tp.lds_bytes = o;
 }
 
@@ -229,7 +241,7 @@ bool tile_geometry(const fbx_plan& p, uint64_t raw_len, uint64_t n_records, Tile
     const uint32_t cap = p.raw_cap ? p.raw_cap : round16(std::min<uint64_t>(std::max<uint64_t>(want, 1024), 65000));
     tile_lds_layout(p, static_cast<uint32_t>(lt), p.raw_cap ? p.raw_cap : want, cap, tp);
     const uint32_t limit = (lt == lt_lo) ? dev_max : std::min(p.lds_budget, dev_max);
-    if (tp.lds_bytes <= limit) return true;
+    if (tp.o_lists <= limit) return true;
   }
   return false;
 }
@@ -521,7 +533,9 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   const double compile_ms_before = plan->jit.compile_ms();
   // The tile kernel in one of its modes: the one compiled for this plan if the plan asks for
   // that and it can be had, else the generic one.
-  auto tile_launch = [&](const TileParams& Q, int mode) -> hipError_t {
+  auto tile_launch = [&](TileParams Q, int mode) -> hipError_t {
+    if (mode == 0) Q.lds_bytes = Q.o_lists;  // (counting writes no lists)
+    Q.lds_bytes = std::max(Q.lds_bytes, plan->lds_pad);
     if (plan->compile && !reg.own_tables)
       if (const FixedTileKernel* k = plan->jit.get(Q, mode, plan->host, plan->tile_threads, plan->lane_ops)) return launch_tile_fixed(*k, Q, st);
     return launch_tile(Q, mode, plan->resident, st);
@@ -612,7 +626,6 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
       Q.aux_bytes = static_cast<uint32_t>(h.aux.size());
 
       Q.n_tiles = g.n_tiles; Q.n_fields = h.n_fields; Q.n_stage = h.n_stage;
-      Q.lds_bytes = std::max(Q.lds_bytes, plan->lds_pad);
       Q.grid = plan->grid_limit;  // 0: as many persistent workgroups as run at the same time
       Q.spin_limit = plan->spin_limit;
       Q.prof = nullptr;

@@ -85,6 +85,8 @@ struct TileParams {
   uint32_t o_tot, o_ioff, o_ctab, o_ctot, o_cfirst, o_cap, o_gfirst, o_gtot;
   uint32_t commas;      // how commas are found (kCommas...)
   uint32_t comma_cap;   // comma positions kept per record (kCommasWithTabs)
+  uint32_t o_lists;     // lists of layer 1 that later operators read: the last section, which counting does without
+  uint32_t list_cap;    // signs it holds
   uint32_t lds_bytes;
   // What the host needs to know when the call is done: the last workgroup to finish copies the control block and
   // `export_words` words from `export_from` on to `export_to` (host memory; null: nothing is copied).
@@ -116,7 +118,7 @@ struct UnorderedParams {
   X(n_ops) X(n_layers) X(n_ragged) X(n_rnr) X(n_lists) X(aux_bytes) X(rnr_words) X(alias_at) X(n_alias) X(n_mh) X(n_split) X(n_gen) X(n_fields) \
   X(n_stage) X(log2T) X(raw_cap) X(row_stride) X(o_off) X(o_rs) X(o_re) X(o_rows) X(o_raw) X(o_stage) X(o_cnt)     \
   X(o_start) X(o_run) X(o_base) X(o_prog) X(o_lbeg) X(o_rnr) X(o_aux) X(o_tot) X(o_ioff) X(o_ctab) X(o_ctot) X(o_cfirst) X(o_cap) \
-  X(o_gfirst) X(o_gtot) X(commas) X(comma_cap) X(lds_bytes)
+  X(o_gfirst) X(o_gtot) X(commas) X(comma_cap) X(o_lists) X(list_cap) X(lds_bytes)
 
 #ifndef __HIPCC_RTC__  // (the launch wrappers are host code: not for the run-time compiler)
 // mode 0: counting launch; 1: writing launch (bases from the scan over tiles);

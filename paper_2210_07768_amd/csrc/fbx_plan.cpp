@@ -373,6 +373,14 @@ fbx_status parse_plan(const char* spec, size_t len, PlanHost& plan, std::string&
   std::stable_sort(lists[TL_RAGROOT].begin(), lists[TL_RAGROOT].end(), [&](uint32_t x, uint32_t y) {
     return root_class(x) != root_class(y) ? root_class(x) < root_class(y) : plan.ops[x].d.kind < plan.ops[y].d.kind;
   });
+  // List operators of a layer: neighbouring signs run the same code where crosses, and the few of fixed arity, are kept together.
+  for (uint32_t layer = 2; layer <= plan.n_layers; ++layer) {
+    std::vector<uint32_t>& l = lists[TL_LAYER + 2 * (layer - 2) + 1];
+    std::stable_sort(l.begin(), l.end(), [&](uint32_t x, uint32_t y) {
+      const OpDesc &a = plan.ops[x].d, &b = plan.ops[y].d;
+      return (a.arity != 0) != (b.arity != 0) ? b.arity != 0 : a.kind < b.kind;
+    });
+  }
   for (HostOp& op : plan.ops) {
     OpDesc& d = op.d;
     if (d.kind == OP_FILTER && (d.flags & F_MULTI) && d.aux_len &&

@@ -651,34 +651,34 @@ __device__ __forceinline__ uint32_t ragged_root_count(const Src& src, const OpPr
   return cnt;
 }
 
-// Writes the signs of a ragged root operator (not n-gram) on [s, e) to dst[0 .. count).
-template <class Src>
+// Hands the signs of a ragged root operator (not n-gram) on [s, e) to put, in order.
+template <class Src, class Put>
 __device__ __forceinline__ void ragged_root_emit(const Src& src, const OpProg& d, const uint8_t* aux, uint32_t r, uint32_t s,
-                                                 uint32_t e, G64 dst, uint32_t& malformed) {
+                                                 uint32_t e, Put&& put, uint32_t& malformed) {
   const bool multi = d.flags & F_MULTI;
   if (d.kind == OP_HASH) {  // a ragged hash is always multi-valued
     uint64_t h = d.key;
     const uint64_t key = d.key;
     for_each_byte(src, s, e, [&](uint32_t b) {
-      if (b == ',') { *dst++ = h; h = key; }
+      if (b == ',') { put(h); h = key; }
       else h = (h ^ b) * kPrime;
     });
-    *dst = h;
+    put(h);
   } else if (d.kind == OP_FILTER) {  // only the tokens that pass are hashed
     const Prefix pre(aux, d);
     const uint64_t key = d.key;
     for_each_token(src, r, s, e, multi, [&](uint32_t t, uint32_t te) {
-      if (starts_with(src, t, te, pre)) *dst++ = hash_span(src, t, te, key);
+      if (starts_with(src, t, te, pre)) put(hash_span(src, t, te, key));
     });
   } else {  // OP_BUCKET, multi-valued
     NumState ns;
     for_each_byte(src, s, e, [&](uint32_t b) {
       if (b == ',') {
-        *dst++ = bucket_sign(d, aux, ns, malformed);
+        put(bucket_sign(d, aux, ns, malformed));
         ns = NumState();
       } else ns.step(b);
     });
-    *dst = bucket_sign(d, aux, ns, malformed);
+    put(bucket_sign(d, aux, ns, malformed));
   }
 }
 
@@ -1032,6 +1032,14 @@ struct Pass {
     store_single(d->values, g, v);
     if (d->stage != kNoRow) sh.stage[d->stage * T + r] = v;
   }
+  // A sign of a list operator: position `pos` of the tile's signs of that operator (of a fixed-arity one: of the pass's),
+  // entry `at` of its array.  A list that a later operator reads stays on chip where there was room (gen_offsets); its
+  // copy in memory is then only the caller's, if the operator is emitted at all.
+  __device__ __forceinline__ void put_list(const OpProg& d, uint32_t pos, uint64_t at, uint64_t v) const {
+    const bool on_chip = P.n_gen && d.stage != kNoRow;
+    if (on_chip) reinterpret_cast<uint64_t*>(smem)[d.stage + pos] = v;
+    if (!on_chip || (d.flags & F_EMIT)) store_sign(gptr<uint64_t>(d.values) + at, v, on_chip || (d.flags & F_STREAM));
+  }
   // where this lane's list of a ragged operator starts; writes its offsets entry
   __device__ __forceinline__ uint64_t place(const OpProg& d, uint32_t rr, uint64_t gg) const {
     const uint64_t first = sh.base[d.rag_row] + sh.start[d.rag_row * T + rr];
@@ -1055,7 +1063,9 @@ struct Pass {
     const uint64_t first = place(*d, r, g);
     uint32_t s, e;
     src.span(r, d->field, s, e);
-    ragged_root_emit(src, *d, sh.aux, r, s, e, gptr<uint64_t>(d->values) + first, malformed);
+    uint32_t pos = sh.start[d->rag_row * T + r];
+    uint64_t at = first;
+    ragged_root_emit(src, *d, sh.aux, r, s, e, [&](uint64_t v) { put_list(*d, pos++, at++, v); }, malformed);
   }
   // Multi-valued hashes (the first P.n_mh entries of the ragged root list): lanes
   // are items.  All items of the pass, operator after operator and record after
@@ -1128,21 +1138,21 @@ struct Pass {
       if (gg + 1 == P.n_records) off[gg + 1] = first + cnt;
     }
     const uint64_t v = hash_span(src, is, ie, d.key);
-    store_sign(gptr<uint64_t>(d.values) + first, v, d.flags & F_STREAM);
+    put_list(d, pos, first, v);
     // crosses of this hash with a single sign: one sign per item, in the items' order
     const uint32_t* fused = sh.rnr + 4u * ((P.n_layers + 3u) >> 2) + 4u * P.n_rnr + d.a;
     for (uint32_t k = 0; k < d.b; ++k) {
       const OpProg& c = sh.prog[fused[k]];
       const uint64_t other = sh.stage[c.aux_off * T + rr];
-      const uint64_t at = sh.base[c.rag_row] + sh.start[c.rag_row * T + rr] + j;
+      const uint32_t cpos = sh.start[c.rag_row * T + rr] + j;
+      const uint64_t at = sh.base[c.rag_row] + cpos;
       if (j == 0 && (c.flags & F_EMIT)) {
         G64 off = gptr<uint64_t>(c.offsets);
         const uint64_t gg = g_first + rr;
         __builtin_nontemporal_store(at, off + gg);
         if (gg + 1 == P.n_records) off[gg + 1] = at + cnt;
       }
-      store_sign(gptr<uint64_t>(c.values) + at, c.aux_len ? mix64(mix64(v + c.key) + other) : mix64(mix64(other + c.key) + v),
-                 c.flags & F_STREAM);
+      put_list(c, cpos, at, c.aux_len ? mix64(mix64(v + c.key) + other) : mix64(mix64(other + c.key) + v));
     }
   }
 
@@ -1160,9 +1170,8 @@ struct Pass {
     uint64_t first = 0;
     if (lane == 0) first = place(d, rr, g_first + rr);
     first = __shfl(first, 0, 64);
-    G64 vals = gptr<uint64_t>(d.values) + first;
+    const uint32_t pos = sh.start[d.rag_row * T + rr];
     const uint64_t key = d.key;
-    const bool stream = d.flags & F_STREAM;
     if constexpr (Src::kTable) {
       if (n <= 4u) {  // one word holds a gram, and every lane hashes as many bytes
         const uint32_t* raw32 = reinterpret_cast<const uint32_t*>(src.raw8);
@@ -1173,12 +1182,12 @@ struct Pass {
           if (n > 1u) h = fnv_step<1>(h, w);
           if (n > 2u) h = fnv_step<2>(h, w);
           if (n > 3u) h = fnv_step<3>(h, w);
-          store_sign(vals + q, h, stream);
+          put_list(d, pos + q, first + q, h);
         }
         return;
       }
     }
-    for (uint32_t q = lane; q < ng; q += 64) store_sign(vals + q, hash_span(src, s + q, s + q + n, key), stream);
+    for (uint32_t q = lane; q < ng; q += 64) put_list(d, pos + q, first + q, hash_span(src, s + q, s + q + n, key));
   }
 
   // A 64-bit literal of generated code, handed over in scalar registers at the place of its use (otherwise
@@ -1312,7 +1321,38 @@ struct Pass {
       }
       if (lane == 0) sh.gtot[layer] = carry;
     }
+    keep_lists();
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  }
+  // Where the lists that later operators read lie on chip, operator after operator: OpProg::stage becomes the word of LDS at
+  // which the tile's sign 0 would lie (its signs before this pass have no place).  Lists of layer 1, and those made
+  // along with them, go to a section of their own; those of later layers to where the text was, which nobody reads any
+  // more by then.  A list that finds no room stays in memory only.
+  // (Where all inputs are read back from memory, a unit waits for them and, loads and stores being counted together, for the
+  // signs of the unit before.  200,000 records of 18 lists and 12 crosses of two of them: 0.92 against 0.88 ms a call.)
+  __device__ __forceinline__ void keep_lists() {
+    const uint32_t lane = lane_id();
+    uint32_t used = 0;
+    bool later = false;
+    for (uint32_t i0 = sh.lbeg(TL_RAGROOT); i0 < P.n_ops;) {
+      const uint32_t end = later ? P.n_ops : sh.lbeg(TL_LAYER);
+      const uint32_t i = i0 + lane;
+      uint32_t n = 0, before = 0;
+      if (i < end) {
+        const OpProg& d = sh.prog[i];
+        if (!(d.flags & F_STREAM)) {  // (a list: gen_unit reads no single sign that is not in the table of them)
+          n = min(gen_total(d), 1u << 20);
+          if (!d.arity) before = sh.run[d.rag_row] - sh.tot[d.rag_row];
+        }
+      }
+      const uint32_t incl = group_prefix(n, 6u, lane);
+      const uint32_t first = later ? P.o_raw >> 3 : P.o_lists >> 3;
+      const uint32_t room = later ? (kRawPad + P.raw_cap) >> 3 : P.list_cap;
+      if (n) const_cast<OpProg*>(sh.prog)[i].stage = used + incl <= room ? first + used + incl - n - before : kNoRow;
+      used = min(used + __shfl(incl, 63, 64), 1u << 24);
+      i0 += 64u;
+      if (!later && i0 >= end) { later = true; used = 0; i0 = end; }
+    }
   }
   // a / b for the sizes that occur: by way of a float quotient, which below 2^22 is off by at most one
   __device__ __forceinline__ static uint32_t small_div(uint32_t a, uint32_t b) {
@@ -1334,7 +1374,7 @@ struct Pass {
       uint32_t n = 0;
 #pragma unroll
       for (uint32_t k = 1; k < 8u; ++k)
-        if (k < T) n += st[k] <= pos && k < nb ? 1u : 0u;
+        if (k < T) n += st[k] <= pos ? 1u : 0u;
       return n;
     }
 #endif
@@ -1348,9 +1388,12 @@ struct Pass {
   // sign x of record rr of an earlier operator (single signs from the on-chip table, lists
   // from the arrays this workgroup wrote before the layer barrier)
   __device__ __forceinline__ uint64_t input_sign(const OpProg& d, uint32_t rr, uint32_t x) const {
-    if (d.arity == 1u && d.stage != kNoRow) return sh.stage[d.stage * T + rr];
-    const uint64_t at = d.arity ? (g_first + rr) * d.arity : sh.base[d.rag_row] + sh.start[d.rag_row * T + rr];
-    return gptr<const uint64_t>(d.values)[at + x];
+    const uint32_t pos = (d.arity ? rr * d.arity : sh.start[d.rag_row * T + rr]) + x;
+    if (d.stage != kNoRow) {
+      const uint32_t word = d.arity == 1u ? (P.o_stage >> 3) + d.stage * T + rr : d.stage + pos;
+      return reinterpret_cast<const uint64_t*>(smem)[word];
+    }
+    return gptr<const uint64_t>(d.values)[(d.arity ? g_first * d.arity : sh.base[d.rag_row]) + pos];
   }
   __device__ __forceinline__ uint32_t gen_place_units(uint32_t layer) const {
     return (sh.lbeg(gen_list(layer) + 1u) - sh.lbeg(gen_list(layer)) + G - 1u) / G;
@@ -1395,30 +1438,35 @@ struct Pass {
     const OpProg& d = sh.prog[lb + lo];
     const uint32_t qq = q - op_first;  // the sign's number among the operator's signs of this pass
     const uint32_t row = d.rag_row;
-    uint32_t rr, j;
+    uint32_t rr, j, pos;
     uint64_t at;  // where the sign goes
     if (d.arity) {
       rr = small_div(qq, d.arity);
       j = qq - rr * d.arity;
-      at = (g_first + rr) * d.arity + j;
+      pos = qq;
+      at = g_first * d.arity + qq;
     } else {
-      const uint32_t pos = sh.run[row] - sh.tot[row] + qq;  // position inside the tile (earlier passes come first)
+      pos = sh.run[row] - sh.tot[row] + qq;  // position inside the tile (earlier passes come first)
       rr = record_at(row, pos);
       j = pos - sh.start[row * T + rr];
       at = sh.base[row] + pos;
     }
-    const OpProg& da = sh.prog[d.a];
-    const OpProg& db = sh.prog[d.b];
-    const uint32_t na = da.arity ? da.arity : sh.cnt[da.rag_row * T + rr];
-    const uint32_t nbv = db.arity ? db.arity : sh.cnt[db.rag_row * T + rr];
-    uint64_t v;
-    if (d.kind == OP_CROSS) {  // A outer, B inner
-      const uint32_t x = small_div(j, nbv), y = j - x * nbv;
-      v = mix64(mix64(input_sign(da, rr, x) + d.key) + input_sign(db, rr, y));
-    } else {
-      v = j < na ? input_sign(da, rr, j) : input_sign(db, rr, j - na);
+    // A cross takes the sign x of A (outer) and y of B (inner), a concat one sign of either: the look-up of the first is
+    // the same code for both.
+    const bool cross = d.kind == OP_CROSS;
+    const OpProg& dn = sh.prog[cross ? d.b : d.a];
+    const uint32_t n = dn.arity ? dn.arity : sh.cnt[dn.rag_row * T + rr];
+    uint32_t x = j, y = 0, from = d.a;
+    if (cross) {
+      x = small_div(j, n);
+      y = j - x * n;
+    } else if (j >= n) {
+      x = j - n;
+      from = d.b;
     }
-    store_sign(gptr<uint64_t>(d.values) + at, v, d.flags & F_STREAM);
+    uint64_t v = input_sign(sh.prog[from], rr, x);
+    if (cross) v = mix64(mix64(v + d.key) + input_sign(dn, rr, y));
+    put_list(d, pos, at, v);
   }
 };
 
@@ -2095,7 +2143,7 @@ __global__ __launch_bounds__(kBlock) void k_unordered(UnorderedParams U) {
       if (d.kind == OP_NGRAM) {
         for (uint32_t q = 0; q < cnt; ++q) dst[q] = hash_span(src, s + q, s + q + d.aux_len, d.key);
       } else {
-        ragged_root_emit(src, d, U.aux, 0u, s, e, dst, malformed);
+        ragged_root_emit(src, d, U.aux, 0u, s, e, [&](uint64_t v) { *dst++ = v; }, malformed);
       }
     }
   }

@@ -918,3 +918,39 @@ def test_layers_of_many_list_crosses(crosses, tile_log2):
     raw, off = _cat([("\t".join(rng.choice(["a", "a,bc", ",,d", "q,w,e,r"]) for _ in range(6)) + "\n").encode() for _ in range(101)])
     for compiled in (0, 1):
         check(spec, raw, off, {"tile_log2": tile_log2, "compile": compiled}, label=f"{crosses} {tile_log2} {compiled}")
+
+
+LISTS_ON_CHIP_SPEC = ("fbx 1\nfields 5\n"
+                      "op s hash slot=0 seed=1 emit=0 field=0 multi=0\n"
+                      "op m hash slot=1 seed=2 emit=0 field=1 multi=1\n"
+                      "op n hash slot=2 seed=3 emit=1 field=2 multi=1\n"
+                      "op b bucket slot=3 seed=4 emit=0 field=3 multi=1 bounds=0,2000000\n"
+                      "op f filter slot=4 seed=5 emit=0 field=2 multi=1 prefix=61\n"
+                      "op g ngram slot=5 seed=6 emit=0 field=4 n=3\n"
+                      "op c concat slot=6 emit=0 a=s b=s\n"
+                      "op k cross slot=7 seed=7 emit=0 a=s b=m\n"
+                      "op x cross slot=8 seed=8 emit=0 a=m b=n\n"
+                      "op y cross slot=9 seed=9 emit=1 a=b b=f\n"
+                      "op z concat slot=10 emit=0 a=g b=m\n"
+                      "op d cross slot=11 seed=10 emit=1 a=c b=n\n"
+                      "op e concat slot=12 emit=1 a=c b=c\n"
+                      "op w concat slot=13 emit=0 a=x b=z\n"
+                      "op q cross slot=14 seed=11 emit=0 a=k b=f\n"
+                      "op r concat slot=15 emit=1 a=w b=q\n"
+                      "op t cross slot=16 seed=12 emit=1 a=q b=c\n")
+
+
+@pytest.mark.parametrize("most", [3, 30])
+@pytest.mark.parametrize("options", [{}, {"one_launch": 0}, {"compile": 1}, {"tile_log2": 0}, {"tile_log2": 5, "raw_cap": 1024},
+                                     {"tile_log2": 4, "raw_cap": 1024, "compile": 1}, {"lds_budget": 20000}])
+def test_lists_that_stay_on_chip(options, most):
+    """Lists that later operators read (of every kind of operator, emitted or not) where all, some or none of them find room
+    on chip, in tiles of one pass and of several, and of records that are read in place."""
+    rng = random.Random(most)
+    word = lambda: "".join(rng.choice("abc019") for _ in range(rng.randint(0, 6)))
+    items = lambda make: ",".join(make() for _ in range(rng.randint(1, most)))
+    recs = []
+    for i in range(150):
+        rec = "\t".join([word(), items(word), items(word), items(lambda: f"{rng.randint(-3, 9)}.{rng.randint(0, 9)}"), word() * rng.randint(0, 9)])
+        recs.append((word() if i % 11 == 3 else rec * (40 if i % 50 == 7 else 1)).encode() + b"\n")
+    check(LISTS_ON_CHIP_SPEC, *_cat(recs), options, label=f"{options} {most}")
