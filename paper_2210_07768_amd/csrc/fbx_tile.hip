@@ -1728,7 +1728,7 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
     });
   }
   FBX_MARK(8);
-  if (!P.n_ragged) return;  // (list operators need a ragged input somewhere below them)
+  if (!P.n_ragged && !P.n_gen) return;  // (a concat of single signs is a list operator without a ragged input below it)
 
   // ---- one-launch mode: the tile's bases come from the tiles before it.  The count went out
   // long ago, so the tiles before this one have had time to count.

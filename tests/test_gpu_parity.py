@@ -954,3 +954,11 @@ def test_lists_that_stay_on_chip(options, most):
         rec = "\t".join([word(), items(word), items(word), items(lambda: f"{rng.randint(-3, 9)}.{rng.randint(0, 9)}"), word() * rng.randint(0, 9)])
         recs.append((word() if i % 11 == 3 else rec * (40 if i % 50 == 7 else 1)).encode() + b"\n")
     check(LISTS_ON_CHIP_SPEC, *_cat(recs), options, label=f"{options} {most}")
+
+
+@pytest.mark.parametrize("options", [{}, {"compile": 1}, {"fused": 0}])
+def test_concats_of_single_signs_without_any_list(options):
+    spec = ("fbx 1\nfields 2\nop a hash slot=0 seed=1 emit=0 field=0 multi=0\nop b hash slot=1 seed=2 emit=1 field=1 multi=0\n"
+            "op c concat slot=2 emit=1 a=a b=b\nop d cross slot=3 seed=3 emit=1 a=c b=a\n")
+    raw, off = _cat([f"{i}\tx{i * i}\n".encode() for i in range(333)])
+    check(spec, raw, off, options, label=str(options))
