@@ -75,6 +75,7 @@ struct fbx_plan {
   // where arrays go, worked out on the host when their sizes are known before the call
   std::vector<uint32_t> units;         // per operator and row, as launch_setup wants them
   uint32_t n_mh = 0, n_split = 0, n_gen = 0;  // as in TileParams
+  bool whole_tiles = false;  // the workspace has no room for the tables of smaller tiles (few_tiles)
   bool keeps_roots = false;  // a later operator reads lists of layer 1, or lists made along with them
   uint32_t n_comma_fields = 0;                // fields that some operator reads as a list
   TileResident resident[4];
@@ -157,6 +158,7 @@ namespace {
 
 struct CallGeometry {
   bool tile_engine = false;
+  bool split = false;      // tiles smaller than the LDS admits, because there are few (few_tiles)
   uint32_t n_tiles = 0, count_waves = 1;
   uint64_t off_tile_cnt = 0, off_tile_base = 0, off_scan_part = 0, arena_base = 0;
   TileParams tp{};  // LDS layout and tile size (tile engine only)
@@ -246,9 +248,38 @@ bool tile_geometry(const fbx_plan& p, uint64_t raw_len, uint64_t n_records, Tile
   return false;
 }
 
-CallGeometry geometry(const fbx_plan& p, uint64_t raw_len, uint64_t n_records) {
+// A batch of few tiles leaves most of the chip idle while each of them runs through its phases: its tiles are halved as
+// long as that pays.  The section of staged text stays as large as it was (fewer records vary more).
+// Down to 4 records while there are at most 64 tiles, which a look-back finds in one window (us a call, before and after:
+// 1 to 64 records of the 100-field workload 39 to 43 and 35 to 37, 257 of them 43 and 38, 1,000 of them 44 and 40, where twice
+// as many tiles take 41; 64 and 2,000 of the numeric one 43 and 32, 45 and 39; 16 and 200 with 18 lists 53 and 41, 55 and 43; of
+// the four-layer graph 64, 65 and 61).  Where more look-backs than pay are counted instead, down to 8 records and up to a
+// tile a compute unit (1,999 records with 18 lists: 71 and 63; 4 records: 68).  Kernels compiled for the plan are compiled for
+// one size, and in arrival order the caller is told it: there tiles stay as they are.
+uint64_t back_bytes(uint32_t n_back) { return uint64_t(n_back) * (n_back <= 8u ? 1024u : 1792u); }  // (see extract_impl)
+bool few_tiles(const fbx_plan& p, uint64_t raw_len, uint64_t n_records, TileParams& tp) {
+  if (p.tile_log2 >= 0 || p.compile || p.placement || !n_records) return false;
+  const uint64_t per_record = raw_len / n_records, avg = (raw_len + n_records - 1) / n_records;
+  const uint32_t n_back = p.host.n_ragged - p.host.n_alias;
+  bool any = false;
+  while (tp.log2T > 2u) {
+    const uint32_t lt = tp.log2T - 1u;
+    const uint64_t tiles = (n_records + (1ull << lt) - 1) >> lt;
+    const bool counted = n_back > 8u && back_bytes(n_back) > per_record << tp.log2T;
+    if (tiles > (counted && lt >= 3u ? tile_cu_count() : 64u)) break;
+    TileParams half = tp;
+    tile_lds_layout(p, lt, p.raw_cap ? p.raw_cap : (avg << lt) * 5 / 4 + 64, tp.raw_cap, half);
+    if (half.o_lists > std::min(p.lds_budget, tile_max_lds())) break;
+    tp = half;
+    any = true;
+  }
+  return any;
+}
+
+CallGeometry geometry(const fbx_plan& p, uint64_t raw_len, uint64_t n_records, bool may_split) {
   CallGeometry g;
   g.tile_engine = p.fused && p.tile_engine && tile_geometry(p, raw_len, n_records, g.tp);
+  if (g.tile_engine && may_split) g.split = few_tiles(p, raw_len, n_records, g.tp);
   if (g.tile_engine) {
     g.n_tiles = static_cast<uint32_t>((n_records + (1ull << g.tp.log2T) - 1) >> g.tp.log2T);
   } else {
@@ -333,7 +364,7 @@ fbx_status fbx_plan_compiled(const fbx_plan* plan, uint32_t* n_kernels, double* 
 fbx_status fbx_plan_kernel_source(const fbx_plan* plan, uint64_t raw_len, uint64_t n_records, int mode, char* buf,
                                   size_t buf_len, size_t* needed) {
   if (!plan || mode < 0 || mode > 3 || (!buf && buf_len)) return FBX_E_ARG;
-  const CallGeometry g = geometry(*plan, raw_len, n_records);
+  const CallGeometry g = geometry(*plan, raw_len, n_records, false);
   if (!g.tile_engine) return FBX_E_ARG;  // (plans too wide for the tile kernel have no such kernel)
   TileParams Q = g.tp;
   const PlanHost& h = plan->host;
@@ -425,7 +456,7 @@ fbx_status fbx_plan_set_option(fbx_plan* plan, const char* key, int64_t value) {
 
 fbx_status fbx_plan_workspace_hint(const fbx_plan* plan, uint64_t raw_len, uint64_t n_records, uint64_t* bytes) {
   if (!plan || !bytes) return FBX_E_ARG;
-  const CallGeometry g = geometry(*plan, raw_len, n_records);
+  const CallGeometry g = geometry(*plan, raw_len, n_records, true);
   // fixed-arity operators are exact; a ragged root operator cannot emit more
   // signs than its field has bytes + 1, for which raw_len / #fields + records
   // is a fair guess; a ragged cross or concat is guessed at four times that.
@@ -452,6 +483,7 @@ fbx_status fbx_plan_set_workspace(fbx_plan* plan, void* d_workspace, uint64_t by
   hipError_t e = hipMemcpy(d_workspace, plan->tables.data(), plan->tables.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_fail(plan, e, "copying plan tables");
   plan->ws = static_cast<uint8_t*>(d_workspace);
+  plan->whole_tiles = false;
   plan->ws_bytes = bytes;
   return FBX_OK;
 }
@@ -758,7 +790,7 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   bool one = !resting && g.tile_engine && plan->one_launch && plan->learned && h.n_ragged && n_records && plan->learned_records &&
              ws_bytes > plan->margin_failed_ws &&
              (plan->placement || (g.n_tiles <= 64u && n_back <= 48u) ||
-              uint64_t(n_back) * (n_back <= 8u ? 1024u : 1792u) <= (raw_len / n_records) << g.tp.log2T);
+              back_bytes(n_back) <= (raw_len / n_records) << g.tp.log2T);
   if (one) {
     plan->cap_host.resize(h.n_ragged);
     for (uint32_t r = 0; r < h.n_ragged; ++r) {
@@ -881,14 +913,19 @@ fbx_status fbx_extract(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, c
   }
   if (!plan->ws) { plan->error = "no workspace set"; return FBX_E_ARG; }
   if (n_records >= (1ull << 32)) { plan->error = "more than 2^32-1 records in one call"; return FBX_E_ARG; }
-  const CallGeometry g = geometry(*plan, raw_len, n_records);
+  CallGeometry g = geometry(*plan, raw_len, n_records, !plan->whole_tiles);
+  if (g.split && g.arena_base > plan->ws_bytes) g = geometry(*plan, raw_len, n_records, false);
   if (g.arena_base > plan->ws_bytes) {
     out->arena_high_water = g.arena_base;
     plan->error = "workspace too small for the per-tile tables; need more than " + std::to_string(g.arena_base) + " bytes";
     return FBX_E_NOMEM;
   }
   const Regions reg{plan->ws, plan->ws_bytes, reinterpret_cast<uint64_t>(plan->ws), plan->ws_bytes, false};
-  return extract_impl(plan, d_raw, raw_len, d_rec_off, n_records, hip_stream, out, reg, g);
+  const fbx_status st = extract_impl(plan, d_raw, raw_len, d_rec_off, n_records, hip_stream, out, reg, g);
+  if (st != FBX_E_NOMEM || !g.split) return st;
+  // More tiles have larger tables: a workspace that is only just large enough without them is used without them, from now on.
+  plan->whole_tiles = true;
+  return extract_impl(plan, d_raw, raw_len, d_rec_off, n_records, hip_stream, out, reg, geometry(*plan, raw_len, n_records, false));
 }
 
 // ---- the entry point that allocates nothing
@@ -946,7 +983,8 @@ fbx_status fbx_extract_static(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw
   }
   if (reinterpret_cast<uintptr_t>(d_out) & 255u) { plan->error = "the output buffer must be 256-byte aligned"; return FBX_E_ARG; }
   if (n_records >= (1ull << 32)) { plan->error = "more than 2^32-1 records in one call"; return FBX_E_ARG; }
-  const CallGeometry g = geometry(*plan, raw_len, n_records);
+  CallGeometry g = geometry(*plan, raw_len, n_records, true);
+  if (g.split && g.arena_base > kScratchBytes) g = geometry(*plan, raw_len, n_records, false);
   if (g.arena_base > kScratchBytes) {
     // (rejected before anything is enqueued: the tables of this batch do not fit the library's own array)
     out->arena_high_water = 0;

@@ -962,3 +962,35 @@ def test_concats_of_single_signs_without_any_list(options):
             "op c concat slot=2 emit=1 a=a b=b\nop d cross slot=3 seed=3 emit=1 a=c b=a\n")
     raw, off = _cat([f"{i}\tx{i * i}\n".encode() for i in range(333)])
     check(spec, raw, off, options, label=str(options))
+
+
+@pytest.mark.parametrize("cfg,n", [(1, 1), (1, 65), (1, 513), (5, 1), (5, 5), (5, 255), (5, 256), (5, 257), (5, 513), (5, 1025), (2, 9), (2, 257), (2, 700),
+                                   (3, 257), (3, 2048), (3, 2049), (4, 65), (4, 300)])
+def test_batches_of_few_tiles(cfg, n):
+    """Tiles are halved while a batch has few of them: sizes around the steps, in the call that counts and in the ones that look
+    back, with a workspace that has room for their tables and with one that only has room for those of whole tiles."""
+    import torch
+    w = W.get(cfg, n)
+    raw, off = w.generate()
+    want = O.extract(w.spec, raw, off)
+    d_raw, d_off = to_device(raw, off)
+    plan = B.Plan(w.spec)
+    res, ws = B.extract_with_retry(plan, d_raw, d_off)
+    for _ in range(2):
+        res = plan.extract(d_raw, d_off)
+        assert_same({s: expand(res.slots[s], n) for s in res.slot_ids}, res, want, f"config{cfg} {n}")
+    plan.close()
+    plan = B.Plan(w.spec)
+    size = 512 << 10
+    for _ in range(5):  # (what is asked for when a call is refused has to be enough in the end, and stay enough)
+        small = torch.empty(size, dtype=torch.uint8, device="cuda")
+        plan.set_workspace(small)
+        try:
+            for _ in range(3):
+                res = plan.extract(d_raw, d_off)
+            break
+        except B.FbxError as e:
+            assert e.status == B.E_NOMEM and e.required_bytes > size
+            size = e.required_bytes
+    assert_same({s: expand(res.slots[s], n) for s in res.slot_ids}, res, want, f"config{cfg} {n}, tight")
+    plan.close()
