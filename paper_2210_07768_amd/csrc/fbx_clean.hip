@@ -275,6 +275,9 @@ __device__ __forceinline__ u32x4 text_chunk(uintptr_t ca, uintptr_t ok_lo, uintp
   }
   return v;
 }
+// The same where all chunks lie inside the buffer (plain global loads: flat ones would also wait on the LDS counter).
+using ChunkPtr = const __attribute__((address_space(1))) u32x4*;
+__device__ __forceinline__ ChunkPtr chunks_at(uintptr_t a) { return reinterpret_cast<ChunkPtr>(a); }
 // A table of the specification into LDS, all lanes taking part (sizes are whole words).
 __device__ __forceinline__ void clean_table(uint32_t to, const void* from, uint32_t bytes) {
   for (uint32_t i = threadIdx.x; i < bytes / 4u; i += kCleanThreads)
@@ -356,8 +359,21 @@ __global__ __launch_bounds__(kCleanThreads, kCleanWaves) void k_clean_measure_ti
       {
         const uint32_t nchunks = (delta + (uint32_t)(s_off[nb] - o0) + 15u) >> 4;
         const uintptr_t a0 = ok_lo + o0 - delta;
-        for (uint32_t c = tid; c < nchunks; c += kCleanThreads)
-          *reinterpret_cast<u32x4*>(raw + kCleanRawPad + 16u * c) = text_chunk(a0 + 16u * c, ok_lo, ok_hi);
+        if (a0 >= ok_lo && a0 + 16ull * nchunks <= ok_hi) {  // whole chunks (all but the ends of the caller's buffer), four of a lane in flight
+          constexpr uint32_t kInFlight = 4;
+          const ChunkPtr from = chunks_at(a0);
+          for (uint32_t c = tid; c < nchunks; c += kInFlight * kCleanThreads) {
+            u32x4 v[kInFlight];
+#pragma unroll
+            for (uint32_t k = 0; k < kInFlight; ++k) v[k] = from[min(c + k * kCleanThreads, nchunks - 1u)];
+#pragma unroll
+            for (uint32_t k = 0; k < kInFlight; ++k)
+              if (c + k * kCleanThreads < nchunks) *reinterpret_cast<u32x4*>(raw + kCleanRawPad + 16u * (c + k * kCleanThreads)) = v[k];
+          }
+        } else {
+          for (uint32_t c = tid; c < nchunks; c += kCleanThreads)
+            *reinterpret_cast<u32x4*>(raw + kCleanRawPad + 16u * c) = text_chunk(a0 + 16u * c, ok_lo, ok_hi);
+        }
       }
       request_offsets(tile + 1u);
       __syncthreads();
@@ -623,14 +639,44 @@ __global__ __launch_bounds__(kCleanThreads, kCleanWaves) void k_clean_write_tile
       const uint64_t o0 = s_off[0];
       const uint32_t delta = (uint32_t)((ok_lo + o0) & 15u);
       const uintptr_t a0 = ok_lo + o0 - delta;
-      for (uint32_t r = wave; r < nb; r += kCleanThreads / 64u) {
-        if (s_out[r] == kDropped) continue;
-        const uint32_t c1 = (delta + (uint32_t)(s_off[r + 1] - o0) + 15u) >> 4;
-        for (uint32_t c = ((delta + (uint32_t)(s_off[r] - o0)) >> 4) + lane; c < c1; c += 64u)
-          *reinterpret_cast<u32x4*>(raw + kCleanRawPad + 16u * c) = text_chunk(a0 + 16u * c, ok_lo, ok_hi);
+      const uint32_t* segs = C.segs + g0 * (2ull * C.n_of + 3u);
+      const uint32_t seg0 = tid < n_segs ? segs[tid] : 0u;  // (on its way together with the text)
+      auto bounds = [&](uint32_t r, uint32_t& c, uint32_t& c1) {  // this lane's first chunk of the record, and where the record's end
+        c = ((delta + (uint32_t)(s_off[r] - o0)) >> 4) + lane;
+        c1 = s_out[r] == kDropped ? 0u : (delta + (uint32_t)(s_off[r + 1] - o0) + 15u) >> 4;
+      };
+      constexpr uint32_t kWaves = kCleanThreads / 64u, kInFlight = 4;
+      const bool inside = a0 >= ok_lo && a0 + (delta + (s_off[nb] - o0) + 16u) / 16u * 16u <= ok_hi;  // (one at least)
+      if (inside) {  // whole chunks (all but the ends of the caller's buffer): the first ones of four records on their way at a time
+        const ChunkPtr from = chunks_at(a0);
+        for (uint32_t r0 = wave; r0 < nb; r0 += kInFlight * kWaves) {
+          u32x4 v[kInFlight];
+#pragma unroll
+          for (uint32_t k = 0; k < kInFlight; ++k) {
+            uint32_t c, c1;
+            bounds(min(r0 + k * kWaves, nb - 1u), c, c1);
+            v[k] = from[c < c1 ? c : 0u];
+          }
+#pragma unroll
+          for (uint32_t k = 0; k < kInFlight; ++k) {
+            const uint32_t r = r0 + k * kWaves;
+            if (r >= nb) break;
+            uint32_t c, c1;
+            bounds(r, c, c1);
+            if (c < c1) *reinterpret_cast<u32x4*>(raw + kCleanRawPad + 16u * c) = v[k];
+            for (c += 64u; c < c1; c += 64u) *reinterpret_cast<u32x4*>(raw + kCleanRawPad + 16u * c) = from[c];
+          }
+        }
+      } else {
+        for (uint32_t r = wave; r < nb; r += kWaves) {
+          uint32_t c, c1;
+          bounds(r, c, c1);
+          for (; c < c1; c += 64u) *reinterpret_cast<u32x4*>(raw + kCleanRawPad + 16u * c) = text_chunk(a0 + 16u * c, ok_lo, ok_hi);
+        }
       }
       const uint32_t total = (uint32_t)total64;
-      for (uint32_t i = tid; i < n_segs; i += kCleanThreads) seg[i] = C.segs[g0 * (2ull * C.n_of + 3u) + i];
+      if (tid < n_segs) seg[tid] = seg0;
+      for (uint32_t i = tid + kCleanThreads; i < n_segs; i += kCleanThreads) seg[i] = segs[i];
       if (tid == 0) seg[n_segs] = two(total, 0u);
       __syncthreads();
       // Lanes as 16-byte chunks of the output: chunk c holds the tile's bytes [16 c - shift, 16 c - shift + 16).  Most
