@@ -375,6 +375,7 @@ fbx_status fbx_plan_kernel_source(const fbx_plan* plan, uint64_t raw_len, uint64
   Q.n_lists = static_cast<uint32_t>(h.tile_list_begin.size()) - 1u;
   Q.aux_bytes = static_cast<uint32_t>(h.aux.size());
   Q.n_fields = h.n_fields; Q.n_stage = h.n_stage;
+  if (mode == 0) Q.lds_bytes = Q.o_lists;  // (as extract_impl launches it)
   Q.lds_bytes = std::max(Q.lds_bytes, plan->lds_pad);
   const std::string text = tile_kernel_source(Q, mode, h, plan->tile_threads, plan->lane_ops);
   if (needed) *needed = text.size() + 1;
