@@ -248,25 +248,34 @@ bool tile_geometry(const fbx_plan& p, uint64_t raw_len, uint64_t n_records, Tile
   return false;
 }
 
+// Whether a call that knows its sizes skips the counting launch (extract_impl says where the lines lie).
+bool one_launch_pays(const fbx_plan& p, uint64_t per_record, uint32_t log2T, uint64_t n_tiles) {
+  const uint32_t n_back = p.host.n_ragged - p.host.n_alias;
+  return p.placement || (n_tiles <= 64u && n_back <= 48u) ||
+         uint64_t(n_back) * (n_back <= 8u ? 1024u : 1792u) <= per_record << log2T;
+}
+
 // A batch of few tiles leaves most of the chip idle while each of them runs through its phases: its tiles are halved as
 // long as that pays.  The section of staged text stays as large as it was (fewer records vary more).
 // Down to 4 records while there are at most 64 tiles, which a look-back finds in one window (us a call, before and after:
 // 1 to 64 records of the 100-field workload 39 to 43 and 35 to 37, 257 of them 43 and 38, 1,000 of them 44 and 40, where twice
 // as many tiles take 41; 64 and 2,000 of the numeric one 43 and 32, 45 and 39; 16 and 200 with 18 lists 53 and 41, 55 and 43; of
-// the four-layer graph 64, 65 and 61).  Where more look-backs than pay are counted instead, down to 8 records and up to a
-// tile a compute unit (1,999 records with 18 lists: 71 and 63; 4 records: 68).  Kernels compiled for the plan are compiled for
-// one size, and in arrival order the caller is told it: there tiles stay as they are.
-uint64_t back_bytes(uint32_t n_back) { return uint64_t(n_back) * (n_back <= 8u ? 1024u : 1792u); }  // (see extract_impl)
+// the four-layer graph 64, 65 and 61).  Where more look-backs than pay are counted with the tiles as they are, down to 8
+// records and up to a tile a compute unit (1,999 records with 18 lists: 71 and 63; 4 records: 68), but a batch that looks
+// back is not halved into one that counts (24 look-backs, 513 to 1,024 records: 70 with tiles of 16 in one launch, 73
+// with tiles of 8 counted; 20 short lists, 700 and 1,500 records: 40 and 47, 46 and 50).  Kernels compiled for the plan
+// are compiled for one size, and in arrival order the caller is told it: there tiles stay as they are.
 bool few_tiles(const fbx_plan& p, uint64_t raw_len, uint64_t n_records, TileParams& tp) {
   if (p.tile_log2 >= 0 || p.compile || p.placement || !n_records) return false;
   const uint64_t per_record = raw_len / n_records, avg = (raw_len + n_records - 1) / n_records;
-  const uint32_t n_back = p.host.n_ragged - p.host.n_alias;
+  auto tiles_of = [&](uint32_t lt) { return (n_records + (1ull << lt) - 1) >> lt; };
   bool any = false;
   while (tp.log2T > 2u) {
     const uint32_t lt = tp.log2T - 1u;
-    const uint64_t tiles = (n_records + (1ull << lt) - 1) >> lt;
-    const bool counted = n_back > 8u && back_bytes(n_back) > per_record << tp.log2T;
-    if (tiles > (counted && lt >= 3u ? tile_cu_count() : 64u)) break;
+    const bool pays = one_launch_pays(p, per_record, tp.log2T, tiles_of(tp.log2T));
+    if (pays && !one_launch_pays(p, per_record, lt, tiles_of(lt))) break;
+    const bool counted = !pays && p.host.n_ragged - p.host.n_alias > 8u;
+    if (tiles_of(lt) > (counted && lt >= 3u ? tile_cu_count() : 64u)) break;
     TileParams half = tp;
     tile_lds_layout(p, lt, p.raw_cap ? p.raw_cap : (avg << lt) * 5 / 4 + 64, tp.raw_cap, half);
     if (half.o_lists > std::min(p.lds_budget, tile_max_lds())) break;
@@ -787,11 +796,8 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
   // sequence is then left untried for 1, 2, 4 ... up to 64 calls, so that such batches do not pay for two attempts each)
   const bool resting = plan->passes_skip > 0;
   if (resting) --plan->passes_skip;
-  const uint32_t n_back = h.n_ragged - h.n_alias;
   bool one = !resting && g.tile_engine && plan->one_launch && plan->learned && h.n_ragged && n_records && plan->learned_records &&
-             ws_bytes > plan->margin_failed_ws &&
-             (plan->placement || (g.n_tiles <= 64u && n_back <= 48u) ||
-              back_bytes(n_back) <= (raw_len / n_records) << g.tp.log2T);
+             ws_bytes > plan->margin_failed_ws && one_launch_pays(*plan, raw_len / n_records, g.tp.log2T, g.n_tiles);
   if (one) {
     plan->cap_host.resize(h.n_ragged);
     for (uint32_t r = 0; r < h.n_ragged; ++r) {

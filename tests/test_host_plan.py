@@ -246,3 +246,19 @@ def test_where_commas_are_looked_for_along_with_the_tabs(hashes, filters, record
                   + "".join(f"op f{k} filter slot={k} seed={k} emit=1 field={k} multi=1 prefix=61\n" for k in range(60 + hashes, 60 + n)))
     assert f"P.commas = {commas}u;" in plan.kernel_source(record * 10000, 10000, 1)
     plan.close()
+
+
+@pytest.mark.parametrize("records,log2", [(512, 3), (513, 4), (700, 4), (1000, 4), (1024, 4), (1025, 3), (1999, 3), (2048, 3), (2049, 4)])
+def test_a_batch_that_looks_back_is_not_halved_into_one_that_counts(records, log2):
+    """24 lists, tiles of 16: up to 64 tiles take one launch, whichever text they have; more are counted, and then in smaller
+    tiles up to one a compute unit.  (A workspace's hint tells tile sizes apart: their tables are in it.)"""
+    spec = "fbx 1\nfields 24\n" + "".join(f"op h{k} hash slot={k} seed={k} emit=1 field={k} multi=1\n" for k in range(24))
+
+    def hint(tile_log2):
+        plan = B.Plan(spec)
+        plan.set_option("tile_log2", tile_log2)
+        size = plan.workspace_hint(2100 * records, records)
+        plan.close()
+        return size
+
+    assert [t for t in range(7) if hint(t) == hint(-1)] == [log2]
