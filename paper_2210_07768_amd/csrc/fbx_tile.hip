@@ -1771,6 +1771,9 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
   if (!ragged_roots_done) for_units(&s_ctr[3], ragged_root_units(), ragged_root_unit);
   FBX_MARK(10);
   // ---- the list crosses / concats, layer by layer
+#ifndef FBX_FIXED_MODE  // (where the lists' bounds are literals nothing is left to leave out, and the line costs: 1.20 against 1.11 ms for a million of 100 fields)
+  if (!P.n_gen) return;
+#endif
   for (uint32_t layer = 2, turn = 0; layer <= P.n_layers; ++layer) {
     const uint32_t list = ps.gen_list(layer);
     if (sh.lbeg(list + 1) == sh.lbeg(list)) continue;  // (no such operator in this layer: no barrier either)
@@ -2183,8 +2186,15 @@ __global__ __launch_bounds__(kBlock) void k_unordered(UnorderedParams U) {
 // spilled and where shifts with every addition.  3,000,000 records of the 100-field workload: 4.16 ms for one kernel with
 // both ways, both cross layouts and both record searches, 3.82 for this one; a million of 16 single-valued fields: 0.41
 // and 0.37.)
-template <int MODE, int COMMAS>
-__global__ __launch_bounds__(kTileThreads, 4) void k_tile(TileParams P) {
+// GEN: whether the plan has list operators in later layers.  One kernel for plans with and without them has every store of a
+// list ask whether the list stays on chip, and both need more scalar registers than there are (213 spilled against 163 and
+// 199 here; 170 before lists stayed on chip): 200,000 records of 12 lists 272 us a call against 244 (247), of 12 list
+// filters 286 and 269 (270), a million of 100 fields 1.39 ms and 1.29 (1.31); with list operators, 50,000 of the four-layer
+// graph 571 and 527 (562), 200,000 of 12 lists and 4 crosses of them 550 and 487 (490).
+template <int MODE, int COMMAS, bool GEN>
+__global__ __launch_bounds__(kTileThreads, 4) void k_tile(TileParams Pin) {
+  TileParams P = Pin;
+  if constexpr (!GEN) P.n_gen = 0;
   tile_entry<MODE, COMMAS>(P);
 }
 #endif
@@ -2231,17 +2241,17 @@ uint32_t tile_max_lds() {
   return cached;
 }
 
-template <int MODE>
+template <int MODE, bool GEN>
 static const void* tile_kernel_of(uint32_t commas) {
-  return commas == kCommasOfHashes  ? reinterpret_cast<const void*>(&k_tile<MODE, kCommasOfHashes>)
-         : commas == kCommasByField ? reinterpret_cast<const void*>(&k_tile<MODE, kCommasByField>)
-                                    : reinterpret_cast<const void*>(&k_tile<MODE, kCommasWithTabs>);
+  return commas == kCommasOfHashes  ? reinterpret_cast<const void*>(&k_tile<MODE, kCommasOfHashes, GEN>)
+         : commas == kCommasByField ? reinterpret_cast<const void*>(&k_tile<MODE, kCommasByField, GEN>)
+                                    : reinterpret_cast<const void*>(&k_tile<MODE, kCommasWithTabs, GEN>);
 }
-static const void* tile_kernel(int mode, uint32_t commas) {
-  return mode == 0   ? tile_kernel_of<0>(commas)
-         : mode == 1 ? tile_kernel_of<1>(commas)
-         : mode == 2 ? tile_kernel_of<2>(commas)
-                     : tile_kernel_of<3>(commas);
+static const void* tile_kernel(int mode, uint32_t commas, bool gen) {
+  if (mode == 0) return tile_kernel_of<0, true>(commas);  // (counting stops before list operators are computed)
+  if (mode == 1) return gen ? tile_kernel_of<1, true>(commas) : tile_kernel_of<1, false>(commas);
+  if (mode == 2) return gen ? tile_kernel_of<2, true>(commas) : tile_kernel_of<2, false>(commas);
+  return gen ? tile_kernel_of<3, true>(commas) : tile_kernel_of<3, false>(commas);
 }
 
 hipError_t launch_tile(const TileParams& P, int mode, TileResident* known, hipStream_t st) {
@@ -2249,7 +2259,7 @@ hipError_t launch_tile(const TileParams& P, int mode, TileResident* known, hipSt
   TileResident& k = known[mode];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); dev = 0; }
-  const void* fn = tile_kernel(mode, P.commas);
+  const void* fn = tile_kernel(mode, P.commas, P.n_gen != 0u);
   if (k.dev != dev || k.lds != P.lds_bytes || k.fn != fn) {
     if (P.lds_bytes > 48u * 1024u) {
       // (the limit belongs to the function, which all plans share: what the device has beside the kernel's own, never

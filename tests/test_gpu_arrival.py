@@ -190,3 +190,38 @@ def test_arrival_order_falls_back_to_record_order():
     assert res.tile_launches == 1
     assert_same_in_arrival_order(res, O.extract(spec, *cat(long_)), 4000, "with the new sizes")
     plan.close()
+
+
+@pytest.mark.parametrize("gen", [0, 1], ids=["lists_only", "cross_of_lists"])
+@pytest.mark.parametrize("lists,others,pad,commas", [(3, 0, 0, 0), (3, 4, 0, 1), (3, 4, 3000, 2), (40, 0, 0, 2)])
+def test_the_kernels_for_plans_with_and_without_list_operators(lists, others, pad, commas, gen):
+    """Every way to find commas, with and without operators of two lists, in the launch that follows counting, in the one that
+    looks back and in the one that places tiles as they arrive."""
+    rng = random.Random(lists + others)
+    F = lists + others + 2
+    spec = f"fbx 1\nfields {F}\nop t hash slot=900 seed=1 emit=1 field=0 multi=0\n"
+    spec += "".join(f"op h{k} hash slot={k} seed={k} emit=1 field={1 + k} multi=1\n" for k in range(lists))
+    for k in range(others):
+        spec += (f"op o{k} filter slot={100 + k} seed={k} emit=1 field={1 + lists + k} multi=1 prefix=61\n" if k % 2 == 0 else
+                 f"op o{k} bucket slot={100 + k} seed={k} emit=1 field={1 + lists + k} multi=1 bounds=1000000,5000000\n")
+    spec += "op g ngram slot=903 seed=7 emit=1 field=0 n=3\nop y cross slot=902 seed=6 emit=1 a=t b=h2\n"
+    if gen:
+        spec += "op x cross slot=901 seed=5 emit=1 a=h0 b=h1\n"
+    recs = []
+    for i in range(301):
+        items = lambda: ",".join(rng.choice(["", "a", "ab", "abc7", "5.25", "x" * 20]) for _ in range(rng.choice([1, 1, 2, 4, 18])))
+        recs.append(("\t".join(["q" * (i % 9)] + [items() for _ in range(lists + others)] + ["z" * (pad + rng.randrange(20))]) + "\n").encode())
+    raw = np.frombuffer(b"".join(recs), np.uint8)
+    off = np.cumsum([0] + [len(r) for r in recs]).astype(np.uint64)
+    want = O.extract(spec, raw, off)
+    plan = B.Plan(spec)
+    text = plan.kernel_source(raw.size, 301, 1)
+    assert f"P.commas = {commas}u;" in text and f"P.n_gen = {gen}u;" in text
+    d_raw, d_off = to_device(raw, off)
+    res, ws = B.extract_with_retry(plan, d_raw, d_off)  # (counts)
+    for launches in (2, 1):
+        assert res.tile_launches == launches, res.note
+        assert_same({s: expand(res.slots[s], 301) for s in res.slot_ids}, res, want, f"{launches} launches")
+        res = plan.extract(d_raw, d_off)
+    plan.close()
+    _arrival_calls(spec, raw, off, {}, f"{lists} {others} {pad} {gen}", may_fall_back=True)
