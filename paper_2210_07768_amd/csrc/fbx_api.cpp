@@ -75,7 +75,7 @@ struct fbx_plan {
   // where arrays go, worked out on the host when their sizes are known before the call
   std::vector<uint32_t> units;         // per operator and row, as launch_setup wants them
   uint32_t n_mh = 0, n_split = 0, n_gen = 0;  // as in TileParams
-  bool whole_tiles = false;  // the workspace has no room for the tables of smaller tiles (few_tiles)
+  uint64_t whole_from = ~0ull;  // from so many records on, the workspace has no room for the tables of smaller tiles (few_tiles)
   bool keeps_roots = false;  // a later operator reads lists of layer 1, or lists made along with them
   uint32_t n_comma_fields = 0;                // fields that some operator reads as a list
   TileResident resident[4];
@@ -161,6 +161,7 @@ struct CallGeometry {
   bool split = false;      // tiles smaller than the LDS admits, because there are few (few_tiles)
   uint32_t n_tiles = 0, count_waves = 1;
   uint64_t off_tile_cnt = 0, off_tile_base = 0, off_scan_part = 0, arena_base = 0;
+  uint64_t split_bytes = 0;  // what the tables of smaller tiles take beyond those of whole ones
   TileParams tp{};  // LDS layout and tile size (tile engine only)
 };
 
@@ -288,9 +289,11 @@ bool few_tiles(const fbx_plan& p, uint64_t raw_len, uint64_t n_records, TilePara
 CallGeometry geometry(const fbx_plan& p, uint64_t raw_len, uint64_t n_records, bool may_split) {
   CallGeometry g;
   g.tile_engine = p.fused && p.tile_engine && tile_geometry(p, raw_len, n_records, g.tp);
+  const uint32_t whole_log2 = g.tp.log2T;
   if (g.tile_engine && may_split) g.split = few_tiles(p, raw_len, n_records, g.tp);
+  auto tiles_of = [&](uint32_t log2) { return static_cast<uint32_t>((n_records + (1ull << log2) - 1) >> log2); };
   if (g.tile_engine) {
-    g.n_tiles = static_cast<uint32_t>((n_records + (1ull << g.tp.log2T) - 1) >> g.tp.log2T);
+    g.n_tiles = tiles_of(g.tp.log2T);
   } else {
     g.n_tiles = static_cast<uint32_t>((n_records + kTile - 1) >> kTileLog2);
     // counting pass: one 256-byte LDS row per ragged operator and wavefront; as many
@@ -298,11 +301,16 @@ CallGeometry geometry(const fbx_plan& p, uint64_t raw_len, uint64_t n_records, b
     const uint32_t per_wave = 8960u + p.host.n_ragged * 256u;  // byte ring + count rows
     g.count_waves = std::min(4u, std::max(1u, 65536u / per_wave));
   }
-  uint64_t w = p.off_static_end;
-  g.off_tile_cnt = w; w = align_up(w + uint64_t(p.host.n_ragged) * g.n_tiles * 4);
-  g.off_tile_base = w; w = align_up(w + uint64_t(p.host.n_ragged) * g.n_tiles * 8);
-  g.off_scan_part = w; w = align_up(w + uint64_t(p.host.n_ragged) * scan_segments(g.n_tiles) * 8);
-  g.arena_base = w;
+  auto place_tables = [&](uint32_t n_tiles) {
+    uint64_t w = p.off_static_end;
+    g.off_tile_cnt = w; w = align_up(w + uint64_t(p.host.n_ragged) * n_tiles * 4);
+    g.off_tile_base = w; w = align_up(w + uint64_t(p.host.n_ragged) * n_tiles * 8);
+    g.off_scan_part = w; w = align_up(w + uint64_t(p.host.n_ragged) * scan_segments(n_tiles) * 8);
+    return w;
+  };
+  const uint64_t whole_base = g.split ? place_tables(tiles_of(whole_log2)) : 0;
+  g.arena_base = place_tables(g.n_tiles);
+  if (g.split) g.split_bytes = g.arena_base - whole_base;
   return g;
 }
 
@@ -493,7 +501,7 @@ fbx_status fbx_plan_set_workspace(fbx_plan* plan, void* d_workspace, uint64_t by
   hipError_t e = hipMemcpy(d_workspace, plan->tables.data(), plan->tables.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_fail(plan, e, "copying plan tables");
   plan->ws = static_cast<uint8_t*>(d_workspace);
-  plan->whole_tiles = false;
+  plan->whole_from = ~0ull;
   plan->ws_bytes = bytes;
   return FBX_OK;
 }
@@ -513,8 +521,10 @@ struct Regions {
   bool own_tables;       // the tables are the library's array: no run-time compilation, no event creation
 };
 
-fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, const uint64_t* d_rec_off,
-                        uint64_t n_records, void* hip_stream, fbx_result* out, const Regions& reg, const CallGeometry& g) {
+// whole_fits (where the caller can start over with whole tiles): set, with FBX_E_NOMEM, when the arrays do not fit behind the
+// tables of smaller tiles but do behind those of whole ones.
+fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, const uint64_t* d_rec_off, uint64_t n_records,
+                        void* hip_stream, fbx_result* out, const Regions& reg, const CallGeometry& g, bool* whole_fits = nullptr) {
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const PlanHost& h = plan->host;
   const uint32_t n_ops = static_cast<uint32_t>(h.ops.size());
@@ -817,6 +827,11 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
       plan->error = "internal: a bounded wait between tiles ran out";
       return FBX_E_HIP;
     }
+    if (whole_fits && g.split && (c->err & CE_NOMEM) && !(c->err & (CE_OFFSETS | CE_TILE | CE_OVERFLOW | CE_SPEC | CE_STALL)) &&
+        c->required - g.split_bytes <= ws_bytes) {
+      *whole_fits = true;
+      return FBX_E_NOMEM;
+    }
     if (one && (c->err & (CE_SPEC | CE_NOMEM | CE_STALL))) {
       // Every kernel has exited normally and the tiles that could not be placed wrote nothing: the
       // exact sequence (counting launch, scan, writing launch) can still answer the call.
@@ -857,8 +872,9 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
       out->arena_high_water = c->required - g.arena_base;
       plan->error = "output buffer too small: need " + std::to_string(c->required - g.arena_base) + " bytes";
     } else {
-      out->arena_high_water = c->required;
-      plan->error = "workspace too small: need " + std::to_string(c->required) + " bytes";
+      const uint64_t need = c->required - g.split_bytes;  // (whole tiles are taken where smaller ones' tables find no room)
+      out->arena_high_water = need;
+      plan->error = "workspace too small: need " + std::to_string(need) + " bytes";
     }
     return FBX_E_NOMEM;
   }
@@ -920,7 +936,7 @@ fbx_status fbx_extract(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, c
   }
   if (!plan->ws) { plan->error = "no workspace set"; return FBX_E_ARG; }
   if (n_records >= (1ull << 32)) { plan->error = "more than 2^32-1 records in one call"; return FBX_E_ARG; }
-  CallGeometry g = geometry(*plan, raw_len, n_records, !plan->whole_tiles);
+  CallGeometry g = geometry(*plan, raw_len, n_records, n_records < plan->whole_from);
   if (g.split && g.arena_base > plan->ws_bytes) g = geometry(*plan, raw_len, n_records, false);
   if (g.arena_base > plan->ws_bytes) {
     out->arena_high_water = g.arena_base;
@@ -928,11 +944,15 @@ fbx_status fbx_extract(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, c
     return FBX_E_NOMEM;
   }
   const Regions reg{plan->ws, plan->ws_bytes, reinterpret_cast<uint64_t>(plan->ws), plan->ws_bytes, false};
-  const fbx_status st = extract_impl(plan, d_raw, raw_len, d_rec_off, n_records, hip_stream, out, reg, g);
-  if (st != FBX_E_NOMEM || !g.split) return st;
-  // More tiles have larger tables: a workspace that is only just large enough without them is used without them, from now on.
-  plan->whole_tiles = true;
-  return extract_impl(plan, d_raw, raw_len, d_rec_off, n_records, hip_stream, out, reg, geometry(*plan, raw_len, n_records, false));
+  // More tiles have larger tables: in a workspace that holds the arrays only without them, batches of this size and larger
+  // ones take whole tiles from now on.  (Where sizes are known before the launch nothing has run by then; else counting has.)
+  bool whole_fits = false;
+  const fbx_status st = extract_impl(plan, d_raw, raw_len, d_rec_off, n_records, hip_stream, out, reg, g, &whole_fits);
+  if (!whole_fits) return st;
+  const fbx_status again =
+      extract_impl(plan, d_raw, raw_len, d_rec_off, n_records, hip_stream, out, reg, geometry(*plan, raw_len, n_records, false));
+  if (again == FBX_OK) plan->whole_from = n_records;
+  return again;
 }
 
 // ---- the entry point that allocates nothing

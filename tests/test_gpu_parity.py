@@ -994,3 +994,50 @@ def test_batches_of_few_tiles(cfg, n):
             size = e.required_bytes
     assert_same({s: expand(res.slots[s], n) for s in res.slot_ids}, res, want, f"config{cfg} {n}, tight")
     plan.close()
+
+
+@pytest.mark.parametrize("cfg,n,fewer", [(5, 257, 100), (5, 1000, 300), (3, 2000, 700)])
+def test_workspaces_that_hold_the_tables_of_whole_tiles_only(cfg, n, fewer):
+    """Smaller tiles have larger tables.  A workspace without room for those takes whole tiles, in the call that counts and in
+    one sized from the last call's signs; one that is too small either way is told what whole tiles need, and batches of
+    fewer records still take smaller tiles in it."""
+    import re
+
+    import torch
+    w = W.get(cfg, n)
+    raw, off = w.generate()
+    d_raw, d_off = to_device(raw, off)
+    batch = {m: (d_raw[:int(off[m])], d_off[:m + 1], O.extract(w.spec, raw[:int(off[m])], off[:m + 1])) for m in (n, fewer)}
+
+    def plan_with(size, tile_log2=-1):
+        plan = B.Plan(w.spec)
+        plan.set_option("tile_log2", tile_log2)
+        plan.set_workspace(torch.empty(size, dtype=torch.uint8, device="cuda"))
+        return plan
+
+    def call(plan, m):
+        d, o, want = batch[m]
+        res = plan.extract(d, o)
+        assert_same({s: expand(res.slots[s], m) for s in res.slot_ids}, res, want, f"config{cfg} {m}")
+        return res.arena_high_water, res.tile_launches
+
+    log2 = int(re.search(r"P\.log2T = (\d+)u;", B.Plan(w.spec).kernel_source(raw.size, n, 1)).group(1))
+    room = 256 << 20
+    plan = plan_with(room)
+    (split, _), (split_margin, _) = call(plan, n), call(plan, n)
+    plan = plan_with(room, log2)
+    (whole, _), (whole_margin, _) = call(plan, n), call(plan, n)
+    fewer_split, _ = call(plan_with(room), fewer)
+    assert whole < min(split, whole_margin) and max(split, whole_margin) < split_margin
+
+    assert call(plan_with(whole), n) == (whole, 2)
+    for size in (split, whole_margin):
+        plan = plan_with(size)
+        first = (split if split <= size else whole, 2)
+        then = (whole_margin, 1) if whole_margin <= size else first
+        assert [call(plan, n) for _ in range(3)] == [first, then, then]
+    plan = plan_with(whole - 128)
+    with pytest.raises(B.FbxError) as e:
+        call(plan, n)
+    assert e.value.status == B.E_NOMEM and e.value.required_bytes == whole
+    assert call(plan, fewer) == (fewer_split, 2)
