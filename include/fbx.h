@@ -214,7 +214,8 @@ fbx_status fbx_plan_info(const fbx_plan* plan, uint32_t* n_ops, uint32_t* n_laye
  *   "tile_log2"    -1: records per tile chosen per call (default); 0..6: 2^value records
  *   "raw_cap"      0: bytes of text a workgroup stages at a time chosen per call (default);
  *                  64..65000: that many
- *   "lds_budget"   LDS bytes per workgroup the tile size is chosen for (default 81920)
+ *   "lds_budget"   LDS bytes per workgroup the tile size is chosen for (default 81920); below the
+ *                  default also the most that lists kept on chip for later operators grow it to
  *   "grid_limit"   0: as many workgroups as run at the same time (default); else at most that
  *   "spin_limit"   polls after which a tile of the one-launch sequence stops waiting for an
  *                  earlier tile's count (default 2^22; 0: it never waits).  A wait that runs out

@@ -23,6 +23,8 @@ uint64_t align_up(uint64_t x, uint64_t a = kAlign) { return (x + a - 1) / a * a;
 
 thread_local std::string g_create_error;
 
+constexpr uint32_t kLdsBudget = 80u * 1024u;  // two workgroups per compute unit
+
 struct Timer {
   hipEvent_t ev[2] = {nullptr, nullptr};
   bool used = false;
@@ -49,7 +51,7 @@ struct fbx_plan {
   int profile = 0;
   int tile_log2 = -1;             // -1: chosen per call
   uint32_t raw_cap = 0;           // 0: chosen per call
-  uint32_t lds_budget = 80u * 1024u;  // two workgroups per compute unit
+  uint32_t lds_budget = kLdsBudget;
   uint32_t dbg = 0;
   uint32_t grid_limit = 0;
   uint32_t spin_limit = 1u << 22;   // polls a tile of the one-launch sequence waits for an earlier tile's count
@@ -216,7 +218,8 @@ void tile_lds_layout(const fbx_plan& p, uint32_t lt, uint64_t want, uint32_t raw
   // workgroups and none of these lists on chip, 1.95 with two and all of them; lists of 64 KB, where two run either
   // way: 0.92 ms without and 0.88 with them for 200,000 records.
   const uint32_t dev_max = tile_max_lds(), groups = p.compile ? std::min(4u, std::max(1u, dev_max / std::max(o, 1u))) : 2u;
-  const uint32_t share = dev_max / groups - 1024u;  // (beside the kernel's own)
+  uint32_t share = dev_max / groups - 1024u;  // (beside the kernel's own)
+  if (p.lds_budget < kLdsBudget) share = std::min(share, p.lds_budget);  // (a budget below the default is the caller's)
   tp.list_cap = p.keeps_roots && o < share ? (share - o) / 16u * 2u : 0u;
   o += 8u * tp.list_cap;
   tp.lds_bytes = o;

@@ -262,3 +262,17 @@ def test_a_batch_that_looks_back_is_not_halved_into_one_that_counts(records, log
         return size
 
     assert [t for t in range(7) if hint(t) == hint(-1)] == [log2]
+
+
+@pytest.mark.parametrize("compiled", [0, 1])
+@pytest.mark.parametrize("budget", [16000, 40000, 60000])
+def test_lists_kept_on_chip_stay_inside_a_smaller_lds_budget(budget, compiled):
+    spec = ("fbx 1\nfields 2\nop a hash slot=0 seed=1 emit=1 field=0 multi=1\nop b hash slot=1 seed=2 emit=1 field=1 multi=1\n"
+            "op x cross slot=2 seed=3 emit=1 a=a b=b\n")
+    plan = B.Plan(spec)
+    plan.set_option("compile", compiled)
+    plan.set_option("lds_budget", budget)
+    text = plan.kernel_source(50 * 10000, 10000, 1)
+    size, lists = (int(re.search(rf"P\.{name} = (\d+)u;", text).group(1)) for name in ("lds_bytes", "list_cap"))
+    assert size <= budget and lists > 0
+    plan.close()
