@@ -264,11 +264,14 @@ bool one_launch_pays(const fbx_plan& p, uint64_t per_record, uint32_t log2T, uin
 // Down to 4 records while there are at most 64 tiles, which a look-back finds in one window (us a call, before and after:
 // 1 to 64 records of the 100-field workload 39 to 43 and 35 to 37, 257 of them 43 and 38, 1,000 of them 44 and 40, where twice
 // as many tiles take 41; 64 and 2,000 of the numeric one 43 and 32, 45 and 39; 16 and 200 with 18 lists 53 and 41, 55 and 43; of
-// the four-layer graph 64, 65 and 61).  Where more look-backs than pay are counted with the tiles as they are, down to 8
-// records and up to a tile a compute unit (1,999 records with 18 lists: 71 and 63; 4 records: 68), but a batch that looks
-// back is not halved into one that counts (24 look-backs, 513 to 1,024 records: 70 with tiles of 16 in one launch, 73
-// with tiles of 8 counted; 20 short lists, 700 and 1,500 records: 40 and 47, 46 and 50).  Kernels compiled for the plan
-// are compiled for one size, and in arrival order the caller is told it: there tiles stay as they are.
+// the four-layer graph 64, 65 and 61).  Plans that never look back gain nothing below that line and lose beyond it (16
+// single-valued fields, 1,000 records in tiles of 64, 32, 16, 8: 26.8, 26.8, 26.4, 27.0; 4,096: 27.6, 28.0, 29.1, 34.1).
+// Where more look-backs than pay are counted with the tiles as they are, down to 8 records and up to a tile a compute
+// unit (1,999 records with 18 lists: 71 and 63; 4 records: 68), but a batch that looks back is not halved into one that
+// counts (24 look-backs, 513 to 1,024 records: 70 with tiles of 16 in one launch, 73 with tiles of 8 counted; 20 short
+// lists, 700 and 1,500 records: 40 and 47, 46 and 50).  Tiles stay as they are in arrival order, where the caller is told
+// their size, and with compile=1: its kernels are compiled for one size of tile, and calls that run the kernel for any plan
+// all the same (static ones) keep to that size.
 bool few_tiles(const fbx_plan& p, uint64_t raw_len, uint64_t n_records, TileParams& tp) {
   if (p.tile_log2 >= 0 || p.compile || p.placement || !n_records) return false;
   const uint64_t per_record = raw_len / n_records, avg = (raw_len + n_records - 1) / n_records;

@@ -983,16 +983,17 @@ def test_batches_of_few_tiles(cfg, n):
     plan = B.Plan(w.spec)
     size = 512 << 10
     for _ in range(5):  # (what is asked for when a call is refused has to be enough in the end, and stay enough)
-        small = torch.empty(size, dtype=torch.uint8, device="cuda")
-        plan.set_workspace(small)
+        plan.set_workspace(torch.empty(size, dtype=torch.uint8, device="cuda"))
         try:
-            for _ in range(3):
+            for call in range(3):
                 res = plan.extract(d_raw, d_off)
+                assert_same({s: expand(res.slots[s], n) for s in res.slot_ids}, res, want, f"config{cfg} {n}, tight, call {call}")
             break
         except B.FbxError as e:
             assert e.status == B.E_NOMEM and e.required_bytes > size
             size = e.required_bytes
-    assert_same({s: expand(res.slots[s], n) for s in res.slot_ids}, res, want, f"config{cfg} {n}, tight")
+    else:
+        pytest.fail(f"a workspace of {size} bytes is refused, as were the ones asked for before it")
     plan.close()
 
 
@@ -1041,3 +1042,19 @@ def test_workspaces_that_hold_the_tables_of_whole_tiles_only(cfg, n, fewer):
         call(plan, n)
     assert e.value.status == B.E_NOMEM and e.value.required_bytes == whole
     assert call(plan, fewer) == (fewer_split, 2)
+
+
+@pytest.mark.parametrize("n", range(1, 9))
+@pytest.mark.parametrize("options", [{}, {"compile": 1}, {"tile_log2": 5, "raw_cap": 1024}])
+def test_ngrams_that_later_operators_read(options, n):
+    """Grams of one word and of two, of fields shorter than a gram, of exactly one, of a wavefront's lanes and of one more, where all,
+    some or none of the lists stay on chip, at every place of a word."""
+    spec = (f"fbx 1\nfields 3\nop a ngram slot=0 seed=1 emit=1 field=0 n={n}\nop b ngram slot=1 seed=2 emit=0 field=2 n={n}\n"
+            f"op c ngram slot=2 seed=3 emit=1 field=1 n={n}\nop d concat slot=3 emit=1 a=a b=b\nop e cross slot=4 seed=4 emit=1 a=c b=b\n")
+    rng = random.Random(n)
+    text = lambda k: "".join(rng.choice("abcdef,") for _ in range(k))
+    recs = []
+    for i in range(130):
+        k = rng.choice([0, 1, n - 1, n, n + 1, 20, 62 + n, 63 + n, 64 + n, 128 + n])
+        recs.append(f"{text(k)}\t{text(i % 7 + n - 1)}\t{text(rng.choice([n - 1, n, n + 3]))}\n".encode())
+    check(spec, *_cat(recs), options, label=f"{options} {n}")
