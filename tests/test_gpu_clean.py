@@ -101,6 +101,27 @@ def test_clean_tiles_of_every_shape(F, n, long_every, n_ops, width, keep):
     assert bool((d_out[res.out_len:] == 0x21).all()), "written beyond the cleaned text"
 
 
+@pytest.mark.parametrize("n", [1, 3, 64, 65, 127, 500])
+@pytest.mark.parametrize("kept", ["none", "first", "last", "every_fourth", "runs", "all"])
+def test_clean_keeps_few_many_or_all_records_of_a_tile(n, kept):
+    """Which records of a tile of 64 stay, with records of no bytes, of less than a chunk, and of more than 64 chunks."""
+    rng = random.Random(n)
+    stays = {"none": lambda i: False, "first": lambda i: i % 64 == 0, "last": lambda i: i % 64 == 63 or i == n - 1, "every_fourth": lambda i: i % 4 == 2,
+             "runs": lambda i: i // 5 % 3 == 0, "all": lambda i: True}[kept]
+    recs = [b"" if kept == "all" and i % 7 == 3 else
+            (("k" if stays(i) else "d") + "x" * (rng.randint(1000, 1400) if i % 40 == 9 else rng.randint(0, 20)) + "\t" + "y" * rng.randint(0, 3) + "\n").encode()
+            for i in range(n)]
+    spec = "fbxclean 1\nfields 2\nfill field=1 value=6e6f6e65\n" + ("" if kept == "all" else "keep field=0 prefix=6b\n")
+    raw, off = _cat(recs)
+    want_raw, want_off = C.clean(spec, raw, off)
+    for misalign in (0, 7):
+        res, d_out, d_out_off = _gpu_clean(spec, raw, off, out_cap=want_raw.size + 64, misalign=misalign)
+        assert res.n_kept == len(want_off) - 1 and res.out_len == want_raw.size
+        assert np.array_equal(d_out_off[:res.n_kept + 1].cpu().numpy().view(np.uint64), want_off)
+        assert np.array_equal(d_out[:res.out_len].cpu().numpy(), want_raw)
+        assert bool((d_out[res.out_len:] == 0x21).all()), "written beyond the cleaned text"
+
+
 def test_a_scratch_buffer_without_room_for_segments_still_does():
     """24 bytes a record and the tables: too little to keep segments, enough for the kernel that keeps none."""
     import torch
