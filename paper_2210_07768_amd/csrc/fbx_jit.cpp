@@ -134,6 +134,9 @@ std::string program_text(const TileParams& P, int mode, const PlanHost& h, uint3
   os << "#define FBX_FIXED_COMMAS " << P.commas << "\n";
   os << "#define FBX_FIXED_MODE " << mode << "\n#define FBX_FIXED_NAME fbx_tile_fixed_" << mode << "\n#define FBX_FIXED_ASSIGN";
   FBX_TILE_FIXED_FIELDS(FBX_FIELD_ASSIGN)
+  // How tokens are hashed (hash_span): whether a field takes more than about 11 bytes of text on average (the section is
+  // five quarters of what a tile's records take, rounded up).
+  os << "\n#define FBX_LONG_TOKENS " << (P.raw_cap > uint64_t(14u * P.n_fields) << P.log2T ? 1 : 0);
   // wavefronts per SIMD the kernel must leave registers for: as many workgroups as the LDS admits
   const uint32_t groups = std::max(1u, std::min(4u, tile_max_lds() / std::max(P.lds_bytes, 1u)));
   os << "\n#define FBX_FIXED_WAVES " << std::max(4u, groups * (threads / 64u) / 4u);

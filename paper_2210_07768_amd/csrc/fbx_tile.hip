@@ -59,6 +59,10 @@
 #ifndef FBX_EXP
 #define FBX_EXP 0
 #endif
+// How tokens are hashed (hash_span): 1 for long and mixed ones, 0 for short ones (kernels compiled for a plan only).
+#ifndef FBX_LONG_TOKENS
+#define FBX_LONG_TOKENS 1
+#endif
 
 
 namespace fbx {
@@ -383,11 +387,15 @@ __device__ __forceinline__ uint64_t fnv_step(uint64_t h, uint32_t w) {  // byte 
 }
 template <class Src>
 __device__ __forceinline__ uint64_t hash_span(const Src& src, uint32_t s, uint32_t e, uint64_t h) {
-  if constexpr (Src::kTable) {
+  if constexpr (Src::kTable && FBX_LONG_TOKENS) {
     // Staged text: the odd bytes first (1 to 8 of them), then whole windows of eight.  What bounds this is vector issue, four
-    // instructions a byte and one that asks whether there is a next byte; whole windows need not ask, and tokens of up to
-    // eight bytes run as before.  (1,000,003 records of 16 single-valued fields of 4 to 32 bytes: 246 us a call with the odd
-    // bytes last and every byte asked for, 233 this way; 3 to 8 bytes a token: the same.)
+    // instructions a byte and one that asks whether there is a next byte; whole windows need not ask.  Where the longest token
+    // of a wavefront is shorter than about 13 bytes, eight odd bytes of one lane and eight whole ones of another take longer
+    // than asking for every byte of the longest, which kernels compiled for the plan then do.  (us a call with every byte
+    // asked for and this way, 300,000 records of 16 fields: 6 to 9 bytes 56 and 60, 4 to 10 56 and 60, 4 to 12 58 and 60, 4 to
+    // 14 60 and 61, 4 to 16 61 and 61, 4 to 24 71 and 69, 4 to 32 80 and 76; 200,000 records of long lists 969 and 870.  The kernel
+    // for any plan: 6 to 9 bytes 93 and 93, 4 to 8 89 and 86, 4 to 32 121 and 106.  Asking each wavefront for its longest
+    // token costs the 100-field workload 1.3 %.)
     if (s >= e) return h;
     const uint32_t n = ((e - s - 1u) & 7u) + 1u;
     uint32_t x0, x1;

@@ -1058,3 +1058,23 @@ def test_ngrams_that_later_operators_read(options, n):
         k = rng.choice([0, 1, n - 1, n, n + 1, 20, 62 + n, 63 + n, 64 + n, 128 + n])
         recs.append(f"{text(k)}\t{text(i % 7 + n - 1)}\t{text(rng.choice([n - 1, n, n + 3]))}\n".encode())
     check(spec, *_cat(recs), options, label=f"{options} {n}")
+
+
+@pytest.mark.parametrize("pad,long_tokens", [(0, 0), (40, 1)])
+def test_tokens_of_every_length_in_kernels_compiled_for_short_and_long_ones(pad, long_tokens):
+    """Tokens of no bytes to five windows of eight, each at every place of a word, beside ones of other lengths."""
+    spec = ("fbx 1\nfields 4\nop a hash slot=0 seed=1 emit=1 field=0 multi=0\nop b hash slot=1 seed=2 emit=1 field=1 multi=1\n"
+            "op c filter slot=2 seed=3 emit=1 field=1 multi=1 prefix=61\nop d hash slot=3 seed=4 emit=1 field=2 multi=0\n"
+            "op x cross slot=4 seed=5 emit=1 a=b b=c\n")
+    rng = random.Random(pad)
+    text = lambda k: "".join(rng.choice("abcdefgh") for _ in range(k))
+    recs = []
+    for i in range(410):
+        items = ",".join(text(rng.choice([0, 1, 7, 8, 9, 12, 16, 17])) for _ in range(i % 3))
+        recs.append(f"{text(i % 41 if i % 4 == 0 else i % 9)}\t{items}\t{text(rng.choice([0, 3, 8, 11, 12, 13]))}\t{text(pad)}\n".encode())
+    raw, off = _cat(recs)
+    plan = B.Plan(spec)
+    plan.set_option("compile", 1)
+    assert f"#define FBX_LONG_TOKENS {long_tokens}\n" in plan.kernel_source(len(raw), len(recs), 1)
+    plan.close()
+    check(spec, raw, off, {"compile": 1}, label=f"pad {pad}")
