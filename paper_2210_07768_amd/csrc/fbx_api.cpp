@@ -184,15 +184,16 @@ void tile_lds_layout(const fbx_plan& p, uint32_t lt, uint64_t want, uint32_t raw
   tp.o_rows = o; o = round16(o + 2ull * T * tp.row_stride);
   tp.o_raw = o; o = round16(o + kRawPad + uint64_t(raw_cap) + 32u);
   tp.o_stage = o; o = round16(o + 8ull * T * h.n_stage);
-  tp.o_cnt = o; o = round16(o + 4ull * T * h.n_ragged);
-  tp.o_start = o; o = round16(o + 4ull * T * h.n_ragged);
+  const uint64_t rows = h.n_ragged + h.n_const, later = h.ops.size() - h.tile_list_begin[TL_LAYER];
+  tp.o_cnt = o; o = round16(o + 4ull * T * rows);
+  tp.o_start = o; o = round16(o + 4ull * T * rows);
   tp.o_run = o; o = round16(o + 4ull * h.n_ragged);
-  tp.o_base = o; o = round16(o + 8ull * h.n_ragged);
+  tp.o_base = o; o = round16(o + 8ull * rows);
   tp.o_tot = o; o = round16(o + 4ull * h.n_ragged);
   tp.o_cap = o; o = round16(o + 8ull * h.n_ragged);
-  tp.o_gfirst = o; o = round16(o + (tp.n_gen ? 4ull * h.ops.size() : 0ull));
+  tp.o_gfirst = o; o = round16(o + (tp.n_gen ? 8ull * later : 0ull));
   tp.o_gtot = o; o = round16(o + (tp.n_gen ? 4ull * (h.n_layers + 1u) : 0ull));
-  tp.o_ioff = o; o = round16(o + 4ull * (tp.n_mh + 1));
+  tp.o_ioff = o; o = round16(o + 8ull * (tp.n_mh + 1));
   // Commas.  Finding them along with the tabs classifies every byte of the text twice, whatever the field; finding them field
   // by field is a phase of its own and, of filters, a walk from item to item when they are written.
   // Hashes only: along with the tabs when the fields that are lists would get one lane each of a workgroup (24 list items a

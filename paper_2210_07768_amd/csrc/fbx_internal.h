@@ -17,7 +17,8 @@ enum OpFlags : uint32_t {
   F_MULTI = 1u,
   F_EMIT = 2u,
   F_STREAM = 4u,  // tile kernel: no later operator reads the signs from memory (they are only the caller's)
-  F_NEVER = 8u    // a multi-valued filter whose prefix holds a comma: no token can begin with it
+  F_NEVER = 8u,   // a multi-valued filter whose prefix holds a comma: no token can begin with it
+  F_A_FAR = 16u, F_B_FAR = 32u  // tile kernel, on chip only: the list that a list operator reads as input a / b is not on chip in this pass
 };
 
 // Device-visible operator descriptor (64 bytes).  Filled once at plan time.
@@ -31,7 +32,8 @@ struct OpDesc {
   uint32_t aux_len;  // #bounds, prefix length, or n-gram width
   uint64_t key;      // hash/ngram/filter: FNV state after the 8 seed bytes;
                      // cross/bucket: slot key mix64(seed)
-  uint32_t rag_row;  // row among ragged operators (count tables), 0xffffffff if fixed
+  uint32_t rag_row;  // row among ragged operators (count tables); fixed arity: a row of constants behind those (PlanHost::n_const)
+                     // where a list operator of the tile kernel is or reads it, else 0xffffffff
   uint32_t layer;    // 1-based
   uint32_t placed;   // the operator whose arrays are placed in this one's turn when nothing is released: emitted
                      // operators first, then layer by layer
@@ -124,6 +126,7 @@ struct PlanHost {
   uint32_t n_fields = 0;
   uint32_t n_layers = 0;
   uint32_t n_ragged = 0;
+  uint32_t n_const = 0;                 // distinct arities among the fixed-arity operators that list operators are or read
   std::vector<HostOp> ops;             // spec order
   std::vector<uint32_t> layer_ops;     // operator indices grouped by layer
   std::vector<uint32_t> layer_begin;   // n_layers + 1 entries into layer_ops

@@ -364,6 +364,24 @@ fbx_status parse_plan(const char* spec, size_t len, PlanHost& plan, std::string&
       else lists[TL_LAYER + 2 * (d.layer - 2) + (single ? 0 : 1)].push_back(i);
     }
   }
+  // List operators look every input's and every record's place up in the tables of the ragged operators: what has a fixed
+  // arity there has a row of constants, one for each arity that occurs.
+  {
+    std::vector<uint32_t> arities;
+    auto constant = [&](OpDesc& d) {
+      if (!d.arity) return;
+      const size_t k = static_cast<size_t>(std::find(arities.begin(), arities.end(), d.arity) - arities.begin());
+      if (k == arities.size()) arities.push_back(d.arity);
+      d.rag_row = plan.n_ragged + static_cast<uint32_t>(k);
+    };
+    for (uint32_t layer = 2; layer <= plan.n_layers; ++layer)
+      for (uint32_t i : lists[TL_LAYER + 2 * (layer - 2) + 1]) {
+        constant(plan.ops[i].d);
+        constant(plan.ops[plan.ops[i].d.a].d);
+        constant(plan.ops[plan.ops[i].d.b].d);
+      }
+    plan.n_const = static_cast<uint32_t>(arities.size());
+  }
   // neighbouring lanes run neighbouring list entries: keep like with like.  Multi-valued hashes
   // come first, then the other multi-valued operators, then the single-valued filters.
   auto root_class = [&](uint32_t x) {

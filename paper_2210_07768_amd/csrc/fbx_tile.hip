@@ -138,6 +138,10 @@ __device__ __forceinline__ uint32_t fixed_rnr_head(uint32_t i) {
 }
 #endif
 
+// Where an operator's signs start among those of all operators of its list in this pass, and the same less its signs of the
+// tile's earlier passes: where its rows of `start` count from.
+struct ListFirst { uint32_t sign, base; };
+
 struct Sh {
   uint64_t* off;    // [2][T + 1] record offsets of this tile and of the next one
   uint32_t* rs;     // [T] LDS position of the first byte of a staged record
@@ -145,15 +149,15 @@ struct Sh {
   uint16_t* rows;   // [T][row_stride]: row[0] = rs - 1, row[1 + k] = end of field k
   uint8_t* raw;     // staged text; byte 0 of the staged range sits at kRawPad + (address & 15)
   uint64_t* stage;  // [n_stage][T] single signs kept for later layers
-  uint32_t* cnt;    // [n_ragged][T] signs of a ragged operator per record
-  uint32_t* start;  // [n_ragged][T] their first position, relative to the tile's base
+  uint32_t* cnt;    // [n_ragged][T] signs of a ragged operator per record; behind them [n_const][T] those of fixed-arity operators
+  uint32_t* start;  // [n_ragged][T] their first position, relative to the tile's base; behind them [n_const][T] relative to the pass
   uint32_t* run;    // [n_ragged] signs of the tile's earlier passes
-  uint64_t* base;   // [n_ragged] the tile's base in the operator's values array
+  uint64_t* base;   // [n_ragged] the tile's base in the operator's values array; behind them [n_const] the pass's
   uint32_t* tot;    // [n_ragged] signs of this pass
   uint64_t* cap;    // [n_ragged] signs the operator's array has room for (one-launch mode)
-  uint32_t* gfirst; // [n_ops] list operators of layers >= 2, by program position: first sign among the signs of the layer's list operators in this pass
+  ListFirst* gfirst; // list operators of layers >= 2, by program position from the first list of layer 2 on
   uint32_t* gtot;   // [n_layers + 1] signs of all list operators of a layer in this pass
-  uint32_t* ioff;   // [n_mh + 1] first item of every multi-valued hash among the pass's items
+  ListFirst* ioff;  // [n_mh + 1] multi-valued hashes; behind them the number of all their items
   uint16_t* ctab;   // comma positions: [T][comma_cap + 2] a record's first ones (two more, so that neighbouring records
                     // start in different banks), or [n_mh][T][kItemCap] those of a multi-valued hash's field
   uint16_t* ctot;   // [T] how many the record has (kCommasWithTabs)
@@ -192,9 +196,9 @@ __device__ __forceinline__ Sh views(const TileParams& P) {
   s.base = reinterpret_cast<uint64_t*>(smem + P.o_base);
   s.tot = reinterpret_cast<uint32_t*>(smem + P.o_tot);
   s.cap = reinterpret_cast<uint64_t*>(smem + P.o_cap);
-  s.gfirst = reinterpret_cast<uint32_t*>(smem + P.o_gfirst);
+  s.gfirst = reinterpret_cast<ListFirst*>(smem + P.o_gfirst);
   s.gtot = reinterpret_cast<uint32_t*>(smem + P.o_gtot);
-  s.ioff = reinterpret_cast<uint32_t*>(smem + P.o_ioff);
+  s.ioff = reinterpret_cast<ListFirst*>(smem + P.o_ioff);
   s.ctab = reinterpret_cast<uint16_t*>(smem + P.o_ctab);
   s.ctot = reinterpret_cast<uint16_t*>(smem + P.o_ctot);
   s.cfirst = reinterpret_cast<uint16_t*>(smem + P.o_cfirst);
@@ -697,6 +701,17 @@ __device__ __forceinline__ uint32_t group_incl_scan(uint32_t v, uint32_t T) {
   return group_prefix(v, 31u - (uint32_t)__clz((int)T), lane_id() & (T - 1u));
 }
 
+// Inclusive running maximum over the 64 lanes of a wavefront; every lane must call it.
+__device__ __forceinline__ uint32_t wave_prefix_max(uint32_t v) {
+  v = max(v, row_shr<1>(v));
+  v = max(v, row_shr<2>(v));
+  v = max(v, row_shr<4>(v));
+  v = max(v, row_shr<8>(v));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));  // row_bcast:15 into rows 1 and 3
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
 constexpr uint32_t kWaves = kTileThreads / 64;
 
 // Work counters of a pass (cleared between passes): s_ctr[0] hands out the
@@ -750,7 +765,8 @@ __device__ __forceinline__ void store_sign(G64 at, uint64_t v, bool stream) {
   else *at = v;
 }
 
-template <class Src>
+// PAIRS: whether a multi-valued hash's items are found as list operators' signs are (item_unit).
+template <class Src, bool PAIRS>
 struct Pass {
   const TileParams& P;
   const Sh& sh;
@@ -1076,52 +1092,106 @@ struct Pass {
     uint64_t at = first;
     ragged_root_emit(src, *d, sh.aux, r, s, e, [&](uint64_t v) { put_list(*d, pos++, at++, v); }, malformed);
   }
+  // The signs of a list of operators in this pass, operator after operator and record after record, form one index space; a
+  // wavefront takes the 64 from q0 on.  Returns the (operator, record) pair that the lane's sign belongs to, operator * T +
+  // record (of lanes beyond the last sign: any).  The operator of q0 is found with one look at all first signs; from its first pair on 64 pairs at a time
+  // say where they start, each hands its number to the lane of that sign (a pair without signs starts where the next one
+  // does, and of several that write to a lane the highest-numbered one wins), and a running maximum fills the lanes in between.
+  // (What bounds a unit is the chain of look-ups and its vector instructions.  Against two binary searches a sign and fields of the
+  // programs looked through for every input: 4,000,000 records of the 100-field workload, 4 lists, 4,265 -> 4,130 us a call;
+  // 200,000 of 18 lists and 6 crosses of two of them 868 -> 817; 250,000 of the four-layer graph 1,618 -> 1,562.)
+  // TODO-FIGURES
+  __device__ __forceinline__ uint32_t pair_at(const OpProg* ops, const ListFirst* first, uint32_t m, uint32_t q0) const {
+    const uint32_t lane = lane_id();
+    uint32_t lo = 0;
+    if (m <= 64u) {
+      const uint32_t f = lane < m ? first[lane].sign : ~0u;
+      lo = (uint32_t)__popcll(__ballot(f <= q0)) - 1u;
+    } else {
+      uint32_t hi = m - 1u;
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1u) >> 1;
+        if (first[mid].sign <= q0) lo = mid; else hi = mid - 1u;
+      }
+      lo = __builtin_amdgcn_readfirstlane(lo);
+    }
+    uint32_t pair = 0;  // (plus one)
+    for (uint32_t w = lo << P.log2T;; w += 64u) {
+      const uint32_t i = (w + lane) >> P.log2T;
+      uint32_t s = 64u;
+      if (i < m) {
+        const uint32_t at = first[i].base + sh.start[ops[i].rag_row * T + min((w + lane) & (T - 1u), nb)];  // (records beyond the pass start at its end)
+        s = at > q0 ? min(at - q0, 64u) : 0u;
+      }
+      const uint32_t in = (uint32_t)__popcll(__ballot(s < 64u));  // (starts only grow: the first ones)
+      // (a pair that starts beyond the unit names the last one inside it, which is what the last lane is to know)
+      const uint32_t got = (uint32_t)__builtin_amdgcn_ds_permute((int)(4u * min(s, 63u)), (int)(s < 64u ? w + lane + 1u : w + in));
+      pair = max(pair, got);
+      if (in < 64u) break;
+    }
+    return wave_prefix_max(pair) - 1u;
+  }
   // Multi-valued hashes (the first P.n_mh entries of the ragged root list): lanes
   // are items.  All items of the pass, operator after operator and record after
-  // record, form one index space; a lane finds its operator and record by two
-  // small searches, its item's bounds in the comma table, and writes the sign to
+  // record, form one index space; a lane finds its operator and record (pair_at),
+  // its item's bounds in the comma table, and writes the sign to
   // the item's own position: neighbouring lanes write neighbouring signs.
   __device__ __forceinline__ void item_offsets() {  // one wavefront, after the positions are known
     const uint32_t lane = lane_id();
     uint32_t carry = 0;
     for (uint32_t i0 = 0; i0 < P.n_mh; i0 += 64u) {
       const uint32_t i = i0 + lane;
-      uint32_t v = 0;
-      if (i < P.n_mh) v = sh.tot[sh.prog[sh.lbeg(TL_RAGROOT) + i].rag_row];
+      uint32_t v = 0, before = 0;
+      if (i < P.n_mh) {
+        const uint32_t row = sh.prog[sh.lbeg(TL_RAGROOT) + i].rag_row;
+        v = sh.tot[row];
+        before = sh.run[row] - v;  // items of the tile's earlier passes
+      }
       uint32_t incl = v;
       for (uint32_t d = 1; d < 64u; d <<= 1) {
         const uint32_t t = __shfl_up(incl, d, 64);
         if (lane >= d) incl += t;
       }
-      if (i < P.n_mh) sh.ioff[i] = carry + incl - v;
+      if (i < P.n_mh) sh.ioff[i] = ListFirst{carry + incl - v, carry + incl - v - before};
       carry += __shfl(incl, 63, 64);
     }
-    if (lane == 0) sh.ioff[P.n_mh] = carry;
+    if (lane == 0) sh.ioff[P.n_mh].sign = carry;
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   }
-  __device__ __forceinline__ uint32_t item_units() const { return (sh.ioff[P.n_mh] + 63u) >> 6; }
+  __device__ __forceinline__ uint32_t item_units() const { return (sh.ioff[P.n_mh].sign + 63u) >> 6; }
   __device__ __forceinline__ void item_unit(uint32_t u) {
-    const uint32_t q = u * 64u + lane_id();
-    if (q >= sh.ioff[P.n_mh]) return;
-    // operator: the last one whose first item is <= q
-    uint32_t lo = 0, hi = P.n_mh - 1u;
-    while (lo < hi) {
-      const uint32_t mid = (lo + hi + 1u) >> 1;
-      if (sh.ioff[mid] <= q) lo = mid; else hi = mid - 1u;
+    const uint32_t q0 = u * 64u, q = q0 + lane_id();
+    const OpProg* list_ops = sh.prog + sh.lbeg(TL_RAGROOT);
+    uint32_t i, rr;
+    if constexpr (PAIRS) {
+      const uint32_t pair = pair_at(list_ops, sh.ioff, P.n_mh, q0);
+      if (q >= sh.ioff[P.n_mh].sign) return;
+      i = pair >> P.log2T;
+      rr = pair & (T - 1u);
+    } else {
+      // (The kernel for any plan, where few lists are read by nothing: two searches, the operator's and the record's.  What
+      // pair_at keeps alive costs it more than it saves: 200,000 records of the 100-field workload 320 us a call with it, 309
+      // without; kernels compiled for the plan 4,130 and 4,270 for 4,000,000.)
+      if (q >= sh.ioff[P.n_mh].sign) return;
+      uint32_t lo = 0, hi = P.n_mh - 1u;
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1u) >> 1;
+        if (sh.ioff[mid].sign <= q) lo = mid; else hi = mid - 1u;
+      }
+      i = lo;
+      const uint32_t* st = sh.start + list_ops[i].rag_row * T;
+      const uint32_t at = q - sh.ioff[i].base;
+      lo = 0; hi = nb - 1u;  // (every record has at least one item)
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1u) >> 1;
+        if (st[mid] <= at) lo = mid; else hi = mid - 1u;
+      }
+      rr = lo;
     }
-    const uint32_t i = lo;
-    const OpProg& d = sh.prog[sh.lbeg(TL_RAGROOT) + i];
+    const OpProg& d = list_ops[i];
     const uint32_t row = d.rag_row;
-    const uint32_t before = sh.run[row] - sh.tot[row];     // signs of the tile's earlier passes
-    const uint32_t pos = before + (q - sh.ioff[i]);         // the item's position inside the tile
-    // record: the last one whose first position is <= pos (every record has at least one item)
-    const uint32_t* st = sh.start + row * T;
-    lo = 0; hi = nb - 1u;
-    while (lo < hi) {
-      const uint32_t mid = (lo + hi + 1u) >> 1;
-      if (st[mid] <= pos) lo = mid; else hi = mid - 1u;
-    }
-    const uint32_t rr = lo, j = pos - st[rr], cnt = sh.cnt[row * T + rr];
+    const uint32_t pos = q - sh.ioff[i].base;  // the item's position inside the tile
+    const uint32_t j = pos - sh.start[row * T + rr], cnt = sh.cnt[row * T + rr];
     uint32_t s, e;
     src.span(rr, d.field, s, e);
     // the item's bounds: of the positions that are kept, then comma by comma from the last of them on
@@ -1328,28 +1398,51 @@ struct Pass {
   // the ragged operators to lanes, one (operator, record) each.
   __device__ __forceinline__ uint32_t gen_total(const OpProg& d) const { return d.arity ? d.arity * nb : sh.tot[d.rag_row]; }
   __device__ __forceinline__ uint32_t gen_list(uint32_t layer) const { return TL_LAYER + 2u * (layer - 2u) + 1u; }
-  // one wavefront, after the positions are known: where every list operator's signs start
+  // one wavefront, after the positions are known: where every list operator's signs start, and where its inputs lie
   __device__ __forceinline__ void gen_offsets() {
-    const uint32_t lane = lane_id();
+    const uint32_t lane = lane_id(), first_later = sh.lbeg(TL_LAYER);
     for (uint32_t layer = 2; layer <= P.n_layers; ++layer) {
       const uint32_t lb = sh.lbeg(gen_list(layer)), m = sh.lbeg(gen_list(layer) + 1u) - lb;
       uint32_t carry = 0;
       for (uint32_t i0 = 0; i0 < m; i0 += 64u) {
         const uint32_t i = i0 + lane;
-        const uint32_t v = i < m ? gen_total(sh.prog[lb + i]) : 0u;
+        uint32_t v = 0, before = 0;
+        if (i < m) {
+          const OpProg& d = sh.prog[lb + i];
+          v = gen_total(d);
+          if (!d.arity) before = sh.run[d.rag_row] - v;
+          else sh.base[d.rag_row] = g_first * d.arity;
+        }
         const uint32_t incl = group_prefix(v, 6u, lane);
-        if (i < m) sh.gfirst[lb + i] = carry + incl - v;
+        if (i < m) sh.gfirst[lb - first_later + i] = ListFirst{carry + incl - v, carry + incl - v - before};
         carry += __shfl(incl, 63, 64);
       }
       if (lane == 0) sh.gtot[layer] = carry;
     }
     keep_lists();
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    // (kept in words of the program that such operators have no other use for)
+    for (uint32_t layer = 2; layer <= P.n_layers; ++layer) {
+      const uint32_t lb = sh.lbeg(gen_list(layer)), m = sh.lbeg(gen_list(layer) + 1u) - lb;
+      for (uint32_t i = lane; i < m; i += 64u) {
+        OpProg& d = const_cast<OpProg&>(sh.prog[lb + i]);
+        const OpProg &a = sh.prog[d.a], &b = sh.prog[d.b];
+        d.aux_off = a.rag_row << P.log2T | (b.rag_row << P.log2T) << 16;  // (what two tables of four bytes an entry leave room for in LDS stays below 2^16 entries)
+        d.aux_len = input_word(a);
+        d.field = input_word(b);
+        d.flags = (d.flags & ~(uint32_t)(F_A_FAR | F_B_FAR)) | (a.stage == kNoRow ? F_A_FAR : 0u) | (b.stage == kNoRow ? F_B_FAR : 0u);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  }
+  // the word of LDS at which an input's sign of place 0 (as its row of `start` counts places) lies; only where it is on chip
+  __device__ __forceinline__ uint32_t input_word(const OpProg& d) const {
+    return d.arity == 1u ? (P.o_stage >> 3) + d.stage * T : d.stage;
   }
   // Where the lists that later operators read lie on chip, operator after operator: OpProg::stage becomes the word of LDS at
   // which the tile's sign 0 would lie (its signs before this pass have no place).  Lists of layer 1, and those made
-  // along with them, go to a section of their own; those of later layers to where the text was, which nobody reads any
-  // more by then.  Room is given in the order of the work lists, whether a list fits or not: from the first that does not on,
+  // along with them, go to a section of their own, or behind the pass's text where its section has more room left (a fifth
+  // of it on average); those of later layers to where the text was, which nobody reads any more by then.  Room is given in the order of the work lists, whether a list fits or not: from the first that does not on,
   // all of a section's lists stay in memory only.
   // (Where all inputs are read back from memory, a unit waits for them and, loads and stores being counted together, for the
   // signs of the unit before.  200,000 records of 18 lists and 12 crosses of two of them: 0.92 against 0.88 ms a call.)
@@ -1357,6 +1450,10 @@ struct Pass {
     const uint32_t lane = lane_id();
     uint32_t used = 0;
     bool later = false;
+    const uint32_t all = (kRawPad + P.raw_cap) >> 3;               // words of the text's section
+    uint32_t text = 0;                                             // those that hold the pass's text
+    if constexpr (Src::kTable) text = (sh.re[nb - 1u] + 7u) >> 3;  // (bytes behind it are read with its last ones, and of no account)
+    const bool tail = all - text > P.list_cap;
     for (uint32_t i0 = sh.lbeg(TL_RAGROOT); i0 < P.n_ops;) {
       const uint32_t end = later ? P.n_ops : sh.lbeg(TL_LAYER);
       const uint32_t i = i0 + lane;
@@ -1369,8 +1466,8 @@ struct Pass {
         }
       }
       const uint32_t incl = group_prefix(n, 6u, lane);
-      const uint32_t first = later ? P.o_raw >> 3 : P.o_lists >> 3;
-      const uint32_t room = later ? (kRawPad + P.raw_cap) >> 3 : P.list_cap;
+      const uint32_t first = later ? P.o_raw >> 3 : (tail ? (P.o_raw >> 3) + text : P.o_lists >> 3);
+      const uint32_t room = later ? (tail ? text : all) : (tail ? all - text : P.list_cap);
       if (n) const_cast<OpProg*>(sh.prog)[i].stage = used + incl <= room ? first + used + incl - n - before : kNoRow;
       used = min(used + __shfl(incl, 63, 64), 1u << 24);
       i0 += 64u;
@@ -1386,37 +1483,10 @@ struct Pass {
     else if (r >= b) ++x;
     return x;
   }
-  // The last record of the pass whose first position in a ragged row is <= pos: the one that has the sign there.
-  __device__ __forceinline__ uint32_t record_at(uint32_t row, uint32_t pos) const {
-    const uint32_t* st = sh.start + row * T;
-#ifdef FBX_FIXED_MODE
-    // Few records: all of them at once instead of one look-up after the other (those beyond nb start at the end).  Only where
-    // the tile size is a literal: a kernel that holds both ways is slower for all plans (3,000,000 records of the
-    // 100-field workload 4.15 against 3.77 ms, 1,000,000 of the numeric one 0.81 against 0.76).
-    if (P.log2T <= 3u) {
-      uint32_t n = 0;
-#pragma unroll
-      for (uint32_t k = 1; k < 8u; ++k)
-        if (k < T) n += st[k] <= pos ? 1u : 0u;
-      return n;
-    }
-#endif
-    uint32_t lo = 0, hi = nb - 1u;
-    while (lo < hi) {
-      const uint32_t mid = (lo + hi + 1u) >> 1;
-      if (st[mid] <= pos) lo = mid; else hi = mid - 1u;
-    }
-    return lo;
-  }
-  // sign x of record rr of an earlier operator (single signs from the on-chip table, lists from LDS where they
-  // were kept, else from the arrays this workgroup wrote before the layer barrier)
-  __device__ __forceinline__ uint64_t input_sign(const OpProg& d, uint32_t rr, uint32_t x) const {
-    const uint32_t pos = (d.arity ? rr * d.arity : sh.start[d.rag_row * T + rr]) + x;
-    if (d.stage != kNoRow) {
-      const uint32_t word = d.arity == 1u ? (P.o_stage >> 3) + d.stage * T + rr : d.stage + pos;
-      return reinterpret_cast<const uint64_t*>(smem)[word];
-    }
-    return gptr<const uint64_t>(d.values)[(d.arity ? g_first * d.arity : sh.base[d.rag_row]) + pos];
+  // sign `at` (a place as the row of `start` counts them) of an earlier operator that is not on chip: from the array that
+  // this workgroup wrote before the layer barrier
+  __device__ __forceinline__ uint64_t far_sign(const OpProg& d, uint32_t at) const {
+    return gptr<const uint64_t>(d.values)[sh.base[d.rag_row] + at];
   }
   __device__ __forceinline__ uint32_t gen_place_units(uint32_t layer) const {
     return (sh.lbeg(gen_list(layer) + 1u) - sh.lbeg(gen_list(layer)) + G - 1u) / G;
@@ -1434,61 +1504,40 @@ struct Pass {
       }
       return;
     }
-    // operator: the last one whose first sign is <= q (operators without signs in this pass share
-    // their first sign with the one after them and are passed over).  Most units lie inside one or two operators: the
-    // wavefront finds the one its first sign belongs to with one look at all their first signs, and goes on from there.
-    const uint32_t lane = lane_id(), q0 = (u - up) * 64u, q = q0 + lane, total = sh.gtot[layer];
-    uint32_t lo = 0, op_first = 0;
-    if (m <= 64u) {
-      const uint32_t f = lane < m ? sh.gfirst[lb + lane] : ~0u;
-      const uint64_t at_or_before = __ballot(f <= q0), inside = __ballot(f > q0 && f <= q0 + 63u && f < total);
-      lo = (uint32_t)__popcll(at_or_before) - 1u;
-      op_first = (uint32_t)__builtin_amdgcn_readlane((int)f, (int)__builtin_amdgcn_readfirstlane(lo));
-      for (uint64_t left = inside; left; left &= left - 1u) {
-        const uint32_t k = (uint32_t)__builtin_ctzll(left);
-        const uint32_t fk = (uint32_t)__builtin_amdgcn_readlane((int)f, (int)k);
-        if (q >= fk) { lo = k; op_first = fk; }
-      }
-    } else {
-      uint32_t hi = m - 1u;
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi + 1u) >> 1;
-        if (sh.gfirst[lb + mid] <= q) lo = mid; else hi = mid - 1u;
-      }
-      op_first = sh.gfirst[lb + lo];
-    }
-    if (q >= total) return;
-    const OpProg& d = sh.prog[lb + lo];
-    const uint32_t qq = q - op_first;  // the sign's number among the operator's signs of this pass
-    const uint32_t row = d.rag_row;
-    uint32_t rr, j, pos;
-    uint64_t at;  // where the sign goes
-    if (d.arity) {
-      rr = small_div(qq, d.arity);
-      j = qq - rr * d.arity;
-      pos = qq;
-      at = g_first * d.arity + qq;
-    } else {
-      pos = sh.run[row] - sh.tot[row] + qq;  // position inside the tile (earlier passes come first)
-      rr = record_at(row, pos);
-      j = pos - sh.start[row * T + rr];
-      at = sh.base[row] + pos;
-    }
+    const uint32_t q0 = (u - up) * 64u, q = q0 + lane_id(), later = lb - sh.lbeg(TL_LAYER);
+    const uint32_t pair = pair_at(sh.prog + lb, sh.gfirst + later, m, q0);
+    if (q >= sh.gtot[layer]) return;
+    const uint32_t i = pair >> P.log2T, rr = pair & (T - 1u);
+    const OpProg& d = sh.prog[lb + i];
+    const uint32_t pos = q - sh.gfirst[later + i].base;  // the sign's position inside the tile (fixed arity: the pass)
+    const uint32_t j = pos - sh.start[d.rag_row * T + rr];
     // A cross takes the sign x of A (outer) and y of B (inner), a concat one sign of either: the look-up of the first is
     // the same code for both.
+    const uint32_t ra = (d.aux_off & 0xffffu) + rr, rb = (d.aux_off >> 16) + rr;
     const bool cross = d.kind == OP_CROSS;
-    const OpProg& dn = sh.prog[cross ? d.b : d.a];
-    const uint32_t n = dn.arity ? dn.arity : sh.cnt[dn.rag_row * T + rr];
-    uint32_t x = j, y = 0, from = d.a;
+    const uint32_t n = sh.cnt[cross ? rb : ra];
+    const uint64_t* lds = reinterpret_cast<const uint64_t*>(smem);
+    uint32_t x = j, y = 0;
+    bool second = false;  // (concat) the sign is one of B's
     if (cross) {
       x = small_div(j, n);
       y = j - x * n;
     } else if (j >= n) {
       x = j - n;
-      from = d.b;
+      second = true;
     }
-    uint64_t v = input_sign(sh.prog[from], rr, x);
-    if (cross) v = mix64(mix64(v + d.key) + input_sign(dn, rr, y));
+    x += sh.start[second ? rb : ra];
+    uint64_t v;
+    if (d.flags & (second ? F_B_FAR : F_A_FAR)) v = far_sign(sh.prog[second ? d.b : d.a], x);
+    else v = lds[(second ? d.field : d.aux_len) + x];
+    if (cross) {
+      y += sh.start[rb];
+      uint64_t w;
+      if (d.flags & F_B_FAR) w = far_sign(sh.prog[d.b], y);
+      else w = lds[d.field + y];
+      v = mix64(mix64(v + d.key) + w);
+    }
+    const uint64_t at = sh.base[d.rag_row] + pos;
     put_list(d, pos, at, v);
   }
 };
@@ -1594,13 +1643,13 @@ __device__ __forceinline__ bool lb_place_row(const TileParams& P, const Sh& sh, 
 // Runs every layer on the nb records of one pass.  WRITE = false stops after the
 // counts.  hook() is called by every lane right after barriers (the caller
 // advances the next tile's loads there).
-template <int MODE, class Src, class Hook>
+template <int MODE, bool PAIRS, class Src, class Hook>
 __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, const Src& src, uint32_t nb, uint64_t g_first,
                                          uint32_t tile, uint32_t& malformed, bool& overflow, Hook&& hook) {
   constexpr bool WRITE = MODE != 0;
   const uint32_t tid = thread_id(), lane = tid & 63u, wave = tid >> 6;
   const uint32_t T = 1u << P.log2T;
-  Pass<Src> ps{P, sh, src, nb, g_first, T, 64u >> P.log2T, lane & (T - 1u), lane >> P.log2T, false, 0, malformed, overflow, MODE == 2 ? tile : kNoRow, WRITE};
+  Pass<Src, PAIRS> ps{P, sh, src, nb, g_first, T, 64u >> P.log2T, lane & (T - 1u), lane >> P.log2T, false, 0, malformed, overflow, MODE == 2 ? tile : kNoRow, WRITE};
   ps.live = ps.r < nb;
   ps.g = g_first + ps.r;
   // the single-valued hashes and buckets of layer 1 fill whatever phase has idle wavefronts
@@ -1829,7 +1878,7 @@ __device__ __forceinline__ u32x4 load_chunk(uintptr_t ca, uintptr_t ok_lo, uintp
 
 // Workgroups are persistent: each copies the plan tables into LDS once and then
 // takes tiles off a shared counter until none is left.
-template <int MODE, int COMMAS>
+template <int MODE, int COMMAS, bool PAIRS>
 __device__ __forceinline__ void tile_body(const TileParams& P) {
   constexpr bool WRITE = MODE != 0;
   __shared__ uint32_t s_err, s_len, s_cur, s_nxt;
@@ -1891,6 +1940,14 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
 #endif
   __syncthreads();
   if (s_err) return;
+  if (WRITE && P.n_gen) {  // the constant rows (several operators of an arity write the same)
+    for (uint32_t i = tid; i < P.n_ops << P.log2T; i += kTileThreads) {
+      const OpProg& d = sh.prog[i >> P.log2T];
+      if (!d.arity || d.rag_row == kNoRow) continue;
+      sh.cnt[d.rag_row * T + (i & (T - 1u))] = d.arity;
+      sh.start[d.rag_row * T + (i & (T - 1u))] = (i & (T - 1u)) * d.arity;
+    }
+  }
   // Offsets are checked before a tile touches the text: non-decreasing, inside the text, a record shorter than 2 GiB.
   auto offsets_fault = [&](uint64_t a, uint64_t b) -> uint32_t {
     if (a > b || b > P.raw_len) return CE_OFFSETS;
@@ -2048,7 +2105,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
         std::conditional_t<COMMAS == kCommasWithTabs, LdsListSrc, std::conditional_t<COMMAS == kCommasByField, LdsOthersSrc, LdsSrc>> src;
         src.raw8 = sh.raw; src.rows = sh.rows; src.stride = P.row_stride;
         if constexpr (COMMAS == kCommasWithTabs) { src.ctab = sh.ctab; src.ctot = sh.ctot; src.cap = P.comma_cap; }
-        run_pass<MODE>(P, sh, src, nb, g0 + r0, tile, malformed, overflow, next_tile_hook);
+        run_pass<MODE, PAIRS>(P, sh, src, nb, g0 + r0, tile, malformed, overflow, next_tile_hook);
         r0 = r1;
       } else {
         // record r0 alone exceeds the section: it is read in place
@@ -2060,7 +2117,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
         }
         __syncthreads();
         GlobalSrc src{gptr(P.raw) + o0, s_len};
-        run_pass<MODE>(P, sh, src, 1u, g0 + r0, tile, malformed, overflow, next_tile_hook);
+        run_pass<MODE, PAIRS>(P, sh, src, 1u, g0 + r0, tile, malformed, overflow, next_tile_hook);
         r0 += 1u;
       }
       __syncthreads();  // the sections are reused by the next pass
@@ -2120,9 +2177,9 @@ __device__ __forceinline__ void export_results(Params& P) {
   }
 }
 
-template <int MODE, int COMMAS>
+template <int MODE, int COMMAS, bool PAIRS>
 __device__ __forceinline__ void tile_entry(const TileParams& P) {
-  tile_body<MODE, COMMAS>(P);
+  tile_body<MODE, COMMAS, PAIRS>(P);
 #ifndef FBX_FIXED_MODE
   if constexpr (COMMAS != kCommasWithTabs) {
     // the launch's arguments where they lie, so that the main loop does not hold on to those that only this needs (a million
@@ -2208,7 +2265,7 @@ template <int MODE, int COMMAS, bool GEN>
 __global__ __launch_bounds__(kTileThreads, 4) void k_tile(TileParams Pin) {
   TileParams P = Pin;
   if constexpr (!GEN) P.n_gen = 0;
-  tile_entry<MODE, COMMAS>(P);
+  tile_entry<MODE, COMMAS, GEN>(P);
 }
 #endif
 
@@ -2235,7 +2292,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void k_tile(TileParams Pin) {
 extern "C" __global__ __launch_bounds__(kTileThreads, FBX_FIXED_WAVES) FBX_SIZE_ATTR void FBX_FIXED_NAME(TileParams Pin) {
   TileParams P = Pin;
   FBX_FIXED_ASSIGN
-  tile_entry<FBX_FIXED_MODE, FBX_FIXED_COMMAS>(P);
+  tile_entry<FBX_FIXED_MODE, FBX_FIXED_COMMAS, true>(P);
 }
 #endif
 

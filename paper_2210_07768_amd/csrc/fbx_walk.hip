@@ -494,7 +494,7 @@ __global__ __launch_bounds__(kBlock) void k_count(WalkParams P) {
     else e = find_end<false>(t.ctx, t.pos, t.end, commas);
     for (uint32_t q = 0; q < fd.op_count; ++q) {
       const OpDesc d = cload(&P.ops[cload(&P.field_ops[fd.op_begin + q])]);
-      if (d.rag_row == kNoRow) continue;
+      if (d.arity) continue;
       uint32_t c;
       if (d.kind == OP_NGRAM) {
         const uint32_t L = e > t.pos ? e - t.pos : 0u;
@@ -510,7 +510,7 @@ __global__ __launch_bounds__(kBlock) void k_count(WalkParams P) {
   bool overflow = false;
   for (uint32_t k = 0; k < P.n_nonroot; ++k) {
     const OpDesc d = cload(&P.ops[cload(&P.nonroot[k])]);
-    if (d.rag_row == kNoRow) continue;
+    if (d.arity) continue;
     const OpDesc da = cload(&P.ops[d.a]);
     const OpDesc db = cload(&P.ops[d.b]);
     const uint64_t ca = da.arity ? da.arity : cnt[da.rag_row * 64u + lane];

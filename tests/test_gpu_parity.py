@@ -1078,3 +1078,24 @@ def test_tokens_of_every_length_in_kernels_compiled_for_short_and_long_ones(pad,
     assert f"#define FBX_LONG_TOKENS {long_tokens}\n" in plan.kernel_source(len(raw), len(recs), 1)
     plan.close()
     check(spec, raw, off, {"compile": 1}, label=f"pad {pad}")
+
+
+@pytest.mark.parametrize("options", [{"tile_log2": 0}, {"tile_log2": 3}, {"tile_log2": 6}, {"tile_log2": 4, "raw_cap": 1024}, {"tile_log2": 3, "compile": 1},
+                                     {"tile_log2": 6, "one_launch": 0, "compile": 1}], ids=str)
+@pytest.mark.parametrize("rare", [1, 70])
+def test_list_operators_that_are_mostly_empty(rare, options):
+    """Runs of (operator, record) pairs without signs, as long as several wavefronts, between pairs of a few signs and of more
+    than a wavefront; layers of few and of more than 64 operators; fixed arities 2, 3 and 6 beside them."""
+    rng = random.Random(rare)
+    spec = "fbx 1\nfields 4\nop s hash slot=0 seed=1 emit=0 field=0 multi=0\nop m hash slot=1 seed=2 emit=0 field=1 multi=1\n"
+    spec += "op q filter slot=2 seed=3 emit=0 field=2 multi=0 prefix=7a7a\n"
+    spec += "".join(f"op r{k} cross slot={10 + k} seed={rng.getrandbits(64)} emit={k % 2} a={'qm'[k % 2]} b={'qmq'[k % 3]}\n" for k in range(rare))
+    spec += "op c2 concat slot=3 emit=1 a=s b=s\nop c3 concat slot=4 emit=1 a=c2 b=s\nop x6 cross slot=5 seed=4 emit=1 a=c3 b=c2\n"
+    spec += "op l concat slot=6 emit=1 a=q b=m\nop y cross slot=7 seed=5 emit=1 a=c3 b=l\nop z cross slot=8 seed=6 emit=1 a=r0 b=x6\n"
+    recs = []
+    for i in range(403):
+        items = rng.choice([0, 1, 2]) if i % 40 else 90
+        recs.append(("\t".join([f"t{i}", ",".join(rng.choice(["", "a", "bcd"]) for _ in range(items + 1)),
+                                "zz9" if rng.random() < 0.02 else "y", "pad" * rng.randrange(5)]) + "\n").encode())
+    raw, off = _cat(recs)
+    check(spec, raw, off, options, label=f"{rare} {options}")
