@@ -205,7 +205,7 @@ void tile_lds_layout(const fbx_plan& p, uint32_t lt, uint64_t want, uint32_t raw
   const bool along = others ? want >= T * (2048ull * 5u / 4u) : 2u * p.n_mh * T > 512u;
   tp.commas = along ? kCommasWithTabs : (others ? kCommasByField : kCommasOfHashes);
   // (a record with more is rare; places in the table are kept in 15 bits)
-  tp.comma_cap = along ? std::min({16u * p.n_comma_fields, 2048u, 32767u / T - 2u}) : 0u;
+  tp.comma_cap = along ? std::min({16u * p.n_comma_fields, 2048u, 32767u / T - 2u}) & ~1u : 0u;  // (even: tables are moved four bytes at a time)
   tp.o_ctab = o; o = round16(o + 2ull * T * (along ? tp.comma_cap + 2u : p.n_mh * kItemCap));
   tp.o_ctot = o; o = round16(o + (along ? 2ull * T : 0ull));
   tp.o_cfirst = o; o = round16(o + (along ? 2ull * T * tp.n_mh : 0ull));
@@ -224,6 +224,11 @@ void tile_lds_layout(const fbx_plan& p, uint32_t lt, uint64_t want, uint32_t raw
   tp.list_cap = p.keeps_roots && o < share ? (share - o) / 16u * 2u : 0u;
   o += 8u * tp.list_cap;
   tp.lds_bytes = o;
+  // (room for six commas a field where there are three on average, or thirty in one field)
+  tp.kept_commas = along ? std::min(round16(2u * (6u * p.n_comma_fields + 24u)) / 2u, tp.comma_cap / 8u * 8u) : 0u;
+  tp.kept_bytes = along ? 16u + round16(2ull * T * tp.row_stride) + round16(2ull * T * tp.n_mh) + round16(2ull * T) +
+                              2u * round16(2ull * T * h.n_ragged) + round16(2ull * h.n_ragged) + 2u * T * tp.kept_commas
+                        : 0u;
 }
 
 // Tile size: the largest power of two (at most 64 records) whose LDS sections
@@ -629,6 +634,26 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
     for (uint32_t r = 0; r < h.n_ragged; ++r) plan->units[n_ops + r] = static_cast<uint32_t>(one ? plan->cap_host[r] * 8 / kPlaceUnit : 0);
     return head;
   };
+  // Whether the counting launch leaves what it finds for the writing launch: in a workspace (a caller's output buffer is for
+  // results) with room for it behind the arrays.  How large those will be is known from the last call, or the tables may take
+  // half of what there is; arrays that grow into them all the same cost the writing launch what it would have saved.
+  auto keep_tables = [&](TileParams& Q) {
+    Q.kept = nullptr;
+    const uint64_t size = align_up(uint64_t(g.n_tiles) * Q.kept_bytes);
+    if (!size || reg.own_tables || ws_bytes < g.arena_base + size) return;
+    const uint64_t at = (ws_bytes - size) / kAlign * kAlign, room = at - g.arena_base;
+    uint64_t need = size;
+    if (plan->learned && plan->learned_records) {
+      double arrays = 0;
+      for (const HostOp& op : h.ops)
+        arrays += op.d.arity ? 8.0 * n_records * op.d.arity + kPlaceUnit
+                             : 8.0 * n_records + 8.2 * plan->learned_total[op.d.rag_row] * (double(n_records) / plan->learned_records) + 2 * kPlaceUnit;
+      need = arrays < 1e18 ? static_cast<uint64_t>(arrays) : ~0ull;
+    }
+    if (need > room) return;
+    Q.kept = ws + at;
+    Q.kept_at = at;
+  };
   // One attempt: everything is enqueued on the stream, then one synchronisation.
   auto run = [&](bool one) -> fbx_status {
     for (Timer& t : plan->timers) t.used = false;
@@ -717,6 +742,7 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
         plan->tile_launch_layer.push_back(1);
       } else {
         if (g.n_tiles) {
+          keep_tables(Q);
           tick(1, 0);
           FBX_LAUNCH(tile_launch(Q, 0), "tile kernel (counting)");
           tick(1, 1);

@@ -88,6 +88,12 @@ struct TileParams {
   uint32_t o_lists;     // lists of layer 1 that later operators read: the last section, which counting does without
   uint32_t list_cap;    // signs it holds
   uint32_t lds_bytes;
+  // What the counting launch finds out about a tile's text and the writing launch would find out again (kCommasWithTabs): one
+  // slot of kept_bytes a tile, in what is left at the end of a workspace; null: not kept.
+  uint8_t* kept;
+  uint64_t kept_at;      // where the slots start, as arrays' places count: arrays that end beyond it have overwritten them
+  uint32_t kept_bytes;
+  uint32_t kept_commas;  // comma positions a record has room for there, a multiple of 8; a tile with more is not kept
   // What the host needs to know when the call is done: the last workgroup to finish copies the control block and
   // `export_words` words from `export_from` on to `export_to` (host memory; null: nothing is copied).
   uint64_t* export_to;
@@ -118,7 +124,7 @@ struct UnorderedParams {
   X(n_ops) X(n_layers) X(n_ragged) X(n_rnr) X(n_lists) X(aux_bytes) X(rnr_words) X(alias_at) X(n_alias) X(n_mh) X(n_split) X(n_gen) X(n_fields) \
   X(n_stage) X(log2T) X(raw_cap) X(row_stride) X(o_off) X(o_rs) X(o_re) X(o_rows) X(o_raw) X(o_stage) X(o_cnt)     \
   X(o_start) X(o_run) X(o_base) X(o_prog) X(o_lbeg) X(o_rnr) X(o_aux) X(o_tot) X(o_ioff) X(o_ctab) X(o_ctot) X(o_cfirst) X(o_cap) \
-  X(o_gfirst) X(o_gtot) X(commas) X(comma_cap) X(o_lists) X(list_cap) X(lds_bytes)
+  X(o_gfirst) X(o_gtot) X(commas) X(comma_cap) X(o_lists) X(list_cap) X(lds_bytes) X(kept_bytes) X(kept_commas)
 
 #ifndef __HIPCC_RTC__  // (the launch wrappers are host code: not for the run-time compiler)
 // mode 0: counting launch; 1: writing launch (bases from the scan over tiles);

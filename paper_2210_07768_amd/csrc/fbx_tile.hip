@@ -284,6 +284,10 @@ struct GlobalSrc {
   }
 };
 
+// The number of a tile that is not kept for the writing launch (keep_tile): the last one that was seen to have too many
+// commas in a record or too many signs of an operator.
+__shared__ uint32_t s_drop;
+
 // ------------------------------------------------------------ splitting
 // (eq_flags, group_prefix and split_bytes: fbx_split.h)
 
@@ -291,7 +295,7 @@ struct GlobalSrc {
 // record and place its tabs.  Entries from the record's tab count on hold the
 // record's end.
 template <int COMMAS>
-__device__ __forceinline__ void tokenize(const TileParams& P, const Sh& sh, uint32_t nb) {
+__device__ __forceinline__ void tokenize(const TileParams& P, const Sh& sh, uint32_t nb, uint32_t tile) {
   const uint32_t tid = thread_id();
   constexpr uint32_t kLogThreads = kTileThreads == 1024 ? 10u : (kTileThreads == 512 ? 9u : 8u);
   const uint32_t lg = kLogThreads - P.log2T < 6u ? kLogThreads - P.log2T : 6u;  // log2 of the lanes per record
@@ -312,7 +316,10 @@ __device__ __forceinline__ void tokenize(const TileParams& P, const Sh& sh, uint
     uint16_t* list = sh.ctab + r * (P.comma_cap + 2u);
     total = split_bytes<true>(sh.raw, rs, re, act, lg, j, kTabs, F, put_tab, kCommas, P.comma_cap,
                               [&](uint32_t k, uint32_t pos) { list[k] = (uint16_t)pos; });
-    if (act && j == 0) sh.ctot[r] = (uint16_t)(total >> 16);
+    if (act && j == 0) {
+      sh.ctot[r] = (uint16_t)(total >> 16);
+      if ((total >> 16) > P.kept_commas) s_drop = tile;
+    }
     total &= 0xffffu;
   } else {
     total = split_bytes<false>(sh.raw, rs, re, act, lg, j, kTabs, F, put_tab, 0u, 0u, [](uint32_t, uint32_t) {});
@@ -779,6 +786,7 @@ struct Pass {
   uint64_t g;
   uint32_t& malformed;
   bool& overflow;
+  uint32_t tile;
   uint32_t lb_tile;   // tile number when counts are to be published (one-launch mode), else kNoRow
   bool need_table;    // the pass goes on to write: keep comma positions while counting
 
@@ -1006,6 +1014,9 @@ struct Pass {
       if (r == T - 1u) {
         sh.run[row] = before + incl;
         sh.tot[row] = incl;
+        if constexpr (Src::kLists) {
+          if (!need_table && incl > 0xffffu) s_drop = tile;
+        }
         if (lb_tile != kNoRow && !row_follows(P, sh, row))  // one-launch mode: later tiles may need it at once
           lb_store(P.lb_state + (uint64_t)row * P.n_tiles + lb_tile, kLbAggregate | incl);
       }
@@ -1100,7 +1111,6 @@ struct Pass {
   // (What bounds a unit is the chain of look-ups and its vector instructions.  Against two binary searches a sign and fields of the
   // programs looked through for every input: 4,000,000 records of the 100-field workload, 4 lists, 4,265 -> 4,130 us a call;
   // 200,000 of 18 lists and 6 crosses of two of them 868 -> 817; 250,000 of the four-layer graph 1,618 -> 1,562.)
-  // TODO-FIGURES
   __device__ __forceinline__ uint32_t pair_at(const OpProg* ops, const ListFirst* first, uint32_t m, uint32_t q0) const {
     const uint32_t lane = lane_id();
     uint32_t lo = 0;
@@ -1642,14 +1652,14 @@ __device__ __forceinline__ bool lb_place_row(const TileParams& P, const Sh& sh, 
 
 // Runs every layer on the nb records of one pass.  WRITE = false stops after the
 // counts.  hook() is called by every lane right after barriers (the caller
-// advances the next tile's loads there).
+// advances the next tile's loads there).  kept: counts and positions are there already (keep_tile).
 template <int MODE, bool PAIRS, class Src, class Hook>
 __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, const Src& src, uint32_t nb, uint64_t g_first,
-                                         uint32_t tile, uint32_t& malformed, bool& overflow, Hook&& hook) {
+                                         uint32_t tile, bool kept, uint32_t& malformed, bool& overflow, Hook&& hook) {
   constexpr bool WRITE = MODE != 0;
   const uint32_t tid = thread_id(), lane = tid & 63u, wave = tid >> 6;
   const uint32_t T = 1u << P.log2T;
-  Pass<Src, PAIRS> ps{P, sh, src, nb, g_first, T, 64u >> P.log2T, lane & (T - 1u), lane >> P.log2T, false, 0, malformed, overflow, MODE == 2 ? tile : kNoRow, WRITE};
+  Pass<Src, PAIRS> ps{P, sh, src, nb, g_first, T, 64u >> P.log2T, lane & (T - 1u), lane >> P.log2T, false, 0, malformed, overflow, tile, MODE == 2 ? tile : kNoRow, WRITE};
   ps.live = ps.r < nb;
   ps.g = g_first + ps.r;
   // the single-valued hashes and buckets of layer 1 fill whatever phase has idle wavefronts
@@ -1688,42 +1698,44 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
     __syncthreads();
   };
 
-  // ---- phase A: counts of the ragged root operators
   bool absurd = false;
-  if constexpr (Src::kTable && !Src::kLists) {
-    if (P.n_mh) ps.template split_lists<true>();
-    if constexpr (Src::kOthers) {
-      if (P.n_split > P.n_mh) ps.template split_lists<false>();
+  if (!kept) {
+    // ---- phase A: counts of the ragged root operators
+    if constexpr (Src::kTable && !Src::kLists) {
+      if (P.n_mh) ps.template split_lists<true>();
+      if constexpr (Src::kOthers) {
+        if (P.n_split > P.n_mh) ps.template split_lists<false>();
+      }
     }
-  }
-  if (P.n_ragged) critical_phase(ps.count_units(), &s_ctr[1], &s_done, [&](uint32_t u) { ps.count_unit(u); });
-  else __syncthreads();
-  if (P.n_ragged && FBX_SKIP(0x800u)) {  // (tuning builds: the counting units once more, to weigh them)
-    for (uint32_t u = wave; u < ps.count_units(); u += kWaves) ps.count_unit(u);
-    __syncthreads();
-  }
-  FBX_MARK(4);
-  hook();
-  // ---- phase B: the counts of later layers, layer by layer
-  if (P.n_rnr) {
-    // (short: the wavefronts just share the units out; the last layer's counts are left to the next phase)
-    for (uint32_t layer = 2; layer < P.n_layers; ++layer) {
-      const uint32_t ud = ps.derive_units(layer);
-      for (uint32_t u = wave; u < ud; u += kWaves) ps.derive_unit(layer, u);
+    if (P.n_ragged) critical_phase(ps.count_units(), &s_ctr[1], &s_done, [&](uint32_t u) { ps.count_unit(u); });
+    else __syncthreads();
+    if (P.n_ragged && FBX_SKIP(0x800u)) {  // (tuning builds: the counting units once more, to weigh them)
+      for (uint32_t u = wave; u < ps.count_units(); u += kWaves) ps.count_unit(u);
       __syncthreads();
+    }
+    FBX_MARK(4);
+    hook();
+    // ---- phase B: the counts of later layers, layer by layer
+    if (P.n_rnr) {
+      // (short: the wavefronts just share the units out; the last layer's counts are left to the next phase)
+      for (uint32_t layer = 2; layer < P.n_layers; ++layer) {
+        const uint32_t ud = ps.derive_units(layer);
+        for (uint32_t u = wave; u < ud; u += kWaves) ps.derive_unit(layer, u);
+        __syncthreads();
+        hook();
+      }
+      FBX_MARK(5);
+    }
+    // ---- phase B2: counts become positions
+    if (P.n_ragged) {
+      const uint32_t us = ps.scan_units();
+      for (uint32_t u = wave; u < us; u += kWaves) ps.scan_unit(u);
+      if (MODE >= 2 && overflow) s_absurd = 1u;  // (rare: a plain flag is cheaper than a vote in every tile)
+      __syncthreads();
+      if (MODE >= 2) absurd = s_absurd != 0u;
+      FBX_MARK(6);
       hook();
     }
-    FBX_MARK(5);
-  }
-  // ---- phase B2: counts become positions
-  if (P.n_ragged) {
-    const uint32_t us = ps.scan_units();
-    for (uint32_t u = wave; u < us; u += kWaves) ps.scan_unit(u);
-    if (MODE >= 2 && overflow) s_absurd = 1u;  // (rare: a plain flag is cheaper than a vote in every tile)
-    __syncthreads();
-    if (MODE >= 2) absurd = s_absurd != 0u;
-    FBX_MARK(6);
-    hook();
   }
   if (MODE >= 2 && absurd) {  // absurd counts: nothing of this tile may be placed (whatever it published is overwritten)
     if (MODE == 2) lb_abort_tile(P, tile);
@@ -1840,6 +1852,7 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
     const uint32_t list = ps.gen_list(layer);
     if (sh.lbeg(list + 1) == sh.lbeg(list)) continue;  // (no such operator in this layer: no barrier either)
     __syncthreads();  // the layer barrier
+    if (MODE == 1) hook();
     uint32_t* ctr = &s_ctr[7u + (turn & 1u)];
     if (tid == 0) s_ctr[7u + ((turn + 1u) & 1u)] = 0;  // the counter of the next layer that has any (idle since the barrier before this one)
     ++turn;
@@ -1847,6 +1860,65 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
       if (!FBX_SKIP(2u)) ps.gen_unit(layer, u);
     });
   }
+}
+
+// ---- what the counting launch leaves for the writing launch
+// Splitting a tile's text and counting is a third of what the writing launch of a list-heavy plan does, and the counting launch
+// has just done it: field ends, commas, counts and positions are a fifth of the text's size, and go to a slot a tile has in
+// memory.  A tile is kept if it was worked off in one pass and what it holds fits the slot's 16-bit entries; the slot's first
+// word says so.  Sections of the slot, 16 bytes at a time: field ends, first commas of the hashes' fields, commas a record has,
+// counts, positions, totals, commas.  Chunk c of the slot, handed to what moves it: LDS address and how entries lie there.
+// (us a call with the slots and without: 200,000 records of 18 lists with crosses 750 and 817, 250,000 of the four-layer graph
+// 1,355 and 1,562, 50,000 and 60,000 of them with the kernel for any plan 276 and 310, 524 and 603.  The counting launch takes 7 %
+// longer for it.)
+template <bool OUT>
+__device__ __forceinline__ void move_kept(const TileParams& P, const Sh& sh, uint32_t tile) {
+  const uint32_t T = 1u << P.log2T, entries = P.n_ragged << P.log2T, per_record = P.kept_commas >> 3;
+  auto chunks = [](uint32_t u16s) { return (u16s + 7u) >> 3; };
+  const uint32_t e_rows = chunks(T * P.row_stride), e_first = e_rows + chunks(T * P.n_mh), e_ctot = e_first + chunks(T),
+                 e_cnt = e_ctot + chunks(entries), e_start = e_cnt + chunks(entries), e_tot = e_start + chunks(P.n_ragged),
+                 all = e_tot + T * per_record;
+  FBX_GLOBAL u32x4* slot = gptr<u32x4>(reinterpret_cast<uint64_t>(P.kept) + (uint64_t)tile * P.kept_bytes + 16u);
+  for (uint32_t c = thread_id(); c < all; c += kTileThreads) {
+    u32x4 v;
+    if (!OUT) v = slot[c];
+    auto straight = [&](uint16_t* at) {
+      if (OUT) v = *reinterpret_cast<u32x4*>(at);
+      else *reinterpret_cast<u32x4*>(at) = v;
+    };
+    // entries of 32 bits, eight of them; the other table gets the same (tot and run)
+    auto widened = [&](uint32_t* at, uint32_t* also, uint32_t k, uint32_t n) {
+      if (OUT) {
+        const u32x4 a = *reinterpret_cast<u32x4*>(at + k), b = *reinterpret_cast<u32x4*>(at + k + 4u);
+        v.x = a.x | a.y << 16; v.y = a.z | a.w << 16; v.z = b.x | b.y << 16; v.w = b.z | b.w << 16;
+      } else {
+#pragma unroll
+        for (uint32_t i = 0; i < 8u; ++i) {
+          const uint32_t w = i < 2u ? v.x : i < 4u ? v.y : i < 6u ? v.z : v.w, x = i & 1u ? w >> 16 : w & 0xffffu;
+          if (k + i < n) {
+            at[k + i] = x;
+            if (also) also[k + i] = x;
+          }
+        }
+      }
+    };
+    if (c < e_rows) straight(sh.rows + 8u * c);
+    else if (c < e_first) straight(sh.cfirst + 8u * (c - e_rows));
+    else if (c < e_ctot) straight(sh.ctot + 8u * (c - e_first));
+    else if (c < e_cnt) widened(sh.cnt, nullptr, 8u * (c - e_ctot), entries);
+    else if (c < e_start) widened(sh.start, nullptr, 8u * (c - e_cnt), entries);
+    else if (c < e_tot) widened(sh.tot, sh.run, 8u * (c - e_start), P.n_ragged);
+    else {
+      const uint32_t r = (c - e_tot) / per_record, q = c - e_tot - r * per_record;
+      uint32_t* at = reinterpret_cast<uint32_t*>(sh.ctab + r * (P.comma_cap + 2u) + 8u * q);  // (four bytes aligned)
+      if (OUT) { v.x = at[0]; v.y = at[1]; v.z = at[2]; v.w = at[3]; }
+      else { at[0] = v.x; at[1] = v.y; at[2] = v.z; at[3] = v.w; }
+    }
+    if (OUT) slot[c] = v;
+  }
+}
+__device__ __forceinline__ FBX_GLOBAL uint32_t* kept_word(const TileParams& P, uint32_t tile) {
+  return gptr<uint32_t>(reinterpret_cast<uint64_t>(P.kept) + (uint64_t)tile * P.kept_bytes);
 }
 
 // ------------------------------------------------------------------- kernel
@@ -1882,6 +1954,7 @@ template <int MODE, int COMMAS, bool PAIRS>
 __device__ __forceinline__ void tile_body(const TileParams& P) {
   constexpr bool WRITE = MODE != 0;
   __shared__ uint32_t s_err, s_len, s_cur, s_nxt;
+  __shared__ uint32_t s_kept;   // tiles' slots are there and nothing has overwritten them
   __shared__ uint32_t s_bad[2];  // what is wrong with the offsets of the current and of the next tile (CE_ bits)
   Sh sh_ = views(P);
 #ifndef FBX_FIXED_MODE
@@ -1889,9 +1962,14 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
 #endif
   const Sh& sh = sh_;
   const uint32_t tid = threadIdx.x;
+  // In the kernels of list-heavy plans, which have the most to hold on to, addresses that follow from the lane's number are
+  // worked out where they are used (thread_id); the others have registers for them (a million records of 16 single-valued
+  // fields 232 us a call otherwise and 222, of the numeric workload 590 and 577; the four-layer graph 1,546 so and 1,353).
+  auto my_id = [&]() -> uint32_t { return COMMAS == kCommasWithTabs && MODE <= 1 ? thread_id() : tid; };
   const uint32_t T = 1u << P.log2T;
   const FBX_GLOBAL uint64_t* rec_off = gptr(P.rec_off);
   uint32_t* ticket = &P.ctrl->ticket[WRITE ? 1 : 0];
+  constexpr bool kKeep = MODE <= 1 && COMMAS == kCommasWithTabs;  // what the counting launch finds may be kept for the writing one
   const uintptr_t ok_lo = reinterpret_cast<uintptr_t>(P.raw), ok_hi = ok_lo + P.raw_len;
   // Where tiles wait for the tiles before them (MODE 2, see lb_place_row) they are taken off a counter.  A
   // workgroup takes its next tile when it starts on the current one (that early, so that the
@@ -1914,6 +1992,10 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
     s_err = P.ctrl->err;  // set by an earlier kernel of this call: nothing may be written
     s_cur = kInOrder ? atomicAdd(ticket, 1u) : blockIdx.x;
     s_bad[0] = s_bad[1] = 0;
+    if constexpr (kKeep) {
+      s_drop = ~0u;
+      s_kept = P.kept && (!WRITE || P.ctrl->high_water <= P.kept_at) ? 1u : 0u;
+    }
   }
   {  // the operators' programs in the order of the work lists, their inputs a and b renumbered alike
     static_assert(sizeof(OpProg) == 64 && offsetof(OpProg, a) == 24 && offsetof(OpProg, b) == 28, "OpProg layout");
@@ -1970,6 +2052,10 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
   uint32_t malformed = 0;
   bool overflow = false;
   uint32_t tile = s_cur;
+  bool keeps = false;
+  if constexpr (kKeep) keeps = __builtin_amdgcn_readfirstlane(s_kept) != 0u;
+  uint32_t kept_now = 0, kept_next = 0;  // (writing) the first words of this tile's slot and of the next one's
+  if (WRITE && keeps && tile < P.n_tiles) kept_now = *kept_word(P, tile);
   for (;;) {
     if (tile >= P.n_tiles) break;
     uint32_t my_ticket = 0;
@@ -1985,8 +2071,10 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
     uint64_t* off2 = sh.off + (par ^ 1u) * (T + 1u);
     const uint64_t g0 = (uint64_t)tile << P.log2T;
     const uint32_t nrec = (uint32_t)min((uint64_t)T, P.n_records - g0);
+    bool kept = false;
+    if constexpr (WRITE && kKeep) kept = __builtin_amdgcn_readfirstlane(kept_now) != 0u;
     for (uint32_t row = tid; row < P.n_ragged; row += kTileThreads) {
-      sh.run[row] = 0;
+      if (!kept) sh.run[row] = 0;
       if (MODE == 1) sh.base[row] = gptr(P.tile_base)[(uint64_t)row * P.n_tiles + tile];
     }
     if (tid < 9) s_ctr[tid] = 0;
@@ -2010,9 +2098,10 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
     // and one byte of every 128-byte line of its text is requested, which brings the text into
     // the L2 cache without holding registers for it.  Only the two outer offsets decide what is
     // touched; the tile itself is checked when its turn comes.
-    uint32_t pf_stage = counter ? 0u : 1u, nxt = 0xffffffffu, nrec2 = 0, touch = 0;
+    uint32_t pf_stage = counter ? 0u : 1u, nxt = 0xffffffffu, nrec2 = 0, touch = 0, touch_kept = 0;
     uint64_t off_next = 0, off_next1 = 0, nx_lo = 0, nx_hi = 0;
     auto next_tile_step = [&]() {  // every lane, right after a barrier
+      const uint32_t tid = my_id();
       if (pf_stage == 0) {
         if (tid == 0) s_nxt = late_ticket ? atomicAdd(ticket, 1u) : my_ticket;
       } else if (pf_stage == 1) {
@@ -2024,6 +2113,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
           if (tid < nrec2) off_next1 = rec_off[g1 + tid + 1u];
           nx_lo = rec_off[g1];
           nx_hi = rec_off[g1 + nrec2];
+          if (WRITE && keeps) kept_next = *kept_word(P, nxt);
         }
       } else if (pf_stage == 2) {
         if (nxt < P.n_tiles) {
@@ -2036,6 +2126,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
             const uintptr_t first = ok_lo + nx_lo, end = ok_lo + nx_hi;
             const uintptr_t line = (first & ~(uintptr_t)127) + 128u * tid;  // (tiles beyond 64 KiB of text: the first 64 KiB)
             if (line < end) touch = *gptr<const uint8_t>((uint64_t)max(line, first));
+            if (WRITE && keeps && 128u * tid < P.kept_bytes) touch_kept = kept_word(P, nxt)[32u * tid];
           }
         }
       }
@@ -2046,6 +2137,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
     };
 
     uint32_t r0 = nrec_ok ? 0u : nrec;
+    bool in_one_pass = false;
     if (MODE >= 2 && nrec_ok) {
       // placement needs the whole tile's counts at once: a tile that takes several passes
       // (or holds a record that is read in place) sends the call back to the counting launch
@@ -2067,9 +2159,10 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
         const uint32_t mid = (lo + hi + 1u) >> 1;
         if (off[mid] - o0 + delta <= (uint64_t)P.raw_cap) lo = mid; else hi = mid - 1u;
       }
-      const uint32_t r1 = lo;
+      const uint32_t r1 = lo, tid = my_id();
       if (r1 > r0) {
         const uint32_t nb = r1 - r0;
+        in_one_pass = nb == nrec;
         const uint32_t nchunks = (delta + (uint32_t)(off[r1] - o0) + 15u) >> 4;
         const uintptr_t a0 = addr0 - delta;
         if (a0 >= ok_lo && a0 + 16ull * nchunks <= ok_hi) {  // whole chunks (all but the ends of the caller's buffer)
@@ -2089,23 +2182,28 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
           for (uint32_t c = tid; c < nchunks; c += kTileThreads)
             *reinterpret_cast<u32x4*>(sh.raw + kRawPad + 16u * c) = load_chunk(a0 + 16u * c, ok_lo, ok_hi);
         }
+        if (kept) move_kept<false>(P, sh, tile);
         if (tid < nb) {
           sh.rs[tid] = kRawPad + delta + (uint32_t)(off[r0 + tid] - o0);
           sh.re[tid] = kRawPad + delta + (uint32_t)(off[r0 + tid + 1] - o0);
         }
         __syncthreads();
         FBX_MARK(2);
-        if (!FBX_SKIP(8u)) tokenize<COMMAS>(P, sh, nb);
-        if (FBX_SKIP(0x100u)) {  // (tuning builds: once more, to weigh it)
+        if (kept) {
+          next_tile_hook();
+        } else {
+          if (!FBX_SKIP(8u)) tokenize<COMMAS>(P, sh, nb, tile);
+          if (FBX_SKIP(0x100u)) {  // (tuning builds: once more, to weigh it)
+            __syncthreads();
+            tokenize<COMMAS>(P, sh, nb, tile);
+          }
           __syncthreads();
-          tokenize<COMMAS>(P, sh, nb);
         }
-        __syncthreads();
         FBX_MARK(3);
         std::conditional_t<COMMAS == kCommasWithTabs, LdsListSrc, std::conditional_t<COMMAS == kCommasByField, LdsOthersSrc, LdsSrc>> src;
         src.raw8 = sh.raw; src.rows = sh.rows; src.stride = P.row_stride;
         if constexpr (COMMAS == kCommasWithTabs) { src.ctab = sh.ctab; src.ctot = sh.ctot; src.cap = P.comma_cap; }
-        run_pass<MODE, PAIRS>(P, sh, src, nb, g0 + r0, tile, malformed, overflow, next_tile_hook);
+        run_pass<MODE, PAIRS>(P, sh, src, nb, g0 + r0, tile, kept, malformed, overflow, next_tile_hook);
         r0 = r1;
       } else {
         // record r0 alone exceeds the section: it is read in place
@@ -2117,7 +2215,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
         }
         __syncthreads();
         GlobalSrc src{gptr(P.raw) + o0, s_len};
-        run_pass<MODE, PAIRS>(P, sh, src, 1u, g0 + r0, tile, malformed, overflow, next_tile_hook);
+        run_pass<MODE, PAIRS>(P, sh, src, 1u, g0 + r0, tile, false, malformed, overflow, next_tile_hook);
         r0 += 1u;
       }
       __syncthreads();  // the sections are reused by the next pass
@@ -2126,6 +2224,11 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
       if (tid == 10) s_good = 1u;
       if (tid == 11) s_absurd = 0u;
       FBX_MARK(11);
+    }
+    if (!WRITE && keeps) {
+      const bool keep = in_one_pass && s_drop != tile;  // (the next tile's splitting, which may set it, lies behind a barrier)
+      if (keep) move_kept<true>(P, sh, tile);
+      if (tid == 0) *kept_word(P, tile) = keep ? 1u : 0u;
     }
     if (!WRITE) {
       for (uint32_t row = tid; row < P.n_ragged; row += kTileThreads)
@@ -2138,7 +2241,8 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
       } while (pf_stage < 3);
       __syncthreads();  // the parked offsets are read by other lanes
     }
-    asm volatile("" ::"v"(touch));  // the touched byte itself is of no use
+    asm volatile("" ::"v"(touch), "v"(touch_kept));  // the touched bytes themselves are of no use
+    kept_now = kept_next;
     par ^= 1u;
     tile = nxt;  // every lane has read the ticket by now
     FBX_MARK(12);

@@ -1099,3 +1099,47 @@ def test_list_operators_that_are_mostly_empty(rare, options):
                                 "zz9" if rng.random() < 0.02 else "y", "pad" * rng.randrange(5)]) + "\n").encode())
     raw, off = _cat(recs)
     check(spec, raw, off, options, label=f"{rare} {options}")
+
+
+@pytest.mark.parametrize("compiled", [0, 1])
+def test_what_counting_leaves_for_the_writing_launch(compiled):
+    """Batches that count: what the counting launch found is taken over tile by tile, except for tiles with too many commas in
+    a record or more signs of an operator than 16 bits hold, and for all of them where the workspace has no room for it or the
+    arrays have grown into it.  Every size of workspace between what the arrays need and far beyond gives the same results."""
+    import torch
+    rng = random.Random(3)
+    F = 16
+    spec = f"fbx 1\nfields {F}\n" + "".join(f"op h{k} hash slot={k} seed={k} emit=1 field={k} multi=1\n" for k in range(12))
+    spec += "op f filter slot=20 seed=7 emit=1 field=13 multi=1 prefix=61\nop s hash slot=21 seed=8 emit=1 field=14 multi=0\n"
+    spec += "op x cross slot=22 seed=9 emit=1 a=h0 b=h1\nop y cross slot=23 seed=10 emit=1 a=x b=s\nop z concat slot=24 emit=1 a=f b=h2\n"
+    def batch(n, dense):
+        recs = []
+        for i in range(n):
+            many = {7: 300, 8: 90, 9: 17}.get(i % dense, 0)
+            lists = [",".join(rng.choice(["a", "bb", "", "a" * 30]) for _ in range(rng.randrange(1, 5) + many)) for _ in range(14)]
+            recs.append(("\t".join(lists + [f"k{i}", "t" * (1500 + rng.randrange(300))]) + "\n").encode())
+        raw, off = _cat(recs)
+        return np.frombuffer(raw, np.uint8), off
+    for n, dense in ((331, 100), (40, 10)):
+        raw, off = batch(n, dense)
+        want = O.extract(spec, raw, off)
+        d_raw, d_off = to_device(raw, off, 5)
+        need = None
+        for extra in (None, 0, 3000, 200_000, 1 << 20, 1 << 23):
+            plan = B.Plan(spec)
+            plan.set_option("one_launch", 0)
+            plan.set_option("tile_log2", 3)
+            plan.set_option("compile", compiled)
+            assert "P.kept_bytes = 0u;" not in plan.kernel_source(raw.size, n, 1)
+            if extra is None:
+                res, ws = B.extract_with_retry(plan, d_raw, d_off)
+                need = res.arena_high_water
+            else:
+                ws = torch.full((need + extra,), 0xff, dtype=torch.uint8, device="cuda")
+                plan.set_workspace(ws)
+                res = plan.extract(d_raw, d_off)
+            for _ in range(2):
+                assert res.tile_launches == 2, res.note
+                assert_same({s: expand(res.slots[s], n) for s in res.slot_ids}, res, want, f"{n} {extra}")
+                res = plan.extract(d_raw, d_off)
+            plan.close()
