@@ -398,7 +398,7 @@ fbx_status fbx_plan_kernel_source(const fbx_plan* plan, uint64_t raw_len, uint64
   TileParams Q = g.tp;
   const PlanHost& h = plan->host;
   Q.n_ops = static_cast<uint32_t>(h.ops.size()); Q.n_layers = h.n_layers; Q.n_ragged = h.n_ragged;
-  Q.n_rnr = h.n_derive;
+  Q.n_rnr = h.n_derive; Q.root_step = h.root_step;
   Q.rnr_words = static_cast<uint32_t>(h.derive_tab.size());
   Q.alias_at = h.alias_at; Q.n_alias = h.n_alias;
   Q.n_lists = static_cast<uint32_t>(h.tile_list_begin.size()) - 1u;
@@ -703,7 +703,7 @@ fbx_status extract_impl(fbx_plan* plan, const uint8_t* d_raw, uint64_t raw_len, 
       Q.tile_cnt = P.tile_cnt; Q.tile_base = P.tile_base;
       Q.lb_state = nullptr; Q.row_cap = nullptr; Q.row_actual = nullptr;
       Q.n_ops = n_ops; Q.n_layers = h.n_layers; Q.n_ragged = h.n_ragged;
-      Q.n_rnr = h.n_derive;
+      Q.n_rnr = h.n_derive; Q.root_step = h.root_step;
       Q.rnr_words = static_cast<uint32_t>(h.derive_tab.size());
       Q.alias_at = h.alias_at; Q.n_alias = h.n_alias;
       Q.n_lists = static_cast<uint32_t>(h.tile_list_begin.size()) - 1u;

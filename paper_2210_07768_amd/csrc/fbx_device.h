@@ -73,6 +73,7 @@ struct TileParams {
   uint32_t n_mh;        // multi-valued hashes: the first n_mh entries of the ragged root list
   uint32_t n_split;     // multi-valued root operators of any kind: the first n_split entries of that list
   uint32_t n_gen;       // list operators of layers >= 2 (crosses and concats that are not computed along with their input)
+  uint32_t root_step;   // first layer whose step may hold the ragged root operators (PlanHost::root_step)
   uint32_t n_tiles, n_fields, n_stage;
   uint32_t grid;        // upper limit of workgroups to launch (0: as many as run at the same time)
   uint32_t spin_limit;  // polls after which a wait for an earlier tile's count is given up (mode 2)
@@ -121,7 +122,7 @@ struct UnorderedParams {
 // The fields of TileParams that the plan and the tile size fix (all but addresses, sizes of
 // the batch and tuning switches): a kernel compiled for one plan has them as literals.
 #define FBX_TILE_FIXED_FIELDS(X)                                                                                     \
-  X(n_ops) X(n_layers) X(n_ragged) X(n_rnr) X(n_lists) X(aux_bytes) X(rnr_words) X(alias_at) X(n_alias) X(n_mh) X(n_split) X(n_gen) X(n_fields) \
+  X(n_ops) X(n_layers) X(n_ragged) X(n_rnr) X(n_lists) X(aux_bytes) X(rnr_words) X(alias_at) X(n_alias) X(n_mh) X(n_split) X(n_gen) X(root_step) X(n_fields) \
   X(n_stage) X(log2T) X(raw_cap) X(row_stride) X(o_off) X(o_rs) X(o_re) X(o_rows) X(o_raw) X(o_stage) X(o_cnt)     \
   X(o_start) X(o_run) X(o_base) X(o_prog) X(o_lbeg) X(o_rnr) X(o_aux) X(o_tot) X(o_ioff) X(o_ctab) X(o_ctot) X(o_cfirst) X(o_cap) \
   X(o_gfirst) X(o_gtot) X(commas) X(comma_cap) X(o_lists) X(list_cap) X(lds_bytes) X(kept_bytes) X(kept_commas)

@@ -126,6 +126,7 @@ struct PlanHost {
   uint32_t n_fields = 0;
   uint32_t n_layers = 0;
   uint32_t n_ragged = 0;
+  uint32_t root_step = 2;               // the layer after the last one whose single signs are crossed along with a multi-valued hash's items (at least 2)
   uint32_t n_const = 0;                 // distinct arities among the fixed-arity operators that list operators are or read
   std::vector<HostOp> ops;             // spec order
   std::vector<uint32_t> layer_ops;     // operator indices grouped by layer

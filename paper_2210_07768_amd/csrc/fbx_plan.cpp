@@ -360,8 +360,12 @@ fbx_status parse_plan(const char* spec, size_t len, PlanHost& plan, std::string&
       if (d.kind == OP_CROSS && multi_hash(d.a) && plan.ops[d.b].d.arity == 1) fuse = 1;
       if (d.kind == OP_CROSS && multi_hash(d.b) && plan.ops[d.a].d.arity == 1) fuse = 2;
       plan.ops[i].d.fuse = fuse;
-      if (fuse) lists[TL_FUSED].push_back(i);
-      else lists[TL_LAYER + 2 * (d.layer - 2) + (single ? 0 : 1)].push_back(i);
+      if (fuse) {
+        lists[TL_FUSED].push_back(i);
+        plan.root_step = std::max(plan.root_step, plan.ops[fuse == 1 ? d.b : d.a].d.layer + 1u);
+      } else {
+        lists[TL_LAYER + 2 * (d.layer - 2) + (single ? 0 : 1)].push_back(i);
+      }
     }
   }
   // List operators look every input's and every record's place up in the tables of the ragged operators: what has a fixed

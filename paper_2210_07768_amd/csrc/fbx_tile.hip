@@ -1791,6 +1791,42 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
   // operator) are requested now, so that they arrive while the single crosses run.
   uint64_t early = kLbPrefix;
   if (MODE == 2 && wave < P.n_ragged && !row_follows(P, sh, wave)) early = lb_window(P, wave, tile);
+  // The kernel for any plan with list operators shares roots, single crosses and list operators out in steps, long units first,
+  // with a barrier a step instead of one a layer and kind: step l holds the single crosses of layer l; the roots come as soon as
+  // the single signs that are crossed along with their items are in place (P.root_step), the list operators of a layer once the
+  // layer before it is done.  (us a call, without and with steps: 60,000 records of the four-layer graph 524 and 515, 50,000 of 18
+  // lists 276 and 272.  Kernels compiled for the plan, where both are as many barriers' worth faster, lose: 250,000 of the
+  // four-layer graph 1,350 and 1,380, 200,000 of 18 lists 750 and 765.  Without list operators steps are the layers.)
+#ifdef FBX_FIXED_MODE
+  constexpr bool kSteps = false;
+#else
+  constexpr bool kSteps = kEarlyBases && PAIRS;
+#endif
+  if constexpr (kSteps) {
+    const uint32_t root_step = P.root_step, last = root_step + P.n_layers - 1u;
+    for (uint32_t step = 2, turn = 0; step <= last; ++step) {
+      const uint32_t gl = step > root_step ? step - root_step + 1u : 0u;  // the layer whose list operators run
+      const bool roots = P.n_ragged && step == root_step;
+      const bool lists = gl >= 2u && sh.lbeg(ps.gen_list(gl) + 1u) != sh.lbeg(ps.gen_list(gl));
+      const uint32_t ux = step > P.n_layers ? 0u : ps.x11_units(step);
+      if (!roots && !lists && !ux) continue;  // (nothing: no barrier either)
+      __syncthreads();  // every sign this step reads is in place
+      hook();
+      if (MODE == 3 && roots && !s_good) return;  // the call falls back: leave the arrays alone
+      uint32_t* ctr = &s_ctr[4u + (turn & 1u)];
+      if (tid == 0) s_ctr[4u + ((turn + 1u) & 1u)] = 0;  // the next step's counter (idle since the barrier before this one)
+      ++turn;
+      const uint32_t ur = roots ? ragged_root_units() : 0u, ul = ur + (lists ? ps.gen_units(gl) : 0u);
+      for_units(ctr, ul + ux, [&](uint32_t u) {
+        if (u < ur) { ragged_root_unit(u); return; }
+        if (FBX_SKIP(2u)) return;
+        if (u < ul) { ps.gen_unit(gl, u - ur); return; }
+        ps.x11_unit(step, u - ul);
+      });
+    }
+    FBX_MARK(8);
+    return;
+  }
   // ---- the single crosses of every later layer: they only read signs kept on chip
   for (uint32_t layer = 2; layer <= P.n_layers; ++layer) {
     __syncthreads();  // the layer barrier: every sign this layer reads is in place
