@@ -1141,6 +1141,11 @@ struct Pass {
     }
     return wave_prefix_max(pair) - 1u;
   }
+  // the first item of the i-th multi-valued hash among the pass's items (a table of pairs only where pair_at reads it)
+  __device__ __forceinline__ uint32_t& item_first(uint32_t i) const {
+    if constexpr (PAIRS) return sh.ioff[i].sign;
+    else return reinterpret_cast<uint32_t*>(sh.ioff)[i];
+  }
   // Multi-valued hashes (the first P.n_mh entries of the ragged root list): lanes
   // are items.  All items of the pass, operator after operator and record after
   // record, form one index space; a lane finds its operator and record (pair_at),
@@ -1155,52 +1160,57 @@ struct Pass {
       if (i < P.n_mh) {
         const uint32_t row = sh.prog[sh.lbeg(TL_RAGROOT) + i].rag_row;
         v = sh.tot[row];
-        before = sh.run[row] - v;  // items of the tile's earlier passes
+        if constexpr (PAIRS) before = sh.run[row] - v;  // items of the tile's earlier passes
       }
       uint32_t incl = v;
       for (uint32_t d = 1; d < 64u; d <<= 1) {
         const uint32_t t = __shfl_up(incl, d, 64);
         if (lane >= d) incl += t;
       }
-      if (i < P.n_mh) sh.ioff[i] = ListFirst{carry + incl - v, carry + incl - v - before};
+      if (i < P.n_mh) {
+        item_first(i) = carry + incl - v;
+        if constexpr (PAIRS) sh.ioff[i].base = carry + incl - v - before;
+      }
       carry += __shfl(incl, 63, 64);
     }
-    if (lane == 0) sh.ioff[P.n_mh].sign = carry;
+    if (lane == 0) item_first(P.n_mh) = carry;
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   }
-  __device__ __forceinline__ uint32_t item_units() const { return (sh.ioff[P.n_mh].sign + 63u) >> 6; }
+  __device__ __forceinline__ uint32_t item_units() const { return (item_first(P.n_mh) + 63u) >> 6; }
   __device__ __forceinline__ void item_unit(uint32_t u) {
+    uint32_t i, rr, pos;  // pos: the item's position inside the tile
     const uint32_t q0 = u * 64u, q = q0 + lane_id();
     const OpProg* list_ops = sh.prog + sh.lbeg(TL_RAGROOT);
-    uint32_t i, rr;
     if constexpr (PAIRS) {
       const uint32_t pair = pair_at(list_ops, sh.ioff, P.n_mh, q0);
-      if (q >= sh.ioff[P.n_mh].sign) return;
+      if (q >= item_first(P.n_mh)) return;
       i = pair >> P.log2T;
       rr = pair & (T - 1u);
     } else {
       // (The kernel for any plan, where few lists are read by nothing: two searches, the operator's and the record's.  What
       // pair_at keeps alive costs it more than it saves: 200,000 records of the 100-field workload 320 us a call with it, 309
       // without; kernels compiled for the plan 4,130 and 4,270 for 4,000,000.)
-      if (q >= sh.ioff[P.n_mh].sign) return;
+      if (q >= item_first(P.n_mh)) return;
       uint32_t lo = 0, hi = P.n_mh - 1u;
       while (lo < hi) {
         const uint32_t mid = (lo + hi + 1u) >> 1;
-        if (sh.ioff[mid].sign <= q) lo = mid; else hi = mid - 1u;
+        if (item_first(mid) <= q) lo = mid; else hi = mid - 1u;
       }
       i = lo;
-      const uint32_t* st = sh.start + list_ops[i].rag_row * T;
-      const uint32_t at = q - sh.ioff[i].base;
+      const uint32_t row = sh.prog[sh.lbeg(TL_RAGROOT) + i].rag_row;
+      const uint32_t before = sh.run[row] - sh.tot[row];  // signs of the tile's earlier passes
+      pos = before + (q - item_first(i));
+      const uint32_t* st = sh.start + row * T;
       lo = 0; hi = nb - 1u;  // (every record has at least one item)
       while (lo < hi) {
         const uint32_t mid = (lo + hi + 1u) >> 1;
-        if (st[mid] <= at) lo = mid; else hi = mid - 1u;
+        if (st[mid] <= pos) lo = mid; else hi = mid - 1u;
       }
       rr = lo;
     }
-    const OpProg& d = list_ops[i];
+    const OpProg& d = PAIRS ? list_ops[i] : sh.prog[sh.lbeg(TL_RAGROOT) + i];  // (the same; a pointer less to keep over the searches)
     const uint32_t row = d.rag_row;
-    const uint32_t pos = q - sh.ioff[i].base;  // the item's position inside the tile
+    if constexpr (PAIRS) pos = q - sh.ioff[i].base;
     const uint32_t j = pos - sh.start[row * T + rr], cnt = sh.cnt[row * T + rr];
     uint32_t s, e;
     src.span(rr, d.field, s, e);
@@ -2001,7 +2011,21 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
   // In the kernels of list-heavy plans, which have the most to hold on to, addresses that follow from the lane's number are
   // worked out where they are used (thread_id); the others have registers for them (a million records of 16 single-valued
   // fields 232 us a call otherwise and 222, of the numeric workload 590 and 577; the four-layer graph 1,546 so and 1,353).
-  auto my_id = [&]() -> uint32_t { return COMMAS == kCommasWithTabs && MODE <= 1 ? thread_id() : tid; };
+  // (Those get the variable itself: a copy of it at every use has the kernel for any plan spill a tenth more scalar registers, and
+  // the smallest calls took 31.3 us where they take 30.7, 64 records of 16 fields, 46.7 and 46.0, 257 of 100.  Kernels compiled for
+  // plans with lists are the exception: 4,000,000 records of 100 fields 4,112 us with the copy and 4,165 without.)
+  constexpr bool kAgain = COMMAS == kCommasWithTabs && MODE <= 1;
+#ifdef FBX_FIXED_MODE
+  constexpr uint32_t kBegin[] = FBX_FIXED_LIST_BEGIN;
+  constexpr bool kCopy = kBegin[TL_RAGROOT + 1] != kBegin[TL_RAGROOT];
+#else
+  constexpr bool kCopy = false;
+#endif
+  using Id = std::conditional_t<kAgain || kCopy, const uint32_t, const uint32_t&>;
+  auto my_id = [&]() -> Id {
+    if constexpr (kAgain) return thread_id();
+    else return tid;
+  };
   const uint32_t T = 1u << P.log2T;
   const FBX_GLOBAL uint64_t* rec_off = gptr(P.rec_off);
   uint32_t* ticket = &P.ctrl->ticket[WRITE ? 1 : 0];
@@ -2137,7 +2161,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
     uint32_t pf_stage = counter ? 0u : 1u, nxt = 0xffffffffu, nrec2 = 0, touch = 0, touch_kept = 0;
     uint64_t off_next = 0, off_next1 = 0, nx_lo = 0, nx_hi = 0;
     auto next_tile_step = [&]() {  // every lane, right after a barrier
-      const uint32_t tid = my_id();
+      Id tid = my_id();
       if (pf_stage == 0) {
         if (tid == 0) s_nxt = late_ticket ? atomicAdd(ticket, 1u) : my_ticket;
       } else if (pf_stage == 1) {
@@ -2195,7 +2219,8 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
         const uint32_t mid = (lo + hi + 1u) >> 1;
         if (off[mid] - o0 + delta <= (uint64_t)P.raw_cap) lo = mid; else hi = mid - 1u;
       }
-      const uint32_t r1 = lo, tid = my_id();
+      const uint32_t r1 = lo;
+      Id tid = my_id();
       if (r1 > r0) {
         const uint32_t nb = r1 - r0;
         in_one_pass = nb == nrec;
@@ -2277,8 +2302,11 @@ __device__ __forceinline__ void tile_body(const TileParams& P) {
       } while (pf_stage < 3);
       __syncthreads();  // the parked offsets are read by other lanes
     }
-    asm volatile("" ::"v"(touch), "v"(touch_kept));  // the touched bytes themselves are of no use
-    kept_now = kept_next;
+    asm volatile("" ::"v"(touch));  // the touched byte itself is of no use
+    if constexpr (WRITE && kKeep) {
+      asm volatile("" ::"v"(touch_kept));
+      kept_now = kept_next;
+    }
     par ^= 1u;
     tile = nxt;  // every lane has read the ticket by now
     FBX_MARK(12);
