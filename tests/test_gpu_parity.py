@@ -1143,3 +1143,81 @@ def test_what_counting_leaves_for_the_writing_launch(compiled):
                 assert_same({s: expand(res.slots[s], n) for s in res.slot_ids}, res, want, f"{n} {extra}")
                 res = plan.extract(d_raw, d_off)
             plan.close()
+
+
+@pytest.mark.parametrize("compiled", [0, 1])
+@pytest.mark.parametrize("log2,pad", [(0, 2200), (3, 2200), (6, 200)])
+def test_slots_of_the_counting_launch_are_taken_over_tile_by_tile(log2, pad, compiled):
+    """The first word of a tile's slot says whether the writing launch takes it over: 1 for tiles worked off in one pass whose
+    commas and signs a slot has room for, 0 for the others, and no slot is written where the workspace has no room for all."""
+    import re
+
+    import torch
+    rng = random.Random(log2)
+    n = {0: 37, 3: 203, 6: 403}[log2]  # (the last tile of 8 and of 64 records is not full)
+    spec = "fbx 1\nfields 16\n" + "".join(f"op h{k} hash slot={k} seed={k} emit=1 field={k} multi=1\n" for k in range(12))
+    spec += "op s hash slot=21 seed=8 emit=1 field=14 multi=0\nop x cross slot=22 seed=9 emit=1 a=h0 b=h1\nop y cross slot=23 seed=10 emit=1 a=x b=s\n"
+    if log2 < 6:
+        spec += "op f filter slot=20 seed=7 emit=1 field=13 multi=1 prefix=61\nop z concat slot=24 emit=1 a=f b=h2\n"
+    recs = []
+    for i in range(n):
+        # (a record with more commas than a slot has room for; one with 270 * 270 signs of the cross; one beside the usual)
+        many = {5: [200] * 3, n // 2: [270] * 2, n - 1: [9]}.get(i, [0])
+        lists = [",".join(rng.choice(["a", "bb", "", "ccc"]) for _ in range(rng.randrange(1, 5) + (many[k] if k < len(many) else 0))) for k in range(14)]
+        text = "t" * (pad + rng.randrange(pad // 5 + 1))
+        if log2 == 6 and 256 <= i < 320:  # (more than 65,535 signs of the cross from lists that a slot has room for)
+            lists, text = ["a" + ",a" * 35] * 2 + ["b"] * 12, ""
+        recs.append(("\t".join(lists + [f"k{i}", text]) + "\n").encode())
+    raw, off = _cat(recs)
+    raw = np.frombuffer(raw, np.uint8)
+    want = O.extract(spec, raw, off)
+    d_raw, d_off = to_device(raw, off, 3)
+
+    def plan_of():
+        plan = B.Plan(spec)
+        for k, v in (("one_launch", 0), ("tile_log2", log2), ("compile", compiled)):
+            plan.set_option(k, v)
+        return plan
+
+    plan = plan_of()
+    text = plan.kernel_source(raw.size, n, 1)
+    field = {k: int(re.search(rf"P\.{k} = (\d+)u;", text).group(1)) for k in ("log2T", "commas", "raw_cap", "kept_bytes", "kept_commas")}
+    assert field["log2T"] == log2 and field["commas"] == 2 and field["kept_bytes"]
+    res, _ = B.extract_with_retry(plan, d_raw, d_off)
+    need = res.arena_high_water
+    plan.close()
+    T = 1 << log2
+    expected = []
+    ragged = [want.slots[s][1] for s in want.slot_ids if want.slots[s][2] == 0]
+    for t in range(0, n, T):
+        e = min(t + T, n)
+        delta = (d_raw.data_ptr() + int(off[t])) % 16
+        fits = int(off[e]) - int(off[t]) + delta <= field["raw_cap"]
+        commas = max(r.count(b",") for r in recs[t:e])
+        signs = max(int(o[e]) - int(o[t]) for o in ragged)
+        expected.append(1 if fits and commas <= field["kept_commas"] and signs <= 0xffff else 0)
+        if t == 256 and log2 == 6:
+            assert fits and commas <= field["kept_commas"] and signs > 0xffff
+    assert 0 in expected and 1 in expected and (log2 == 6 or expected[-1] == 1)
+    size = (len(expected) * field["kept_bytes"] + 255) // 256 * 256
+    for extra in (size + 4096, (1 << 21) + size):
+        plan = plan_of()
+        ws = torch.full((need + extra,), 0xff, dtype=torch.uint8, device="cuda")
+        plan.set_workspace(ws)
+        res = plan.extract(d_raw, d_off)
+        assert res.tile_launches == 2, res.note
+        assert_same({s: expand(res.slots[s], n) for s in res.slot_ids}, res, want, f"{log2} {extra}")
+        at = (need + extra - size) // 256 * 256
+        words = ws[at:at + len(expected) * field["kept_bytes"]].view(len(expected), -1)[:, :4].contiguous().cpu().numpy().view(np.uint32)[:, 0]
+        assert words.tolist() == expected
+        plan.close()
+    # a workspace of the size that the call needs, once the plan knows that: nothing is written behind the arrays
+    plan = plan_of()
+    plan.set_workspace(torch.empty(need + size + 4096, dtype=torch.uint8, device="cuda"))
+    plan.extract(d_raw, d_off)
+    ws = torch.full((need + 4096,), 0xff, dtype=torch.uint8, device="cuda")
+    plan.set_workspace(ws)
+    res = plan.extract(d_raw, d_off)
+    assert_same({s: expand(res.slots[s], n) for s in res.slot_ids}, res, want, f"{log2} no room")
+    assert bool((ws[need:] == 0xff).all())
+    plan.close()
