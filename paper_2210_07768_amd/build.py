@@ -12,7 +12,7 @@ LIB = os.path.join(_HERE, "libfbx.so")
 NATIVE = os.path.join(_HERE, "_native.so")          # the part of the Python binding that runs once per call
 NATIVE_SOURCE = os.path.join(CSRC, "fbx_native.cpp")
 SOURCES = ["fbx_plan.cpp", "fbx_api.cpp", "fbx_jit.cpp", "fbx_support.hip", "fbx_walk.hip", "fbx_tile.hip", "fbx_clean.hip"]
-HEADERS = ["fbx_internal.h", "fbx_device.h", "fbx_arena.h", "fbx_split.h", os.path.join(_ROOT, "include", "fbx.h")]
+HEADERS = ["fbx_internal.h", "fbx_device.h", "fbx_arena.h", "fbx_lists.h", "fbx_split.h", os.path.join(_ROOT, "include", "fbx.h")]
 
 
 def hipcc() -> str:

@@ -48,6 +48,7 @@
 
 #include "fbx_arena.h"
 #include "fbx_device.h"
+#include "fbx_lists.h"
 #include "fbx_split.h"
 
 // How a tile of 64 records runs its single-sign operators (kernels compiled for a plan only): 0 as any
@@ -1106,8 +1107,8 @@ struct Pass {
   // The signs of a list of operators in this pass, operator after operator and record after record, form one index space; a
   // wavefront takes the 64 from q0 on.  Returns the (operator, record) pair that the lane's sign belongs to, operator * T +
   // record (of lanes beyond the last sign: any).  The operator of q0 is found with one look at all first signs; from its first pair on 64 pairs at a time
-  // say where they start, each hands its number to the lane of that sign (a pair without signs starts where the next one
-  // does, and of several that write to a lane the highest-numbered one wins), and a running maximum fills the lanes in between.
+  // say where they start, each hands its number to the lane of that sign, the last of those that start there alone (pair_send),
+  // and a running maximum fills the lanes in between.
   // (What bounds a unit is the chain of look-ups and its vector instructions.  Against two binary searches a sign and fields of the
   // programs looked through for every input: 4,000,000 records of the 100-field workload, 4 lists, 4,265 -> 4,130 us a call;
   // 200,000 of 18 lists and 6 crosses of two of them 868 -> 817; 250,000 of the four-layer graph 1,618 -> 1,562.)
@@ -1128,14 +1129,12 @@ struct Pass {
     uint32_t pair = 0;  // (plus one)
     for (uint32_t w = lo << P.log2T;; w += 64u) {
       const uint32_t i = (w + lane) >> P.log2T;
-      uint32_t s = 64u;
-      if (i < m) {
-        const uint32_t at = first[i].base + sh.start[ops[i].rag_row * T + min((w + lane) & (T - 1u), nb)];  // (records beyond the pass start at its end)
-        s = at > q0 ? min(at - q0, 64u) : 0u;
-      }
-      const uint32_t in = (uint32_t)__popcll(__ballot(s < 64u));  // (starts only grow: the first ones)
-      // (a pair that starts beyond the unit names the last one inside it, which is what the last lane is to know)
-      const uint32_t got = (uint32_t)__builtin_amdgcn_ds_permute((int)(4u * min(s, 63u)), (int)(s < 64u ? w + lane + 1u : w + in));
+      uint32_t from = ~0u;  // q0 or beyond
+      if (i < m) from = __builtin_elementwise_sub_sat(first[i].base + sh.start[ops[i].rag_row * T + min((w + lane) & (T - 1u), nb)], q0);  // (records beyond the pass start at its end)
+      const uint32_t in = (uint32_t)__popcll(__ballot(from < 64u));  // (starts only grow: the first ones)
+      const uint32_t s = min(from, 63u), next = (uint32_t)__builtin_amdgcn_update_dpp(63, (int)s, 0x130, 0xf, 0xf, false);  // (wave_shl:1, the next lane's)
+      const PairSend to = pair_send(s, next, w + lane + 1u, w + in);
+      const uint32_t got = (uint32_t)__builtin_amdgcn_ds_permute((int)(4u * to.lane), (int)to.number);
       pair = max(pair, got);
       if (in < 64u) break;
     }
