@@ -17,4 +17,13 @@ constexpr PairSend pair_send(uint32_t s, uint32_t next, uint32_t number, uint32_
   return s != next ? PairSend{s, number} : PairSend{63u, last};
 }
 
+// Where a pass's lists lie on chip (Pass::keep_lists), in words: `all` is the section of the staged text, of which the pass's
+// text takes `text`; `cap` the section for lists of layer 1.  Those go behind the text where there is more room; later layers'
+// lists go where the text was, or, if none is staged (a record read in place), to all of its section.
+struct ListRoom { bool behind; uint32_t first, later; };
+constexpr ListRoom list_room(bool staged, uint32_t all, uint32_t text, uint32_t cap) {
+  const bool behind = staged && all - text > cap;
+  return ListRoom{behind, behind ? all - text : cap, behind ? text : all};
+}
+
 }  // namespace fbx

@@ -1472,7 +1472,7 @@ struct Pass {
     const uint32_t all = (kRawPad + P.raw_cap) >> 3;               // words of the text's section
     uint32_t text = 0;                                             // those that hold the pass's text
     if constexpr (Src::kTable) text = (sh.re[nb - 1u] + 7u) >> 3;  // (bytes behind it are read with its last ones, and of no account)
-    const bool tail = all - text > P.list_cap;
+    const ListRoom to = list_room(Src::kTable, all, text, P.list_cap);
     for (uint32_t i0 = sh.lbeg(TL_RAGROOT); i0 < P.n_ops;) {
       const uint32_t end = later ? P.n_ops : sh.lbeg(TL_LAYER);
       const uint32_t i = i0 + lane;
@@ -1485,8 +1485,8 @@ struct Pass {
         }
       }
       const uint32_t incl = group_prefix(n, 6u, lane);
-      const uint32_t first = later ? P.o_raw >> 3 : (tail ? (P.o_raw >> 3) + text : P.o_lists >> 3);
-      const uint32_t room = later ? (tail ? text : all) : (tail ? all - text : P.list_cap);
+      const uint32_t first = later ? P.o_raw >> 3 : (to.behind ? (P.o_raw >> 3) + text : P.o_lists >> 3);
+      const uint32_t room = later ? to.later : to.first;
       if (n) const_cast<OpProg*>(sh.prog)[i].stage = used + incl <= room ? first + used + incl - n - before : kNoRow;
       used = min(used + __shfl(incl, 63, 64), 1u << 24);
       i0 += 64u;

@@ -1,5 +1,5 @@
 // Pass::pair_at on the CPU: 64 lanes, their permute, and a choice of which lane is heard where several name the same one.
-// Prints nothing but "ok" if every sign of every unit finds its (operator, record) pair, whichever lane is heard.
+// Prints "ok" if every sign of every unit finds its (operator, record) pair, whichever lane is heard.
 #include <algorithm>
 #include <cstdio>
 #include <random>
@@ -7,7 +7,22 @@
 
 #include "fbx_lists.h"
 
+// The rooms of lists of layer 1 and of later layers: apart from each other, from the staged text while that is read, and all of
+// the text's section for later layers where no text is staged.
+static bool rooms() {
+  for (uint32_t all : {0u, 10u, 400u})
+    for (uint32_t text = 0; text <= all; ++text)
+      for (uint32_t cap : {0u, 5u, 100u, 1000u}) {
+        const fbx::ListRoom r = fbx::list_room(true, all, text, cap);
+        if (r.behind ? r.first != all - text || r.first <= cap || r.later != text : r.first != cap || r.later != all) return false;
+        const fbx::ListRoom p = fbx::list_room(false, all, 0, cap);
+        if (p.behind || p.first != cap || p.later != all) return false;
+      }
+  return true;
+}
+
 int main() {
+  if (!rooms()) { std::printf("rooms\n"); return 1; }
   std::mt19937 rng(7);
   for (int round = 0; round < 3000; ++round) {
     const uint32_t pairs = 1 + rng() % 400, mostly = rng() % 4;
