@@ -224,7 +224,7 @@ void tile_lds_layout(const fbx_plan& p, uint32_t lt, uint64_t want, uint32_t raw
   tp.list_cap = p.keeps_roots && o < share ? (share - o) / 16u * 2u : 0u;
   o += 8u * tp.list_cap;
   tp.lds_bytes = o;
-  // (room for six commas a field where there are three on average, or thirty in one field)
+  // (room for six commas a field, where there are three on average, and 24 more, as far as the list of commas goes: 16 a field)
   tp.kept_commas = along ? std::min(round16(2u * (6u * p.n_comma_fields + 24u)) / 2u, tp.comma_cap / 8u * 8u) : 0u;
   tp.kept_bytes = along ? 16u + round16(2ull * T * tp.row_stride) + round16(2ull * T * tp.n_mh) + round16(2ull * T) +
                               2u * round16(2ull * T * h.n_ragged) + round16(2ull * h.n_ragged) + 2u * T * tp.kept_commas

@@ -285,7 +285,7 @@ struct GlobalSrc {
   }
 };
 
-// The number of a tile that is not kept for the writing launch (keep_tile): the last one that was seen to have too many
+// The number of a tile that is not kept for the writing launch (move_kept): the last one that was seen to have too many
 // commas in a record or too many signs of an operator.
 __shared__ uint32_t s_drop;
 
@@ -725,7 +725,8 @@ constexpr uint32_t kWaves = kTileThreads / 64;
 // Work counters of a pass (cleared between passes): s_ctr[0] hands out the
 // single-valued hash / bucket units of layer 1, which fill every phase that has
 // idle wavefronts; s_ctr[1] the counting units, s_ctr[3] the ragged root units,
-// s_ctr[4 + (l & 1)] the single crosses of layer l, s_ctr[7 + (l & 1)] its list operators.
+// s_ctr[4 + (l & 1)] the single crosses of layer l, s_ctr[7] and s_ctr[8] in turn the list operators, layer by layer.
+// Where roots, single crosses and list operators share steps, s_ctr[4] and s_ctr[5] in turn hand out a step's units.
 // s_done: finished counting units.
 __shared__ uint32_t s_ctr[9];
 __shared__ uint32_t s_done;
@@ -1109,9 +1110,10 @@ struct Pass {
   // record (of lanes beyond the last sign: any).  The operator of q0 is found with one look at all first signs; from its first pair on 64 pairs at a time
   // say where they start, each hands its number to the lane of that sign, the last of those that start there alone (pair_send),
   // and a running maximum fills the lanes in between.
-  // (What bounds a unit is the chain of look-ups and its vector instructions.  Against two binary searches a sign and fields of the
-  // programs looked through for every input: 4,000,000 records of the 100-field workload, 4 lists, 4,265 -> 4,130 us a call;
-  // 200,000 of 18 lists and 6 crosses of two of them 868 -> 817; 250,000 of the four-layer graph 1,618 -> 1,562.)
+  // (What bounds a unit is the chain of look-ups and its vector instructions.  us a call with two binary searches a sign, and so:
+  // 4,000,000 records of the 100-field workload, 4 lists, 4,257 and 4,147; with inputs' places worked out once for an operator and
+  // not for a sign, 200,000 of 18 lists with crosses of them 866 and 832, but 250,000 of the four-layer graph 1,618 and
+  // 1,640, which gains by where its lists lie: keep_lists.)
   __device__ __forceinline__ uint32_t pair_at(const OpProg* ops, const ListFirst* first, uint32_t m, uint32_t q0) const {
     const uint32_t lane = lane_id();
     uint32_t lo = 0;
@@ -1188,7 +1190,7 @@ struct Pass {
     } else {
       // (The kernel for any plan, where few lists are read by nothing: two searches, the operator's and the record's.  What
       // pair_at keeps alive costs it more than it saves: 200,000 records of the 100-field workload 320 us a call with it, 309
-      // without; kernels compiled for the plan 4,130 and 4,270 for 4,000,000.)
+      // without; kernels compiled for the plan 4,147 and 4,257 for 4,000,000.)
       if (q >= item_first(P.n_mh)) return;
       uint32_t lo = 0, hi = P.n_mh - 1u;
       while (lo < hi) {
@@ -1410,9 +1412,8 @@ struct Pass {
   // Every other cross or concat: lanes are output signs.  The signs that the list operators of
   // one layer produce in this pass, operator after operator and record after record, form one
   // index space; a unit is 64 consecutive ones, whichever operators they belong to, so that
-  // operators with few signs share wavefronts.  A lane finds its operator by a search over the
-  // operators' first signs (gen_offsets), its record by a search over the records' first
-  // positions; its place in the record's list tells which input signs it combines, and
+  // operators with few signs share wavefronts.  A lane finds its operator and record in one sweep over the pairs of the two
+  // (pair_at); its place in the record's list tells which input signs it combines, and
   // neighbouring lanes write neighbouring signs.  Units before those hand the offsets entries of
   // the ragged operators to lanes, one (operator, record) each.
   __device__ __forceinline__ uint32_t gen_total(const OpProg& d) const { return d.arity ? d.arity * nb : sh.tot[d.rag_row]; }
@@ -1461,8 +1462,9 @@ struct Pass {
   // Where the lists that later operators read lie on chip, operator after operator: OpProg::stage becomes the word of LDS at
   // which the tile's sign 0 would lie (its signs before this pass have no place).  Lists of layer 1, and those made
   // along with them, go to a section of their own, or behind the pass's text where its section has more room left (a fifth
-  // of it on average); those of later layers to where the text was, which nobody reads any more by then.  Room is given in the order of the work lists, whether a list fits or not: from the first that does not on,
-  // all of a section's lists stay in memory only.
+  // of it on average); those of later layers to where the text was, which nobody reads any more by then.  Room is given in the
+  // order of the work lists, whether a list fits or not: from the first that does not on, all of a section's lists stay in memory
+  // only.  (250,000 records of the four-layer graph with no list behind the text: 1,640 us a call against 1,563.)
   // (Where all inputs are read back from memory, a unit waits for them and, loads and stores being counted together, for the
   // signs of the unit before.  200,000 records of 18 lists and 12 crosses of two of them: 0.92 against 0.88 ms a call.)
   __device__ __forceinline__ void keep_lists() {
@@ -1661,7 +1663,7 @@ __device__ __forceinline__ bool lb_place_row(const TileParams& P, const Sh& sh, 
 
 // Runs every layer on the nb records of one pass.  WRITE = false stops after the
 // counts.  hook() is called by every lane right after barriers (the caller
-// advances the next tile's loads there).  kept: counts and positions are there already (keep_tile).
+// advances the next tile's loads there).  kept: counts and positions are there already (move_kept).
 template <int MODE, bool PAIRS, class Src, class Hook>
 __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, const Src& src, uint32_t nb, uint64_t g_first,
                                          uint32_t tile, bool kept, uint32_t& malformed, bool& overflow, Hook&& hook) {
@@ -1803,8 +1805,8 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
   // The kernel for any plan with list operators shares roots, single crosses and list operators out in steps, long units first,
   // with a barrier a step instead of one a layer and kind: step l holds the single crosses of layer l; the roots come as soon as
   // the single signs that are crossed along with their items are in place (P.root_step), the list operators of a layer once the
-  // layer before it is done.  (us a call, without and with steps: 60,000 records of the four-layer graph 524 and 515, 50,000 of 18
-  // lists 276 and 272.  Kernels compiled for the plan, where both are as many barriers' worth faster, lose: 250,000 of the
+  // layer before it is done.  (us a call, without and with steps: 60,000 records of the four-layer graph 526 and 515, 50,000 of 18
+  // lists 279 and 277.  Kernels compiled for the plan, where both are as many barriers' worth faster, lose: 250,000 of the
   // four-layer graph 1,350 and 1,380, 200,000 of 18 lists 750 and 765.  Without list operators steps are the layers.)
 #ifdef FBX_FIXED_MODE
   constexpr bool kSteps = false;
@@ -1909,12 +1911,13 @@ __device__ __forceinline__ void run_pass(const TileParams& P, const Sh& sh, cons
 
 // ---- what the counting launch leaves for the writing launch
 // Splitting a tile's text and counting is a third of what the writing launch of a list-heavy plan does, and the counting launch
-// has just done it: field ends, commas, counts and positions are a fifth of the text's size, and go to a slot a tile has in
-// memory.  A tile is kept if it was worked off in one pass and what it holds fits the slot's 16-bit entries; the slot's first
-// word says so.  Sections of the slot, 16 bytes at a time: field ends, first commas of the hashes' fields, commas a record has,
-// counts, positions, totals, commas.  Chunk c of the slot, handed to what moves it: LDS address and how entries lie there.
-// (us a call with the slots and without: 200,000 records of 18 lists with crosses 750 and 817, 250,000 of the four-layer graph
-// 1,355 and 1,562, 50,000 and 60,000 of them with the kernel for any plan 276 and 310, 524 and 603.  The counting launch takes 7 %
+// has just done it: field ends, commas, counts and positions are a quarter of the text's size (18 lists) to a third (the
+// four-layer graph), and go to a slot a tile has in memory.  A tile is kept if it was worked off in one pass and what it holds
+// fits the slot's 16-bit entries; the slot's first word says so.  Sections of the slot, 16 bytes at a time: field ends, first
+// commas of the hashes' fields, commas a record has, counts, positions, totals, commas.  Chunk c of the slot, handed to what
+// moves it: LDS address and how entries lie there.
+// (us a call with the slots and without: 200,000 records of 18 lists with crosses 753 and 832, 250,000 of the four-layer graph
+// 1,344 and 1,564, 50,000 and 60,000 of them with the kernel for any plan 277 and 314, 513 and 600.  The counting launch takes 7 %
 // longer for it.)
 template <bool OUT>
 __device__ __forceinline__ void move_kept(const TileParams& P, const Sh& sh, uint32_t tile) {
